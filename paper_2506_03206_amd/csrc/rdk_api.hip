@@ -1,4 +1,5 @@
 // C ABI of the RDK library: argument checks, storage / workspace carving, dispatch to the launchers.
+#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -25,6 +26,7 @@ struct TimedRecord {
     hipEvent_t start, stop;
 };
 std::mutex g_timing_mutex;
+std::atomic<bool> g_timing_on{false};      // any kernel selected: the one thing a launch looks at when none is
 std::string g_timing_selected;             // "" = off, "*" = every instrumented kernel
 long g_timing_every = 1, g_timing_seen = 0;   // of the launches of the selected kernel, every g_timing_every-th is timed
 std::vector<TimedRecord> g_timing_records;
@@ -45,6 +47,7 @@ hipEvent_t timing_event()
 
 bool timing_events(const char *kernel_name, hipEvent_t *start, hipEvent_t *stop)
 {
+    if (!g_timing_on.load(std::memory_order_relaxed)) return false;
     std::lock_guard<std::mutex> lock(g_timing_mutex);
     if (g_timing_selected.empty()) return false;
     if (g_timing_selected != "*" && g_timing_selected != kernel_name) return false;
@@ -619,6 +622,7 @@ rdk_status_t rdk_timing_select(const char *kernel_name)
         g_timing_every = every > 0 ? every : 1;
         g_timing_selected.resize(slash);
     }
+    g_timing_on.store(!g_timing_selected.empty(), std::memory_order_relaxed);
     return RDK_OK;
 }
 

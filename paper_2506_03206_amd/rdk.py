@@ -1,9 +1,10 @@
-"""ctypes binding of the RDK HIP library (``librdk_hip.so``): argument marshalling only.
+"""Binding of the RDK HIP library (``librdk_hip.so``): argument marshalling only.
 
 Function names and arguments mirror ``include/rdk.h``.  Tensors are torch CUDA (ROCm) tensors; torch is
 used for device memory and streams, nothing else: every step of the path runs in the library's kernels.
-Loading fails loudly if the library has not been built (``python -m paper_2506_03206_amd.build``);
-there is no fallback path.
+The calls of a decoding step go through the CPython extension ``_rdk_binding.so`` (``csrc/rdk_binding.cpp``), the
+one-off ones through ctypes.  Loading fails loudly if either has not been built
+(``python -m paper_2506_03206_amd.build``); there is no fallback path.
 """
 import ctypes
 import os
@@ -12,6 +13,7 @@ import torch  # noqa: F401  (imported first so that the HIP runtime already in t
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "librdk_hip.so")
+BINDING_PATH = os.path.join(_HERE, "_rdk_binding.so")
 
 OK = 0
 DENSE_F32, DENSE_BF16, SPARSE_TOPK, IDENTITY = 0, 1, 2, 3
@@ -55,6 +57,19 @@ class RdkError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def native():
+    """The CPython extension with the per-step calls (raises if it was never built)."""
+    global _native
+    if _native is None:
+        lib()
+        if not os.path.exists(BINDING_PATH):
+            raise ImportError("%s is missing: build it with `python -m paper_2506_03206_amd.build`" % BINDING_PATH)
+        from . import _rdk_binding
+        _native = _rdk_binding
+    return _native
 
 
 def lib():
@@ -139,12 +154,13 @@ class Kernel:
 
     def __init__(self, handle, storage, N, n, k, fmt):
         self.handle, self.storage, self.N, self.n, self.k, self.format = handle, storage, N, n, k, fmt
-        self._ws = None
+        self._h = handle.value
+        self._ws = self._draft_ws = None
 
     def __del__(self):
         if getattr(self, "handle", None) and _lib is not None:
             _lib.rdk_destroy_kernel(self.handle)
-            self.handle = None
+            self.handle, self._h = None, 0
 
     def workspace(self, B):
         need = ctypes.c_size_t()
@@ -214,22 +230,16 @@ def rdk_kernel_get_dense(kernel):
 
 
 def rdk_redistribute_exact(kernel, q, q_kind="prob", out=None):
-    B = q.shape[0]
-    out = torch.empty((B, kernel.N), dtype=torch.float32, device=q.device) if out is None else out
-    ws = kernel.workspace(B)
-    _check(lib().rdk_redistribute_exact(kernel.handle, _ptr(q), _kind_of(q, q_kind), _rows(q), B, _ptr(out), _rows(out),
-                                        _ptr(ws), ws.numel(), _stream()), "rdk_redistribute_exact")
+    if out is None:
+        out = torch.empty((q.shape[0], kernel.N), dtype=torch.float32, device=q.device)
+    _check((_native or native()).redistribute_exact(kernel, q, q_kind, out), "rdk_redistribute_exact")
     return out
 
 
 def rdk_redistribute_linear(kernel, mode, q, q_kind="prob", p=None, p_kind="prob", out=None):
-    B = q.shape[0]
-    out = torch.empty((B, kernel.N), dtype=torch.float32, device=q.device) if out is None else out
-    ws = kernel.workspace(B)
-    pk, ldp = (PROB_F32, 0) if p is None else (_kind_of(p, p_kind), _rows(p))
-    _check(lib().rdk_redistribute_linear(kernel.handle, mode, _ptr(p), pk, ldp, _ptr(q), _kind_of(q, q_kind), _rows(q), B,
-                                         _ptr(out), _rows(out), _ptr(ws), ws.numel(), _stream()),
-           "rdk_redistribute_linear")
+    if out is None:
+        out = torch.empty((q.shape[0], kernel.N), dtype=torch.float32, device=q.device)
+    _check((_native or native()).redistribute_linear(kernel, mode, q, q_kind, p, p_kind, out), "rdk_redistribute_linear")
     return out
 
 
@@ -250,20 +260,15 @@ class VerifyOutputs:
         need = ctypes.c_size_t()
         _check(lib().rdk_verify_workspace_bytes(ctypes.byref(d), ctypes.byref(need)), "rdk_verify_workspace_bytes")
         self.ws = torch.empty(need.value, dtype=torch.uint8, device=device)
+        self.fused_ws = None       # scratch of rdk_redistribute_verify, made by the first call that needs it
 
 
 def rdk_verify_sample(p, q_prime, seed, offset=0, gamma=0, p_kind="prob", draft_ids=None, outputs=None):
     """Alg. 4 steps 2, 4-10 for every row.  draft_ids given -> they are verified instead of sampled."""
-    B, N = p.shape
-    o = outputs or VerifyOutputs(B, N, gamma, p.device)
-    assert (o.B, o.N, o.gamma) == (B, N, gamma)
+    o = outputs or VerifyOutputs(p.shape[0], p.shape[1], gamma, p.device)
     if draft_ids is not None:
         o.draft_ids.copy_(draft_ids)
-    d = VerifyDesc(B=B, N=N, gamma=gamma, sample_draft=0 if draft_ids is not None else 1, seed=seed, offset=offset)
-    ldq = 0 if q_prime is None else _rows(q_prime)
-    _check(lib().rdk_verify_sample(ctypes.byref(d), _ptr(p), _kind_of(p, p_kind), _rows(p), _ptr(q_prime), ldq,
-                                   _ptr(o.draft_ids), _ptr(o.accept), _ptr(o.alpha), _ptr(o.resid_mass), _ptr(o.resid_ids),
-                                   _ptr(o.n_accepted), _ptr(o.out_tokens), _ptr(o.ws), o.ws.numel(), _stream()),
+    _check((_native or native()).verify_sample(p, q_prime, seed, offset, gamma, p_kind, draft_ids is None, o, True),
            "rdk_verify_sample")
     return o
 
@@ -271,16 +276,11 @@ def rdk_verify_sample(p, q_prime, seed, offset=0, gamma=0, p_kind="prob", draft_
 def rdk_verify_sample_static(p, q_prime, seed, offset=0, gamma=0, p_kind="prob", draft_ids=None, outputs=None):
     """rdk_verify_sample without a workspace: the scratch is a fixed device array inside the library.  `outputs` must
     be given (the call itself allocates nothing); its own workspace tensor is not used."""
-    B, N = p.shape
     o = outputs
-    assert o is not None and (o.B, o.N, o.gamma) == (B, N, gamma)
+    assert o is not None
     if draft_ids is not None:
         o.draft_ids.copy_(draft_ids)
-    d = VerifyDesc(B=B, N=N, gamma=gamma, sample_draft=0 if draft_ids is not None else 1, seed=seed, offset=offset)
-    ldq = 0 if q_prime is None else _rows(q_prime)
-    _check(lib().rdk_verify_sample_static(ctypes.byref(d), _ptr(p), _kind_of(p, p_kind), _rows(p), _ptr(q_prime), ldq,
-                                          _ptr(o.draft_ids), _ptr(o.accept), _ptr(o.alpha), _ptr(o.resid_mass),
-                                          _ptr(o.resid_ids), _ptr(o.n_accepted), _ptr(o.out_tokens), _stream()),
+    _check((_native or native()).verify_sample(p, q_prime, seed, offset, gamma, p_kind, draft_ids is None, o, False),
            "rdk_verify_sample_static")
     return o
 
@@ -288,23 +288,11 @@ def rdk_verify_sample_static(p, q_prime, seed, offset=0, gamma=0, p_kind="prob",
 def rdk_redistribute_verify(kernel, mode, p, q, seed, offset=0, gamma=0, p_kind="prob", q_kind="prob", draft_ids=None,
                             outputs=None, q_prime=None):
     """Fused rdk_redistribute_linear + rdk_verify_sample.  q_prime: optional [B,N] tensor that receives q'."""
-    B, N = p.shape
-    o = outputs or VerifyOutputs(B, N, gamma, p.device)
-    assert (o.B, o.N, o.gamma) == (B, N, gamma)
+    o = outputs or VerifyOutputs(p.shape[0], p.shape[1], gamma, p.device)
     if draft_ids is not None:
         o.draft_ids.copy_(draft_ids)
-    d = VerifyDesc(B=B, N=N, gamma=gamma, sample_draft=0 if draft_ids is not None else 1, seed=seed, offset=offset)
-    need = ctypes.c_size_t()
-    _check(lib().rdk_redistribute_verify_workspace_bytes(kernel.handle, mode, ctypes.byref(d), ctypes.byref(need)),
-           "rdk_redistribute_verify_workspace_bytes")
-    if getattr(o, "fused_ws", None) is None or o.fused_ws.numel() < need.value:
-        o.fused_ws = torch.empty(need.value, dtype=torch.uint8, device=p.device)
-    ldo = 0 if q_prime is None else _rows(q_prime)
-    _check(lib().rdk_redistribute_verify(kernel.handle, mode, ctypes.byref(d), _ptr(p), _kind_of(p, p_kind), _rows(p),
-                                         _ptr(q), _kind_of(q, q_kind), _rows(q), _ptr(q_prime), ldo, _ptr(o.draft_ids),
-                                         _ptr(o.accept), _ptr(o.alpha), _ptr(o.resid_mass), _ptr(o.resid_ids),
-                                         _ptr(o.n_accepted), _ptr(o.out_tokens), _ptr(o.fused_ws), o.fused_ws.numel(),
-                                         _stream()), "rdk_redistribute_verify")
+    _check((_native or native()).redistribute_verify(kernel, mode, p, q, seed, offset, gamma, p_kind, q_kind, draft_ids is None, o,
+                                                     q_prime), "rdk_redistribute_verify")
     return o
 
 
@@ -312,19 +300,11 @@ def rdk_sample_draft(kernel, q, seed, offset=0, q_kind="prob", q_prime=None, dra
     """Draft tokens drawn from q' = M^T TLI(q) before any target row exists.  Returns (draft_ids [B] int32,
     q_draft [B] fp32 = q' at the drafted id).  q_prime: [B,N] tensor that receives the rows (required unless the
     kernel is a top-k sparse one)."""
-    B = q.shape[0]
     if draft_ids is None:
-        draft_ids = torch.empty(B, dtype=torch.int32, device=q.device)
+        draft_ids = torch.empty(q.shape[0], dtype=torch.int32, device=q.device)
     if q_draft is None:
-        q_draft = torch.empty(B, dtype=torch.float32, device=q.device)
-    need = ctypes.c_size_t()
-    _check(lib().rdk_sample_draft_workspace_bytes(kernel.handle, B, ctypes.byref(need)), "rdk_sample_draft_workspace_bytes")
-    if getattr(kernel, "_draft_ws", None) is None or kernel._draft_ws.numel() < need.value:
-        kernel._draft_ws = torch.empty(need.value, dtype=torch.uint8, device=q.device)
-    ldo = 0 if q_prime is None else _rows(q_prime)
-    _check(lib().rdk_sample_draft(kernel.handle, _ptr(q), _kind_of(q, q_kind), _rows(q), B, seed, offset, _ptr(draft_ids),
-                                  _ptr(q_draft), _ptr(q_prime), ldo, _ptr(kernel._draft_ws), kernel._draft_ws.numel(),
-                                  _stream()), "rdk_sample_draft")
+        q_draft = torch.empty(q.shape[0], dtype=torch.float32, device=q.device)
+    _check((_native or native()).sample_draft(kernel, q, seed, offset, q_kind, q_prime, draft_ids, q_draft), "rdk_sample_draft")
     return draft_ids, q_draft
 
 
@@ -342,31 +322,19 @@ class MultiOutputs:
 def rdk_verify_multi(p, q_prime, C, seed, offset=0, p_kind="prob", cand_ids=None, outputs=None):
     """Several candidates per position: kept candidate (or the residual draw) for every row.
     cand_ids [B,C] given -> they are verified instead of drawn from q_prime."""
-    B, N = p.shape
+    B = p.shape[0]
     o = outputs or MultiOutputs(B, C, p.device)
     if cand_ids is not None:
         o.cand_ids.copy_(cand_ids.reshape(B, C))
-    d = MultiDesc(B=B, N=N, C=C, seed=seed, offset=offset, sample_candidates=0 if cand_ids is not None else 1)
-    kind = _kind_of(p, p_kind)
-    need = ctypes.c_size_t()
-    _check(lib().rdk_verify_multi_workspace_bytes(ctypes.byref(d), kind, ctypes.byref(need)), "rdk_verify_multi_workspace_bytes")
-    if o.ws is None or o.ws.numel() < need.value:
-        o.ws = torch.empty(need.value, dtype=torch.uint8, device=p.device)
-    _check(lib().rdk_verify_multi(ctypes.byref(d), _ptr(p), kind, _rows(p), _ptr(q_prime), _rows(q_prime), _ptr(o.cand_ids),
-                                  _ptr(o.accepted), _ptr(o.token), _ptr(o.resid_mass), _ptr(o.ws), o.ws.numel(), _stream()),
-           "rdk_verify_multi")
+    _check((_native or native()).verify_multi(p, q_prime, C, seed, offset, p_kind, cand_ids is None, o), "rdk_verify_multi")
     return o
 
 
 def rdk_tree_walk(child_node, accepted, token):
     """Walk through verified token trees.  child_node [S, nodes, C] int32; accepted, token [S * nodes] from
     rdk_verify_multi on the nodes.  Returns (n_accepted [S], out_tokens [S, nodes])."""
-    S, nodes, C = child_node.shape
-    assert child_node.is_contiguous() and accepted.numel() == S * nodes and token.numel() == S * nodes
-    n_acc = torch.zeros(S, dtype=torch.int32, device=child_node.device)
-    out = torch.full((S, nodes), -1, dtype=torch.int32, device=child_node.device)
-    _check(lib().rdk_tree_walk(S, nodes, C, _ptr(child_node), _ptr(accepted), _ptr(token), _ptr(n_acc), _ptr(out), _stream()),
-           "rdk_tree_walk")
+    status, n_acc, out = (_native or native()).tree_walk(child_node, accepted, token)
+    _check(status, "rdk_tree_walk")
     return n_acc, out
 
 
