@@ -1,5 +1,6 @@
 // C ABI of the RDK library: argument checks, storage / workspace carving, dispatch to the launchers.
 #include <atomic>
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -17,6 +18,18 @@ rdk_status_t hip_fail(hipError_t e, const char *what)
 {
     g_last_hip_error = std::string(what) + ": " + hipGetErrorString(e);
     return RDK_ERR_HIP;
+}
+
+uint64_t call_nonce()
+{
+    // successive values of a counter, spread over all 64 bits (the finaliser of SplitMix64: a bijection, so no value comes
+    // twice); the start differs from process to process
+    static std::atomic<uint64_t> counter{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull};
+    uint64_t z = counter.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return z ? z : 1;
 }
 
 // ---- optional event timing of selected kernels (used by benchmarks)

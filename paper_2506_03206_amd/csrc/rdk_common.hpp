@@ -10,6 +10,7 @@ namespace rdk {
 
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kChunk = 1024;     // ids summed by one wavefront step: 64 lanes x 4 x float4
+constexpr int kComputeUnits = 256;   // of an MI355X
 constexpr int kMaxSplits = 64;   // upper bound on workgroups sharing one row
 
 // Host-side description of a built kernel; every pointer points into the caller's storage blob.
@@ -58,6 +59,9 @@ rdk_status_t hip_fail(hipError_t e, const char *what);
         hipError_t e_ = hipGetLastError();                              \
         if (e_ != hipSuccess) return ::rdk::hip_fail(e_, name);         \
     } while (0)
+
+// A 64-bit number that no other call of this process uses (see scan_sequence).
+uint64_t call_nonce();
 
 struct RowInput {            // a [B, len] input of some kind
     const void *ptr;

@@ -2,13 +2,12 @@
 // verify call and by the fused redistribute+verify calls.
 //
 // Input: for every row three partial sums per block of BLOCK ids (sum q', sum max(0, p - q'),
-// sum min(p, q')), written by a streaming pass.  One wavefront per row (small batches; large ones spread the same
-// steps over four or eight wavefronts, see verify_finalize_wide_kernel and finish_row_quarters) then
+// sum min(p, q')), written by a streaming pass.  One workgroup per row (verify_finalize_wide_kernel, finish_row_quarters;
+// the bonus draw takes one wavefront per row) then
 //   1. adds the partials in fp64 (alpha, residual mass, sum q'), draws the Philox uniforms,
 //   2. finds the blocks in which the two inverse-CDF thresholds are crossed,
 //   3. re-reads (or re-computes) those blocks and scans them in fp64 for the exact ids,
-//   4. decides acceptance in fp64, and, when a workgroup holds one whole sequence, runs the
-//      first-rejection scan.
+//   4. decides acceptance in fp64, and, when its row is the last of its sequence to arrive, runs the first-rejection scan.
 // Where q' comes from is the `QP` policy: memory (a materialised q' row) or a formula.  A policy hands out q' of
 // four consecutive ids in kStages steps on a `Pending` record, each step issuing the loads whose addresses the
 // step before produced; the kernel runs step k for ALL blocks it needs before step k + 1, so a chain of dependent
@@ -27,13 +26,67 @@ struct FinalizeArgs {
     int p_splits;
     const float *part_q, *part_r, *part_a;   // [B, nblk]
     int nblk;
-    int rows_per_block;
-    bool scan_here;
     int32_t *draft_ids;
     uint8_t *accept;
     float *alpha, *resid_mass;
     int32_t *resid_ids, *n_accepted, *out_tokens;
+    uint64_t *seq_rec;       // [B, 2] one record per row for the per-sequence scan in the finish (NULL: the scan is not done there)
+    uint64_t nonce;          // its bits mark a record as written by this call
 };
+
+// ---- A meeting of workgroups without a second launch.  Each party stores its record -- what the others need of it, tagged
+// with bits of a number that no other call uses, so that the records need no clearing beforehand -- with device-scope
+// stores (they go through to the memory that all XCDs share), waits until it has arrived there, and reads the records of
+// all.  The party whose record arrives last finds all of them: it carries on alone, the others are done.  (Several may find
+// all of them: what follows has to give the same result when it is done twice.)  Nobody waits for anybody, so the order in
+// which workgroups run does not matter.  The one that carries on clears the records, so that a replay of the same call from
+// a HIP graph, which brings the same number again, starts from cleared ones.  Two round trips to memory, about 2.5 us,
+// where a launch of its own takes about 4; a release fence instead would write back the whole L2 of the XCD.
+template <typename T>
+__device__ __forceinline__ void agent_store(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T agent_load(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+constexpr int kScanMaxGamma = 63;   // one lane per token of a sequence: gamma drafts and the residual token
+
+// Steps 4-10 of Alg. 4 for the sequence of `row`, done by the row of the sequence whose record arrives last.  Called by one
+// wavefront of the row's workgroup, with the row's draft, residual token and accept flag in lane 0.
+// Record of a row: {draft, tag} and {residual token, tag with the accept flag as its lowest bit}.
+__device__ __forceinline__ void scan_sequence(const FinalizeArgs &a, int64_t row, int32_t dtok, int32_t rtok, uint8_t acc)
+{
+    if (a.seq_rec == nullptr) return;
+    const int g = a.d.gamma, lane = lane_id();
+    const int64_t s = row / g, b0 = s * g;
+    const uint64_t tag0 = a.nonce & 0xFFFFFFFF00000000ull, tag1 = (a.nonce << 32) & 0xFFFFFFFE00000000ull;
+    if (lane == 0) {
+        agent_store(a.seq_rec + 2 * row, tag0 | (uint32_t)dtok);
+        agent_store(a.seq_rec + 2 * row + 1, tag1 | ((uint64_t)(acc != 0) << 32) | (uint32_t)rtok);
+    }
+    wait_for_stores();
+    const bool in = lane < g;
+    uint64_t r0 = tag0, r1 = tag1;
+    if (in) {
+        r0 = agent_load(a.seq_rec + 2 * (b0 + lane));
+        r1 = agent_load(a.seq_rec + 2 * (b0 + lane) + 1);
+    }
+    if (__ballot((r0 & 0xFFFFFFFF00000000ull) != tag0 || (r1 & 0xFFFFFFFE00000000ull) != tag1) != 0ull) return;
+    if (in) {
+        agent_store(a.seq_rec + 2 * (b0 + lane), (uint64_t)0);
+        agent_store(a.seq_rec + 2 * (b0 + lane) + 1, (uint64_t)0);
+    }
+    const unsigned long long rejected = __ballot(in && ((r1 >> 32) & 1ull) == 0ull);
+    const int j = rejected ? __ffsll(rejected) - 1 : g;
+    if (lane == 0 && a.n_accepted) a.n_accepted[s] = j;
+    if (lane <= g && a.out_tokens)
+        a.out_tokens[s * (g + 1) + lane] = lane < j ? (int32_t)(uint32_t)r0 : (lane == j && in) ? (int32_t)(uint32_t)r1 : -1;
+}
 
 // q' read back from memory.
 struct QpMemory {
@@ -225,8 +278,6 @@ __device__ __forceinline__ int search_block1(float w, int base, double thr_local
     return pos != 0ull ? base + (63 - __clzll(pos)) : -1;
 }
 
-constexpr int kFinalizeRows = 8;   // rows (wavefronts) per workgroup at most: leaves 256 VGPRs per lane
-
 // Which row a one-row workgroup takes when the policy re-computes q' from tables that the kernel before it left in the
 // L2 of one XCD (the sparse product sweeps the rows of a 32-position block on one XCD when there are 8 k such blocks):
 // consecutive workgroup ids go to consecutive XCDs, so workgroup i takes a row of the blocks that XCD i % 8 has swept.
@@ -237,21 +288,18 @@ __device__ __forceinline__ int64_t xcd_row(int64_t i, int B)
     const int64_t per_xcd = B / 8;
     return (i % 8) * per_xcd + i / 8;
 }
-constexpr int kSpreadMinRows = 128;   // from this many rows on every row gets a workgroup of its own
+constexpr int kFinalizeRows = 4;   // rows (wavefronts) per workgroup of the bonus draw
 
-// The finish of one row by one wavefront: pq, prr, pa = the row's block sums of q', max(0, p - q') and min(p, q').
-// Writes the row's outputs and hands back the drafted id, the residual id and the accept flag (for a scan by the caller).
-// BLOCK = ids per block of partial sums: a multiple of 256, or 64 (then one id per lane).
-template <int KIND, int BLOCK, bool HAS_Q, class QP>
-__device__ __forceinline__ void finalize_row(const FinalizeArgs &a, const QP &qp, int64_t row, const float *pq, const float *prr,
-                                             const float *pa, int32_t &dtok_out, int32_t &rtok_out, uint8_t &acc_out)
+// The bonus draw t ~ p (Alg. 4, step 8, else-branch) of one row by one wavefront: part_r = the row's block sums of p.
+template <int KIND, int BLOCK>
+__global__ __launch_bounds__(kFinalizeRows * kWave) void bonus_finalize_kernel(FinalizeArgs a)
 {
-    constexpr int SUB = BLOCK >= 256 ? BLOCK / 256 : 1;
-    constexpr int kLanes = BLOCK >= 256 ? kWave : BLOCK / 4;      // lanes that hold ids of a block
-    constexpr int kRegBlocks = QP::kSpreadRows ? 32 : 8;          // block partials a lane keeps in registers
+    constexpr int SUB = BLOCK / 256;
+    constexpr int kRegBlocks = 8;                                   // block sums a lane keeps in registers
     const rdk_verify_desc_t &d = a.d;
-    const int lane = lane_id();
-    const int N = d.N;
+    const int wid = threadIdx.x / kWave, lane = lane_id();
+    const int64_t row = (int64_t)blockIdx.x * kFinalizeRows + wid;
+    if (row >= d.B) return;                                         // a whole wavefront; the kernel has no barrier
     const void *pr = row_ptr<KIND>(a.p, a.ldp, row);
     float m = 0.f, inv = 1.f;
     if (KIND != RDK_PROB_F32) {
@@ -260,195 +308,38 @@ __device__ __forceinline__ void finalize_row(const FinalizeArgs &a, const QP &qp
         inv = 1.0f / rs.s;
     }
     const float pfill = KIND == RDK_PROB_F32 ? 0.f : -INFINITY;
+    const float *part = a.part_r + row * a.nblk;
     const int per_lane = ((a.nblk + kWave - 1) / kWave + 3) & ~3;   // blocks per lane, in whole groups of four
-    const bool draw_draft = HAS_Q && d.sample_draft;
-
-    // 1. block partials (one round trip; kept in registers when they fit), the row's own constants and the
-    //    uniforms meanwhile
     const bool in_regs = per_lane <= kRegBlocks;
-    float vq[kRegBlocks], vr[kRegBlocks], va[kRegBlocks];
-    double lane_r, lane_q = 0.0, lane_a = 0.0;
-    if (in_regs) {
-        load_partials(prr, a.nblk, per_lane, vr);
-        if (draw_draft) load_partials(pq, a.nblk, per_lane, vq);
-        if (HAS_Q) load_partials(pa, a.nblk, per_lane, va);
-    }
-    const typename QP::Row qrow = qp.row(row);
-    if (in_regs) {
-        lane_r = sum_partials(vr);
-        if (draw_draft) lane_q = sum_partials(vq);
-        if (HAS_Q) lane_a = sum_partials(va);
-    } else {
-        lane_r = lane_partial_sum(prr, a.nblk, per_lane);
-        if (draw_draft) lane_q = lane_partial_sum(pq, a.nblk, per_lane);
-        if (HAS_Q) lane_a = lane_partial_sum(pa, a.nblk, per_lane);
-    }
-    int32_t dtok = (HAS_Q && !d.sample_draft) ? a.draft_ids[row] : -1;
+    float v[kRegBlocks];
+    if (in_regs) load_partials(part, a.nblk, per_lane, v);
+    const double lane_r = in_regs ? sum_partials(v) : lane_partial_sum(part, a.nblk, per_lane);
     uint32_t words[4];
     position_words(d.seed, d.offset + (uint64_t)row, words);
     const double R = wave_sum(lane_r);
-    const double Q = draw_draft ? wave_sum(lane_q) : 0.0;
-    const double A = HAS_Q ? wave_sum(lane_a) : 0.0;
-
-    // 2. the blocks that hold the two prefix-sum crossings
-    double thr_d = 0.0, thr_r = 0.0, before_d = 0.0, before_r = 0.0;
-    int blk_d = -1, blk_r = -1;
-    if (draw_draft && Q > 0.0) {
-        thr_d = word_to_unit(words[0]) * Q;
-        blk_d = in_regs ? locate_block_regs(vq, a.nblk, per_lane, lane_q, thr_d, before_d)
-                        : locate_block(pq, a.nblk, per_lane, lane_q, thr_d, before_d);
-    }
-    if (R > 0.0) {
-        thr_r = word_to_unit(words[HAS_Q ? 2 : 3]) * R;
-        blk_r = in_regs ? locate_block_regs(vr, a.nblk, per_lane, lane_r, thr_r, before_r)
-                        : locate_block(prr, a.nblk, per_lane, lane_r, thr_r, before_r);
-    }
-
-    // 3. both blocks are fetched together (q' and the target weights of each), then scanned.  A draft token
-    //    that the caller supplied may lie anywhere: its two values are requested in the same round trip.
-    const int base_d = max(blk_d, 0) * BLOCK, base_r = max(blk_r, 0) * BLOCK;
-    const bool same = draw_draft && blk_r == blk_d;
-    float pd_w = 0.f, qd = 0.f;
-    const bool given = HAS_Q && !d.sample_draft && dtok >= 0 && dtok < N;
-    if (given) {
-        pd_w = to_weight<KIND>(load1<KIND>(pr, dtok), m, inv);
-        qd = qrow.load1(dtok);
-    }
-    const bool want_r = HAS_Q && !same;
     int32_t rtok = -1;
-    if constexpr (BLOCK == 64) {
-        // blocks of 64 ids, one id per lane: the policy's chain of dependent loads is as short as it gets (one
-        // slot, one table row, its gathers) and all 64 lanes share it
-        typename QP::Row::Pending1 td, tr;
-        const int id_d = base_d + lane, id_r = base_r + lane;
-        if (draw_draft) qrow.template stage1<0>(td, id_d);
-        if (want_r) qrow.template stage1<0>(tr, id_r);
-        float pdv = pfill, wpv = pfill;
-        if (draw_draft && id_d < N) pdv = load1<KIND>(pr, id_d);
-        if (!same && id_r < N) wpv = load1<KIND>(pr, id_r);
-        if (draw_draft) qrow.template stage1<1>(td, id_d);
-        if (want_r) qrow.template stage1<1>(tr, id_r);
-        if (draw_draft) qrow.template stage1<2>(td, id_d);
-        if (want_r) qrow.template stage1<2>(tr, id_r);
-        const float wdv = draw_draft ? qrow.result1(td, id_d) : 0.f;
-        float wqv = want_r ? qrow.result1(tr, id_r) : 0.f;
-        if (same) {
-            wpv = pdv;
-            wqv = wdv;
-        }
-        if (blk_d >= 0) {
-            dtok = search_block1(wdv, base_d, thr_d - before_d);
-            if (dtok >= 0) {
-                qd = lane_value(wdv, dtok - base_d);
-                pd_w = to_weight<KIND>(lane_value(pdv, dtok - base_d), m, inv);
-            }
-        }
-        if (blk_r >= 0) {
-            wpv = to_weight<KIND>(wpv, m, inv);
-            if (HAS_Q) wpv = fmaxf(wpv - wqv, 0.f);
-            rtok = search_block1(wpv, base_r, thr_r - before_r);
-        }
-    } else {
-        float4 wd[SUB], pd[SUB], wp[SUB], wq[SUB];
-        const bool holds = lane < kLanes;
-        typename QP::Row::Pending td[SUB], tr[SUB];
-        const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f), fill4 = make_float4(pfill, pfill, pfill, pfill);
-        stage_block<0, SUB>(qrow, td, base_d, draw_draft && holds);
-        stage_block<0, SUB>(qrow, tr, base_r, want_r && holds);
+    if (R > 0.0) {
+        const double thr = word_to_unit(words[3]) * R;
+        double before = 0.0;
+        const int blk = in_regs ? locate_block_regs(v, a.nblk, per_lane, lane_r, thr, before)
+                                : locate_block(part, a.nblk, per_lane, lane_r, thr, before);
+        if (blk >= 0) {
+            const int base = blk * BLOCK;
+            float4 w[SUB];
 #pragma unroll
-        for (int i = 0; i < SUB; ++i) {
-            if (draw_draft) pd[i] = holds ? load4<KIND>(pr, base_d + i * 256 + lane * 4, N, a.vec_p, pfill) : fill4;
-            if (!same) wp[i] = holds ? load4<KIND>(pr, base_r + i * 256 + lane * 4, N, a.vec_p, pfill) : fill4;
-        }
-        if (QP::kStages > 1) {
-            stage_block<1, SUB>(qrow, td, base_d, draw_draft && holds);
-            stage_block<1, SUB>(qrow, tr, base_r, want_r && holds);
-        }
-        if (QP::kStages > 2) {
-            stage_block<2, SUB>(qrow, td, base_d, draw_draft && holds);
-            stage_block<2, SUB>(qrow, tr, base_r, want_r && holds);
-        }
+            for (int i = 0; i < SUB; ++i) w[i] = load4<KIND>(pr, base + i * 256 + lane * 4, d.N, a.vec_p, pfill);
 #pragma unroll
-        for (int i = 0; i < SUB; ++i) {
-            if (draw_draft) wd[i] = holds ? qrow.result(td[i], (int64_t)base_d + i * 256 + lane * 4) : zero4;
-            if (want_r) wq[i] = holds ? qrow.result(tr[i], (int64_t)base_r + i * 256 + lane * 4) : zero4;
-            if (same) {
-                wp[i] = pd[i];
-                wq[i] = wd[i];
-            }
-        }
-        if (blk_d >= 0) {
-            dtok = search_block<SUB>(wd, base_d, thr_d - before_d);
-            // 4. the accept test needs p and q' at the draft token: both sit in the registers of one lane
-            if (dtok >= 0) {
-                const int off = dtok - base_d, i = off / 256, src = (off % 256) / 4, e = off % 4;
-                qd = lane_value(pick<SUB>(wd, i, e), src);
-                pd_w = to_weight<KIND>(lane_value(pick<SUB>(pd, i, e), src), m, inv);
-            }
-        }
-        if (blk_r >= 0) {
-#pragma unroll
-            for (int i = 0; i < SUB; ++i) {
-                wp[i].x = to_weight<KIND>(wp[i].x, m, inv);
-                wp[i].y = to_weight<KIND>(wp[i].y, m, inv);
-                wp[i].z = to_weight<KIND>(wp[i].z, m, inv);
-                wp[i].w = to_weight<KIND>(wp[i].w, m, inv);
-                if (HAS_Q) {
-                    wp[i].x = fmaxf(wp[i].x - wq[i].x, 0.f);
-                    wp[i].y = fmaxf(wp[i].y - wq[i].y, 0.f);
-                    wp[i].z = fmaxf(wp[i].z - wq[i].z, 0.f);
-                    wp[i].w = fmaxf(wp[i].w - wq[i].w, 0.f);
-                }
-            }
-            rtok = search_block<SUB>(wp, base_r, thr_r - before_r);
+            for (int i = 0; i < SUB; ++i)
+                w[i] = make_float4(to_weight<KIND>(w[i].x, m, inv), to_weight<KIND>(w[i].y, m, inv), to_weight<KIND>(w[i].z, m, inv),
+                                   to_weight<KIND>(w[i].w, m, inv));
+            rtok = search_block<SUB>(w, base, thr - before);
         }
     }
-    const bool d_ok = HAS_Q && dtok >= 0 && dtok < N;
-    uint8_t acc = 0;
-    if (d_ok) acc = (word_to_unit(words[1]) * (double)qd < (double)pd_w) ? 1 : 0;
     if (lane == 0) {
-        if (draw_draft) a.draft_ids[row] = dtok;
-        a.accept[row] = acc;
-        if (a.alpha) a.alpha[row] = (float)A;
+        a.accept[row] = 0;
+        if (a.alpha) a.alpha[row] = 0.f;
         if (a.resid_mass) a.resid_mass[row] = (float)R;
         a.resid_ids[row] = rtok;
-    }
-    dtok_out = dtok;
-    rtok_out = rtok;
-    acc_out = acc;
-}
-
-template <int KIND, int BLOCK, bool HAS_Q, class QP>
-__global__ __launch_bounds__(QP::kSpreadRows ? kWave : kFinalizeRows * kWave) void verify_finalize_kernel(FinalizeArgs a, QP qp)
-{
-    __shared__ int32_t sh_draft[kFinalizeRows], sh_resid[kFinalizeRows];
-    __shared__ uint8_t sh_acc[kFinalizeRows];
-    const rdk_verify_desc_t &d = a.d;
-    const int wid = threadIdx.x / kWave, lane = lane_id();
-    const int64_t row = QP::kSpreadRows ? xcd_row(blockIdx.x, d.B) : (int64_t)blockIdx.x * a.rows_per_block + wid;
-    if (row < d.B) {
-        int32_t dtok, rtok;
-        uint8_t acc;
-        finalize_row<KIND, BLOCK, HAS_Q, QP>(a, qp, row, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk,
-                                             dtok, rtok, acc);
-        if (a.scan_here && lane == 0) {
-            sh_draft[wid] = dtok;
-            sh_resid[wid] = rtok;
-            sh_acc[wid] = acc;
-        }
-    }
-    if (a.scan_here) {  // the workgroup holds exactly one sequence: steps 4-10 of Alg. 4
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const int g = d.gamma;
-            int j = 0;
-            while (j < g && sh_acc[j]) ++j;
-            if (a.n_accepted) a.n_accepted[blockIdx.x] = j;
-            if (a.out_tokens) {
-                int32_t *o = a.out_tokens + (int64_t)blockIdx.x * (g + 1);
-                for (int i = 0; i <= g; ++i) o[i] = i < j ? sh_draft[i] : (i == j && j < g) ? sh_resid[i] : -1;
-            }
-        }
     }
 }
 
@@ -456,7 +347,7 @@ __global__ __launch_bounds__(QP::kSpreadRows ? kWave : kFinalizeRows * kWave) vo
 // of 64 ids).  A lone wavefront pays the full latency of every dependent instruction, and half of its time went into
 // adding up and searching the three kinds of block sums one after the other; here wavefront 0 takes the sums of q' and
 // the draft's block, wavefront 1 the residual sums and the residual's block, wavefront 2 alpha (and the two values of a
-// draft the caller supplied), each with the routines of finalize_row, so the results are the same bits.
+// draft the caller supplied), each with the routines that a lone wavefront would use.
 template <int KIND, class QP>
 __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(FinalizeArgs a, QP qp)
 {
@@ -538,10 +429,11 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
     }
     __syncthreads();
     // 3. the accept test and the row's outputs
+    int32_t dtok = -1;
+    uint8_t acc = 0;
     if (threadIdx.x == 0) {
-        const int32_t dtok = draw_draft ? sh_i[0] : a.draft_ids[row];
+        dtok = draw_draft ? sh_i[0] : a.draft_ids[row];
         const bool d_ok = dtok >= 0 && dtok < N;
-        uint8_t acc = 0;
         if (d_ok) acc = (word_to_unit(words[1]) * (double)sh_f[0] < (double)sh_f[1]) ? 1 : 0;
         if (draw_draft) a.draft_ids[row] = dtok;
         a.accept[row] = acc;
@@ -549,6 +441,7 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
         if (a.resid_mass) a.resid_mass[row] = (float)sh_d[1];
         a.resid_ids[row] = sh_i[1];
     }
+    if (wid == 0) scan_sequence(a, row, dtok, sh_i[1], acc);
 }
 
 // ---- The finish of one row by eight wavefronts, for block sums over 1024 ids (Alg. 4, steps 2 and 4-6 for one position).
@@ -560,7 +453,7 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
 //   3. with the totals of the quarters before its own, each finds the crossing in its quarter (or its last id with
 //      a positive weight, the answer when rounding leaves no crossing);
 //   4. the first wavefront picks the first crossing, tests acceptance in fp64 and writes the row's outputs.
-// The arithmetic, its order and the conventions are those of the one-wavefront finish (finalize_row, search_block).
+// The arithmetic, its order and the conventions are those of the one-wavefront search (search_block).
 // Every wavefront of the workgroup calls it (more than eight may; the others only meet the barriers).
 //   scratch        kFinishFloats floats of LDS
 //   sq, sr, sa     the row's nblk block sums of q', max(0, p - q') and min(p, q') (LDS or memory)
@@ -568,9 +461,10 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
 //   words          the position's four uniforms (Alg. 4: draft, accept, residual, bonus)
 //   quads          where q' comes from: begin() issues the loads that need no target value, end() hands out q' of four
 //                  ids given their target weights, at() q' of one id
+//   SCAN           whether the per-sequence scan follows (scan_sequence)
 constexpr int kFinishFloats = 64;
 
-template <int KIND, class Quads>
+template <int KIND, bool SCAN, class Quads>
 __device__ __forceinline__ void finish_row_quarters(float *scratch, const float *sq, const float *sr, const float *sa, int nblk,
                                                     const FinalizeArgs &fin, int64_t row, const void *pr, float pm, float pinv,
                                                     int N, bool vec_p, const Quads &quads, const uint32_t (&words)[4], int wid,
@@ -659,8 +553,10 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
         if (lane == 0) fc[wid] = make_float4(__int_as_float(hit), __int_as_float(last_pos), qc, pc);
     }
     __syncthreads();
+    int tok[2] = {-1, -1};
+    int32_t dtok = -1;
+    uint8_t acc = 0;
     if (threadIdx.x == 0) {
-        int tok[2] = {-1, -1};
         float qd = 0.f, pd_w = 0.f;
         for (int b = 0; b < 2; ++b) {
             if (fi[b] < 0) continue;
@@ -679,7 +575,7 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
                 }
             }
         }
-        int32_t dtok = tok[0];
+        dtok = tok[0];
         if (!draw_draft) {                            // the caller's draft: its two values are fetched here
             dtok = fin.draft_ids[row];
             if (dtok >= 0 && dtok < N) {
@@ -688,7 +584,6 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
             }
         }
         const bool d_ok = dtok >= 0 && dtok < N;
-        uint8_t acc = 0;
         if (d_ok) acc = (word_to_unit(words[1]) * (double)qd < (double)pd_w) ? 1 : 0;
         if (draw_draft) fin.draft_ids[row] = dtok;
         fin.accept[row] = acc;
@@ -696,6 +591,7 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
         if (fin.resid_mass) fin.resid_mass[row] = (float)fd[3];
         fin.resid_ids[row] = tok[1];
     }
+    if (SCAN && wid == 0) scan_sequence(fin, row, dtok, tok[1], acc);
 }
 
 // q' of four ids from a policy's row (its steps run back to back: one quarter of a block per wavefront).
@@ -738,7 +634,7 @@ __global__ __launch_bounds__(8 * kWave) void verify_finalize_quarters_kernel(Fin
     position_words(d.seed, d.offset + (uint64_t)row, words);
     const typename QP::Row qrow = qp.row(row);
     const PolicyQuads<typename QP::Row, QP::kStages> quads{qrow};
-    finish_row_quarters<KIND>(scratch, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, a.nblk, a, row, pr,
+    finish_row_quarters<KIND, true>(scratch, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, a.nblk, a, row, pr,
                               m, inv, d.N, a.vec_p, quads, words, wid, lane);
 }
 
@@ -831,40 +727,46 @@ __global__ void sequence_scan_kernel(int S, int gamma, const int32_t *draft_ids,
 rdk_status_t launch_sequence_scan(const rdk_verify_desc_t &d, const int32_t *draft_ids, const uint8_t *accept,
                                   const int32_t *resid_ids, int32_t *n_accepted, int32_t *out_tokens, hipStream_t st);
 
+// Whether the finish itself runs the per-sequence scan of a call, and the records for it.  rec: [B, 2] uint64 of scratch.
+inline void set_scan(FinalizeArgs &a, uint64_t *rec)
+{
+    const bool wanted = a.d.gamma > 0 && a.d.gamma <= kScanMaxGamma && (a.n_accepted || a.out_tokens);
+    a.seq_rec = wanted ? rec : nullptr;
+    a.nonce = wanted ? call_nonce() : 0;
+}
+
+// The scan as a launch of its own where the finish has not done it.
+inline rdk_status_t scan_if_left(const FinalizeArgs &a, hipStream_t st)
+{
+    if (a.d.gamma > 0 && !a.seq_rec && (a.n_accepted || a.out_tokens))
+        return launch_sequence_scan(a.d, a.draft_ids, a.accept, a.resid_ids, a.n_accepted, a.out_tokens, st);
+    return RDK_OK;
+}
+
+// rec: [B, 2] uint64 of scratch for the per-sequence scan.
 template <int KIND, int BLOCK, bool HAS_Q, class QP>
-rdk_status_t launch_finalize(FinalizeArgs a, QP qp, hipStream_t st)
+rdk_status_t launch_finalize(FinalizeArgs a, QP qp, uint64_t *rec, hipStream_t st)
 {
     const rdk_verify_desc_t &d = a.d;
-    // One wavefront per row is bound by its own chain of dependent steps, and eight of them on one compute unit share
-    // its four vector units: a large batch gets a workgroup per row (and the per-sequence scan a launch of its own),
-    // a small one keeps a sequence together and scans it in place.  A policy that re-computes q' is heavy on the vector
-    // memory pipe of its compute unit and always gets one per row.
-    const bool spread = QP::kSpreadRows || d.B >= kSpreadMinRows;
-    a.scan_here = d.gamma >= 1 && d.gamma <= kFinalizeRows && !spread;
-    a.rows_per_block = a.scan_here ? d.gamma : (spread ? 1 : 4);
-    const int blocks = (d.B + a.rows_per_block - 1) / a.rows_per_block;
-    constexpr bool kWide = QP::kSpreadRows && BLOCK == 64 && HAS_Q;   // four wavefronts per row, one id per lane
-    constexpr bool kQuarters = BLOCK == 1024 && HAS_Q;                // eight wavefronts per row when rows are spread
-    bool launched = false;
-    if constexpr (kWide) {
-        RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_wide_kernel<KIND, QP>), dim3((unsigned)d.B), dim3(4 * kWave), 0,
-                         st, a, qp);
-        launched = true;
-    } else if constexpr (kQuarters) {
-        if (spread) {
-            RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_quarters_kernel<KIND, QP>), dim3((unsigned)d.B),
-                             dim3(8 * kWave), 0, st, a, qp);
-            launched = true;
-        }
+    if constexpr (!HAS_Q) {
+        // the bonus draw: one wavefront per row, four rows per workgroup
+        const int blocks = (d.B + kFinalizeRows - 1) / kFinalizeRows;
+        RDK_TIMED_LAUNCH("verify_finalize_kernel", (bonus_finalize_kernel<KIND, BLOCK>), dim3(blocks), dim3(kFinalizeRows * kWave), 0, st, a);
+        RDK_LAUNCH_CHECK("verify_finalize_kernel");
+        return RDK_OK;
+    } else {
+        // One wavefront per row is bound by its own chain of dependent steps: every row gets a workgroup, four wavefronts
+        // for blocks of 64 ids whose q' is re-computed, eight for blocks of 1024.
+        set_scan(a, rec);
+        if constexpr (BLOCK == 64)
+            RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_wide_kernel<KIND, QP>), dim3((unsigned)d.B), dim3(4 * kWave), 0,
+                             st, a, qp);
+        else
+            RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_quarters_kernel<KIND, QP>), dim3((unsigned)d.B), dim3(8 * kWave),
+                             0, st, a, qp);
+        RDK_LAUNCH_CHECK("verify_finalize_kernel");
+        return scan_if_left(a, st);
     }
-    if (!launched) {
-        RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_kernel<KIND, BLOCK, HAS_Q, QP>), dim3(blocks),
-                         dim3(a.rows_per_block * kWave), 0, st, a, qp);
-    }
-    RDK_LAUNCH_CHECK("verify_finalize_kernel");
-    if (d.gamma > 0 && !a.scan_here && (a.n_accepted || a.out_tokens))
-        return launch_sequence_scan(d, a.draft_ids, a.accept, a.resid_ids, a.n_accepted, a.out_tokens, st);
-    return RDK_OK;
 }
 
 }  // namespace rdk

@@ -741,7 +741,7 @@ struct Eq3Quads {
 // The finish of a row inside the one-pass kernels, out of the three block sums per chunk in LDS and the position's
 // uniforms that the kernel left behind them (all wavefronts of the workgroup have to call it).
 // pm, pinv: softmax maximum and 1 / normaliser of a logit target row (0 and 1 for probabilities).
-template <int PK, int QK, class RCP>
+template <int PK, int QK, bool SCAN, class RCP>
 __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, int l_sum_r, int l_sum_a,
                                            const FinalizeArgs &fin, int64_t row, int nchunks,
                                            const void *pr, float pm, float pinv, const void *qr, float qm,
@@ -751,7 +751,7 @@ __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, i
     const uint32_t *fw = (const uint32_t *)(lds + l_fin + kFinishFloats);
     const uint32_t words[4] = {fw[0], fw[1], fw[2], fw[3]};
     const Eq3Quads<QK, RCP> quads{lane_map, chunk_lo, slot_of, qr, qm, nzs, ths, rcp, N};
-    finish_row_quarters<PK>(lds + l_fin, lds + l_sum_q, lds + l_sum_r, lds + l_sum_a, nchunks, fin, row, pr, pm, pinv, N, vec_p,
+    finish_row_quarters<PK, SCAN>(lds + l_fin, lds + l_sum_q, lds + l_sum_r, lds + l_sum_a, nchunks, fin, row, pr, pm, pinv, N, vec_p,
                             quads, words, wid, lane);
 }
 
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_kernel(const float *p,
     __syncthreads();
 
     // ---- the finish of the row (draws, accept test), spread over the wavefronts
-    row_finish<RDK_PROB_F32, QK>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, 0.f, 1.f, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp,
+    row_finish<RDK_PROB_F32, QK, true>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, 0.f, 1.f, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp,
                                  wid, lane);
 }
 
@@ -1230,7 +1230,7 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
     __syncthreads();
 
     // ---- the finish of the row (draws, accept test), spread over the wavefronts
-    row_finish<PK, QK>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid,
+    row_finish<PK, QK, false>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid,
                        lane);
 }
 
@@ -1275,11 +1275,15 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
 {
     LinearWs w = carve(h, B, ws);
     rdk_status_t rc;
+    // the fused call: three block sums per 1024 ids and row, one record per row for the per-sequence scan
+    const int nchunks = (h.N + kChunk - 1) / kChunk;
+    const size_t per = align_up((size_t)B * nchunks * sizeof(float), 256);
+    char *fused_ws = (char *)ws + taylor_workspace_bytes(h, B);
+    uint64_t *seq_rec = (uint64_t *)(fused_ws + 3 * per);
     {
         // the fused call without q': one pass over the target rows, one workgroup per position, when the kept target
         // values of a row fit the LDS of a compute unit and there are enough positions to fill the chip (logit rows: from
         // the vocabulary size on at which the series of their chunk sums are exact to fp32 rounding)
-        const int nchunks = (h.N + kChunk - 1) / kChunk;
         const size_t lds_bytes = (size_t)row_lds_layout(h.n, nchunks).total * sizeof(float);
         const int min_N = PK == RDK_PROB_F32 ? 2 : kOnePassMinN;
         if (c && !out && h.N >= min_N && B >= kRowMinBatch && lds_bytes <= row_lds_limit()) {
@@ -1311,6 +1315,10 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             fa.nblk = nchunks;
             fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
             fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
+            // with more positions than compute units the workgroups take turns, and each would add its round trips to the
+            // chain of its unit: the scan is a launch of its own then.  So it is for logit rows, whose kernel has no scalar
+            // registers left for it (they spill inside its loops: 203 us against 186 at the qwen_extreme shape).
+            if (PK == RDK_PROB_F32 && B <= kComputeUnits) set_scan(fa, seq_rec);
             const bool series = h.N >= kRowSeriesMinN;
 #define RDK_ROW_LAUNCH(KERNEL, PPTR)                                                                                        \
     RDK_TIMED_LAUNCH("taylor_row_kernel", KERNEL, dim3((unsigned)B), dim3(kRowThreads), lds_bytes, st, PPTR, p.ld, q.ptr, q.ld,  \
@@ -1324,9 +1332,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             }
 #undef RDK_ROW_LAUNCH
             RDK_LAUNCH_CHECK("taylor_row_kernel");
-            if (c->d.gamma > 0 && (fa.n_accepted || fa.out_tokens))
-                return launch_sequence_scan(c->d, fa.draft_ids, fa.accept, fa.resid_ids, fa.n_accepted, fa.out_tokens, st);
-            return RDK_OK;
+            return scan_if_left(fa, st);
         }
     }
     // logit target rows of a large vocabulary: the first pass of Eq. 3 also delivers the softmax statistics
@@ -1374,10 +1380,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         RDK_LAUNCH_CHECK("taylor_write_kernel");
         return RDK_OK;
     }
-    const int nchunks = (h.N + kChunk - 1) / kChunk;
-    const size_t per = align_up((size_t)B * nchunks * sizeof(float), 256);
-    char *pp = (char *)ws + taylor_workspace_bytes(h, B);
-    float *part_q = (float *)pp, *part_r = (float *)(pp + per), *part_a = (float *)(pp + 2 * per);
+    float *part_q = (float *)fused_ws, *part_r = (float *)(fused_ws + per), *part_a = (float *)(fused_ws + 2 * per);
     {
         RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, true>), grid, dim3(kThreads), 0, st, a, vec_o, out,
                          ldo, part_q, part_r, part_a);
@@ -1391,7 +1394,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     fa.nblk = nchunks;
     fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
     fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
-    return launch_finalize<PK, 1024, true, QpTaylor<PK, QK>>(fa, QpTaylor<PK, QK>{a}, st);
+    return launch_finalize<PK, 1024, true, QpTaylor<PK, QK>>(fa, QpTaylor<PK, QK>{a}, seq_rec, st);
 }
 
 template <int QK>
@@ -1421,7 +1424,8 @@ size_t taylor_workspace_bytes(const KernelHandle &h, int32_t B)
 size_t taylor_fused_workspace_bytes(const KernelHandle &h, int32_t B)
 {
     const int nchunks = (h.N + kChunk - 1) / kChunk;
-    return taylor_workspace_bytes(h, B) + 3 * align_up((size_t)B * nchunks * sizeof(float), 256);
+    return taylor_workspace_bytes(h, B) + 3 * align_up((size_t)B * nchunks * sizeof(float), 256) +
+           align_up((size_t)B * 2 * sizeof(uint64_t), 256);
 }
 
 rdk_status_t launch_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B, float *out, int64_t ldo, void *ws,

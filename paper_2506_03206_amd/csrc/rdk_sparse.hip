@@ -415,7 +415,7 @@ __global__ __launch_bounds__(kThreads) void sparse_product_kernel(SparseArgs a, 
 // q' of one position recomputed from the sparse kernel (the finalize step needs two 64-id blocks of it).
 struct QpSparse {
     static constexpr bool kSpreadRows = true;
-    static constexpr int kStages = 3;
+    
     SparseArgs a;
     struct Row {
         const int32_t *slot_of;
@@ -594,7 +594,7 @@ size_t fused_extra_bytes(const KernelHandle &h, int32_t B)
 {
     const size_t blocks = (size_t)((h.N + kTileIds - 1) / kTileIds) * (kTileIds / kSubIds);
     return align_up((size_t)B * kMaxSplits * sizeof(SoftStat), 256) + align_up((size_t)B * sizeof(SoftStat), 256) +
-           3 * align_up((size_t)B * blocks * sizeof(float), 256);
+           3 * align_up((size_t)B * blocks * sizeof(float), 256) + align_up((size_t)B * 2 * sizeof(uint64_t), 256);
 }
 
 SparseArgs make_args(const KernelHandle &h, const SparseWs &w, int32_t B, float *out, int64_t ldo)
@@ -662,7 +662,8 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     const size_t per = align_up((size_t)B * blocks * sizeof(float), 256);
     f.part_q = (float *)p; p += per;
     f.part_r = (float *)p; p += per;
-    f.part_a = (float *)p;
+    f.part_a = (float *)p; p += per;
+    uint64_t *seq_rec = (uint64_t *)p;   // [B, 2]
     rdk_status_t rc;
     if (PK != RDK_PROB_F32) {
         rc = launch_row_stats<PK>(c.p, h.N, B, p_splits, ppart, st);
@@ -688,7 +689,7 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     fa.nblk = (int)blocks;
     fa.draft_ids = c.draft_ids; fa.accept = c.accept; fa.alpha = c.alpha; fa.resid_mass = c.resid_mass;
     fa.resid_ids = c.resid_ids; fa.n_accepted = c.n_accepted; fa.out_tokens = c.out_tokens;
-    return launch_finalize<PK, kSubIds, true, QpSparse>(fa, QpSparse{a}, st);
+    return launch_finalize<PK, kSubIds, true, QpSparse>(fa, QpSparse{a}, seq_rec, st);
 }
 
 template <int QK>

@@ -23,6 +23,7 @@ constexpr int kWavesPerBlock = kStreamThreads / kWave;
 struct VerifyWs {
     float *part_q, *part_r, *part_a;  // [B, nchunks]
     SoftStat *pstat;                  // [B, stat_splits] (logit input only)
+    uint64_t *seq_rec;                // [B, 2] records of the per-sequence scan
     int nchunks, stat_splits;
 };
 
@@ -38,7 +39,8 @@ VerifyWs carve(const rdk_verify_desc_t &d, void *ws)
     w.part_q = (float *)p; p += per;
     w.part_r = (float *)p; p += per;
     w.part_a = (float *)p; p += per;
-    w.pstat = (SoftStat *)p;
+    w.pstat = (SoftStat *)p; p += align_up((size_t)d.B * w.stat_splits * sizeof(SoftStat), 256);
+    w.seq_rec = (uint64_t *)p;
     return w;
 }
 
@@ -172,7 +174,7 @@ rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, 
     fa.draft_ids = draft_ids; fa.accept = accept; fa.alpha = alpha; fa.resid_mass = resid_mass;
     fa.resid_ids = resid_ids; fa.n_accepted = n_accepted; fa.out_tokens = out_tokens;
     QpMemory qp{q, ldq, vec_q, d.N};
-    return launch_finalize<KIND, 1024, HAS_Q, QpMemory>(fa, qp, st);
+    return launch_finalize<KIND, 1024, HAS_Q, QpMemory>(fa, qp, w.seq_rec, st);
 }
 
 // Sums of each 1024-id block of materialised rows (the draft draw from a q' that sits in memory).
@@ -218,7 +220,8 @@ size_t verify_workspace_bytes(const rdk_verify_desc_t &d)
 {
     const int nchunks = chunks_of(d.N);
     const size_t per = align_up((size_t)d.B * nchunks * sizeof(float), 256);
-    return 3 * per + align_up((size_t)d.B * row_splits(d.B, d.N, kWavesPerBlock) * sizeof(SoftStat), 256);
+    return 3 * per + align_up((size_t)d.B * row_splits(d.B, d.N, kWavesPerBlock) * sizeof(SoftStat), 256) +
+           align_up((size_t)d.B * 2 * sizeof(uint64_t), 256);
 }
 
 rdk_status_t launch_verify(const rdk_verify_desc_t &d, RowInput p, const float *q_prime, int64_t ldq, int32_t *draft_ids,
