@@ -343,41 +343,39 @@ __global__ __launch_bounds__(kFinalizeRows * kWave) void bonus_finalize_kernel(F
     }
 }
 
-// The finish of one row by a workgroup of four wavefronts, for the policies that re-compute q' one id per lane (blocks
-// of 64 ids).  A lone wavefront pays the full latency of every dependent instruction, and half of its time went into
-// adding up and searching the three kinds of block sums one after the other; here wavefront 0 takes the sums of q' and
-// the draft's block, wavefront 1 the residual sums and the residual's block, wavefront 2 alpha (and the two values of a
-// draft the caller supplied), each with the routines that a lone wavefront would use.
-template <int KIND, class QP>
-__global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(FinalizeArgs a, QP qp)
+// The finish of one row by a workgroup, for the policies that re-compute q' one id per lane (blocks of 64 ids).  A lone
+// wavefront pays the full latency of every dependent instruction, and half of its time went into adding up and searching the
+// three kinds of block sums one after the other; here wavefront 0 takes the sums of q' and the draft's block, wavefront 1
+// the residual sums and the residual's block, wavefront 2 alpha (and the two values of a draft the caller supplied).  Every
+// wavefront of the workgroup calls it.
+//   REGS               block sums a lane keeps in registers (one kind per wavefront)
+//   part_q, _r, _a     the row's a.nblk block sums of q', max(0, p - q') and min(p, q') (LDS or memory)
+//   m, inv             softmax maximum and 1 / normaliser of a logit target row (0 and 1 for probabilities)
+struct WideScratch {   // LDS
+    double d[2];       // alpha, residual mass
+    int i[2];          // the drafted id, the residual id
+    float f[2];        // q' and p at the draft
+};
+
+template <int KIND, int REGS, class Row>
+__device__ __forceinline__ void finish_row_wide(const FinalizeArgs &a, const Row &qrow, int64_t row, const void *pr, float m, float inv,
+                                                const float *part_q, const float *part_r, const float *part_a, WideScratch &sh,
+                                                int wid, int lane)
 {
-    constexpr int kRegBlocks = 64;   // block sums a lane keeps in registers: one kind per wavefront, so 4096 blocks (N = 262144) fit
-    __shared__ double sh_d[2];   // alpha, residual mass
-    __shared__ int sh_i[2];      // the drafted id, the residual id
-    __shared__ float sh_f[2];    // q' and p at the draft
     const rdk_verify_desc_t &d = a.d;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-    const int64_t row = xcd_row(blockIdx.x, d.B);
     const int N = d.N;
-    const void *pr = row_ptr<KIND>(a.p, a.ldp, row);
-    float m = 0.f, inv = 1.f;
-    if (KIND != RDK_PROB_F32) {
-        const SoftStat rs = merged_row_stat<KIND>(a.pstat, a.p_splits, row);
-        m = rs.m;
-        inv = 1.0f / rs.s;
-    }
     const float pfill = KIND == RDK_PROB_F32 ? 0.f : -INFINITY;
     const bool draw_draft = d.sample_draft;
     const int per_lane = ((a.nblk + kWave - 1) / kWave + 3) & ~3;   // blocks per lane, in whole groups of four
-    const bool in_regs = per_lane <= kRegBlocks;
+    const bool in_regs = per_lane <= REGS;
     uint32_t words[4] = {0u, 0u, 0u, 0u};
     int blk = -1;                // the block of this wavefront's draw (-1: nothing to draw) and the threshold inside it
     double thr_local = 0.0;
     // 1. one kind of block sums per wavefront
     if (wid < 3) {
-        const float *part = (wid == 0 ? a.part_q : wid == 1 ? a.part_r : a.part_a) + row * a.nblk;
+        const float *part = wid == 0 ? part_q : wid == 1 ? part_r : part_a;
         const bool wanted = wid == 0 ? draw_draft : true;
-        float v[kRegBlocks];
+        float v[REGS];
         double lane_s = 0.0;
         if (wanted && in_regs) load_partials(part, a.nblk, per_lane, v);
         position_words(d.seed, d.offset + (uint64_t)row, words);   // while the sums are on their way
@@ -390,16 +388,15 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
                           : locate_block(part, a.nblk, per_lane, lane_s, thr, before);
             thr_local = thr - before;
         }
-        if (lane == 0 && wid >= 1) sh_d[2 - wid] = T;   // wavefront 1: residual mass -> [1], wavefront 2: alpha -> [0]
+        if (lane == 0 && wid >= 1) sh.d[2 - wid] = T;   // wavefront 1: residual mass -> [1], wavefront 2: alpha -> [0]
     }
     // 2. the block of the draft (wavefront 0) and of the residual draw (wavefront 1), one id per lane; the two values of
     //    a caller's draft (wavefront 2)
-    const typename QP::Row qrow = qp.row(row);
     if (wid < 2) {
         int tok = -1;
         if (blk >= 0) {
             const int base = blk * 64, id = base + lane;
-            typename QP::Row::Pending1 t;
+            typename Row::Pending1 t;
             qrow.template stage1<0>(t, id);
             float pv = pfill;
             if (id < N) pv = load1<KIND>(pr, id);
@@ -411,19 +408,19 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
             if (wid == 0 && tok >= 0) {
                 const float qd = lane_value(wq, tok - base), pd = lane_value(pw, tok - base);
                 if (lane == 0) {
-                    sh_f[0] = qd;
-                    sh_f[1] = pd;
+                    sh.f[0] = qd;
+                    sh.f[1] = pd;
                 }
             }
         }
-        if (lane == 0) sh_i[wid] = tok;
+        if (lane == 0) sh.i[wid] = tok;
     } else if (wid == 2 && !draw_draft) {
         const int32_t dtok = a.draft_ids[row];
         if (dtok >= 0 && dtok < N) {
             const float pd = to_weight<KIND>(load1<KIND>(pr, dtok), m, inv), qd = qrow.load1(dtok);
             if (lane == 0) {
-                sh_f[0] = qd;
-                sh_f[1] = pd;
+                sh.f[0] = qd;
+                sh.f[1] = pd;
             }
         }
     }
@@ -432,16 +429,36 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
     int32_t dtok = -1;
     uint8_t acc = 0;
     if (threadIdx.x == 0) {
-        dtok = draw_draft ? sh_i[0] : a.draft_ids[row];
+        dtok = draw_draft ? sh.i[0] : a.draft_ids[row];
         const bool d_ok = dtok >= 0 && dtok < N;
-        if (d_ok) acc = (word_to_unit(words[1]) * (double)sh_f[0] < (double)sh_f[1]) ? 1 : 0;
+        if (d_ok) acc = (word_to_unit(words[1]) * (double)sh.f[0] < (double)sh.f[1]) ? 1 : 0;
         if (draw_draft) a.draft_ids[row] = dtok;
         a.accept[row] = acc;
-        if (a.alpha) a.alpha[row] = (float)sh_d[0];
-        if (a.resid_mass) a.resid_mass[row] = (float)sh_d[1];
-        a.resid_ids[row] = sh_i[1];
+        if (a.alpha) a.alpha[row] = (float)sh.d[0];
+        if (a.resid_mass) a.resid_mass[row] = (float)sh.d[1];
+        a.resid_ids[row] = sh.i[1];
     }
-    if (wid == 0) scan_sequence(a, row, dtok, sh_i[1], acc);
+    if (wid == 0) scan_sequence(a, row, dtok, sh.i[1], acc);
+}
+
+// One row per workgroup of four wavefronts, block sums over 64 ids in memory.
+template <int KIND, class QP>
+__global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(FinalizeArgs a, QP qp)
+{
+    __shared__ WideScratch sh;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    const int64_t row = xcd_row(blockIdx.x, a.d.B);
+    const void *pr = row_ptr<KIND>(a.p, a.ldp, row);
+    float m = 0.f, inv = 1.f;
+    if (KIND != RDK_PROB_F32) {
+        const SoftStat rs = merged_row_stat<KIND>(a.pstat, a.p_splits, row);
+        m = rs.m;
+        inv = 1.0f / rs.s;
+    }
+    const typename QP::Row qrow = qp.row(row);
+    // 64 block sums a lane: 4096 blocks (N = 262144) stay in registers
+    finish_row_wide<KIND, 64>(a, qrow, row, pr, m, inv, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, sh,
+                              wid, lane);
 }
 
 // ---- The finish of one row by eight wavefronts, for block sums over 1024 ids (Alg. 4, steps 2 and 4-6 for one position).
@@ -649,21 +666,19 @@ struct DraftArgs {
     float *q_draft;        // may be NULL
 };
 
-template <int BLOCK, class QP>
-__global__ __launch_bounds__(kWave) void draft_finalize_kernel(DraftArgs a, QP qp)
+// One wavefront; pq = the row's block sums of q' (LDS or memory), REGS = how many of them a lane keeps in registers.
+template <int BLOCK, int REGS, int STAGES, class Row>
+__device__ __forceinline__ void draft_row(const DraftArgs &a, const Row &qrow, int64_t row, const float *pq)
 {
     constexpr int SUB = BLOCK >= 256 ? BLOCK / 256 : 1;
     constexpr int kLanes = BLOCK >= 256 ? kWave : BLOCK / 4;
-    constexpr int kRegBlocks = 32;
-    const int64_t row = QP::kSpreadRows ? xcd_row(blockIdx.x, a.B) : (int64_t)blockIdx.x;
+    constexpr int kRegBlocks = REGS;
     const int lane = lane_id();
     const int per_lane = ((a.nblk + kWave - 1) / kWave + 3) & ~3;   // blocks per lane, in whole groups of four
-    const float *pq = a.part_q + row * a.nblk;
     const bool in_regs = per_lane <= kRegBlocks;
     float vq[kRegBlocks];
     double lane_q;
     if (in_regs) load_partials(pq, a.nblk, per_lane, vq);
-    const typename QP::Row qrow = qp.row(row);
     lane_q = in_regs ? sum_partials(vq) : lane_partial_sum(pq, a.nblk, per_lane);
     uint32_t words[4];
     position_words(a.seed, a.offset + (uint64_t)row, words);
@@ -680,7 +695,7 @@ __global__ __launch_bounds__(kWave) void draft_finalize_kernel(DraftArgs a, QP q
     if (blk >= 0) {
         const int base = blk * BLOCK;
         if constexpr (BLOCK == 64) {
-            typename QP::Row::Pending1 td;
+            typename Row::Pending1 td;
             const int id = base + lane;
             qrow.template stage1<0>(td, id);
             qrow.template stage1<1>(td, id);
@@ -690,11 +705,11 @@ __global__ __launch_bounds__(kWave) void draft_finalize_kernel(DraftArgs a, QP q
             if (dtok >= 0) qd = lane_value(wdv, dtok - base);
         } else {
             const bool holds = lane < kLanes;
-            typename QP::Row::Pending td[SUB];
+            typename Row::Pending td[SUB];
             float4 wd[SUB];
             stage_block<0, SUB>(qrow, td, base, holds);
-            if (QP::kStages > 1) stage_block<1, SUB>(qrow, td, base, holds);
-            if (QP::kStages > 2) stage_block<2, SUB>(qrow, td, base, holds);
+            if (STAGES > 1) stage_block<1, SUB>(qrow, td, base, holds);
+            if (STAGES > 2) stage_block<2, SUB>(qrow, td, base, holds);
 #pragma unroll
             for (int i = 0; i < SUB; ++i)
                 wd[i] = holds ? qrow.result(td[i], (int64_t)base + i * 256 + lane * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -709,6 +724,14 @@ __global__ __launch_bounds__(kWave) void draft_finalize_kernel(DraftArgs a, QP q
         a.draft_ids[row] = dtok;
         if (a.q_draft) a.q_draft[row] = qd;
     }
+}
+
+template <int BLOCK, class QP>
+__global__ __launch_bounds__(kWave) void draft_finalize_kernel(DraftArgs a, QP qp)
+{
+    const int64_t row = QP::kSpreadRows ? xcd_row(blockIdx.x, a.B) : (int64_t)blockIdx.x;
+    const typename QP::Row qrow = qp.row(row);
+    draft_row<BLOCK, 32, QP::kStages>(a, qrow, row, a.part_q + row * a.nblk);
 }
 
 template <int BLOCK, class QP>

@@ -12,7 +12,7 @@
 //   * workgroups are numbered so that each XCD sweeps all id tiles of one position block before moving
 //     on: the 4 MB slab of that block stays in the XCD's own L2;
 //   * results are staged in LDS and leave as full 1 KB row segments.
-#include "rdk_finalize.hpp"
+#include "rdk_slab.hpp"
 
 namespace rdk {
 
@@ -26,7 +26,6 @@ constexpr int kTGroup = 8;        // tiles per workgroup of the transposition ke
 constexpr int kPosBlock = 32;    // positions per gather: 32 fp32 = one 128-byte line
 constexpr int kTileIds = 256;    // target ids per workgroup
 constexpr int kStageLd = kTileIds + 4;   // rows stay 16-byte aligned for the float4 read-out
-constexpr int kSubIds = 64;       // ids per block of verification sums in the fused form: 16 lanes x 4 ids
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -297,16 +296,6 @@ __device__ __forceinline__ bool xcd_work(const SparseArgs &a, int &pb, int &tile
     return true;
 }
 
-// What the fused form adds to the product: the target rows, and where the per-block sums go.
-struct FuseArgs {
-    const void *p;
-    int64_t ldp;
-    bool vec_p;
-    const SoftStat *pstat;             // [B] softmax statistics of the logit target rows, one merged pair per row
-    int p_splits;                      // = 1 (the layout the finish kernel expects: partials per row)
-    float *part_q, *part_r, *part_a;   // [B, tiles * 4]: one entry per 64-id block
-};
-
 // PK = -1: plain product (q' is written).  PK = -2: also the sum of q' per 64-id block (draft draw without a
 // target row; q' written only if WRITE_Q).  PK >= 0: fused with the verification sums against the target
 // rows of kind PK -- per (position, 64-id block) the sums of q', max(0, p - q') and min(p, q') --
@@ -412,187 +401,44 @@ __global__ __launch_bounds__(kThreads) void sparse_product_kernel(SparseArgs a, 
     }
 }
 
-// q' of one position recomputed from the sparse kernel (the finalize step needs two 64-id blocks of it).
-struct QpSparse {
-    static constexpr bool kSpreadRows = true;
-    
-    SparseArgs a;
+// Where the finish finds the drafter weight of a slot: in the position-minor copy, or in the drafter row itself (with the
+// row's maximum and 1 / mass as the product out of LDS left them).
+struct SlabColumn {
+    const float *qT;
+    const float *zpart;
+    int zt, n;
     struct Row {
-        const int32_t *slot_of;
-        const int2 *nbr;
-        const float *self_w;
-        int kk, N;
         const float *qcol;   // qT + (pb * n) * 32 + r : element of slot s is qcol[s * 32]
         float inv_z;
-        __device__ __forceinline__ float value(int j) const
-        {
-            if (j >= N) return 0.f;
-            const int s = slot_of[j];
-            if (s >= 0) return self_w[s] * qcol[(int64_t)s * kPosBlock] * inv_z;
-            const int64_t u = -s - 1;
-            float acc = 0.f;
-            for (int t0 = 0; t0 < kk; t0 += 2) {   // same order of additions as the product kernel
-                const int4 ev = *(const int4 *)(nbr + u * kk + t0);
-                acc += __int_as_float(ev.y) * qcol[(int64_t)ev.x * kPosBlock];
-                acc += __int_as_float(ev.w) * qcol[(int64_t)ev.z * kPosBlock];
-            }
-            return acc * inv_z;
-        }
-        // Four consecutive ids in three steps: slots; the first sixteen table entries of each id (a kept id is
-        // treated as a row whose entries all point at its own slot, the first with the diagonal weight); the
-        // gathers.  Rows longer than sixteen entries are finished round by round in result().
-        struct Pending {
-            int se[4];
-            int ii[4][16];
-            float ww[4][16], gg[4][16];
-        };
-        template <int K>
-        __device__ __forceinline__ void stage(Pending &t, int64_t idx) const
-        {
-            if (K == 0) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) t.se[e] = idx + e < N ? slot_of[idx + e] : 0;   // beyond N: computed, discarded
-            } else if (K == 1) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int s = t.se[e];
-                    const bool kept = s >= 0;
-                    const int64_t u = kept ? 0 : -s - 1;
-#pragma unroll
-                    for (int x = 0; x < 16; x += 2) {
-                        const int4 ev = *(const int4 *)(nbr + u * kk + x);
-                        t.ii[e][x] = ev.x; t.ww[e][x] = __int_as_float(ev.y);
-                        t.ii[e][x + 1] = ev.z; t.ww[e][x + 1] = __int_as_float(ev.w);
-                    }
-                    const float sw = self_w[max(s, 0)];
-                    if (kept) {
-#pragma unroll
-                        for (int x = 0; x < 16; ++x) {
-                            t.ii[e][x] = s;
-                            t.ww[e][x] = x == 0 ? sw : 0.f;
-                        }
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) t.gg[e][x] = qcol[(int64_t)t.ii[e][x] * kPosBlock];
-            }
-        }
-        // The record is reused for the rounds beyond the first: all pairs of a round for the four ids, then all their
-        // gathers, then the sums -- two round trips per round, whatever the number of ids.  A kept id takes its own
-        // slot with zero weights there (its row has the diagonal only).
-        __device__ __forceinline__ float4 result(Pending &t, int64_t idx) const
-        {
-            float acc[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                acc[e] = 0.f;
-#pragma unroll
-                for (int x = 0; x < 16; ++x) acc[e] += t.ww[e][x] * t.gg[e][x];   // same order of additions as the product kernel
-            }
-            for (int x0 = 16; x0 < kk; x0 += 16) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const bool kept = t.se[e] >= 0;
-                    const int64_t u = kept ? 0 : -t.se[e] - 1;
-#pragma unroll
-                    for (int x = 0; x < 16; x += 2) {
-                        const int4 ev = *(const int4 *)(nbr + u * kk + x0 + x);
-                        t.ii[e][x] = kept ? t.se[e] : ev.x; t.ww[e][x] = kept ? 0.f : __int_as_float(ev.y);
-                        t.ii[e][x + 1] = kept ? t.se[e] : ev.z; t.ww[e][x + 1] = kept ? 0.f : __int_as_float(ev.w);
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) t.gg[e][x] = qcol[(int64_t)t.ii[e][x] * kPosBlock];
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) acc[e] += t.ww[e][x] * t.gg[e][x];
-            }
-            float out[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) out[e] = idx + e < N ? acc[e] * inv_z : 0.f;
-            return make_float4(out[0], out[1], out[2], out[3]);
-        }
-        // One id per lane (blocks of 64 ids): the slot, then the first sixteen table entries, then their gathers; a kept
-        // id is a row whose entries all point at its own slot, the first with the diagonal weight.
-        struct Pending1 {
-            int se;
-            int ii[16];
-            float ww[16], gg[16];
-        };
-        template <int K>
-        __device__ __forceinline__ void stage1(Pending1 &t, int64_t idx) const
-        {
-            if (K == 0) {
-                t.se = idx < N ? slot_of[idx] : 0;   // beyond N: computed, discarded
-            } else if (K == 1) {
-                const int s = t.se;
-                const bool kept = s >= 0;
-                const int64_t u = kept ? 0 : -s - 1;
-#pragma unroll
-                for (int x = 0; x < 16; x += 2) {
-                    const int4 ev = *(const int4 *)(nbr + u * kk + x);
-                    t.ii[x] = ev.x; t.ww[x] = __int_as_float(ev.y);
-                    t.ii[x + 1] = ev.z; t.ww[x + 1] = __int_as_float(ev.w);
-                }
-                const float sw = self_w[max(s, 0)];
-                if (kept) {
-#pragma unroll
-                    for (int x = 0; x < 16; ++x) {
-                        t.ii[x] = s;
-                        t.ww[x] = x == 0 ? sw : 0.f;
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int x = 0; x < 16; ++x) t.gg[x] = qcol[(int64_t)t.ii[x] * kPosBlock];
-            }
-        }
-        __device__ __forceinline__ float result1(Pending1 &t, int64_t idx) const
-        {
-            float acc = 0.f;
-#pragma unroll
-            for (int x = 0; x < 16; ++x) acc += t.ww[x] * t.gg[x];   // same order of additions as the product kernel
-            const bool kept = t.se >= 0;
-            const int64_t u = kept ? 0 : -t.se - 1;
-            for (int x0 = 16; x0 < kk; x0 += 16) {
-#pragma unroll
-                for (int x = 0; x < 16; x += 2) {
-                    const int4 ev = *(const int4 *)(nbr + u * kk + x0 + x);
-                    t.ii[x] = kept ? t.se : ev.x; t.ww[x] = kept ? 0.f : __int_as_float(ev.y);
-                    t.ii[x + 1] = kept ? t.se : ev.z; t.ww[x + 1] = kept ? 0.f : __int_as_float(ev.w);
-                }
-#pragma unroll
-                for (int x = 0; x < 16; ++x) t.gg[x] = qcol[(int64_t)t.ii[x] * kPosBlock];
-#pragma unroll
-                for (int x = 0; x < 16; ++x) acc += t.ww[x] * t.gg[x];
-            }
-            return idx < N ? acc * inv_z : 0.f;
-        }
-        __device__ __forceinline__ float load1(int j) const { return value(j); }
+        __device__ __forceinline__ float operator()(int s) const { return qcol[(int64_t)s * kPosBlock]; }
     };
     __device__ __forceinline__ Row row(int64_t b) const
     {
         const int pb = (int)(b / kPosBlock), r = (int)(b % kPosBlock);
-        return Row{a.slot_of, a.nbr, a.self_w, a.kk, a.N, a.qT + (int64_t)pb * a.n * kPosBlock + r, row_mass_inv(a.zpart, a.zt, b)};
+        return Row{qT + (int64_t)pb * n * kPosBlock + r, row_mass_inv(zpart, zt, b)};
     }
 };
 
-struct SparseFusedWs {
-    SparseWs base;
-    SoftStat *pstat;
-    float *part_q, *part_r, *part_a;
-    int p_splits;
+template <int QK>
+struct RowColumn {
+    const void *q;
+    int64_t ldq;
+    const SoftStat *qrow;
+    struct Row {
+        const void *qr;
+        float m, inv_z;
+        __device__ __forceinline__ float operator()(int s) const { return to_weight<QK>(rdk::load1<QK>(qr, s), m, 1.f); }
+    };
+    __device__ __forceinline__ Row row(int64_t b) const
+    {
+        const SoftStat st = qrow[b];
+        return Row{row_ptr<QK>(q, ldq, b), st.m, st.s};
+    }
 };
 
 size_t fused_extra_bytes(const KernelHandle &h, int32_t B)
 {
-    const size_t blocks = (size_t)((h.N + kTileIds - 1) / kTileIds) * (kTileIds / kSubIds);
+    const size_t blocks = (size_t)sparse_blocks(h.N);
     return align_up((size_t)B * kMaxSplits * sizeof(SoftStat), 256) + align_up((size_t)B * sizeof(SoftStat), 256) +
            3 * align_up((size_t)B * blocks * sizeof(float), 256) + align_up((size_t)B * 2 * sizeof(uint64_t), 256);
 }
@@ -634,6 +480,7 @@ template <int QK>
 rdk_status_t run_sparse(const KernelHandle &h, RowInput q, int32_t B, float *out, int64_t ldo, void *ws, hipStream_t st)
 {
     SparseWs w = carve(h, B, ws);
+    if (slab_taken(h, B)) return launch_slab_product(h, q, B, out, ldo, w.qpart, -1, FuseArgs{}, FinalizeArgs{}, DraftArgs{}, st);
     rdk_status_t rc = prepare_q<QK>(h, q, B, w, st);
     if (rc != RDK_OK) return rc;
     const SparseArgs a = make_args(h, w, B, out, ldo);
@@ -656,19 +503,38 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     const int p_splits = row_splits(B, h.N, kStatThreads / kWave);
     SoftStat *ppart = (SoftStat *)p; p += align_up((size_t)B * kMaxSplits * sizeof(SoftStat), 256);   // partials per split
     SoftStat *pmerged = (SoftStat *)p; p += align_up((size_t)B * sizeof(SoftStat), 256);              // one per row
-    f.pstat = pmerged;
-    f.p_splits = 1;
-    const size_t blocks = (size_t)((h.N + kTileIds - 1) / kTileIds) * (kTileIds / kSubIds);
+    const size_t blocks = (size_t)sparse_blocks(h.N);
     const size_t per = align_up((size_t)B * blocks * sizeof(float), 256);
     f.part_q = (float *)p; p += per;
     f.part_r = (float *)p; p += per;
     f.part_a = (float *)p; p += per;
     uint64_t *seq_rec = (uint64_t *)p;   // [B, 2]
     rdk_status_t rc;
-    if (PK != RDK_PROB_F32) {
+    const bool slab = slab_taken(h, B), finishes = slab && slab_finishes(h, B);
+    if (PK != RDK_PROB_F32 && !finishes) {
         rc = launch_row_stats<PK>(c.p, h.N, B, p_splits, ppart, st);
         if (rc != RDK_OK) return rc;
     }
+    FinalizeArgs fa{};
+    fa.d = c.d;
+    fa.p = c.p.ptr; fa.ldp = c.p.ld; fa.vec_p = f.vec_p;
+    fa.pstat = pmerged; fa.p_splits = 1;
+    fa.part_q = f.part_q; fa.part_r = f.part_r; fa.part_a = f.part_a;
+    fa.nblk = (int)blocks;
+    fa.draft_ids = c.draft_ids; fa.accept = c.accept; fa.alpha = c.alpha; fa.resid_mass = c.resid_mass;
+    fa.resid_ids = c.resid_ids; fa.n_accepted = c.n_accepted; fa.out_tokens = c.out_tokens;
+    if (slab) {
+        f.pstat = ppart; f.p_splits = p_splits;
+        f.pmerged = pmerged;
+        SoftStat *qrow = w.qpart;
+        if (finishes) set_scan(fa, seq_rec);
+        rc = launch_slab_product(h, c.q, B, c.q_prime, c.ldo, qrow, PK, f, fa, DraftArgs{}, st);
+        if (rc != RDK_OK) return rc;
+        if (finishes) return scan_if_left(fa, st);
+        typedef QpSparse<RowColumn<QK>> QP;
+        return launch_finalize<PK, kSubIds, true, QP>(fa, QP{tables_of(h), RowColumn<QK>{c.q.ptr, c.q.ld, qrow}}, seq_rec, st);
+    }
+    f.pstat = pmerged; f.p_splits = 1;
     rc = PK != RDK_PROB_F32 ? prepare_q<QK>(h, c.q, B, w, st, ppart, p_splits, pmerged) : prepare_q<QK>(h, c.q, B, w, st);
     if (rc != RDK_OK) return rc;
     const SparseArgs a = make_args(h, w, B, c.q_prime, c.ldo);
@@ -681,15 +547,8 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
                              0, st, a, f);
     }
     RDK_LAUNCH_CHECK("sparse_product_kernel");
-    FinalizeArgs fa{};
-    fa.d = c.d;
-    fa.p = c.p.ptr; fa.ldp = c.p.ld; fa.vec_p = f.vec_p;
-    fa.pstat = f.pstat; fa.p_splits = f.p_splits;
-    fa.part_q = f.part_q; fa.part_r = f.part_r; fa.part_a = f.part_a;
-    fa.nblk = (int)blocks;
-    fa.draft_ids = c.draft_ids; fa.accept = c.accept; fa.alpha = c.alpha; fa.resid_mass = c.resid_mass;
-    fa.resid_ids = c.resid_ids; fa.n_accepted = c.n_accepted; fa.out_tokens = c.out_tokens;
-    return launch_finalize<PK, kSubIds, true, QpSparse>(fa, QpSparse{a}, seq_rec, st);
+    typedef QpSparse<SlabColumn> QP;
+    return launch_finalize<PK, kSubIds, true, QP>(fa, QP{tables_of(h), SlabColumn{w.qT, w.zpart, w.zt, h.n}}, seq_rec, st);
 }
 
 template <int QK>
@@ -699,7 +558,16 @@ rdk_status_t run_sparse_draft(const KernelHandle &h, RowInput q, int32_t B, uint
     SparseWs w = carve(h, B, ws);
     FuseArgs f{};
     f.part_q = (float *)((char *)ws + sparse_workspace_bytes(h, B));
-    rdk_status_t rc = prepare_q<QK>(h, q, B, w, st);
+    const DraftArgs da{B, h.N, seed, offset, f.part_q, sparse_blocks(h.N), draft_ids, q_draft};
+    rdk_status_t rc;
+    if (slab_taken(h, B)) {
+        SoftStat *qrow = w.qpart;
+        rc = launch_slab_product(h, q, B, q_prime, ldo, qrow, -2, f, FinalizeArgs{}, da, st);
+        if (rc != RDK_OK || slab_finishes(h, B)) return rc;
+        typedef QpSparse<RowColumn<QK>> QP;
+        return launch_draft_finalize<kSubIds, QP>(da, QP{tables_of(h), RowColumn<QK>{q.ptr, q.ld, qrow}}, st);
+    }
+    rc = prepare_q<QK>(h, q, B, w, st);
     if (rc != RDK_OK) return rc;
     const SparseArgs a = make_args(h, w, B, q_prime, ldo);
     if (q_prime)
@@ -709,16 +577,15 @@ rdk_status_t run_sparse_draft(const KernelHandle &h, RowInput q, int32_t B, uint
         RDK_TIMED_LAUNCH("sparse_product_kernel", (sparse_product_kernel<-2, false>), dim3(8 * a.per_xcd), dim3(kThreads), 0,
                          st, a, f);
     RDK_LAUNCH_CHECK("sparse_product_kernel");
-    const int blocks = a.tiles * (kTileIds / kSubIds);
-    DraftArgs da{B, h.N, seed, offset, f.part_q, blocks, draft_ids, q_draft};
-    return launch_draft_finalize<kSubIds, QpSparse>(da, QpSparse{a}, st);
+    typedef QpSparse<SlabColumn> QP;
+    return launch_draft_finalize<kSubIds, QP>(da, QP{tables_of(h), SlabColumn{w.qT, w.zpart, w.zt, h.n}}, st);
 }
 
 }  // namespace
 
 size_t sparse_draft_workspace_bytes(const KernelHandle &h, int32_t B)
 {
-    const size_t blocks = (size_t)((h.N + kTileIds - 1) / kTileIds) * (kTileIds / kSubIds);
+    const size_t blocks = (size_t)sparse_blocks(h.N);
     return sparse_workspace_bytes(h, B) + align_up((size_t)B * blocks * sizeof(float), 256);
 }
 
