@@ -17,15 +17,15 @@ __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ float dpp_move(float v)   // lanes without a source (or outside ROW_MASK) get 0
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, false));
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK, 0xf, ROW_MASK == 0xf));
 }
 
 template <int CTRL, int ROW_MASK = 0xf>
 __device__ __forceinline__ double dpp_move(double v)
 {
     const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROW_MASK, 0xf, false);
-    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROW_MASK, 0xf, false);
+    const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROW_MASK, 0xf, ROW_MASK == 0xf);
+    const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROW_MASK, 0xf, ROW_MASK == 0xf);
     return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 

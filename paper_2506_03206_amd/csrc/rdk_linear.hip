@@ -480,24 +480,35 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 }
 
 // ------------------------------------------------------------------------------------------------
-// Eq. 3 and the verification sums in ONE pass over the target row (the fused call on probability rows when q' is not
-// asked for).  The two-pass kernels above read p twice because the row constants (theta, sum of pt) are only known
-// after the whole row has been seen.  Here one workgroup of sixteen wavefronts owns one position and keeps what the
-// second step needs on chip:
+// Eq. 3 and the verification sums in ONE pass over the target row (the fused call when q' is not asked for).  The two-pass
+// kernels above read p twice because the row constants (theta, sum of pt) are only known after the whole row has been seen.
+// Here one workgroup owns one position and keeps what the second step needs on chip:
 //   * an id j that is not kept has q'_j = (theta / S) p_j / (N + p_j), which is below p_j (theta <= 1, S >= 1/2,
 //     N >= 2), so its share of the three block sums is a closed form of  P = sum p_j  and  A = sum p_j / (N + p_j)
 //     over the not-kept ids of the block: sum q' = sum min(p, q') = (theta / S) A,  sum max(0, p - q') = P - (theta / S) A;
 //   * a kept id needs its own p and q^: while the row streams by, the target values of the kept ids are scattered
 //     into LDS, chunk by chunk in slot order (4 n bytes: one value per drafter slot; the run of every chunk starts
 //     on a 16-byte boundary).
+// The softmax of a logit row is not known while it streams, so step A works relative to the maximum of each chunk:
+// e = exp(z - chunk maximum) goes to LDS for the kept ids, and the chunk keeps power sums of e, from which the sums of
+// p / (N + p) and q^ / (N + p) follow once the scale is known (x = p / N: p / (N + p) = x - x^2 + ..., N / (N + p) = 1 - x +
+// x^2 - ...): over the not-kept ids sum e and e^2, over the kept ids the same and sum q^, q^ e, q^ e^2.  Drafter logits are
+// taken relative to the largest of the chunk's run in the same way.  (Probability rows: e = p, all maxima zero.)  Which
+// powers: see Powers.
 // Step A streams p, guided by the kernel's lane map (L2-resident, shared by all rows), a wavefront per chunk.  The chunk's
 // run of drafter values is fetched alongside (one contiguous piece of the drafter row); the wavefront reads its own
-// scattered target values back in slot order and adds up q^, q^ p and q^ / (N + p) -- the sums of the row constants cost
-// no pass of their own.  Step C, once the constants are known, forms q', max(0, p - q') and min(p, q') on the kept slots.
-// Its unit of work is a piece of at most 64 slots of one chunk (a table of the kernel), dealt out to groups of sixteen
-// lanes in turn, so that vocabularies whose kept ids crowd into a few chunks keep every lane busy; the drafter values of
-// the pieces are asked for before the constants are known, the sums of a piece take four register-speed lane exchanges,
-// and the pieces of a chunk are added up in their order.  HBM traffic: p and q once.
+// scattered target values back in slot order and adds up the kept ids' sums -- those of the row constants cost no pass of
+// their own.  After the barrier the chunks' sums are brought to the row maxima; their totals give the softmax normalisers
+// and the row constants.  Step C forms q', max(0, p - q') and min(p, q') on the kept slots.  Its unit of work is a piece of
+// at most 64 slots of one chunk (a table of the kernel), dealt out to groups of sixteen lanes in turn, so that vocabularies
+// whose kept ids crowd into a few chunks keep every lane busy; the drafter values of the pieces are asked for before the
+// constants are known, the sums of a piece take four register-speed lane exchanges, and the pieces of a chunk are added up
+// in their order.  HBM traffic: p and q once.
+// What bounds it, measured on MI355X: probability rows, HBM while the row streams and then, with one workgroup on a unit,
+// about 10 us in the steps after it (N = 128256, n = 32064, 256 rows: 38.6 us a call; N = 151936, n = 16384, 1024 rows: 124.8
+// us, 5.5 TB/s); bf16 logit rows, the vector unit in step A (same shape, half the bytes: 124.8 us, 184 before the loads
+// stayed raw in registers -- a conversion next to a load waits for it, so nothing was ever in flight -- and before the
+// scatter became a block on the execution mask, eight sums were reduced together, and two workgroups shared a unit).
 // q' of Eq. 3 re-computed from the row constants (the finish step needs the two blocks of the crossings).
 template <int PK, int QK>
 struct QpTaylor {
@@ -510,11 +521,10 @@ struct QpTaylor {
 
 constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / kWave;
-constexpr int kRowGroups = kRowThreads / 16;   // groups of sixteen lanes: one piece of kept slots each per round of step C
 constexpr int kRowHeld = 10;                   // pieces per group whose drafter values are requested ahead of the row constants
 
 struct RowLds {      // offsets in floats into the dynamic LDS block
-    int pk, zero, blk_p, blk_a, blk_all, blk_aq, red, items, item_lo, isum, sum_q, sum_r, sum_a, fin, total;
+    int pk, zero, blk, red, items, item_lo, sum_q, sum_r, sum_a, fin, total;
 };
 
 // Where the run of chunk c (first slot lo) starts in the LDS array of kept target values: a multiple of four floats, and
@@ -524,7 +534,8 @@ __host__ __device__ inline int row_run_start(int lo, int c) { return (lo & ~3) +
 // Upper bound on the number of pieces (the size of the kernel's table): one per chunk and one per 64 slots.
 __host__ __device__ inline int row_max_items(int n, int nchunks) { return nchunks + n / 64 + 1; }
 
-__host__ __device__ inline RowLds row_lds_layout(int n, int nchunks)
+// arrays: how many floats step A leaves behind per chunk; waves: wavefronts of the workgroup.
+__host__ __device__ inline RowLds row_lds_layout(int n, int nchunks, int arrays, int waves)
 {
     RowLds L;
     int off = 0;
@@ -532,15 +543,12 @@ __host__ __device__ inline RowLds row_lds_layout(int n, int nchunks)
     // (their values are masked)
     L.pk = off; off += ((n + 3) & ~3) + 4 * nchunks + 4;
     L.zero = off; off += 4;                            // a quad of zeros for the lanes past the end of a piece
-    L.blk_p = off; off += 4 * nchunks;                 // per chunk, in four partial sums: p over the not-kept ids
-    L.blk_a = off; off += 4 * nchunks;                 //            p / (N + p) over the not-kept ids
-    L.blk_all = off; off += 4 * nchunks;               //            p / (N + p) over all ids
-    L.blk_aq = off; off += 4 * nchunks;                //            q^ / (N + p) over the kept ids
-    L.red = off; off += kRowWaves * 9;                 // what the wavefronts hand to each other between the steps
+    L.blk = off; off += (arrays * nchunks + 3) & ~3;   // what step A leaves behind per chunk
+    L.red = off; off += waves * 8;                     // what the wavefronts hand to each other between the steps
     const int mi = (row_max_items(n, nchunks) + 1) & ~1;
-    L.items = off; off += 2 * mi;                      // the kernel's table of pieces
+    // the kernel's table of pieces; the sums of a piece (max(0, p - q') and min(p, q')) take the place of its entry
+    L.items = off; off += 2 * mi;
     L.item_lo = off; off += (nchunks + 1 + 3) & ~3;    // first piece of every chunk
-    L.isum = off; off += 2 * mi;                       // per piece: sums of max(0, p - q') and min(p, q')
     // per chunk: the three block sums the finish step draws from.  They are formed when the kept target values have
     // served their purpose, and take their place (4 nchunks + 8 floats are there at least).
     L.sum_q = L.pk;
@@ -549,24 +557,6 @@ __host__ __device__ inline RowLds row_lds_layout(int n, int nchunks)
     L.fin = off; off += kFinishFloats + 4;             // what the wavefronts of the finish step hand to each other, the uniforms
     L.total = off;
     return L;
-}
-
-// One chunk of target values (16 ids per lane, the layout of load_chunk), the lane's record of the kernel's lane map
-// for that chunk, and the chunk's run of slots [lo, hi).
-struct RowChunk {
-    float4 p[4];
-    uint64_t map;
-    int lo, hi;
-};
-
-template <int PK = RDK_PROB_F32>
-__device__ __forceinline__ void row_fetch(const void *pr, const uint64_t *lane_map, const int32_t *chunk_lo, int c, int N,
-                                          bool vec_p, RowChunk &b)
-{
-    load_chunk<PK>(pr, (int64_t)c * kChunk, N, vec_p, PK == RDK_PROB_F32 ? 0.f : -INFINITY, b.p);
-    b.map = lane_map[(int64_t)c * kWave + lane_id()];
-    b.lo = chunk_lo[c];
-    b.hi = chunk_lo[c + 1];
 }
 
 // 1 / (N + p) for 0 <= p <= 1.  For a large vocabulary the first two terms of the series in p / N are exact to fp32
@@ -580,119 +570,6 @@ struct RowRcp {
         return SERIES ? fmaf(-p, invN2, invN) : __builtin_amdgcn_rcpf(fN + p);
     }
 };
-
-// Step A for one chunk c: target values of kept ids go to their slots in LDS; sp, sa: sums of p and of p / (N + p) over
-// the ids that are not kept; sall: p / (N + p) over all of them.
-template <bool SERIES>
-__device__ __forceinline__ void row_scatter(const RowChunk &b, int c, int lo, const RowRcp<SERIES> &rcp, float *pk, float &sp,
-                                            float &sa, float &sall)
-{
-    const uint32_t mask = (uint32_t)b.map & 0xFFFFu;
-    const int run = row_run_start(lo, c);                         // where the chunk's first slot sits in LDS
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        char *at = (char *)(pk + run + (int)((b.map >> (16 + 12 * i)) & 0xFFFu));   // slot of the lane's first kept id of this group
-        const float pe[4] = {b.p[i].x, b.p[i].y, b.p[i].z, b.p[i].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t kept = (mask >> (4 * i + e)) & 1u;
-            if (kept) *(float *)at = pe[e];
-            at += 4 * kept;
-            const float r = rcp(pe[e]);
-            const float pn = kept ? 0.f : pe[e];
-            sp += pn;
-            sa = fmaf(pn, r, sa);
-            sall = fmaf(pe[e], r, sall);
-        }
-    }
-}
-
-// The raw drafter values of four consecutive slots from s on, for the lanes whose quad starts below `end` (the others get
-// the value of weight zero; n = slots in the row).  One 16-byte load when the quad lies inside the row -- four bytes of
-// alignment are all a global load of that size needs; its slots from `end` on belong to the row but not to the caller --
-// and single loads for the quad that crosses the end of the row.  Every load writes the one result under a one-sided
-// branch, so a sequence of calls issues its loads back to back (loads merged from two code paths would each be waited
-// for at the merge).
-template <int QK>
-__device__ __forceinline__ float4 row_raw_quad(const void *qr, int s, int end, int n)
-{
-    const float none = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
-    float4 raw = make_float4(none, none, none, none);
-    if (QK == RDK_LOGIT_BF16) {
-        const uint16_t *r = (const uint16_t *)qr;
-        if (s < end && s + 3 < n) {
-            typedef unsigned short u16x4a __attribute__((ext_vector_type(4), aligned(2)));
-            const u16x4a v = *(const u16x4a *)(r + s);
-            raw = make_float4(bf16_to_f32(v.x), bf16_to_f32(v.y), bf16_to_f32(v.z), bf16_to_f32(v.w));
-        }
-        if (s < end && s + 3 >= n) {
-            raw.x = bf16_to_f32(r[s]);
-            if (s + 1 < n) raw.y = bf16_to_f32(r[s + 1]);
-            if (s + 2 < n) raw.z = bf16_to_f32(r[s + 2]);
-        }
-    } else {
-        const float *r = (const float *)qr;
-        if (s < end && s + 3 < n) {
-            typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
-            const f32x4a v = *(const f32x4a *)(r + s);
-            raw = make_float4(v.x, v.y, v.z, v.w);
-        }
-        if (s < end && s + 3 >= n) {
-            raw.x = r[s];
-            if (s + 1 < n) raw.y = r[s + 1];
-            if (s + 2 < n) raw.z = r[s + 2];
-        }
-    }
-    return raw;
-}
-
-// The drafter weights of a raw quad (a slot that was not loaded gives zero).
-template <int QK>
-__device__ __forceinline__ float4 row_weights_of(const float4 raw, float qm)
-{
-    return make_float4(to_weight<QK>(raw.x, qm, 1.f), to_weight<QK>(raw.y, qm, 1.f), to_weight<QK>(raw.z, qm, 1.f),
-                       to_weight<QK>(raw.w, qm, 1.f));
-}
-
-// The drafter values of a chunk's run of slots [lo, hi): lane l takes the quads lo + 4 l + 256 i (a run has at most
-// 1024 slots).
-template <int QK>
-__device__ __forceinline__ void row_q_fetch(const void *qr, int lo, int hi, int n, float4 (&qv)[4])
-{
-#pragma unroll
-    for (int i = 0; i < 4; ++i) qv[i] = row_raw_quad<QK>(qr, lo + 4 * (lane_id() + 64 * i), hi, n);
-}
-
-// Sums over the kept ids of chunk c, in slot order: the wavefront reads back the target values it has just scattered.
-// A lane past the end of the run reads the run's first quad instead (its drafter weights are zero); in the one quad that
-// crosses the end, the weights of the slots past it are set to zero.
-template <int QK, bool SERIES>
-__device__ __forceinline__ void row_kept_sums(int c, int lo, int hi, const float4 (&qv)[4], const float *pk,
-                                              const RowRcp<SERIES> &rcp, float qm, float &zq, float &tn, float &aq)
-{
-    const float *run = pk + row_run_start(lo, c);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (lo + 256 * i < hi) {
-            const int o = 4 * (lane_id() + 64 * i);
-            const int left = hi - lo - o;              // slots of the run from the lane's quad on
-            const float4 p4 = *(const float4 *)(run + (left > 0 ? o : 0));
-            const float4 w4 = row_weights_of<QK>(qv[i], qm);
-            float qe[4] = {w4.x, w4.y, w4.z, w4.w};
-            const float pe[4] = {p4.x, p4.y, p4.z, p4.w};
-            if (left > 0 && left < 4) {
-#pragma unroll
-                for (int e = 1; e < 4; ++e) qe[e] = e < left ? qe[e] : 0.f;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                zq += qe[e];
-                tn = fmaf(qe[e], pe[e], tn);
-                aq = fmaf(qe[e], rcp(pe[e]), aq);
-            }
-        }
-    }
-}
 
 // q' of Eq. 3 for the finish of a row inside the one-pass kernels (finish_row_quarters): the drafter values of the kept ids
 // of a quarter chunk through the lane map, the row constants nzs and ths, and 1 / (N + p) as the block sums took it.
@@ -755,204 +632,9 @@ __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, i
                             quads, words, wid, lane);
 }
 
-template <int QK, bool SERIES>
-__global__ __launch_bounds__(kRowThreads) void taylor_row_kernel(const float *p, int64_t ldp, const void *q, int64_t ldq,
-                                                                 const uint64_t *lane_map, const int32_t *chunk_lo,
-                                                                 const int32_t *item_lo, const int2 *row_items, int N, int n,
-                                                                 bool vec_p, const SoftStat *qstat, const int32_t *slot_of,
-                                                                 FinalizeArgs fin)
-{
-    extern __shared__ __attribute__((aligned(16))) float lds[];
-    const int nchunks = (N + kChunk - 1) / kChunk;
-    const RowLds L = row_lds_layout(n, nchunks);
-    float *pk = lds + L.pk;
-    int2 *il = (int2 *)(lds + L.items);
-    int *ilo = (int *)(lds + L.item_lo);
-    float2 *isum = (float2 *)(lds + L.isum);
-    const int64_t row = blockIdx.x;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-    const float *pr = p + row * ldp;
-    const void *qr = row_ptr<QK>(q, ldq, row);
-    const float qm = QK == RDK_PROB_F32 ? 0.f : qstat[row].m;
-    const float fN = (float)N;
-    RowRcp<SERIES> rcp;
-    rcp.fN = fN;
-    rcp.invN = 1.0f / fN;
-    rcp.invN2 = rcp.invN * rcp.invN;
-
-    // ---- the kernel's table of pieces goes to LDS (entries past the last piece are never used), the array of kept target
-    // values starts at zero, and the first two chunks of every wavefront are on their way meanwhile
-    const int max_items = row_max_items(n, nchunks);
-    const int nitems = item_lo[nchunks];
-    int2 it0 = make_int2(0, 0);
-    if ((int)threadIdx.x < max_items) it0 = row_items[threadIdx.x];
-    RowChunk b0, b1, b2;
-    int c = wid;
-    if (c < nchunks) row_fetch(pr, lane_map, chunk_lo, c, N, vec_p, b0);
-    if (c + kRowWaves < nchunks) row_fetch(pr, lane_map, chunk_lo, c + kRowWaves, N, vec_p, b1);
-    if (threadIdx.x == 0) {                           // the position's four uniforms (Alg. 4: draft, accept, residual, bonus)
-        uint32_t words[4];
-        position_words(fin.d.seed, fin.d.offset + (uint64_t)row, words);
-        uint32_t *fw = (uint32_t *)(lds + L.fin + kFinishFloats);
-        fw[0] = words[0]; fw[1] = words[1]; fw[2] = words[2]; fw[3] = words[3];
-    }
-    {
-        float4 *z = (float4 *)pk;
-        const int quads = (L.blk_p - L.pk) / 4;
-        for (int i = threadIdx.x; i < quads; i += kRowThreads) z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if ((int)threadIdx.x < max_items) il[threadIdx.x] = it0;
-        for (int k = threadIdx.x + kRowThreads; k < max_items; k += kRowThreads) il[k] = row_items[k];
-        for (int cc = threadIdx.x; cc <= nchunks; cc += kRowThreads) ilo[cc] = item_lo[cc];
-    }
-    __syncthreads();
-
-    // ---- step A: one pass over the row, two chunks requested ahead of the one being worked on; the drafter values of a
-    // chunk's run are requested one chunk ahead, into the registers the sums of this chunk have just freed
-    float zq = 0.f, tn = 0.f, an = 0.f, ball = 0.f;   // ball: sum of p / (N + p) over all ids
-    float4 qv[4];
-    if (c < nchunks) row_q_fetch<QK>(qr, b0.lo, b0.hi, n, qv);
-#define RDK_ROW_STEP(CUR, NEXT, FREE)                                                                        \
-    {                                                                                                        \
-        if (c + 2 * kRowWaves < nchunks) row_fetch(pr, lane_map, chunk_lo, c + 2 * kRowWaves, N, vec_p, FREE); \
-        const int lo_c = __builtin_amdgcn_readfirstlane(CUR.lo), hi_c = __builtin_amdgcn_readfirstlane(CUR.hi); \
-        float sp = 0.f, sa = 0.f, sall = 0.f, aq = 0.f;                                                      \
-        row_scatter<SERIES>(CUR, c, lo_c, rcp, pk, sp, sa, sall);                                            \
-        row_kept_sums<QK, SERIES>(c, lo_c, hi_c, qv, pk, rcp, qm, zq, tn, aq);                               \
-        ball += sall;                                                                                        \
-        an += aq;                                                                                            \
-        sp = row16_sum(sp);                           /* per chunk: four partial sums, one per row of sixteen lanes */ \
-        sa = row16_sum(sa);                                                                                  \
-        sall = row16_sum(sall);                                                                              \
-        aq = row16_sum(aq);                                                                                  \
-        if ((lane & 15) == 0) {                                                                              \
-            const int o = 4 * c + (lane >> 4);                                                               \
-            lds[L.blk_p + o] = sp;                                                                           \
-            lds[L.blk_a + o] = sa;                                                                           \
-            lds[L.blk_all + o] = sall;                                                                       \
-            lds[L.blk_aq + o] = aq;                                                                          \
-        }                                                                                                    \
-        if (c + kRowWaves < nchunks)                                                                         \
-            row_q_fetch<QK>(qr, __builtin_amdgcn_readfirstlane(NEXT.lo), __builtin_amdgcn_readfirstlane(NEXT.hi), n, qv); \
-        c += kRowWaves;                                                                                      \
-    }
-    while (c < nchunks) {
-        RDK_ROW_STEP(b0, b1, b2)
-        if (c >= nchunks) break;
-        RDK_ROW_STEP(b1, b2, b0)
-        if (c >= nchunks) break;
-        RDK_ROW_STEP(b2, b0, b1)
-    }
-#undef RDK_ROW_STEP
-    zq = wave_sum(zq);
-    tn = wave_sum(tn);
-    an = wave_sum(an) * fN;
-    ball = wave_sum(ball);
-    if (lane == 0) *(float4 *)(lds + L.red + wid * 4) = make_float4(zq, tn, an, ball);
-
-    // ---- step C works on pieces: group g of sixteen lanes takes the pieces g, g + 64, ...; lane li of the group the slots
-    // 4 li .. 4 li + 3 of the piece.  The drafter values of the first rounds are asked for here, before the barrier, and
-    // so is where the lane finds its target values in LDS: a lane wholly past the end of the piece is pointed at a quad of
-    // zeros; the quad that crosses the end runs into the zeros that separate the runs (a piece shorter than 64 ends its
-    // run).  Where the target value is zero, q' adds nothing to either sum whatever the drafter value, so nothing needs
-    // masking later.
-    const int grp = threadIdx.x >> 4, li = threadIdx.x & 15;
-    float4 qh[kRowHeld];
-    int pat[kRowHeld];
-    auto piece_of = [&](int k, int &len) {            // LDS offset of the lane's quad of piece k, and the piece's length
-        const int2 it = il[k];
-        len = (int)((uint32_t)it.y >> 24);
-        return 4 * li < len ? L.pk + it.x - ((it.y >> 22) & 3) + 4 * (it.y & 0x3FFFFF) + 4 * li : L.zero;
-    };
-#pragma unroll
-    for (int t = 0; t < kRowHeld; ++t) {
-        const int k = grp + kRowGroups * t;
-        int len = 0, first = 0;
-        pat[t] = L.zero;
-        if (k < nitems) {
-            pat[t] = piece_of(k, len);
-            first = il[k].x;
-        }
-        qh[t] = row_raw_quad<QK>(qr, first + 4 * li, first + len, n);
-    }
-    __syncthreads();
-    float tot[4];
-    {
-        float4 t = *(const float4 *)(lds + L.red);
-        for (int i = 1; i < kRowWaves; ++i) {
-            const float4 o = *(const float4 *)(lds + L.red + i * 4);
-            t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-        }
-        tot[0] = t.x; tot[1] = t.y; tot[2] = t.z; tot[3] = t.w;
-    }
-    const float inv_zq = inv_mass(tot[0]);
-    const float theta = tot[1] * inv_zq;
-    const float inv_S = inv_mass(tot[2] * inv_zq + theta * tot[3]);
-    const float nzs = fN * inv_zq * inv_S, ths = theta * inv_S;
-
-    // ---- step C: max(0, p - q') and min(p, q') on the kept slots, piece by piece (the sum of q' over the kept ids of a
-    // chunk needs no pass: it is nzs * sum q^ / (N + p) + ths * sum p / (N + p), both known from step A)
-    auto piece_sums = [&](int k, const float4 raw, int at) {
-        const float4 w4 = row_weights_of<QK>(raw, qm);
-        const float4 p4 = *(const float4 *)(lds + at);
-        const float qe[4] = {w4.x, w4.y, w4.z, w4.w}, pe[4] = {p4.x, p4.y, p4.z, p4.w};
-        float sr = 0.f, sa = 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float v = (nzs * qe[e] + ths * pe[e]) * rcp(pe[e]);
-            const float m = __builtin_amdgcn_fmed3f(pe[e], v, -INFINITY);   // min(p, q'): neither is a NaN
-            sa += m;
-            sr += pe[e] - m;
-        }
-        // the sixteen lanes of the group hold the piece: four lane exchanges at register speed
-        sr = row16_sum(sr);
-        sa = row16_sum(sa);
-        if (li == 0) isum[k] = make_float2(sr, sa);
-    };
-#pragma unroll
-    for (int t = 0; t < kRowHeld; ++t) {
-        const int k = grp + kRowGroups * t;
-        if (k < nitems) piece_sums(k, qh[t], pat[t]);
-    }
-    for (int k = grp + kRowGroups * kRowHeld; k < nitems; k += kRowGroups) {   // more pieces than the registers were given
-        int len;
-        const int at = piece_of(k, len);
-        const int first = il[k].x;
-        piece_sums(k, row_raw_quad<QK>(qr, first + 4 * li, first + len, n), at);
-    }
-    __syncthreads();
-
-    // ---- the block sums of a chunk: its pieces in order (at most sixteen: one lane each), and the closed forms
-    for (int cc = grp; cc < nchunks; cc += kRowGroups) {
-        const int k = ilo[cc] + li;
-        const float2 f = k < ilo[cc + 1] ? isum[k] : make_float2(0.f, 0.f);
-        const float sr = row16_sum(f.x), sa = row16_sum(f.y);
-        if (li == 0) {
-            const float4 bp = *(const float4 *)(lds + L.blk_p + 4 * cc), ba = *(const float4 *)(lds + L.blk_a + 4 * cc);
-            const float4 bl = *(const float4 *)(lds + L.blk_all + 4 * cc), bq = *(const float4 *)(lds + L.blk_aq + 4 * cc);
-            const float ta = ths * ((ba.x + ba.y) + (ba.z + ba.w));   // sum of q' (= sum of min(p, q')) over the not-kept ids
-            lds[L.sum_q + cc] = ths * ((bl.x + bl.y) + (bl.z + bl.w)) + nzs * ((bq.x + bq.y) + (bq.z + bq.w));
-            lds[L.sum_a + cc] = ta + sa;
-            lds[L.sum_r + cc] = (((bp.x + bp.y) + (bp.z + bp.w)) - ta) + sr;
-        }
-    }
-    __syncthreads();
-
-    // ---- the finish of the row (draws, accept test), spread over the wavefronts
-    row_finish<RDK_PROB_F32, QK, true>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, 0.f, 1.f, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp,
-                                 wid, lane);
-}
-
-// ------------------------------------------------------------------------------------------------
-// The same for LOGIT target rows.  The softmax of the row is not known while it streams, so step A works relative to the
-// maximum of each chunk: e = exp(z - chunk maximum) goes to LDS for the kept ids, and instead of sums of p and p / (N + p)
-// the chunk keeps the power sums of e that their series in x = p / N need (p / (N + p) = x - x^2 + x^3 and
-// N / (N + p) = 1 - x + x^2 - x^3 up to x^4 <= N^-4; used from N = 1024 on): over the not-kept ids sum e, e^2, e^3, over the
-// kept ids the same and sum q^ e^k, k = 0..3.  After the barrier the row maximum is the largest chunk maximum, every
-// chunk's sums are brought to it (factor exp(chunk maximum - row maximum) to the power k), their totals give the softmax
-// normaliser and the row constants of Eq. 3, and steps C and the finish run as for probability rows with
-// p = e * factor / normaliser.  One read of the target row instead of the three of the two-pass path (statistics, sums,
-// verification sums), and one exp per id instead of two.
-enum { kLgMax = 0, kLgS1n, kLgS2n, kLgS3n, kLgS1k, kLgS2k, kLgS3k, kLgQ0, kLgQ1, kLgQ2, kLgQ3, kLgScale };   // chunk statistics
+constexpr float kLowest = -1.0e38f;   // stands in for the maximum of nothing: differences from it stay finite
+// The statistics of a chunk (arrays in LDS); the third powers only where the series needs them.
+enum { kRowS1n = 0, kRowS2n, kRowS1k, kRowS2k, kRowQ0, kRowQ1, kRowQ2, kRowMax, kRowQMax, kRowScale, kRowArrays, kRowS3n = kRowArrays, kRowS3k, kRowQ3, kRowAllArrays };
 
 // sum over the 64 lanes, valid in the lanes 48..63
 __device__ __forceinline__ float wave_sum_last(float v)
@@ -963,113 +645,310 @@ __device__ __forceinline__ float wave_sum_last(float v)
     return v;
 }
 
-// Step A of the logit variant for one chunk: statistics to `stat` (arrays of nchunks floats), e of the kept ids to LDS.
-// CUBIC = false (N >= 4096): the third-order terms of the series are below 2^-24 of the first and are left out.
-template <int QK, bool CUBIC>
-__device__ __forceinline__ void row_logit_chunk(const RowChunk &b, int c, int lo, int hi, const float4 (&qv)[4], float *pk,
-                                                const float *zero_quad, float *stat, float qm, int nchunks)
+// The larger of two values, neither of them a NaN that anybody would miss (fmaxf spends an instruction per operand on
+// quieting NaNs).
+__device__ __forceinline__ float raw_max(float a, float b)
 {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float raw_max3(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+// largest value of the 64 lanes, in a scalar register
+__device__ __forceinline__ float wave_max_scalar(float v)
+{
+    v = raw_max(v, dpp_move<0xB1>(v));
+    v = raw_max(v, dpp_move<0x4E>(v));
+    v = raw_max(v, dpp_move<0x141>(v));
+    v = raw_max(v, dpp_move<0x140>(v));
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = raw_max(__uint_as_float(r.x), __uint_as_float(r.y));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = raw_max(__uint_as_float(r.x), __uint_as_float(r.y));
+    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+
+// Eight sums over the 64 lanes at once: lane l gets the total of v[bit reversal of l / 8].  Values are put side by side
+// as they are halved (17 instructions where eight separate sums take 48).
+__device__ __forceinline__ float wave_sum8(const float (&v)[8])
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    auto pair32 = [](float a, float b) {
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r.x) + __uint_as_float(r.y);
+    };
+    auto pair16 = [](float a, float b) {
+        const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+        return __uint_as_float(r.x) + __uint_as_float(r.y);
+    };
+    float a = pair16(pair32(v[0], v[1]), pair32(v[2], v[3]));
+    float b = pair16(pair32(v[4], v[5]), pair32(v[6], v[7]));
+    a += dpp_move<0x128>(a);
+    b += dpp_move<0x128>(b);
+    a = (lane_id() & 8) ? b : a;
+    a += dpp_move<0x141>(a);
+    a += dpp_move<0xB1>(a);
+    a += dpp_move<0x4E>(a);
+    return a;
+}
+
+// Four consecutive raw values as they lie in memory: the conversion of bf16 waits until they are used, or every load would
+// be waited for where it is made.
+template <int KIND>
+struct RawQuad {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+    static __device__ __forceinline__ void to(const type r, float (&v)[4])
+    {
+        v[0] = r.x; v[1] = r.y; v[2] = r.z; v[3] = r.w;
+    }
+};
+template <>
+struct RawQuad<RDK_LOGIT_BF16> {
+    typedef unsigned type __attribute__((ext_vector_type(2), aligned(2)));
+    static __device__ __forceinline__ void to(const type r, float (&v)[4])
+    {
+        v[0] = __uint_as_float(r.x << 16); v[1] = __uint_as_float(r.x & 0xFFFF0000u);
+        v[2] = __uint_as_float(r.y << 16); v[3] = __uint_as_float(r.y & 0xFFFF0000u);
+    }
+};
+template <int KIND>
+__device__ __forceinline__ typename RawQuad<KIND>::type raw_quad(const void *row, int i, int len)
+{
+    typedef typename RawQuad<KIND>::type Raw;
+    return *(const Raw *)((const char *)row + (uint32_t)min(i, len - 4) * (KIND == RDK_LOGIT_BF16 ? 2u : 4u));
+}
+// raw_quad reads the last four values of the row for a quad that crosses its end: `past` places too early.
+__device__ __forceinline__ void quad_shift(float (&v)[4], int past)
+{
+    past = max(past, 0);
+    const bool one = past & 1, two = past & 2;
+    v[0] = one ? v[1] : v[0]; v[1] = one ? v[2] : v[1]; v[2] = one ? v[3] : v[2];
+    v[0] = two ? v[2] : v[0]; v[1] = two ? v[3] : v[1];
+}
+
+// A chunk of a target row, raw.  Quads need the alignment of one element only (that is all that a global load asks for),
+// and no load depends on a branch: the quads that cross the end of the row or lie past it are put right where they are used.
+template <int PK>
+struct PowerChunk {
+    typename RawQuad<PK>::type p[4];
+    uint64_t map;
+    int lo, hi;
+};
+template <int PK>
+__device__ __forceinline__ void power_fetch(const void *pr, const uint64_t *lane_map, const int32_t *chunk_lo, int c, int N,
+                                            PowerChunk<PK> &b)
+{
+    typedef typename RawQuad<PK>::type Raw;
     const int lane = lane_id();
-    float mx = fmaxf(fmaxf(fmaxf(b.p[0].x, b.p[0].y), fmaxf(b.p[0].z, b.p[0].w)), fmaxf(fmaxf(b.p[1].x, b.p[1].y), fmaxf(b.p[1].z, b.p[1].w)));
-    mx = fmaxf(mx, fmaxf(fmaxf(fmaxf(b.p[2].x, b.p[2].y), fmaxf(b.p[2].z, b.p[2].w)), fmaxf(fmaxf(b.p[3].x, b.p[3].y), fmaxf(b.p[3].z, b.p[3].w))));
-    mx = fmaxf(wave_max(mx), -3.0e38f);
-    const uint32_t mask = (uint32_t)b.map & 0xFFFFu;
-    const int run = row_run_start(lo, c);
-    float s1 = 0.f, s2 = 0.f, s3 = 0.f;                // over the ids that are not kept
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        char *at = (char *)(pk + run + (int)((b.map >> (16 + 12 * i)) & 0xFFFu));
-        const float ze[4] = {b.p[i].x, b.p[i].y, b.p[i].z, b.p[i].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t kept = (mask >> (4 * i + e)) & 1u;
-            const float ev = soft_exp(ze[e] - mx);     // ids beyond N carry -inf: zero
-            if (kept) *(float *)at = ev;
-            at += 4 * kept;
-            const float en = kept ? 0.f : ev, en2 = en * en;
-            s1 += en;
-            s2 += en2;
-            if (CUBIC) s3 = fmaf(en2, en, s3);
-        }
+        const uint32_t at = (uint32_t)min(c * kChunk + 256 * i + 4 * lane, N - 4) * (PK == RDK_LOGIT_BF16 ? 2u : 4u);
+        b.p[i] = __builtin_nontemporal_load((const Raw *)((const char *)pr + at));
     }
-    float k1 = 0.f, k2 = 0.f, k3 = 0.f, q0 = 0.f, q1 = 0.f, q2 = 0.f, q3 = 0.f;   // over the kept ids, in slot order
+    b.map = lane_map[c * kWave + lane];
+    b.lo = chunk_lo[c];
+    b.hi = chunk_lo[c + 1];
+}
+
+// The raw drafter values of a run [lo, hi) of at most 1024 slots: lane l the quads lo + 4 l + 256 i; what lies past the run
+// is masked on use.
+template <int QK>
+__device__ __forceinline__ void power_q_fetch(const void *qr, int lo, int hi, int n, typename RawQuad<QK>::type (&qv)[4])
+{
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (lo + 256 * i < hi) {
-            const int o = 4 * (lane + 64 * i);
-            const int left = hi - lo - o;              // slots of the run from the lane's quad on
-            const float4 e4 = *(const float4 *)(left > 0 ? pk + run + o : zero_quad);   // past the run: zeros
-            const float4 w4 = row_weights_of<QK>(qv[i], qm);
-            float qe[4] = {w4.x, w4.y, w4.z, w4.w};
-            const float ee[4] = {e4.x, e4.y, e4.z, e4.w};
-            if (left > 0 && left < 4) {
-#pragma unroll
-                for (int e = 1; e < 4; ++e) qe[e] = e < left ? qe[e] : 0.f;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float e2 = ee[e] * ee[e];
-                k1 += ee[e];
-                k2 += e2;
-                q0 += qe[e];
-                q1 = fmaf(qe[e], ee[e], q1);
-                q2 = fmaf(qe[e], e2, q2);
-                if (CUBIC) {
-                    k3 = fmaf(e2, ee[e], k3);
-                    q3 = fmaf(qe[e] * e2, ee[e], q3);
-                }
-            }
-        }
-    }
-    s1 = wave_sum_last(s1); s2 = wave_sum_last(s2);
-    k1 = wave_sum_last(k1); k2 = wave_sum_last(k2);
-    q0 = wave_sum_last(q0); q1 = wave_sum_last(q1); q2 = wave_sum_last(q2);
-    if (CUBIC) {
-        s3 = wave_sum_last(s3); k3 = wave_sum_last(k3); q3 = wave_sum_last(q3);
-    }
-    if (lane == kWave - 1) {
-        stat[kLgMax * nchunks + c] = mx;
-        stat[kLgS1n * nchunks + c] = s1; stat[kLgS2n * nchunks + c] = s2; stat[kLgS3n * nchunks + c] = s3;
-        stat[kLgS1k * nchunks + c] = k1; stat[kLgS2k * nchunks + c] = k2; stat[kLgS3k * nchunks + c] = k3;
-        stat[kLgQ0 * nchunks + c] = q0; stat[kLgQ1 * nchunks + c] = q1; stat[kLgQ2 * nchunks + c] = q2;
-        stat[kLgQ3 * nchunks + c] = q3;
+    for (int i = 0; i < 4; ++i)
+        if (lo + 256 * i < hi) qv[i] = raw_quad<QK>(qr, lo + 256 * i + 4 * lane_id(), n);   // the same for all lanes
+}
+
+// How 1 / (N + p) is taken from power sums.
+enum class Powers {
+    Series,   // N >= 4096: up to the second power, exact to fp32 rounding (the next term is (p / N)^2 <= 2^-24 of the first)
+    Cubic,    // smaller vocabularies, logit rows: up to the third (N >= 1024: the next one is 2^-30)
+    Exact,    // smaller vocabularies, probability rows: p^2 is replaced by p^2 / (1 + p / N), which closes the series
+};
+
+// One target value: goes to its slot in LDS (byte address `at`, moved on) in the lanes where the id is kept, into the sums
+// of the ids that are not kept in the others.  The map's bits are shifted out at the top, one per value.  Written as one
+// block on the execution mask: four vector instructions; selecting in the sums and computing the address took eight.
+template <Powers POW>
+__device__ __forceinline__ void power_place(uint32_t &bits, uint32_t &at, float ev, float invN, float &s1, float &s2, float &s3)
+{
+    if (POW == Powers::Series) {
+        asm volatile("v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"
+                     "s_mov_b64 exec, vcc\n\t"
+                     "ds_write_b32 %[at], %[ev]\n\t"
+                     "v_add_u32 %[at], 4, %[at]\n\t"
+                     "s_not_b64 exec, exec\n\t"
+                     "v_add_f32 %[s1], %[ev], %[s1]\n\t"
+                     "v_fmac_f32 %[s2], %[ev], %[ev]\n\t"
+                     "s_mov_b64 exec, -1"
+                     : [m] "+v"(bits), [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2)
+                     : [ev] "v"(ev)
+                     : "vcc", "scc", "memory");
+    } else {
+        const float e2 = POW == Powers::Exact ? ev * ev * __builtin_amdgcn_rcpf(fmaf(ev, invN, 1.0f)) : ev * ev;
+        asm volatile("v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"
+                     "s_mov_b64 exec, vcc\n\t"
+                     "ds_write_b32 %[at], %[ev]\n\t"
+                     "v_add_u32 %[at], 4, %[at]\n\t"
+                     "s_not_b64 exec, exec\n\t"
+                     "v_add_f32 %[s1], %[ev], %[s1]\n\t"
+                     "v_add_f32 %[s2], %[e2], %[s2]\n\t"
+                     "v_fmac_f32 %[s3], %[e2], %[ev]\n\t"
+                     "s_mov_b64 exec, -1"
+                     : [m] "+v"(bits), [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2), [s3] "+v"(s3)
+                     : [ev] "v"(ev), [e2] "v"(e2)
+                     : "vcc", "scc", "memory");
     }
 }
 
-template <int PK, int QK, bool SERIES>
-__global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
+// Step A for one chunk: statistics to `stat` (arrays of nchunks floats), e of the kept ids to LDS.
+// lane_stat: which of the statistics the lane writes (-1: none).
+template <int PK, int QK, Powers POW>
+__device__ __forceinline__ void row_power_chunk(const PowerChunk<PK> &b, int c, int lo, int hi, int N,
+                                                const typename RawQuad<QK>::type (&qv)[4], int n, float *pk, const float *zero_quad,
+                                                float *stat, int nchunks, int lane_stat, float invN)
+{
+    constexpr bool CUBIC = POW == Powers::Cubic;
+    const int lane = lane_id();
+    float z[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) RawQuad<PK>::to(b.p[i], z[i]);
+    if (N - c * kChunk < kChunk) {                     // the last chunk of a row that does not fill it
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int left = N - (c * kChunk + 256 * i + 4 * lane);   // ids of the row from the lane's quad on
+            quad_shift(z[i], 4 - left);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e >= left) z[i][e] = PK == RDK_PROB_F32 ? 0.f : -INFINITY;
+        }
+    }
+    float mx = 0.f;
+    if (PK != RDK_PROB_F32) {
+        mx = raw_max3(z[0][0], z[0][1], z[0][2]);
+        mx = raw_max3(mx, z[0][3], z[1][0]);
+        mx = raw_max3(mx, z[1][1], z[1][2]);
+        float my = raw_max3(z[1][3], z[2][0], z[2][1]);
+        my = raw_max3(my, z[2][2], z[2][3]);
+        mx = raw_max3(mx, z[3][0], z[3][1]);
+        my = raw_max3(my, z[3][2], z[3][3]);
+        mx = wave_max_scalar(raw_max3(mx, my, kLowest));
+    }
+    const int run = row_run_start(lo, c);
+    uint32_t bits = __builtin_bitreverse32((uint32_t)b.map);   // the bit of the first id on top
+    const uint32_t first = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)pk + 4 * run;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // power sums, in the order of the enumeration; last the third power
+    float s3k = 0.f, q3 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t at = first + 4 * (uint32_t)((b.map >> (16 + 12 * i)) & 0xFFFu);
+        float ev[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ev[e] = to_weight<PK>(z[i][e], mx, 1.f);   // ids beyond N: zero
+#pragma unroll
+        for (int e = 0; e < 4; ++e) power_place<POW>(bits, at, ev[e], invN, v[kRowS1n], v[kRowS2n], v[7]);
+    }
+    // over the kept ids, in slot order; the drafter values relative to the largest of the run
+    float qf[4][4], qmx = 0.f;
+    if (lo < hi) {
+        constexpr float none = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
+        float m = kLowest;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (lo + 256 * i < hi) {
+                RawQuad<QK>::to(qv[i], qf[i]);
+                const int left = hi - lo - 4 * (lane + 64 * i);   // slots of the run from the lane's quad on
+                if (hi + 3 > n) quad_shift(qf[i], 4 - (n - lo - 4 * (lane + 64 * i)));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) qf[i][e] = e < left ? qf[i][e] : none;
+                if (QK != RDK_PROB_F32) m = raw_max3(raw_max3(m, qf[i][0], qf[i][1]), qf[i][2], qf[i][3]);
+            }
+        }
+        if (QK != RDK_PROB_F32) qmx = wave_max_scalar(m);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (lo + 256 * i < hi) {
+                const int o = 4 * (lane + 64 * i);
+                const float4 e4 = *(const float4 *)(o < hi - lo ? pk + run + o : zero_quad);   // past the run: zeros
+                const float ee[4] = {e4.x, e4.y, e4.z, e4.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float qe = to_weight<QK>(qf[i][e], qmx, 1.f);
+                    float e2 = ee[e] * ee[e];
+                    if (POW == Powers::Exact) e2 *= __builtin_amdgcn_rcpf(fmaf(ee[e], invN, 1.0f));
+                    v[kRowS1k] += ee[e];
+                    v[kRowS2k] += e2;
+                    v[kRowQ0] += qe;
+                    v[kRowQ1] = fmaf(qe, ee[e], v[kRowQ1]);
+                    v[kRowQ2] = fmaf(qe, e2, v[kRowQ2]);
+                    if (CUBIC) {
+                        s3k = fmaf(e2, ee[e], s3k);
+                        q3 = fmaf(qe * e2, ee[e], q3);
+                    }
+                }
+            }
+        }
+    } else if (QK != RDK_PROB_F32) {
+        qmx = kLowest;
+    }
+    float out = wave_sum8(v);
+    if (CUBIC) {
+        s3k = lane_value(wave_sum_last(s3k), kWave - 1);
+        q3 = lane_value(wave_sum_last(q3), kWave - 1);
+        out = lane == 3 ? s3k : lane == 4 ? q3 : out;
+    }
+    out = lane == 1 ? mx : lane == 2 ? qmx : out;
+    if (lane_stat >= 0) stat[lane_stat * nchunks + c] = out;
+}
+
+template <int PK, int QK, Powers POW, int T>
+__global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
                                                                        const uint64_t *lane_map, const int32_t *chunk_lo,
                                                                        const int32_t *item_lo, const int2 *row_items, int N, int n,
-                                                                       bool vec_p, const SoftStat *qstat, const int32_t *slot_of,
+                                                                       bool vec_p, const int32_t *slot_of,
                                                                        FinalizeArgs fin)
 {
+    constexpr bool CUBIC = POW == Powers::Cubic;
+    constexpr int kW = T / kWave, kG = T / 16;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int nchunks = (N + kChunk - 1) / kChunk;
-    const RowLds L = row_lds_layout(n, nchunks);
-    float *pk = lds + L.pk, *stat = lds + L.blk_p;
+    const RowLds L = row_lds_layout(n, nchunks, CUBIC ? kRowAllArrays : kRowArrays, kW);
+    float *pk = lds + L.pk, *stat = lds + L.blk;
     int2 *il = (int2 *)(lds + L.items);
     int *ilo = (int *)(lds + L.item_lo);
-    float2 *isum = (float2 *)(lds + L.isum);
+    float2 *isum = (float2 *)(lds + L.items);          // an entry is read before its sums are written, by the same lanes
     const int64_t row = blockIdx.x;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
     const void *pr = row_ptr<PK>(p, ldp, row);
     const void *qr = row_ptr<QK>(q, ldq, row);
-    const float qm = QK == RDK_PROB_F32 ? 0.f : qstat[row].m;
     const float fN = (float)N;
-    RowRcp<SERIES> rcp;
+    RowRcp<POW == Powers::Series> rcp;
     rcp.fN = fN;
     rcp.invN = 1.0f / fN;
     rcp.invN2 = rcp.invN * rcp.invN;
 
-    // ---- prologue: as for probability rows
+    // ---- prologue: the table of pieces, zeros where the kept target values go, and the first two chunks of every wavefront
+    // on their way meanwhile.  The table of pieces is asked for before the first chunks: loads come back
+    // in the order in which they were issued, and the barrier then waits for the table alone.
     const int max_items = row_max_items(n, nchunks);
     const int nitems = item_lo[nchunks];
-    int2 it0 = make_int2(0, 0);
+    int2 it0 = make_int2(0, 0), it1 = make_int2(0, 0);
+    int lo0 = 0;
     if ((int)threadIdx.x < max_items) it0 = row_items[threadIdx.x];
-    RowChunk b0, b1, b2;
+    if ((int)threadIdx.x + T < max_items) it1 = row_items[threadIdx.x + T];
+    if ((int)threadIdx.x <= nchunks) lo0 = item_lo[threadIdx.x];
+    PowerChunk<PK> b0, b1, b2;
     int c = wid;
-    if (c < nchunks) row_fetch<PK>(pr, lane_map, chunk_lo, c, N, vec_p, b0);
-    if (c + kRowWaves < nchunks) row_fetch<PK>(pr, lane_map, chunk_lo, c + kRowWaves, N, vec_p, b1);
+    // without a condition: a way round these loads would make the wait for the table one for everything
+    power_fetch<PK>(pr, lane_map, chunk_lo, min(c, nchunks - 1), N, b0);
+    power_fetch<PK>(pr, lane_map, chunk_lo, min(c + kW, nchunks - 1), N, b1);
     if (threadIdx.x == 0) {
         uint32_t words[4];
         position_words(fin.d.seed, fin.d.offset + (uint64_t)row, words);
@@ -1078,25 +957,28 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
     }
     {
         float4 *z = (float4 *)pk;
-        const int quads = (L.blk_p - L.pk) / 4;
-        for (int i = threadIdx.x; i < quads; i += kRowThreads) z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        const int quads = (L.blk - L.pk) / 4;
+        for (int i = threadIdx.x; i < quads; i += T) z[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         if ((int)threadIdx.x < max_items) il[threadIdx.x] = it0;
-        for (int k = threadIdx.x + kRowThreads; k < max_items; k += kRowThreads) il[k] = row_items[k];
-        for (int cc = threadIdx.x; cc <= nchunks; cc += kRowThreads) ilo[cc] = item_lo[cc];
+        if ((int)threadIdx.x + T < max_items) il[threadIdx.x + T] = it1;
+        for (int k = threadIdx.x + 2 * T; k < max_items; k += T) il[k] = row_items[k];
+        if ((int)threadIdx.x <= nchunks) ilo[threadIdx.x] = lo0;
+        for (int cc = threadIdx.x + T; cc <= nchunks; cc += T) ilo[cc] = item_lo[cc];
     }
     __syncthreads();
 
-    // ---- step A
-    float4 qv[4];
-    if (c < nchunks) row_q_fetch<QK>(qr, b0.lo, b0.hi, n, qv);
+    // ---- step A.  A lane of every eight writes one of the eight sums, the lanes 1 to 4 what else a chunk leaves behind.
+    const int lane_sum = (int)(__builtin_bitreverse32((uint32_t)lane >> 3) >> 29);
+    const int lane_stat = (lane & 7) == 0 ? (lane_sum < 7 ? lane_sum : CUBIC ? kRowS3n : -1)
+                          : lane == 1 ? kRowMax : lane == 2 ? kRowQMax : CUBIC && lane == 3 ? kRowS3k : CUBIC && lane == 4 ? kRowQ3 : -1;
+    typename RawQuad<QK>::type qv[4];
+    if (c < nchunks) power_q_fetch<QK>(qr, b0.lo, b0.hi, n, qv);
 #define RDK_ROW_STEP(CUR, NEXT, FREE)                                                                        \
     {                                                                                                        \
-        if (c + 2 * kRowWaves < nchunks) row_fetch<PK>(pr, lane_map, chunk_lo, c + 2 * kRowWaves, N, vec_p, FREE); \
-        const int lo_c = __builtin_amdgcn_readfirstlane(CUR.lo), hi_c = __builtin_amdgcn_readfirstlane(CUR.hi); \
-        row_logit_chunk<QK, !SERIES>(CUR, c, lo_c, hi_c, qv, pk, lds + L.zero, stat, qm, nchunks);           \
-        if (c + kRowWaves < nchunks)                                                                         \
-            row_q_fetch<QK>(qr, __builtin_amdgcn_readfirstlane(NEXT.lo), __builtin_amdgcn_readfirstlane(NEXT.hi), n, qv); \
-        c += kRowWaves;                                                                                      \
+        if (c + 2 * kW < nchunks) power_fetch<PK>(pr, lane_map, chunk_lo, c + 2 * kW, N, FREE); \
+        row_power_chunk<PK, QK, POW>(CUR, c, CUR.lo, CUR.hi, N, qv, n, pk, lds + L.zero, stat, nchunks, lane_stat, rcp.invN); \
+        if (c + kW < nchunks) power_q_fetch<QK>(qr, NEXT.lo, NEXT.hi, n, qv);                         \
+        c += kW;                                                                                      \
     }
     while (c < nchunks) {
         RDK_ROW_STEP(b0, b1, b2)
@@ -1106,10 +988,11 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
         RDK_ROW_STEP(b2, b0, b1)
     }
 #undef RDK_ROW_STEP
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the compiler does not count the LDS writes of power_place
 
     // ---- the pieces of step C: drafter values, LDS offsets and chunks of the first rounds, before the barrier
     const int grp = threadIdx.x >> 4, li = threadIdx.x & 15;
-    float4 qh[kRowHeld];
+    typename RawQuad<QK>::type qh[kRowHeld];
     int pat[kRowHeld], pch[kRowHeld];
     auto piece_of = [&](int k, int &len, int &chunk) {
         const int2 it = il[k];
@@ -1119,7 +1002,7 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
     };
 #pragma unroll
     for (int t = 0; t < kRowHeld; ++t) {
-        const int k = grp + kRowGroups * t;
+        const int k = grp + kG * t;
         int len = 0, first = 0;
         pat[t] = L.zero;
         pch[t] = 0;
@@ -1127,46 +1010,53 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
             pat[t] = piece_of(k, len, pch[t]);
             first = il[k].x;
         }
-        qh[t] = row_raw_quad<QK>(qr, first + 4 * li, first + len, n);
+        qh[t] = raw_quad<QK>(qr, first + 4 * li, n);
     }
     __syncthreads();
 
-    // ---- the row maximum, the chunk statistics relative to it, their totals
-    float pm = -INFINITY;
-    for (int cc = threadIdx.x; cc < nchunks; cc += kRowThreads) pm = fmaxf(pm, stat[kLgMax * nchunks + cc]);
-    pm = wave_max(pm);
-    if (lane == 0) lds[L.red + wid] = pm;
-    __syncthreads();
-    pm = lds[L.red];
-    for (int i = 1; i < kRowWaves; ++i) pm = fmaxf(pm, lds[L.red + i]);
-    float t7[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum e, e^2, e^3 over all ids; sum q^ e^k, k = 0..3
-    for (int cc = threadIdx.x; cc < nchunks; cc += kRowThreads) {
-        const float f = soft_exp_fine(stat[kLgMax * nchunks + cc] - pm), f2 = f * f, f3 = f2 * f;   // shared by 1024 ids
-        const float s1n = stat[kLgS1n * nchunks + cc] * f, s2n = stat[kLgS2n * nchunks + cc] * f2, s3n = stat[kLgS3n * nchunks + cc] * f3;
-        const float s1k = stat[kLgS1k * nchunks + cc] * f, s2k = stat[kLgS2k * nchunks + cc] * f2, s3k = stat[kLgS3k * nchunks + cc] * f3;
-        const float q0 = stat[kLgQ0 * nchunks + cc], q1 = stat[kLgQ1 * nchunks + cc] * f, q2 = stat[kLgQ2 * nchunks + cc] * f2;
-        const float q3 = stat[kLgQ3 * nchunks + cc] * f3;
-        stat[kLgS1n * nchunks + cc] = s1n; stat[kLgS2n * nchunks + cc] = s2n; stat[kLgS3n * nchunks + cc] = s3n;
-        stat[kLgS1k * nchunks + cc] = s1k; stat[kLgS2k * nchunks + cc] = s2k; stat[kLgS3k * nchunks + cc] = s3k;
-        stat[kLgQ1 * nchunks + cc] = q1; stat[kLgQ2 * nchunks + cc] = q2; stat[kLgQ3 * nchunks + cc] = q3;
-        stat[kLgScale * nchunks + cc] = f;
-        t7[0] += s1n + s1k; t7[1] += s2n + s2k; t7[2] += s3n + s3k;
-        t7[3] += q0; t7[4] += q1; t7[5] += q2; t7[6] += q3;
+    // ---- the row maxima (every wavefront for itself), the chunk statistics relative to them, their totals
+    float pm = kLowest, qm = kLowest;
+    for (int cc = lane; cc < nchunks; cc += kWave) {
+        pm = raw_max(pm, stat[kRowMax * nchunks + cc]);
+        qm = raw_max(qm, stat[kRowQMax * nchunks + cc]);
     }
-#pragma unroll
-    for (int j = 0; j < 7; ++j) {
-        const float v = wave_sum_last(t7[j]);
-        if (lane == kWave - 1) lds[L.red + kRowWaves + wid * 8 + j] = v;
+    pm = PK == RDK_PROB_F32 ? 0.f : wave_max_scalar(pm);
+    qm = QK == RDK_PROB_F32 ? 0.f : wave_max_scalar(qm);
+    float t7[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum e, e^2, e^3 over all ids; sum q^ e^k, k = 0..3
+    for (int cc = threadIdx.x; cc < nchunks; cc += T) {
+        float *sc = stat + cc;
+        const float f = PK == RDK_PROB_F32 ? 1.f : soft_exp_fine(sc[kRowMax * nchunks] - pm), f2 = f * f, f3 = f2 * f;   // shared by 1024 ids
+        const float fq = QK == RDK_PROB_F32 ? 1.f : soft_exp_fine(sc[kRowQMax * nchunks] - qm);
+        const float s1n = sc[kRowS1n * nchunks] * f, s2n = sc[kRowS2n * nchunks] * f2;
+        const float s1k = sc[kRowS1k * nchunks] * f, s2k = sc[kRowS2k * nchunks] * f2;
+        const float q0 = sc[kRowQ0 * nchunks] * fq, q1 = sc[kRowQ1 * nchunks] * f * fq, q2 = sc[kRowQ2 * nchunks] * f2 * fq;
+        sc[kRowS1n * nchunks] = s1n; sc[kRowS2n * nchunks] = s2n;
+        sc[kRowS1k * nchunks] = s1k; sc[kRowS2k * nchunks] = s2k;
+        sc[kRowQ0 * nchunks] = q0; sc[kRowQ1 * nchunks] = q1; sc[kRowQ2 * nchunks] = q2;
+        sc[kRowScale * nchunks] = f;
+        t7[0] += s1n + s1k; t7[1] += s2n + s2k;
+        t7[3] += q0; t7[4] += q1; t7[5] += q2;
+        if (CUBIC) {
+            const float s3n = sc[kRowS3n * nchunks] * f3, s3k = sc[kRowS3k * nchunks] * f3, q3 = sc[kRowQ3 * nchunks] * f3 * fq;
+            sc[kRowS3n * nchunks] = s3n; sc[kRowS3k * nchunks] = s3k; sc[kRowQ3 * nchunks] = q3;
+            t7[2] += s3n + s3k;
+            t7[6] += q3;
+        }
+    }
+    {
+        const float v8[8] = {t7[0], t7[1], t7[2], t7[3], t7[4], t7[5], t7[6], 0.f};
+        const float v = wave_sum8(v8);
+        if ((lane & 7) == 0) lds[L.red + wid * 8 + lane_sum] = v;
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 7; ++j) t7[j] = 0.f;
-    for (int i = 0; i < kRowWaves; ++i) {
-        const float4 a4 = *(const float4 *)(lds + L.red + kRowWaves + i * 8), b4 = *(const float4 *)(lds + L.red + kRowWaves + i * 8 + 4);
+    for (int i = 0; i < kW; ++i) {
+        const float4 a4 = *(const float4 *)(lds + L.red + i * 8), b4 = *(const float4 *)(lds + L.red + i * 8 + 4);
         t7[0] += a4.x; t7[1] += a4.y; t7[2] += a4.z; t7[3] += a4.w;
         t7[4] += b4.x; t7[5] += b4.y; t7[6] += b4.z;
     }
-    const float pinv = 1.0f / t7[0];                   // the row maximum itself contributes e = 1: never zero
+    const float pinv = PK == RDK_PROB_F32 ? 1.f : 1.0f / t7[0];   // the row maximum itself contributes e = 1: never zero
     const float c1 = pinv / fN, c2 = c1 * c1, c3 = c2 * c1;
     const float zq = t7[3], tn = t7[4] * pinv;
     const float an = t7[3] - t7[4] * c1 + t7[5] * c2 - t7[6] * c3;     // sum q^ N / (N + p)
@@ -1177,11 +1067,15 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
     const float nzs = fN * inv_zq * inv_S, ths = theta * inv_S;
 
     // ---- step C
-    auto piece_sums = [&](int k, const float4 raw, int at, int chunk) {
-        const float g = stat[kLgScale * nchunks + chunk] * pinv;       // e of this chunk -> p
-        const float4 w4 = row_weights_of<QK>(raw, qm);
+    auto piece_sums = [&](int k, const typename RawQuad<QK>::type raw, int at, int chunk) {
+        const float g = stat[kRowScale * nchunks + chunk] * pinv;       // e of this chunk -> p
         const float4 e4 = *(const float4 *)(lds + at);
-        const float qe[4] = {w4.x, w4.y, w4.z, w4.w}, pe[4] = {e4.x * g, e4.y * g, e4.z * g, e4.w * g};
+        float qe[4];
+        RawQuad<QK>::to(raw, qe);
+        if (k >= nitems - 3) quad_shift(qe, row_items[k].x + 4 * li + 4 - n);   // a quad of the last pieces may cross the end of the row
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qe[e] = to_weight<QK>(qe[e], qm, 1.f);
+        const float pe[4] = {e4.x * g, e4.y * g, e4.z * g, e4.w * g};
         float sr = 0.f, sa = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1196,31 +1090,35 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
     };
 #pragma unroll
     for (int t = 0; t < kRowHeld; ++t) {
-        const int k = grp + kRowGroups * t;
+        const int k = grp + kG * t;
         if (k < nitems) piece_sums(k, qh[t], pat[t], pch[t]);
     }
-    for (int k = grp + kRowGroups * kRowHeld; k < nitems; k += kRowGroups) {
+    for (int k = grp + kG * kRowHeld; k < nitems; k += kG) {
         int len, chunk;
         const int at = piece_of(k, len, chunk);
         const int first = il[k].x;
-        piece_sums(k, row_raw_quad<QK>(qr, first + 4 * li, first + len, n), at, chunk);
+        piece_sums(k, raw_quad<QK>(qr, first + 4 * li, n), at, chunk);
     }
     __syncthreads();
 
     // ---- the block sums of a chunk: its pieces in order, and the closed forms from the chunk's power sums.  The three
     // results take the place of the kept values in LDS (no longer needed), the statistics are read before.
-    for (int cc = grp; cc < nchunks; cc += kRowGroups) {
+    for (int cc = grp; cc < nchunks; cc += kG) {
         const int k = ilo[cc] + li;
         const float2 f = k < ilo[cc + 1] ? isum[k] : make_float2(0.f, 0.f);
         const float sr = row16_sum(f.x), sa = row16_sum(f.y);
         if (li == 0) {
-            const float s1n = stat[kLgS1n * nchunks + cc], s2n = stat[kLgS2n * nchunks + cc], s3n = stat[kLgS3n * nchunks + cc];
-            const float s1k = stat[kLgS1k * nchunks + cc], s2k = stat[kLgS2k * nchunks + cc], s3k = stat[kLgS3k * nchunks + cc];
-            const float q0 = stat[kLgQ0 * nchunks + cc], q1 = stat[kLgQ1 * nchunks + cc], q2 = stat[kLgQ2 * nchunks + cc];
-            const float q3 = stat[kLgQ3 * nchunks + cc];
-            const float a_nk = s1n * c1 - s2n * c2 + s3n * c3;         // sum p / (N + p), not-kept ids
-            const float a_k = s1k * c1 - s2k * c2 + s3k * c3;          //                  kept ids
-            const float aq = (q0 - q1 * c1 + q2 * c2 - q3 * c3) * rcp.invN;   // sum q^ / (N + p), kept ids
+            const float *sc = stat + cc;
+            const float s1n = sc[kRowS1n * nchunks];
+            float a_nk = s1n * c1 - sc[kRowS2n * nchunks] * c2;                   // sum p / (N + p), not-kept ids
+            float a_k = sc[kRowS1k * nchunks] * c1 - sc[kRowS2k * nchunks] * c2;   //                  kept ids
+            float aq = sc[kRowQ0 * nchunks] - sc[kRowQ1 * nchunks] * c1 + sc[kRowQ2 * nchunks] * c2;
+            if (CUBIC) {
+                a_nk += sc[kRowS3n * nchunks] * c3;
+                a_k += sc[kRowS3k * nchunks] * c3;
+                aq -= sc[kRowQ3 * nchunks] * c3;
+            }
+            aq *= rcp.invN;                                            // sum q^ / (N + p), kept ids
             const float ta = ths * a_nk;                               // sum of q' (= sum of min(p, q')) over the not-kept ids
             lds[L.sum_q + cc] = ths * (a_nk + a_k) + nzs * aq;
             lds[L.sum_a + cc] = ta + sa;
@@ -1230,12 +1128,17 @@ __global__ __launch_bounds__(kRowThreads) void taylor_row_logit_kernel(const voi
     __syncthreads();
 
     // ---- the finish of the row (draws, accept test), spread over the wavefronts
-    row_finish<PK, QK, false>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid,
+    row_finish<PK, QK, T == kRowThreads>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid,
                        lane);
 }
 
 constexpr int kRowSeriesMinN = 4096;   // from here on 1 / (N + p) is taken from its series in p / N (exact to fp32 rounding)
-constexpr int kRowMinBatch = 64;   // below this the two-pass kernels, which split a row over workgroups, fill the chip better
+// Below these batches the two-pass kernels, which split a row over workgroups, fill the chip better (N = 128256, 24 / 56 / 88
+// rows of probabilities: 16.0 / 22.8 / 30 us against a flat 30; of logits, with one more launch: 36.4 against 36.6 at 60) ...
+constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 64;
+// ... unless the rows are short: at any batch, one launch against three or four (24000 ids, probabilities: 13.2 us against
+// 13.8, from 8192 ids on down 11.6 against 13.7; 48000 ids, logits: 20.4 against 21.6, 8000 ids: 12.5 against 20.9).
+constexpr int kRowShortN = 24 * 1024, kRowShortLogitN = 48 * 1024;
 
 // LDS a workgroup may use on the current device (asked once).
 size_t row_lds_limit()
@@ -1282,32 +1185,25 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     uint64_t *seq_rec = (uint64_t *)(fused_ws + 3 * per);
     {
         // the fused call without q': one pass over the target rows, one workgroup per position, when the kept target
-        // values of a row fit the LDS of a compute unit and there are enough positions to fill the chip (logit rows: from
-        // the vocabulary size on at which the series of their chunk sums are exact to fp32 rounding)
-        const size_t lds_bytes = (size_t)row_lds_layout(h.n, nchunks).total * sizeof(float);
-        const int min_N = PK == RDK_PROB_F32 ? 2 : kOnePassMinN;
-        if (c && !out && h.N >= min_N && B >= kRowMinBatch && lds_bytes <= row_lds_limit()) {
-            if (QK != RDK_PROB_F32) {
-                rc = launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
-                if (rc != RDK_OK) return rc;
+        // values of a row fit the LDS of a compute unit and there are enough positions to fill the chip, or the rows are so
+        // short that splitting them saves less than the extra launches cost (logit rows: from the vocabulary size on at
+        // which the series of their chunk sums are exact to fp32 rounding)
+        const Powers pow = h.N >= kRowSeriesMinN ? Powers::Series : PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
+        const int arrays = pow == Powers::Cubic ? kRowAllArrays : kRowArrays;
+        size_t lds_bytes = (size_t)row_lds_layout(h.n, nchunks, arrays, kRowWaves).total * sizeof(float);
+        const bool fits = h.N >= (PK == RDK_PROB_F32 ? 4 : kOnePassMinN) && h.n >= 4 && lds_bytes <= row_lds_limit();
+        const bool pays = PK == RDK_PROB_F32 ? B >= kRowMinBatch || h.N <= kRowShortN : B >= kRowMinBatchLogit || h.N <= kRowShortLogitN;
+        if (c && !out && fits && pays) {
+            // More rows than compute units: workgroups of half the size, two on a unit where their LDS allows it, so that
+            // one streams while the other is at its barriers and its finish.
+            bool halves = false;
+            if (B > kComputeUnits) {
+                const size_t half_bytes = (size_t)row_lds_layout(h.n, nchunks, arrays, kRowWaves / 2).total * sizeof(float);
+                halves = 2 * align_up(half_bytes, 2048) <= row_lds_limit();
+                if (halves) lds_bytes = half_bytes;
             }
             const bool vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
             if (q.kind != RDK_LOGIT_BF16 && ((uintptr_t)q.ptr % 4 != 0)) return RDK_ERR_ALIGN;
-            static bool attr_set = false;     // per instantiation: dynamic LDS above the default limit has to be granted once
-            if (!attr_set) {
-                if constexpr (PK == RDK_PROB_F32) {
-                    RDK_HIP(hipFuncSetAttribute((const void *)taylor_row_kernel<QK, true>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds_limit()));
-                    RDK_HIP(hipFuncSetAttribute((const void *)taylor_row_kernel<QK, false>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds_limit()));
-                } else {
-                    RDK_HIP(hipFuncSetAttribute((const void *)taylor_row_logit_kernel<PK, QK, true>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds_limit()));
-                    RDK_HIP(hipFuncSetAttribute((const void *)taylor_row_logit_kernel<PK, QK, false>,
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds_limit()));
-                }
-                attr_set = true;
-            }
             FinalizeArgs fa{};                // the block sums stay in the workgroup's LDS
             fa.d = c->d;
             fa.p = p.ptr; fa.ldp = p.ld; fa.vec_p = vec_p;
@@ -1316,19 +1212,28 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
             fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
             // with more positions than compute units the workgroups take turns, and each would add its round trips to the
-            // chain of its unit: the scan is a launch of its own then.  So it is for logit rows, whose kernel has no scalar
-            // registers left for it (they spill inside its loops: 203 us against 186 at the qwen_extreme shape).
-            if (PK == RDK_PROB_F32 && B <= kComputeUnits) set_scan(fa, seq_rec);
-            const bool series = h.N >= kRowSeriesMinN;
-#define RDK_ROW_LAUNCH(KERNEL, PPTR)                                                                                        \
-    RDK_TIMED_LAUNCH("taylor_row_kernel", KERNEL, dim3((unsigned)B), dim3(kRowThreads), lds_bytes, st, PPTR, p.ld, q.ptr, q.ld,  \
-                     h.lane_map, h.chunk_lo, h.item_lo, h.row_items, h.N, h.n, vec_p, w.qstat, h.slot_of, fa)
-            if constexpr (PK == RDK_PROB_F32) {
-                if (series) RDK_ROW_LAUNCH((taylor_row_kernel<QK, true>), (const float *)p.ptr);
-                else RDK_ROW_LAUNCH((taylor_row_kernel<QK, false>), (const float *)p.ptr);
+            // chain of its unit: the scan is a launch of its own then
+            if (B <= kComputeUnits) set_scan(fa, seq_rec);
+            // dynamic LDS above the default limit has to be granted once to every instantiation
+#define RDK_ROW_LAUNCH(POW, THREADS)                                                                                         \
+    {                                                                                                                       \
+        static bool attr_set = false;                                                                                       \
+        if (!attr_set) {                                                                                                    \
+            RDK_HIP(hipFuncSetAttribute((const void *)taylor_row_kernel<PK, QK, POW, THREADS>,                              \
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds_limit()));                 \
+            attr_set = true;                                                                                                \
+        }                                                                                                                   \
+        RDK_TIMED_LAUNCH("taylor_row_kernel", (taylor_row_kernel<PK, QK, POW, THREADS>), dim3((unsigned)B), dim3(THREADS),  \
+                         lds_bytes, st, p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.item_lo, h.row_items, h.N, h.n, \
+                         vec_p, h.slot_of, fa);                                                                             \
+    }
+            constexpr Powers kSmall = PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
+            if (pow == Powers::Series) {
+                if (halves) RDK_ROW_LAUNCH(Powers::Series, kRowThreads / 2)
+                else RDK_ROW_LAUNCH(Powers::Series, kRowThreads)
             } else {
-                if (series) RDK_ROW_LAUNCH((taylor_row_logit_kernel<PK, QK, true>), p.ptr);
-                else RDK_ROW_LAUNCH((taylor_row_logit_kernel<PK, QK, false>), p.ptr);
+                if (halves) RDK_ROW_LAUNCH(kSmall, kRowThreads / 2)
+                else RDK_ROW_LAUNCH(kSmall, kRowThreads)
             }
 #undef RDK_ROW_LAUNCH
             RDK_LAUNCH_CHECK("taylor_row_kernel");

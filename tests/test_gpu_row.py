@@ -1,0 +1,61 @@
+"""Eq. 3 in one pass where it can go wrong: the smallest vocabularies, both sides of the sizes at which the series of its sums
+change, ends inside a quad, runs of one slot at the end of the row, chunks without kept ids or without any target mass, two
+workgroups on a compute unit, rows at odd strides -- against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_03206_amd import synth
+from parity_util import check_verify_outputs
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # N, n, B, gamma, which ids are kept
+    (5, 4, 6, 3, "any"),
+    (1023, 130, 3, 1, "any"),
+    (1025, 131, 3, 3, "any"),
+    (4095, 900, 258, 2, "any"),     # more rows than compute units
+    (4099, 1030, 4, 2, "tail"),     # the last three runs hold one slot each
+    (9001, 700, 260, 4, "first"),   # the kept ids in one chunk
+    (24576, 6001, 2, 2, "any"),
+    (49152, 9999, 2, 1, "tail"),
+]
+
+
+@pytest.mark.parametrize("kind", ["prob", "logit", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_one_pass_rows_against_oracle(shape, kind):
+    from paper_2506_03206_amd import rdk
+    N, n, B, gamma, where = shape
+    rng = np.random.default_rng(N + n)
+    if where == "first":
+        kept = np.sort(rng.choice(1000, size=n, replace=False))
+    elif where == "tail":
+        last = (N - 1) // 1024 * 1024                  # first id of the last chunk
+        kept = np.concatenate([np.sort(rng.choice(last - 2048, size=n - 3, replace=False)), [last - 1500, last - 7, N - 1]])
+    else:
+        kept = np.sort(rng.choice(N, size=n, replace=False))
+    kept = kept.astype(np.int32)
+    zp = (rng.normal(size=(B, N)) * 2).astype(np.float32)
+    zq = (zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept]
+    if kind == "bf16":
+        zp, zq = synth.bf16_round(zp), synth.bf16_round(zq)
+    if N > 3072:
+        zp[0, 1024:2048] = -np.inf                     # a chunk of masked ids
+    pk = "prob" if kind == "prob" else "logit"
+    if kind == "prob":
+        zp, zq = [oracle.probs_from(x, "logit").astype(np.float32) for x in (zp, zq)]
+    dt = torch.bfloat16 if kind == "bf16" else torch.float32
+    wide = lambda a: torch.nn.functional.pad(torch.from_numpy(np.ascontiguousarray(a)).cuda().to(dt), (0, 1), value=float("nan"))[:, :-1]
+    kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
+    p64, q64 = oracle.probs_from(zp, pk), oracle.probs_from(zq, pk)
+    ref_qp = oracle.redistribute_batch("taylor", q64, kept, N, p=p64)
+    rdk.rdk_timing_select("taylor_row_kernel")
+    out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, wide(zp), wide(zq), 9, 4, gamma, pk, pk)
+    torch.cuda.synchronize()
+    rdk.rdk_timing_select(None)
+    one_pass = N >= 1024 if pk == "logit" else N <= 24576
+    assert rdk.rdk_timing_read("taylor_row_kernel")[0] == one_pass
+    ref = oracle.verify_batch(p64, ref_qp, 9, 4, gamma=gamma)
+    check_verify_outputs(out, ref, p64, ref_qp, 9, 4, gamma, pk, min_exact=0.6)
