@@ -698,40 +698,6 @@ __device__ __forceinline__ float wave_sum8(const float (&v)[8])
     return a;
 }
 
-// Four consecutive raw values as they lie in memory: the conversion of bf16 waits until they are used, or every load would
-// be waited for where it is made.
-template <int KIND>
-struct RawQuad {
-    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
-    static __device__ __forceinline__ void to(const type r, float (&v)[4])
-    {
-        v[0] = r.x; v[1] = r.y; v[2] = r.z; v[3] = r.w;
-    }
-};
-template <>
-struct RawQuad<RDK_LOGIT_BF16> {
-    typedef unsigned type __attribute__((ext_vector_type(2), aligned(2)));
-    static __device__ __forceinline__ void to(const type r, float (&v)[4])
-    {
-        v[0] = __uint_as_float(r.x << 16); v[1] = __uint_as_float(r.x & 0xFFFF0000u);
-        v[2] = __uint_as_float(r.y << 16); v[3] = __uint_as_float(r.y & 0xFFFF0000u);
-    }
-};
-template <int KIND>
-__device__ __forceinline__ typename RawQuad<KIND>::type raw_quad(const void *row, int i, int len)
-{
-    typedef typename RawQuad<KIND>::type Raw;
-    return *(const Raw *)((const char *)row + (uint32_t)min(i, len - 4) * (KIND == RDK_LOGIT_BF16 ? 2u : 4u));
-}
-// raw_quad reads the last four values of the row for a quad that crosses its end: `past` places too early.
-__device__ __forceinline__ void quad_shift(float (&v)[4], int past)
-{
-    past = max(past, 0);
-    const bool one = past & 1, two = past & 2;
-    v[0] = one ? v[1] : v[0]; v[1] = one ? v[2] : v[1]; v[2] = one ? v[3] : v[2];
-    v[0] = two ? v[2] : v[0]; v[1] = two ? v[3] : v[1];
-}
-
 // A chunk of a target row, raw.  Quads need the alignment of one element only (that is all that a global load asks for),
 // and no load depends on a branch: the quads that cross the end of the row or lie past it are put right where they are used.
 template <int PK>

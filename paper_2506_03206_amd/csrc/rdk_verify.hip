@@ -1,7 +1,7 @@
 // Verification of a batch of positions: Alg. 4 of the paper, steps 2 and 4-10, given the target
 // rows p and the redistributed drafter rows q' (both over the N target ids).
 //
-// Two launches (three when p arrives as logits):
+// Short rows: one launch (verify_row_kernel).  Otherwise two (three when p arrives as logits):
 //   [row_softstats]   running (max, sum exp) of the logits, a few partials per row
 //   verify_stream     one pass over p and q': per 1024-id block the sums of q', of max(0, p - q')
 //                     and of min(p, q')  (Def. 2.1 and the residual of step 8)
@@ -101,6 +101,145 @@ __global__ __launch_bounds__(kStreamThreads) void verify_stream_kernel(const voi
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The whole verification of a position by one workgroup: softmax statistics (logit rows), block sums in LDS, finish and
+// scan, in one launch where the split form takes two (three for logits).  The chunks of 1024 ids are dealt to the wavefronts
+// in turn; two chunks of both rows are on their way at a time, asked for before anything else, and a logit row whose chunks
+// are all among them (N <= 32768 with sixteen wavefronts) is read once; a longer one is read a second time, out of L2.  Sums
+// and draws are those of the split form, bit for bit with probability rows.
+// What bounds it: the chain of dependent steps of one position (N = 1000: 7.3 us of GPU time, a launch included); for the
+// longest rows the rate at which one compute unit reads (N = 32000, 64 rows: 11.4 us).
+constexpr int kRowMaxChunks = 64;   // of the block sums in LDS
+
+template <int KIND>
+struct RowPair {
+    typename RawQuad<KIND>::type p[4];
+    typename RawQuad<RDK_PROB_F32>::type q[4];
+};
+
+// The lane's four values of quad i of chunk c; ids beyond N come back as `fill`.
+template <int KIND>
+__device__ __forceinline__ void row_quad_values(const typename RawQuad<KIND>::type raw, int c, int i, int N, float fill, float (&v)[4])
+{
+    RawQuad<KIND>::to(raw, v);
+    if (N - c * kChunk < kChunk) {                                        // the same for the whole wavefront
+        const int left = N - (c * kChunk + 256 * i + 4 * lane_id());      // ids of the row from the lane's quad on
+        quad_shift(v, 4 - left);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e >= left) v[e] = fill;
+    }
+}
+
+template <int KIND>
+__device__ __forceinline__ void row_fetch(const void *row, int c, int N, typename RawQuad<KIND>::type (&v)[4])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = raw_quad<KIND>(row, c * kChunk + 256 * i + 4 * lane_id(), N);
+}
+
+template <int KIND>
+__device__ __forceinline__ void row_stat_chunk(const typename RawQuad<KIND>::type (&raw)[4], int c, int N, SoftStat &st)
+{
+    float v[4][4];
+    float mx = st.m;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        row_quad_values<KIND>(raw[i], c, i, N, -INFINITY, v[i]);
+        mx = fmaxf(mx, fmaxf(fmaxf(v[i][0], v[i][1]), fmaxf(v[i][2], v[i][3])));
+    }
+    if (mx > -INFINITY) {
+        float s = st.s == 0.f ? 0.f : st.s * soft_exp(st.m - mx);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            s += (soft_exp(v[i][0] - mx) + soft_exp(v[i][1] - mx)) + (soft_exp(v[i][2] - mx) + soft_exp(v[i][3] - mx));
+        st.m = mx;
+        st.s = s;
+    }
+}
+
+template <int KIND, int T>
+__global__ __launch_bounds__(T) void verify_row_kernel(const void *p, int64_t ldp, const float *q, int64_t ldq, int N,
+                                                                 int nchunks, bool vec_p, bool vec_q, FinalizeArgs fin)
+{
+    constexpr int kRowWaves = T / kWave;
+    __shared__ __attribute__((aligned(16))) float sums[3][kRowMaxChunks];   // of q', max(0, p - q'), min(p, q') per chunk
+    __shared__ __attribute__((aligned(16))) float scratch[kFinishFloats];
+    __shared__ SoftStat sh_stat[kRowWaves];
+    const int64_t row = blockIdx.x;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    const void *pr = row_ptr<KIND>(p, ldp, row);
+    const float *qr = q + row * ldq;
+    RowPair<KIND> buf[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int c = min(wid + t * kRowWaves, nchunks - 1);
+        row_fetch<KIND>(pr, c, N, buf[t].p);
+        row_fetch<RDK_PROB_F32>(qr, c, N, buf[t].q);
+    }
+    uint32_t words[4];
+    position_words(fin.d.seed, fin.d.offset + (uint64_t)row, words);
+    float pm = 0.f, pinv = 1.f;
+    if (KIND != RDK_PROB_F32) {
+        SoftStat st{-INFINITY, 0.f};
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (wid + t * kRowWaves < nchunks) row_stat_chunk<KIND>(buf[t].p, wid + t * kRowWaves, N, st);
+        for (int c = wid + 2 * kRowWaves; c < nchunks; c += kRowWaves) {
+            typename RawQuad<KIND>::type v[4];
+            row_fetch<KIND>(pr, c, N, v);
+            row_stat_chunk<KIND>(v, c, N, st);
+        }
+        st = wave_soft_merge(st);
+        if (lane == 0) sh_stat[wid] = st;
+        __syncthreads();
+        st = sh_stat[0];
+        for (int i = 1; i < kRowWaves; ++i) st = soft_merge(st, sh_stat[i]);
+        pm = st.m;
+        pinv = 1.0f / st.s;
+    }
+    auto chunk_sums = [&](const RowPair<KIND> &b, int c) {
+        float sq = 0.f, sr = 0.f, sa = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float pe[4], qe[4];
+            row_quad_values<KIND>(b.p[i], c, i, N, KIND == RDK_PROB_F32 ? 0.f : -INFINITY, pe);
+            row_quad_values<RDK_PROB_F32>(b.q[i], c, i, N, 0.f, qe);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float w = to_weight<KIND>(pe[e], pm, pinv);
+                sq += qe[e];
+                sr += fmaxf(w - qe[e], 0.f);
+                sa += fminf(w, qe[e]);
+            }
+        }
+        sr = wave_sum(sr);
+        sq = wave_sum(sq);
+        sa = wave_sum(sa);
+        if (lane == 0) {
+            sums[0][c] = sq;
+            sums[1][c] = sr;
+            sums[2][c] = sa;
+        }
+    };
+    for (int c = wid; c < nchunks; c += 2 * kRowWaves) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int cc = c + t * kRowWaves, next = cc + 2 * kRowWaves;
+            if (cc >= nchunks) break;
+            chunk_sums(buf[t], cc);
+            if (next < nchunks) {
+                row_fetch<KIND>(pr, next, N, buf[t].p);
+                row_fetch<RDK_PROB_F32>(qr, next, N, buf[t].q);
+            }
+        }
+    }
+    __syncthreads();
+    const QpMemory::Row qrow{qr, vec_q, N};
+    const PolicyQuads<QpMemory::Row, QpMemory::kStages> quads{qrow};
+    finish_row_quarters<KIND, true>(scratch, sums[0], sums[1], sums[2], nchunks, fin, row, pr, pm, pinv, N, vec_p, quads, words, wid, lane);
+}
+
 }  // namespace
 
 // Per-sequence scan as a launch of its own (sequences longer than one workgroup's waves).
@@ -147,6 +286,22 @@ __global__ void philox_words_kernel(uint64_t seed, uint64_t offset, int count, u
     for (int j = 0; j < 4; ++j) words[(int64_t)i * 4 + j] = w[j];
 }
 
+// Whether a position is verified by one workgroup in one launch.  The split form spreads a row over the chip, which pays
+// for its extra launches where there are few long rows.  Measured in GPU time of a call, split form -> one launch:
+//   probabilities   N = 1000:  4 rows 9.2 -> 7.3 us, 512 rows 12.1 -> 9.1;   N = 16000:  64 rows 11.2 -> 10.1, 256 rows 15.4 -> 12.3;
+//                   N = 24000: 4 rows 9.4 -> 8.9;   N = 32000: 4 rows 9.1 -> 10.0, 64 rows 11.9 -> 11.4, 512 rows 32.2 -> 30.1;
+//                   N = 64000: 96 rows 17.0 -> 20.3, 300 rows 35.5 -> 38.9;   N = 1000, 1024 rows (a second turn of workgroups) 14.5 -> 15.8
+//   bf16 logits     N = 1000:  4 rows 14.1 -> 10.7;   N = 4001: 512 rows 22.5 -> 13.9;   N = 24000: 4 rows 14.2 -> 13.3, 1024 rows
+//                   49.3 -> 43.8;   N = 32000: 4 rows 13.7 -> 15.4, 64 rows 16.8 -> 15.9;   N = 64000: 96 rows 21.7 -> 22.9,
+//                   256 rows 37.6 -> 31.2, 1024 rows 100.2 -> 86.7;   N = 128256: 300 rows 65.1 -> 72.4
+template <int KIND>
+bool row_in_one(const rdk_verify_desc_t &d)
+{
+    if (d.N < 4 || (KIND == RDK_PROB_F32 && d.B > 2 * kComputeUnits)) return false;
+    const int limit = d.B < 48 ? 24 : KIND == RDK_PROB_F32 || d.B < 128 ? 32 : kRowMaxChunks;
+    return d.N <= limit * kChunk;
+}
+
 template <int KIND, bool HAS_Q>
 rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, int64_t ldq, int32_t *draft_ids,
                         uint8_t *accept, float *alpha, float *resid_mass, int32_t *resid_ids, int32_t *n_accepted,
@@ -155,6 +310,28 @@ rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, 
     VerifyWs w = carve(d, ws);
     const bool vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
     const bool vec_q = HAS_Q ? rows_vectorisable(q, ldq, RDK_PROB_F32) : false;
+    FinalizeArgs fa{};
+    fa.d = d;
+    fa.p = p.ptr; fa.ldp = p.ld; fa.vec_p = vec_p;
+    fa.pstat = w.pstat; fa.p_splits = w.stat_splits;
+    fa.part_q = w.part_q; fa.part_r = w.part_r; fa.part_a = w.part_a;
+    fa.nblk = w.nchunks;
+    fa.draft_ids = draft_ids; fa.accept = accept; fa.alpha = alpha; fa.resid_mass = resid_mass;
+    fa.resid_ids = resid_ids; fa.n_accepted = n_accepted; fa.out_tokens = out_tokens;
+    if constexpr (HAS_Q) {
+        if (row_in_one<KIND>(d)) {
+            set_scan(fa, w.seq_rec);
+            // more rows than compute units: workgroups of half the size, two on a unit (512 rows of 1000 ids 14.1 -> 9.1 us)
+            if (d.B <= kComputeUnits)
+                RDK_TIMED_LAUNCH("verify_stream_kernel", (verify_row_kernel<KIND, 1024>), dim3((unsigned)d.B), dim3(1024), 0, st, p.ptr, p.ld,
+                                 q, ldq, d.N, w.nchunks, vec_p, vec_q, fa);
+            else
+                RDK_TIMED_LAUNCH("verify_stream_kernel", (verify_row_kernel<KIND, 512>), dim3((unsigned)d.B), dim3(512), 0, st, p.ptr, p.ld, q,
+                                 ldq, d.N, w.nchunks, vec_p, vec_q, fa);
+            RDK_LAUNCH_CHECK("verify_row_kernel");
+            return scan_if_left(fa, st);
+        }
+    }
     const int splits = row_splits(d.B, d.N, kWavesPerBlock);
     if (KIND != RDK_PROB_F32) {
         rdk_status_t rc = launch_row_stats<KIND>(p, d.N, d.B, w.stat_splits, w.pstat, st);
@@ -165,14 +342,6 @@ rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, 
                          dim3(kStreamThreads), 0, st, p.ptr, p.ld, q, ldq, d.N, splits, vec_p, vec_q, w);
     }
     RDK_LAUNCH_CHECK("verify_stream_kernel");
-    FinalizeArgs fa{};
-    fa.d = d;
-    fa.p = p.ptr; fa.ldp = p.ld; fa.vec_p = vec_p;
-    fa.pstat = w.pstat; fa.p_splits = w.stat_splits;
-    fa.part_q = w.part_q; fa.part_r = w.part_r; fa.part_a = w.part_a;
-    fa.nblk = w.nchunks;
-    fa.draft_ids = draft_ids; fa.accept = accept; fa.alpha = alpha; fa.resid_mass = resid_mass;
-    fa.resid_ids = resid_ids; fa.n_accepted = n_accepted; fa.out_tokens = out_tokens;
     QpMemory qp{q, ldq, vec_q, d.N};
     return launch_finalize<KIND, 1024, HAS_Q, QpMemory>(fa, qp, w.seq_rec, st);
 }
