@@ -5,6 +5,8 @@
 //   bf16 kernel:  M rounded to bf16, the drafter rows to eleven significant bits; both held as scaled fp16 numbers,
 //                 fp32 accumulation on the matrix cores (v_mfma_f32_32x32x16_f16), rows rescaled so that they sum to one.
 // Step 1 (Eq. 1) is folded in: rows of Q' are the drafter rows divided by their sums.
+#include <algorithm>
+
 #include "rdk_rowstats.hpp"
 
 namespace rdk {
@@ -187,16 +189,37 @@ __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_pe
         }
 }
 
-// Sum of the split partials in split order, divided by the drafter row sum (Eq. 1).
-__global__ void exact_reduce_kernel(const float *part, int64_t ldd, int64_t split_stride, int splits, const SoftStat *qstat,
-                                    int N, int B, float *out, int64_t ldo)
+// Sum of the split partials in split order, times the row's scale (fp32 path: 1 / drafter row sum, Eq. 1).  Four ids a
+// thread and four partials in flight, which come out of the memory-side cache: a thread that walked single ids paid that
+// latency once per partial (fp32 path, N = 8000, n = 2000, fourteen splits: 8 positions 40.4 -> 31.5 us a call, 64: 46.3 -> 37.2).
+__global__ __launch_bounds__(256) void exact_reduce_kernel(const float *part, int64_t ldd, int64_t split_stride, int splits,
+                                                           const SoftStat *qstat, const float *out_scale, int N, int B, float *out,
+                                                           int64_t ldo, bool vec_o)
 {
     for (int b = blockIdx.y; b < B; b += gridDim.y) {   // positions beyond the grid's second dimension are looped over
-        const float sc = inv_mass(qstat[b].s);
-        for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += (int64_t)gridDim.x * blockDim.x) {
-            float s = 0.f;
-            for (int z = 0; z < splits; ++z) s += part[(int64_t)z * split_stride + (int64_t)b * ldd + j];
-            out[(int64_t)b * ldo + j] = s * sc;
+        const float sc = out_scale ? out_scale[b] : inv_mass(qstat[b].s);
+        const int j = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
+        if (j >= N) return;
+        const float *src = part + (int64_t)b * ldd + j;     // rows of partials are padded to whole quads
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int z0 = 0; z0 < splits; z0 += 4) {
+            float4 v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = *(const float4 *)(src + (int64_t)min(z0 + t, splits - 1) * split_stride);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                if (z0 + t >= splits) break;
+                s.x += v[t].x; s.y += v[t].y; s.z += v[t].z; s.w += v[t].w;
+            }
+        }
+        float *dst = out + (int64_t)b * ldo + j;
+        const float o[4] = {s.x * sc, s.y * sc, s.z * sc, s.w * sc};
+        if (vec_o && j + 3 < N) {
+            *(float4 *)dst = make_float4(o[0], o[1], o[2], o[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j + e < N) dst[e] = o[e];
         }
     }
 }
@@ -341,6 +364,8 @@ __global__ __launch_bounds__(256) void prep_a_bf16_kernel(const void *q, int64_t
 //   * requests run two (A) and three (B) stages ahead of the MFMAs; large batches use one wavefront per SIMD with
 //     the whole register file (accumulators in the AGPR half), which halves the LDS reads per MFMA.
 // M is streamed from HBM exactly once when all positions fit one row of workgroups (B <= 512).
+// A small vocabulary has fewer column groups than the chip has compute units: the slots are split over blockIdx.z then, in
+// whole turns of six stages, and the partial products go to `out` without their scale (split_stride apart).
 // A record of M: read exactly once per launch, so it is loaded non-temporally and leaves the L2 to the A records,
 // which every workgroup of an XCD reads again.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
@@ -350,9 +375,10 @@ __device__ __forceinline__ f16x8 load_once(const f16x8 *p)
     return __builtin_bit_cast(f16x8, __builtin_nontemporal_load((const u32x4_t *)p));
 }
 
-template <int W, int RB>
-__global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, const uint16_t *Mp, int KB, int N, int B,
-                                                            const float *out_scale, float *out, int64_t ldo)
+template <int W, int RB, bool SPLIT>
+__global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, const uint16_t *Mp, int KB, int KB_split, int N,
+                                                            int B, const float *out_scale, float *out, int64_t ldo,
+                                                            int64_t split_stride)
 {
     constexpr int RPW = 16 / W;   // B records a wavefront fetches per stage
     __shared__ f16x8 bbuf[2][16][64];
@@ -360,7 +386,9 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
     const int jb0 = blockIdx.x * kColBlocksPerWg;
     const int rb0 = (blockIdx.y * W + wid) * RB;
     const int n_jb = (N + kColBlock - 1) / kColBlock;
-    const int stages = KB / 4;
+    const int kb_first = blockIdx.z * KB_split;
+    const int stages = min(KB_split, KB - kb_first) / 4;
+    if (SPLIT) out += (int64_t)blockIdx.z * split_stride;
     f32x16 acc[RB][kColBlocksPerWg];
 #pragma unroll
     for (int r = 0; r < RB; ++r)
@@ -371,14 +399,14 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 
     const f16x8 *a_ptr[RB];
 #pragma unroll
-    for (int r = 0; r < RB; ++r) a_ptr[r] = (const f16x8 *)Ap + ((int64_t)(rb0 + r) * KB) * 64 + lane;
+    for (int r = 0; r < RB; ++r) a_ptr[r] = (const f16x8 *)Ap + ((int64_t)(rb0 + r) * KB + kb_first) * 64 + lane;
     const f16x8 *b_src[RPW];
     int b_rec[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
         b_rec[i] = wid * RPW + i;                               // record = jb * 4 + kb within the stage
         const int jb = min(jb0 + b_rec[i] / 4, n_jb - 1);       // surplus column blocks recompute the last one
-        b_src[i] = (const f16x8 *)Mp + ((int64_t)jb * KB + b_rec[i] % 4) * 64 + lane;
+        b_src[i] = (const f16x8 *)Mp + ((int64_t)jb * KB + kb_first + b_rec[i] % 4) * 64 + lane;
     }
     // Loads return to a wavefront in issue order, so every load inherits the latency of the slowest one before
     // it.  The B records come from HBM: they are requested three stages ahead and kept in a ring of registers.
@@ -455,17 +483,39 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int b = (rb0 + r) * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
-                if (b < B) out[(int64_t)b * ldo + j] = acc[r][c][v] * out_scale[b];
+                if (b < B) out[(int64_t)b * ldo + j] = SPLIT ? acc[r][c][v] : acc[r][c][v] * out_scale[b];
             }
         }
 }
 
-// wavefronts per workgroup and row blocks per wavefront for a batch of B positions
-inline void bf16_shape(int B, int &W, int &RB)
+// How the 16-bit product is cut: wavefronts per workgroup, row blocks per wavefront, and splits of the slots (KB_split slot
+// blocks each, whole turns of six stages), as many as bring one workgroup to every compute unit.  A call, unsplit -> split:
+// N = 8000, n = 2000: 8 positions 30.5 -> 21.8 us, 128: 38.8 -> 32.2, 512: 94.3 -> 57.9; N = 2000, 512 positions 59.6 -> 24.4;
+// N = 16000, 256 positions 76.8 -> 70.9.  Two workgroups to a unit were slower (36.1 and 88.1 us at 128 and 256 positions).
+// Small vocabularies take the smallest workgroups at any batch, several rows of them: M comes out of the caches again
+// (N = 4000, 512 positions, one row of the largest workgroups split seven ways 46.2 us, four rows 33.3).
+constexpr int kSmallGroups = 64;
+struct Bf16Shape {
+    int W, RB, B_pad, groups, KB, KB_split, splits;
+};
+Bf16Shape bf16_shape(const KernelHandle &h, int B)
 {
-    if (B <= 128) { W = 4; RB = 1; }
-    else if (B <= 256) { W = 8; RB = 1; }
-    else { W = 4; RB = 4; }   // one wavefront per SIMD with all 512 registers: half the LDS reads per MFMA
+    Bf16Shape s;
+    s.groups = ((h.N + kColBlock - 1) / kColBlock + kColBlocksPerWg - 1) / kColBlocksPerWg;
+    if (B <= 128 || s.groups <= kSmallGroups) { s.W = 4; s.RB = 1; }
+    else if (B <= 256) { s.W = 8; s.RB = 1; }
+    else { s.W = 4; s.RB = 4; }   // one wavefront per SIMD with all 512 registers: half the LDS reads per MFMA
+    const int rows = s.W * s.RB * 32;
+    s.B_pad = (B + rows - 1) / rows * rows;
+    s.KB = h.n_pad / kKStep;
+    const int turns = s.KB / 24;
+    int want = kComputeUnits / (s.groups * (s.B_pad / rows));
+    if (want > turns) want = turns;
+    if (want < 1) want = 1;
+    const int per = (turns + want - 1) / want;
+    s.KB_split = per * 24;
+    s.splits = (turns + per - 1) / per;
+    return s;
 }
 
 struct ExactWs {
@@ -493,6 +543,19 @@ int split_splits(const KernelHandle &h, int B, int *blocks)
     return splits;
 }
 
+// Rows of partial products are padded to whole quads.
+int64_t padded(int N) { return (N + 3) / 4 * 4; }
+
+rdk_status_t launch_reduce(const float *part, int splits, const SoftStat *qstat, const float *out_scale, int N, int B, float *out,
+                           int64_t ldo, hipStream_t st)
+{
+    RDK_TIMED_LAUNCH("exact_reduce_kernel", exact_reduce_kernel, dim3((N + 1023) / 1024, B < 32768 ? B : 32768), dim3(256), 0, st, part,
+                     padded(N), (int64_t)B * padded(N), splits, qstat, out_scale, N, B, out, ldo,
+                     rows_vectorisable(out, ldo, RDK_PROB_F32));
+    RDK_LAUNCH_CHECK("exact_reduce_kernel");
+    return RDK_OK;
+}
+
 template <int QK>
 rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out, int64_t ldo, void *ws, hipStream_t st)
 {
@@ -509,7 +572,7 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
         const int64_t records = (int64_t)row_groups * 2 * KB;   // of three parts each
         uint16_t *Ap = (uint16_t *)p; p += align_up((size_t)records * 3 * kWave * 8 * sizeof(uint16_t), 256);
         w.part = (float *)p;
-        const int64_t ldd = (h.N + 3) / 4 * 4;
+        const int64_t ldd = padded(h.N);
         {
             RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_split_kernel<QK>), dim3((unsigned)((records * kWave + 255) / 256)),
                              dim3(256), 0, st, q.ptr, q.ld, w.qstat, h.n, B, KB, records, Ap);
@@ -526,39 +589,43 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
             RDK_TIMED_LAUNCH("exact_f32_split_kernel", exact_f32_split_kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
                              h.ldm, h.n, h.N, B, KB, blocks, w.qstat, w.part, ldd, (int64_t)B * ldd, false, true);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
-            RDK_TIMED_LAUNCH("exact_reduce_kernel", exact_reduce_kernel, dim3((h.N + 1023) / 1024, B < 32768 ? B : 32768), dim3(256), 0,
-                             st, w.part, ldd, (int64_t)B * ldd, splits, w.qstat, h.N, B, out, ldo);
-            RDK_LAUNCH_CHECK("exact_reduce_kernel");
+            return launch_reduce(w.part, splits, w.qstat, nullptr, h.N, B, out, ldo, st);
         }
         return RDK_OK;
     }
     // bf16
-    int W, RB;
-    bf16_shape(B, W, RB);
-    const int rows_per_wg = W * RB * 32;
-    const int B_pad = (B + rows_per_wg - 1) / rows_per_wg * rows_per_wg;
-    const int KB = h.n_pad / kKStep;
+    const Bf16Shape c = bf16_shape(h, B);
+    const int KB = c.KB, B_pad = c.B_pad;
     w.A = (uint16_t *)p; p += align_up((size_t)B_pad * h.n_pad * 2, 256);
-    w.out_scale = (float *)p;
+    w.out_scale = (float *)p; p += align_up((size_t)B * sizeof(float), 256);
+    w.part = (float *)p;
     {
         RDK_TIMED_LAUNCH("prep_a_bf16_kernel", (prep_a_bf16_kernel<QK>), dim3(B_pad), dim3(256), 0, st, q.ptr, q.ld, w.qstat,
                          h.row_sum, h.n, KB, B, w.A, w.out_scale);
     }
     RDK_LAUNCH_CHECK("prep_a_bf16_kernel");
-    const int n_jb = (h.N + kColBlock - 1) / kColBlock;
-    dim3 grid((n_jb + kColBlocksPerWg - 1) / kColBlocksPerWg, B_pad / rows_per_wg);
+    const dim3 grid(c.groups, B_pad / (c.W * c.RB * 32), c.splits);
+    const bool split = c.splits > 1;
+    float *dst = split ? w.part : out;
+    const int64_t ldd = split ? padded(h.N) : ldo, stride = split ? (int64_t)B * ldd : 0;
     {
-        if (W == 4 && RB == 1)
-            RDK_TIMED_LAUNCH("exact_bf16_kernel", (exact_bf16_kernel<4, 1>), grid, dim3(256), 0, st, w.A, h.packed, KB, h.N, B,
-                             w.out_scale, out, ldo);
-        else if (W == 8)
-            RDK_TIMED_LAUNCH("exact_bf16_kernel", (exact_bf16_kernel<8, 1>), grid, dim3(512), 0, st, w.A, h.packed, KB, h.N, B,
-                             w.out_scale, out, ldo);
-        else
-            RDK_TIMED_LAUNCH("exact_bf16_kernel", (exact_bf16_kernel<4, 4>), grid, dim3(256), 0, st, w.A, h.packed, KB, h.N, B,
-                             w.out_scale, out, ldo);
+#define RDK_BF16_LAUNCH(W, RB, SPLIT)                                                                                              \
+    RDK_TIMED_LAUNCH("exact_bf16_kernel", (exact_bf16_kernel<W, RB, SPLIT>), grid, dim3(W * 64), 0, st, w.A, h.packed, KB, c.KB_split, \
+                     h.N, B, w.out_scale, dst, ldd, stride)
+        if (c.W == 4 && c.RB == 1) {
+            if (split) RDK_BF16_LAUNCH(4, 1, true);
+            else RDK_BF16_LAUNCH(4, 1, false);
+        } else if (c.W == 8) {
+            if (split) RDK_BF16_LAUNCH(8, 1, true);
+            else RDK_BF16_LAUNCH(8, 1, false);
+        } else {
+            if (split) RDK_BF16_LAUNCH(4, 4, true);
+            else RDK_BF16_LAUNCH(4, 4, false);
+        }
+#undef RDK_BF16_LAUNCH
     }
     RDK_LAUNCH_CHECK("exact_bf16_kernel");
+    if (split) return launch_reduce(w.part, c.splits, nullptr, w.out_scale, h.N, B, out, ldo, st);
     return RDK_OK;
 }
 
@@ -581,13 +648,16 @@ size_t exact_workspace_bytes(const KernelHandle &h, int32_t B)
         const int splits = split_splits(h, B, &blocks);
         const size_t records = (size_t)((B + kRowGroup - 1) / kRowGroup) * 2 * splits * blocks;
         bytes += align_up(records * 3 * kWave * 8 * sizeof(uint16_t), 256);
-        if (splits > 1) bytes += align_up((size_t)splits * B * ((h.N + 3) / 4 * 4) * sizeof(float), 256);
+        if (splits > 1) bytes += align_up((size_t)splits * B * padded(h.N) * sizeof(float), 256);
     } else if (h.format == RDK_DENSE_BF16) {
-        int W, RB;
-        bf16_shape(B, W, RB);
-        const int rows_per_wg = W * RB * 32;
-        const size_t B_pad = (size_t)(B + rows_per_wg - 1) / rows_per_wg * rows_per_wg;
-        bytes += align_up(B_pad * h.n_pad * 2, 256) + align_up((size_t)B * sizeof(float), 256);
+        const Bf16Shape c = bf16_shape(h, B);
+        bytes += align_up((size_t)c.B_pad * h.n_pad * 2, 256) + align_up((size_t)B * sizeof(float), 256);
+        // A workspace for a batch serves every smaller one, so what is asked for must not fall as B grows: the rows of partial
+        // products, splits * B, are at most B times the splits that one row of workgroups can have, and at most those splits of
+        // a full one (its rows, 128 to 512, grow with B).
+        const size_t splits = std::min<size_t>(c.KB / 24, kComputeUnits / c.groups), full = (size_t)c.W * c.RB * 32 * (kComputeUnits / c.groups);
+        const size_t rows = splits > 1 ? std::min(B * splits, full) : 0;
+        bytes += align_up(rows * padded(h.N) * sizeof(float), 256);
     }
     return bytes;
 }
