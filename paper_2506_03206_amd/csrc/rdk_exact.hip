@@ -45,11 +45,109 @@ __device__ __forceinline__ void split3(float x, uint32_t &h, uint32_t &m, uint32
 // two bf16 numbers given in the upper halves of a and b, packed as (a, b) = (low half, high half)
 __device__ __forceinline__ uint32_t pack_upper(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xFFFF0000u); }
 
+// ---- The drafter rows are brought into operand form by one workgroup per row, which also takes the row's statistics: a
+// launch for the statistics alone cost 3 us, and loads of single values more (fp32 path, N = 2000, n = 500, one position: 19.9
+// -> 17.5 us a call; 16-bit path, N = 8000, n = 2000, 16 positions 24.1 -> 20.2, N = 32000, n = 8000, 64 positions 119.7 -> 111.3).
+constexpr int kPrepThreads = 512;
+constexpr int kPrepWaves = kPrepThreads / kWave;
+
+// The raw values of slots s .. s + 7 of a row, `fill` past its end.
+template <int QK>
+__device__ __forceinline__ void load8(const void *qr, int s, int n, float fill, float (&v)[8])
+{
+    if (s + 8 <= n) {
+        float lo[4], hi[4];
+        const typename RawQuad<QK>::type a = raw_quad<QK>(qr, s, n), b = raw_quad<QK>(qr, s + 4, n);
+        RawQuad<QK>::to(a, lo);
+        RawQuad<QK>::to(b, hi);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = lo[e];
+            v[4 + e] = hi[e];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = s + e < n ? load1<QK>(qr, s + e) : fill;
+    }
+}
+
+// Largest value of a logit row, in every thread (0 for probabilities).
+template <int QK>
+__device__ __forceinline__ float prep_row_max(const void *qr, int n, float *sh)
+{
+    if (QK == RDK_PROB_F32) return 0.f;
+    float m = -INFINITY;
+    for (int s = threadIdx.x * 8; s < n; s += kPrepThreads * 8) {
+        float v[8];
+        load8<QK>(qr, s, n, -INFINITY, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, v[e]);
+    }
+    m = wave_max(m);
+    if (lane_id() == 0) sh[threadIdx.x / kWave] = m;
+    __syncthreads();
+    m = sh[0];
+    for (int i = 1; i < kPrepWaves; ++i) m = fmaxf(m, sh[i]);
+    __syncthreads();
+    return m;
+}
+
+// Sum over the workgroup, in every thread.
+template <typename T>
+__device__ __forceinline__ T prep_row_sum(T v, T *sh)
+{
+    v = wave_sum(v);
+    if (lane_id() == 0) sh[threadIdx.x / kWave] = v;
+    __syncthreads();
+    v = sh[0];
+    for (int i = 1; i < kPrepWaves; ++i) v += sh[i];
+    return v;
+}
+
 // A records of this form: for row block rb (32 positions) and slot block kb (16 slots) three consecutive 1 KB
 // records, part p = 0 (leading), 1, 2; lane l = 32 g + r holds part p of the unnormalised drafter weights of
 // position 32 rb + r at slots 16 kb + 8 g + e, e = 0..7 -- the A operand of one 32x32x16 MFMA.  Zero beyond B and n.
+// One workgroup per row (blockIdx.x, whole row groups); qstat[b] receives the row's maximum (logits) and mass.
 template <int QK>
-__global__ void prep_a_split_kernel(const void *q, int64_t ldq, const SoftStat *qstat, int n, int B, int KB, int64_t records,
+__global__ __launch_bounds__(kPrepThreads) void prep_a_split_kernel(const void *q, int64_t ldq, SoftStat *qstat, int n, int B, int KB,
+                                                                    uint16_t *Ap)
+{
+    __shared__ float sh[kPrepWaves];
+    const int b = blockIdx.x;
+    const void *qr = row_ptr<QK>(q, ldq, min(b, B - 1));
+    const float fill = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
+    const float qm = prep_row_max<QK>(qr, n, sh);
+    float z = 0.f;
+    for (int c = threadIdx.x; c < KB * 2; c += kPrepThreads) {   // eight consecutive slots
+        uint32_t h[8], m[8], lo[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) h[e] = m[e] = lo[e] = 0u;
+        if (b < B && c * 8 < n) {
+            float v[8];
+            load8<QK>(qr, c * 8, n, fill, v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float x = to_weight<QK>(v[e], qm, 1.f);
+                z += x;
+                split3(x, h[e], m[e], lo[e]);
+            }
+        }
+        uint4 *dst = (uint4 *)Ap + (((int64_t)(b / 32) * KB + c / 2) * 3) * kWave + (c % 2) * 32 + b % 32;
+        dst[0] = make_uint4(pack_upper(h[0], h[1]), pack_upper(h[2], h[3]), pack_upper(h[4], h[5]), pack_upper(h[6], h[7]));
+        dst[kWave] = make_uint4(pack_upper(m[0], m[1]), pack_upper(m[2], m[3]), pack_upper(m[4], m[5]), pack_upper(m[6], m[7]));
+        dst[2 * kWave] = make_uint4(pack_upper(lo[0], lo[1]), pack_upper(lo[2], lo[3]), pack_upper(lo[4], lo[5]), pack_upper(lo[6], lo[7]));
+    }
+    z = prep_row_sum(z, sh);
+    if (threadIdx.x == 0 && b < B) qstat[b] = SoftStat{qm, z};
+}
+
+// The same for long rows, statistics given: a thread per 16 bytes of the records, in their order.  Workgroups that own a row
+// write 16 bytes of a 128-byte line each, three times per eight slots, which costs more than the launch for the statistics from
+// about 5000 slots on (one launch against two, a call of 16 positions: n = 2000 29.7 us against 32.4, 4000 56.9 : 58.4,
+// 5000 76.2 : 76.3, 8000 198.3 : 196.1).
+constexpr int kPrepRowMax = 4096;
+template <int QK>
+__global__ void prep_a_records_kernel(const void *q, int64_t ldq, const SoftStat *qstat, int n, int B, int KB, int64_t records,
                                     uint16_t *Ap)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -320,39 +418,45 @@ __global__ void unpack_bf16_kernel(const uint16_t *packed, int n, int N, int KB,
 // 2^-30 / sum_s rounded(q'_s) * row_sum[s]: it takes the operand scales out and makes the output row sum to one.
 // One workgroup per position.
 template <int QK>
-__global__ __launch_bounds__(256) void prep_a_bf16_kernel(const void *q, int64_t ldq, const SoftStat *qstat, const float *row_sum,
-                                                          int n, int KB, int B, uint16_t *Ap, float *out_scale)
+__global__ __launch_bounds__(kPrepThreads) void prep_a_bf16_kernel(const void *q, int64_t ldq, const float *row_sum, int n, int KB, int B,
+                                                                   uint16_t *Ap, float *out_scale)
 {
+    __shared__ float sh[kPrepWaves];
+    __shared__ double shd[kPrepWaves];
     const int b = blockIdx.x;
     const int rb = b / 32, r = b % 32;
+    const float fill = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
+    const void *qr = row_ptr<QK>(q, ldq, min(b, B - 1));
+    // the row is normalised before it is rounded: its mass comes out of a pass of its own (the others hit the caches)
+    const float qm = prep_row_max<QK>(qr, n, sh);
+    float z = 0.f;
+    for (int s = threadIdx.x * 8; s < n; s += kPrepThreads * 8) {
+        float v[8];
+        load8<QK>(qr, s, n, fill, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z += to_weight<QK>(v[e], qm, 1.f);
+    }
+    const float inv = inv_mass(prep_row_sum(z, sh));
     double mass = 0.0;
-    const void *qr = b < B ? row_ptr<QK>(q, ldq, b) : nullptr;
-    const float qm = b < B ? qstat[b].m : 0.f, inv = b < B ? inv_mass(qstat[b].s) : 0.f;
-    for (int c = threadIdx.x; c < KB * 2; c += blockDim.x) {   // chunk of 8 consecutive slots
+    for (int c = threadIdx.x; c < KB * 2; c += kPrepThreads) {   // chunk of 8 consecutive slots
         const int kb = c / 2, g = c % 2;
         uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if (qr) {
+        if (b < B && c * 8 < n) {
+            float v[8], ms[8];
+            load8<QK>(qr, c * 8, n, fill, v);
+            load8<RDK_PROB_F32>(row_sum, c * 8, n, 0.f, ms);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int s = c * 8 + e;
-                uint16_t h = 0;
-                if (s < n) {
-                    h = f32_to_operand(to_weight<QK>(load1<QK>(qr, s), qm, 1.f) * inv);
-                    mass += (double)operand_to_f32(h) * (double)row_sum[s];
-                }
+                const uint16_t h = f32_to_operand(to_weight<QK>(v[e], qm, 1.f) * inv);
+                mass += (double)operand_to_f32(h) * (double)ms[e];
                 w[e / 2] |= (uint32_t)h << (16 * (e % 2));
             }
         }
         *(uint4 *)(Ap + (((int64_t)rb * KB + kb) * 64 + g * 32 + r) * 8) = make_uint4(w[0], w[1], w[2], w[3]);
     }
-    mass = wave_sum(mass);
-    __shared__ double sh[4];
-    if (lane_id() == 0) sh[threadIdx.x / kWave] = mass;
-    __syncthreads();
-    if (threadIdx.x == 0 && b < B) {
-        const double total = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    const double total = prep_row_sum(mass, shd);
+    if (threadIdx.x == 0 && b < B)
         out_scale[b] = total > 0.0 ? (float)((double)kOperandUnscale * (double)kOperandUnscale / total) : 0.f;
-    }
 }
 
 // P'[512 x 128] per workgroup: W wavefronts, wavefront w owns RB row blocks (32 positions each) and all four
@@ -562,8 +666,6 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
     char *p = (char *)ws;
     ExactWs w;
     w.qstat = (SoftStat *)p; p += align_up((size_t)B * sizeof(SoftStat), 256);
-    rdk_status_t rc = launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
-    if (rc != RDK_OK) return rc;
     if (h.format == RDK_DENSE_F32) {
         int blocks;
         const int splits = split_splits(h, B, &blocks);
@@ -574,8 +676,15 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
         w.part = (float *)p;
         const int64_t ldd = padded(h.N);
         {
-            RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_split_kernel<QK>), dim3((unsigned)((records * kWave + 255) / 256)),
-                             dim3(256), 0, st, q.ptr, q.ld, w.qstat, h.n, B, KB, records, Ap);
+            if (h.n <= kPrepRowMax) {
+                RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_split_kernel<QK>), dim3(row_groups * kRowGroup), dim3(kPrepThreads), 0, st,
+                                 q.ptr, q.ld, w.qstat, h.n, B, KB, Ap);
+            } else {
+                const rdk_status_t rc = launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
+                if (rc != RDK_OK) return rc;
+                RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_records_kernel<QK>), dim3((unsigned)((records * kWave + 255) / 256)),
+                                 dim3(256), 0, st, q.ptr, q.ld, w.qstat, h.n, B, KB, records, Ap);
+            }
         }
         RDK_LAUNCH_CHECK("prep_a_split_kernel");
         const int tiles = (h.N + kColSet - 1) / kColSet;
@@ -600,8 +709,7 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
     w.out_scale = (float *)p; p += align_up((size_t)B * sizeof(float), 256);
     w.part = (float *)p;
     {
-        RDK_TIMED_LAUNCH("prep_a_bf16_kernel", (prep_a_bf16_kernel<QK>), dim3(B_pad), dim3(256), 0, st, q.ptr, q.ld, w.qstat,
-                         h.row_sum, h.n, KB, B, w.A, w.out_scale);
+        RDK_TIMED_LAUNCH("prep_a_bf16_kernel", (prep_a_bf16_kernel<QK>), dim3(B_pad), dim3(kPrepThreads), 0, st, q.ptr, q.ld, h.row_sum, h.n, KB, B, w.A, w.out_scale);
     }
     RDK_LAUNCH_CHECK("prep_a_bf16_kernel");
     const dim3 grid(c.groups, B_pad / (c.W * c.RB * 32), c.splits);

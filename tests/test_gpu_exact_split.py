@@ -17,6 +17,8 @@ SHAPES = [  # N, n, B
     (9001, 1537, 200),
     (9001, 1537, 300),
     (16500, 400, 6),     # column groups enough: not split
+    (4500, 4097, 3),     # rows long enough for statistics of their own (fp32 path)
+    (4500, 4096, 3),
 ]
 
 
