@@ -13,6 +13,8 @@
 // step before produced; the kernel runs step k for ALL blocks it needs before step k + 1, so a chain of dependent
 // loads costs kStages round trips in total rather than per block.
 #pragma once
+#include <type_traits>
+
 #include "rdk_rowstats.hpp"
 
 namespace rdk {
@@ -441,8 +443,23 @@ __device__ __forceinline__ void finish_row_wide(const FinalizeArgs &a, const Row
     if (wid == 0) scan_sequence(a, row, dtok, sh.i[1], acc);
 }
 
+// How many block sums a lane holds in registers (REGS): the code that adds and searches them is unrolled, runs once, and is
+// fetched while it runs, so a row takes the shortest that holds its blocks; above 4096 of them they are read again from memory.
+// Whole calls of 8 positions: draft draw, N = 32000 (500 blocks): 64 registers 14.7 us, 32 13.4, 8 12.6; N = 128256 (2004 blocks):
+// 64 17.8, 32 16.4; N = 250000 (3908 blocks): read again 36.5, 64 24.7.  Fused, N = 32000: 64 17.4, 8 15.4; N = 128256: 64 20.6,
+// 32 19.8.
+template <class F>
+inline void with_block_regs(int nblk, const F &f)
+{
+    if (nblk <= 8 * kWave) f(std::integral_constant<int, 8>{});
+    else if (nblk <= 16 * kWave) f(std::integral_constant<int, 16>{});
+    else if (nblk <= 32 * kWave) f(std::integral_constant<int, 32>{});
+    else if (nblk <= 40 * kWave) f(std::integral_constant<int, 40>{});
+    else f(std::integral_constant<int, 64>{});
+}
+
 // One row per workgroup of four wavefronts, block sums over 64 ids in memory.
-template <int KIND, class QP>
+template <int KIND, int REGS, class QP>
 __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(FinalizeArgs a, QP qp)
 {
     __shared__ WideScratch sh;
@@ -456,8 +473,7 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
         inv = 1.0f / rs.s;
     }
     const typename QP::Row qrow = qp.row(row);
-    // 64 block sums a lane: 4096 blocks (N = 262144) stay in registers
-    finish_row_wide<KIND, 64>(a, qrow, row, pr, m, inv, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, sh,
+    finish_row_wide<KIND, REGS>(a, qrow, row, pr, m, inv, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, sh,
                               wid, lane);
 }
 
@@ -726,19 +742,21 @@ __device__ __forceinline__ void draft_row(const DraftArgs &a, const Row &qrow, i
     }
 }
 
-template <int BLOCK, class QP>
+template <int BLOCK, int REGS, class QP>
 __global__ __launch_bounds__(kWave) void draft_finalize_kernel(DraftArgs a, QP qp)
 {
     const int64_t row = QP::kSpreadRows ? xcd_row(blockIdx.x, a.B) : (int64_t)blockIdx.x;
     const typename QP::Row qrow = qp.row(row);
-    draft_row<BLOCK, 32, QP::kStages>(a, qrow, row, a.part_q + row * a.nblk);
+    draft_row<BLOCK, REGS, QP::kStages>(a, qrow, row, a.part_q + row * a.nblk);
 }
 
 template <int BLOCK, class QP>
 rdk_status_t launch_draft_finalize(const DraftArgs &a, QP qp, hipStream_t st)
 {
-    RDK_TIMED_LAUNCH("draft_finalize_kernel", (draft_finalize_kernel<BLOCK, QP>), dim3((unsigned)a.B), dim3(kWave), 0, st, a,
-                     qp);
+    with_block_regs(a.nblk, [&](auto regs) {
+        RDK_TIMED_LAUNCH("draft_finalize_kernel", (draft_finalize_kernel<BLOCK, decltype(regs)::value, QP>), dim3((unsigned)a.B), dim3(kWave),
+                         0, st, a, qp);
+    });
     RDK_LAUNCH_CHECK("draft_finalize_kernel");
     return RDK_OK;
 }
@@ -782,8 +800,10 @@ rdk_status_t launch_finalize(FinalizeArgs a, QP qp, uint64_t *rec, hipStream_t s
         // for blocks of 64 ids whose q' is re-computed, eight for blocks of 1024.
         set_scan(a, rec);
         if constexpr (BLOCK == 64)
-            RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_wide_kernel<KIND, QP>), dim3((unsigned)d.B), dim3(4 * kWave), 0,
-                             st, a, qp);
+            with_block_regs(a.nblk, [&](auto regs) {
+                RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_wide_kernel<KIND, decltype(regs)::value, QP>), dim3((unsigned)d.B),
+                                 dim3(4 * kWave), 0, st, a, qp);
+            });
         else
             RDK_TIMED_LAUNCH("verify_finalize_kernel", (verify_finalize_quarters_kernel<KIND, QP>), dim3((unsigned)d.B), dim3(8 * kWave),
                              0, st, a, qp);

@@ -49,3 +49,28 @@ def test_slab_against_oracle(shape, kind):
     ids, qd = rdk.rdk_sample_draft(kern, d(q_in), 9, 4, kind)
     assert torch.equal(ids, out.draft_ids)
     assert_close(qd.cpu().numpy(), ref_qp[np.arange(B), ids.cpu().numpy()], what="q' at the draft")
+
+
+@pytest.mark.parametrize("N", [32513, 65281, 65793, 131073, 163585, 164097, 262400])
+def test_draws_at_the_edges_of_the_held_block_sums(N):
+    """Rows whose block sums just fit, or just miss, what a lane of the finish holds in registers: the draws follow the
+    prefix sums of q' and of max(0, p - q') as the two-call path writes q'."""
+    from paper_2506_03206_amd import rdk
+    n, B, k = 4000, 3, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    kept = torch.sort(torch.randperm(N, generator=g, device="cuda")[:n]).values.to(torch.int32)
+    kern = rdk.rdk_build_kernel(N, kept, rdk.SPARSE_TOPK, embeddings=torch.randn((N, 8), generator=g, device="cuda"), tau=0.1, k=k)
+    p = torch.softmax(torch.randn((B, N), generator=g, device="cuda"), 1)
+    q = torch.softmax(torch.randn((B, n), generator=g, device="cuda"), 1)
+    qp = rdk.rdk_redistribute_linear(kern, rdk.LINEAR_SPARSE, q)
+    out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_SPARSE, p, q, 11, 0, 1, "prob", "prob")
+    ids, qd = rdk.rdk_sample_draft(kern, q, 11, 0)
+    p64, q64 = p.double().cpu().numpy(), qp.double().cpu().numpy()
+    assert torch.equal(ids, out.draft_ids)
+    for b in range(B):
+        u = oracle.uniforms(11, b)
+        for ids_, w, x in ((out.draft_ids, q64[b], u[0]), (out.resid_ids, np.maximum(p64[b] - q64[b], 0), u[2])):
+            c, j = np.cumsum(w), int(ids_[b])
+            tol = 1e-6 * c[-1]                          # fp32 block sums of an fp64 search
+            assert w[j] > 0 and c[j] - w[j] - tol <= x * c[-1] <= c[j] + tol
