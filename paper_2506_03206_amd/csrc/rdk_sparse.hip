@@ -401,8 +401,12 @@ __global__ __launch_bounds__(kThreads) void sparse_product_kernel(SparseArgs a, 
     }
 }
 
-// Where the finish finds the drafter weight of a slot: in the position-minor copy, or in the drafter row itself (with the
-// row's maximum and 1 / mass as the product out of LDS left them).
+// Where the finish finds the drafter weight of a slot: in the position-minor copy (SlabColumn), or in the drafter row itself, with
+// the row's maximum and 1 / mass out of the partials that the transposition worked with (PartialColumn) or as the product out
+// of LDS left them (RowColumn).  In the copy every gather touches a line of its own for four useful bytes; a bf16 row of up to
+// kShortRow slots is at most 256 lines, which the vector L1 holds (whole calls, copy -> row: N = 151936, n = 16384, k = 32, 1024
+// positions 923.6 -> 914.9 us, 700: 675.9 -> 643.8; N = 8000, n = 2000, 700 positions 82.3 -> 69.8).  Rows of 128 KB are cold
+// where the copy is in L2 (N = 128256, n = 32064, fp32: 122.7 -> 123.6, draft draw 95.8 -> 96.8).
 struct SlabColumn {
     const float *qT;
     const float *zpart;
@@ -416,6 +420,33 @@ struct SlabColumn {
     {
         const int pb = (int)(b / kPosBlock), r = (int)(b % kPosBlock);
         return Row{qT + (int64_t)pb * n * kPosBlock + r, row_mass_inv(zpart, zt, b)};
+    }
+};
+
+constexpr int kShortRow = 16384;
+
+template <int QK>
+struct PartialColumn {
+    const void *q;
+    int64_t ldq;
+    const SoftStat *qpart;
+    int q_splits;
+    const float *zpart;
+    int zt;
+    struct Row {
+        const void *qr;
+        float m, inv_z;
+        __device__ __forceinline__ float operator()(int s) const { return to_weight<QK>(rdk::load1<QK>(qr, s), m, 1.f); }
+    };
+    __device__ __forceinline__ Row row(int64_t b) const
+    {
+        float m = 0.f;
+        if (QK != RDK_PROB_F32) {
+            m = -INFINITY;
+            for (int i = lane_id(); i < q_splits; i += kWave) m = fmaxf(m, qpart[b * q_splits + i].m);
+            m = wave_max(m);
+        }
+        return Row{row_ptr<QK>(q, ldq, b), m, row_mass_inv(zpart, zt, b)};
     }
 };
 
@@ -547,6 +578,13 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
                              0, st, a, f);
     }
     RDK_LAUNCH_CHECK("sparse_product_kernel");
+    if constexpr (QK == RDK_LOGIT_BF16) {
+        if (h.n <= kShortRow) {
+            typedef QpSparse<PartialColumn<QK>> QP;
+            return launch_finalize<PK, kSubIds, true, QP>(
+                fa, QP{tables_of(h), PartialColumn<QK>{c.q.ptr, c.q.ld, w.qpart, w.q_splits, w.zpart, w.zt}}, seq_rec, st);
+        }
+    }
     typedef QpSparse<SlabColumn> QP;
     return launch_finalize<PK, kSubIds, true, QP>(fa, QP{tables_of(h), SlabColumn{w.qT, w.zpart, w.zt, h.n}}, seq_rec, st);
 }
@@ -577,6 +615,13 @@ rdk_status_t run_sparse_draft(const KernelHandle &h, RowInput q, int32_t B, uint
         RDK_TIMED_LAUNCH("sparse_product_kernel", (sparse_product_kernel<-2, false>), dim3(8 * a.per_xcd), dim3(kThreads), 0,
                          st, a, f);
     RDK_LAUNCH_CHECK("sparse_product_kernel");
+    if constexpr (QK == RDK_LOGIT_BF16) {
+        if (h.n <= kShortRow) {
+            typedef QpSparse<PartialColumn<QK>> QP;
+            return launch_draft_finalize<kSubIds, QP>(
+                da, QP{tables_of(h), PartialColumn<QK>{q.ptr, q.ld, w.qpart, w.q_splits, w.zpart, w.zt}}, st);
+        }
+    }
     typedef QpSparse<SlabColumn> QP;
     return launch_draft_finalize<kSubIds, QP>(da, QP{tables_of(h), SlabColumn{w.qT, w.zpart, w.zt, h.n}}, st);
 }

@@ -74,3 +74,31 @@ def test_draws_at_the_edges_of_the_held_block_sums(N):
             c, j = np.cumsum(w), int(ids_[b])
             tol = 1e-6 * c[-1]                          # fp32 block sums of an fp64 search
             assert w[j] > 0 and c[j] - w[j] - tol <= x * c[-1] <= c[j] + tol
+
+
+@pytest.mark.parametrize("n", [1001, 16384, 16385])
+def test_finish_reads_short_bf16_rows_themselves(n):
+    """Batches beyond the product out of LDS: the finish takes drafter weights from a short bf16 row or from the position-minor
+    copy; the draws follow the prefix sums of q' and of max(0, p - q') as the two-call path writes q'."""
+    from paper_2506_03206_amd import rdk
+    N, k, gamma = n + 19003, 32, 2
+    B = 66                                              # two position blocks and two rows; 66 x 4.9 MB of table
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    kept = torch.sort(torch.randperm(N, generator=g, device="cuda")[:n]).values.to(torch.int32)
+    kern = rdk.rdk_build_kernel(N, kept, rdk.SPARSE_TOPK, embeddings=torch.randn((N, 8), generator=g, device="cuda"), tau=0.1, k=k)
+    wide = lambda z: torch.nn.functional.pad(z.to(torch.bfloat16), (0, 1), value=float("nan"))[:, :-1]
+    zp = wide(torch.randn((B, N), generator=g, device="cuda") * 2)
+    zq = wide(torch.randn((B, n), generator=g, device="cuda") * 2)
+    qp = rdk.rdk_redistribute_linear(kern, rdk.LINEAR_SPARSE, zq, "logit")
+    out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_SPARSE, zp, zq, 11, 0, gamma, "logit", "logit")
+    ids, qd = rdk.rdk_sample_draft(kern, zq, 11, 0, "logit")
+    p64, q64 = torch.softmax(zp.double(), 1).cpu().numpy(), qp.double().cpu().numpy()
+    assert torch.equal(ids, out.draft_ids)
+    np.testing.assert_allclose(qd.cpu().numpy(), q64[np.arange(B), ids.cpu().numpy()], rtol=1e-5)
+    for b in range(B):
+        u = oracle.uniforms(11, b)
+        for ids_, w, x in ((out.draft_ids, q64[b], u[0]), (out.resid_ids, np.maximum(p64[b] - q64[b], 0), u[2])):
+            c, j = np.cumsum(w), int(ids_[b])
+            tol = 1e-5 * c[-1]                          # a residual is a difference of fp32 softmax outputs
+            assert w[j] > 0 and c[j] - w[j] - tol <= x * c[-1] <= c[j] + tol
