@@ -95,9 +95,12 @@ __device__ __forceinline__ double wave_inclusive_scan(double v)
 __device__ __forceinline__ float soft_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.44269504088896341f); }
 
 // The same with the rounding of the product x * log2(e) carried along (its exact residual and the part of log2(e) that
-// a float drops): about one ulp for any x <= 0.  Three more instructions: for factors that a whole chunk of ids shares.
+// a float drops): about one ulp for any x <= 0.  Five more instructions: for factors that a whole chunk of ids shares.
+// Differences below -256 (a result of zero either way) are taken as -256, or a product beyond the range of a float would
+// make the residual a NaN: the maximum of a masked chunk may be the lowest finite value.
 __device__ __forceinline__ float soft_exp_fine(float x)
 {
+    x = x < -256.f ? -256.f : x;
     const float hi = x * 1.44269504088896341f;
     const float lo = fmaf(x, 1.44269504088896341f, -hi) + x * 1.92596299e-8f;
     return __builtin_amdgcn_exp2f(hi) * fmaf(0.693147180559945309f, lo, 1.0f);

@@ -4,6 +4,8 @@
 //   * the identity kernel: token-level intersection itself.
 // Step 1 (token-level intersection, Eq. 1) is folded in: the drafter row is only ever used divided
 // by its own sum over the kept slots.
+#include <cfloat>
+
 #include "rdk_finalize.hpp"
 
 namespace rdk {
@@ -632,7 +634,9 @@ __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, i
                             quads, words, wid, lane);
 }
 
-constexpr float kLowest = -1.0e38f;   // stands in for the maximum of nothing: differences from it stay finite
+// Stands in for the maximum of nothing, where -inf would make the weight of a masked id exp(-inf + inf).  Nothing finite lies
+// below it: rows masked with the lowest finite value of their type keep their own maximum, and with it their weights.
+constexpr float kLowest = -FLT_MAX;
 // The statistics of a chunk (arrays in LDS); the third powers only where the series needs them.
 enum { kRowS1n = 0, kRowS2n, kRowS1k, kRowS2k, kRowQ0, kRowQ1, kRowQ2, kRowMax, kRowQMax, kRowScale, kRowArrays, kRowS3n = kRowArrays, kRowS3k, kRowQ3, kRowAllArrays };
 

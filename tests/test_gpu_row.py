@@ -59,3 +59,36 @@ def test_one_pass_rows_against_oracle(shape, kind):
     assert rdk.rdk_timing_read("taylor_row_kernel")[0] == one_pass
     ref = oracle.verify_batch(p64, ref_qp, 9, 4, gamma=gamma)
     check_verify_outputs(out, ref, p64, ref_qp, 9, 4, gamma, pk, min_exact=0.6)
+
+
+@pytest.mark.parametrize("kind", ["logit", "bf16"])
+@pytest.mark.parametrize("N,B", [(4099, 6), (4099, 260), (60001, 66), (60001, 6)])
+def test_rows_masked_with_the_lowest_finite_value(N, B, kind):
+    """Masks of finfo.min instead of -inf, over part of a row and over all of it (a uniform row then), in one pass and, for the
+    last shape, split over workgroups; a logit near the largest finite value beside them."""
+    from paper_2506_03206_amd import rdk
+    rng = np.random.default_rng(N + B)
+    kept = np.sort(rng.choice(N, size=N // 5, replace=False)).astype(np.int32)
+    zp = (rng.normal(size=(B, N)) * 2).astype(np.float32)
+    zq = (zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept]
+    dt = torch.bfloat16 if kind == "bf16" else torch.float32
+    if kind == "bf16":
+        zp, zq = synth.bf16_round(zp), synth.bf16_round(zq)
+    low = np.float32(torch.finfo(dt).min)
+    zq[0] = low                                        # the whole drafter row
+    zq[1, : kept.size // 2] = low                      # half of it: chunks whose kept ids are all masked
+    zp[2] = low                                        # the whole target row
+    zp[3, 1024:2048] = low                             # one chunk of it
+    zp[4, 100] = np.float32(torch.finfo(dt).max)       # a one-hot row whose differences leave the range of a float
+    zp[5], zq[5] = low, low
+    kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
+    p64, q64 = oracle.probs_from(zp, "logit"), oracle.probs_from(zq, "logit")
+    ref_qp = oracle.redistribute_batch("taylor", q64, kept, N, p=p64)
+    ref = oracle.verify_batch(p64, ref_qp, 9, 4, gamma=2)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda().to(dt)
+    rdk.rdk_timing_select("taylor_row_kernel")
+    out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, t(zp), t(zq), 9, 4, 2, "logit", "logit")
+    torch.cuda.synchronize()
+    rdk.rdk_timing_select(None)
+    assert rdk.rdk_timing_read("taylor_row_kernel")[0] == ((N, B) != (60001, 6))
+    check_verify_outputs(out, ref, p64, ref_qp, 9, 4, 2, "logit", min_exact=0.6)
