@@ -182,6 +182,8 @@ typedef struct {
     uint64_t offset;      /* Philox counter of position 0 */
 } rdk_verify_desc_t;
 
+/* With 1 <= gamma <= 63 the size holds 16 bytes per position for the per-sequence scan (steps 4-10) to run inside the
+ * last kernel.  A workspace of the size for gamma = 0 is enough for any gamma: the scan is then a launch of its own. */
 rdk_status_t rdk_verify_workspace_bytes(const rdk_verify_desc_t *desc, size_t *bytes);
 
 /*
@@ -213,7 +215,7 @@ rdk_status_t rdk_verify_sample(const rdk_verify_desc_t *desc, const void *p, rdk
  * capture, tight serving loops, harnesses that forbid allocation): same arguments without the workspace, same
  * kernels, same outputs bit for bit.  The scratch (the per-block sums, and the softmax statistics of logit rows) lives
  * in a device array inside the library, 4 MiB per GPU, held until the process ends; the call allocates and frees
- * nothing.  A batch whose scratch need (rdk_verify_workspace_bytes minus its 256 bytes of slack, about
+ * nothing.  A batch whose scratch need (rdk_verify_workspace_bytes with gamma = 0 minus its 256 bytes of slack, about
  * 12 * B * ceil(N / 1024) bytes) exceeds 4 MiB is refused with RDK_ERR_WORKSPACE and nothing is launched.  All calls
  * on one GPU share the one array: calls that overlap on one GPU (different streams, or different threads) race and
  * must be ordered by the caller; nothing in it needs clearing between calls.  Runs on the current device.

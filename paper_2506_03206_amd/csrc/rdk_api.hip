@@ -505,10 +505,10 @@ rdk_status_t rdk_verify_sample(const rdk_verify_desc_t *desc, const void *p, rdk
     }
     if (desc->gamma == 0 && (n_accepted || out_tokens)) return RDK_ERR_SHAPE;
     if (!aligned16(workspace)) return RDK_ERR_ALIGN;
-    if (workspace_bytes < verify_workspace_bytes(*desc)) return RDK_ERR_WORKSPACE;
+    if (workspace_bytes < verify_sums_bytes(*desc)) return RDK_ERR_WORKSPACE;
     RowInput pi{p, p_kind, ldp};
     return launch_verify(*desc, pi, q_prime, ldq, draft_ids, accept, alpha, resid_mass, resid_ids, n_accepted, out_tokens,
-                         workspace, (hipStream_t)stream);
+                         workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 rdk_status_t rdk_verify_sample_static(const rdk_verify_desc_t *desc, const void *p, rdk_input_kind_t p_kind, int64_t ldp,
@@ -529,7 +529,7 @@ rdk_status_t rdk_verify_sample_static(const rdk_verify_desc_t *desc, const void 
         return RDK_ERR_UNSUPPORTED;
     }
     if (desc->gamma == 0 && (n_accepted || out_tokens)) return RDK_ERR_SHAPE;
-    if (verify_workspace_bytes(*desc) > verify_static_scratch_limit()) return RDK_ERR_WORKSPACE;
+    if (verify_sums_bytes(*desc) > verify_static_scratch_limit()) return RDK_ERR_WORKSPACE;
     RowInput pi{p, p_kind, ldp};
     return launch_verify_static(*desc, pi, q_prime, ldq, draft_ids, accept, alpha, resid_mass, resid_ids, n_accepted,
                                 out_tokens, (hipStream_t)stream);

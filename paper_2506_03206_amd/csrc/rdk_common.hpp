@@ -160,10 +160,14 @@ rdk_status_t launch_tree_walk(int32_t S, int32_t nodes, int32_t C, const int32_t
                               const int32_t *token, int32_t *n_accepted, int32_t *out_tokens, hipStream_t st);
 
 // rdk_verify.hip
+// What a call cannot do without, and what it asks for: with room for the records of the per-sequence scan the scan runs inside
+// the finish, with less it is a launch of its own.
+size_t verify_sums_bytes(const rdk_verify_desc_t &d);
 size_t verify_workspace_bytes(const rdk_verify_desc_t &d);
 rdk_status_t launch_verify(const rdk_verify_desc_t &d, RowInput p, const float *q_prime, int64_t ldq,
                            int32_t *draft_ids, uint8_t *accept, float *alpha, float *resid_mass,
-                           int32_t *resid_ids, int32_t *n_accepted, int32_t *out_tokens, void *ws, hipStream_t st);
+                           int32_t *resid_ids, int32_t *n_accepted, int32_t *out_tokens, void *ws, size_t ws_bytes,
+                           hipStream_t st);
 size_t verify_static_scratch_limit();
 rdk_status_t launch_verify_static(const rdk_verify_desc_t &d, RowInput p, const float *q_prime, int64_t ldq,
                                   int32_t *draft_ids, uint8_t *accept, float *alpha, float *resid_mass,

@@ -23,13 +23,18 @@ constexpr int kWavesPerBlock = kStreamThreads / kWave;
 struct VerifyWs {
     float *part_q, *part_r, *part_a;  // [B, nchunks]
     SoftStat *pstat;                  // [B, stat_splits] (logit input only)
-    uint64_t *seq_rec;                // [B, 2] records of the per-sequence scan
+    uint64_t *seq_rec;                // [B, 2] records of the per-sequence scan; NULL where the scratch has no room for them
     int nchunks, stat_splits;
 };
 
 __host__ __device__ inline int chunks_of(int64_t N) { return (int)((N + kChunk - 1) / kChunk); }
 
-VerifyWs carve(const rdk_verify_desc_t &d, void *ws)
+size_t seq_rec_bytes(const rdk_verify_desc_t &d)
+{
+    return d.gamma > 0 && d.gamma <= kScanMaxGamma ? align_up((size_t)d.B * 2 * sizeof(uint64_t), 256) : 0;
+}
+
+VerifyWs carve(const rdk_verify_desc_t &d, void *ws, size_t ws_bytes)
 {
     VerifyWs w;
     w.nchunks = chunks_of(d.N);
@@ -40,7 +45,7 @@ VerifyWs carve(const rdk_verify_desc_t &d, void *ws)
     w.part_r = (float *)p; p += per;
     w.part_a = (float *)p; p += per;
     w.pstat = (SoftStat *)p; p += align_up((size_t)d.B * w.stat_splits * sizeof(SoftStat), 256);
-    w.seq_rec = (uint64_t *)p;
+    w.seq_rec = seq_rec_bytes(d) && ws_bytes >= verify_workspace_bytes(d) ? (uint64_t *)p : nullptr;
     return w;
 }
 
@@ -305,9 +310,9 @@ bool row_in_one(const rdk_verify_desc_t &d)
 template <int KIND, bool HAS_Q>
 rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, int64_t ldq, int32_t *draft_ids,
                         uint8_t *accept, float *alpha, float *resid_mass, int32_t *resid_ids, int32_t *n_accepted,
-                        int32_t *out_tokens, void *ws, hipStream_t st)
+                        int32_t *out_tokens, void *ws, size_t ws_bytes, hipStream_t st)
 {
-    VerifyWs w = carve(d, ws);
+    VerifyWs w = carve(d, ws, ws_bytes);
     const bool vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
     const bool vec_q = HAS_Q ? rows_vectorisable(q, ldq, RDK_PROB_F32) : false;
     FinalizeArgs fa{};
@@ -385,24 +390,25 @@ rdk_status_t launch_draft_from_rows(const float *q_prime, int64_t ldq, int32_t B
     return launch_draft_finalize<1024, QpMemory>(a, QpMemory{q_prime, ldq, vec_q, N}, st);
 }
 
-size_t verify_workspace_bytes(const rdk_verify_desc_t &d)
+size_t verify_sums_bytes(const rdk_verify_desc_t &d)
 {
     const int nchunks = chunks_of(d.N);
     const size_t per = align_up((size_t)d.B * nchunks * sizeof(float), 256);
-    return 3 * per + align_up((size_t)d.B * row_splits(d.B, d.N, kWavesPerBlock) * sizeof(SoftStat), 256) +
-           align_up((size_t)d.B * 2 * sizeof(uint64_t), 256);
+    return 3 * per + align_up((size_t)d.B * row_splits(d.B, d.N, kWavesPerBlock) * sizeof(SoftStat), 256);
 }
+
+size_t verify_workspace_bytes(const rdk_verify_desc_t &d) { return verify_sums_bytes(d) + seq_rec_bytes(d); }
 
 rdk_status_t launch_verify(const rdk_verify_desc_t &d, RowInput p, const float *q_prime, int64_t ldq, int32_t *draft_ids,
                            uint8_t *accept, float *alpha, float *resid_mass, int32_t *resid_ids, int32_t *n_accepted,
-                           int32_t *out_tokens, void *ws, hipStream_t st)
+                           int32_t *out_tokens, void *ws, size_t ws_bytes, hipStream_t st)
 {
 #define RDK_VERIFY_CASE(K)                                                                                                  \
     case K:                                                                                                                 \
         return q_prime ? run_verify<K, true>(d, p, q_prime, ldq, draft_ids, accept, alpha, resid_mass, resid_ids,           \
-                                             n_accepted, out_tokens, ws, st)                                                \
+                                             n_accepted, out_tokens, ws, ws_bytes, st)                                      \
                        : run_verify<K, false>(d, p, q_prime, ldq, draft_ids, accept, alpha, resid_mass, resid_ids,          \
-                                              n_accepted, out_tokens, ws, st);
+                                              n_accepted, out_tokens, ws, ws_bytes, st);
     switch (p.kind) {
         RDK_VERIFY_CASE(RDK_PROB_F32)
         RDK_VERIFY_CASE(RDK_LOGIT_F32)
@@ -429,7 +435,7 @@ rdk_status_t launch_verify_static(const rdk_verify_desc_t &d, RowInput p, const 
                                   uint8_t *accept, float *alpha, float *resid_mass, int32_t *resid_ids, int32_t *n_accepted,
                                   int32_t *out_tokens, hipStream_t st)
 {
-    if (verify_workspace_bytes(d) > kStaticScratchBytes) return RDK_ERR_WORKSPACE;
+    if (verify_sums_bytes(d) > kStaticScratchBytes) return RDK_ERR_WORKSPACE;
     int dev = -1;
     RDK_HIP(hipGetDevice(&dev));
     if (dev < 0 || dev >= kMaxDevices) return RDK_ERR_UNSUPPORTED;
@@ -446,7 +452,8 @@ rdk_status_t launch_verify_static(const rdk_verify_desc_t &d, RowInput p, const 
         ptr = g_scratch_ptr[dev];
     }
     // nothing in the scratch has to start at zero: the streaming pass writes every block sum the finish step reads
-    return launch_verify(d, p, q_prime, ldq, draft_ids, accept, alpha, resid_mass, resid_ids, n_accepted, out_tokens, ptr, st);
+    return launch_verify(d, p, q_prime, ldq, draft_ids, accept, alpha, resid_mass, resid_ids, n_accepted, out_tokens, ptr,
+                         kStaticScratchBytes, st);
 }
 
 rdk_status_t launch_sequence_scan(const rdk_verify_desc_t &d, const int32_t *draft_ids, const uint8_t *accept,

@@ -1,6 +1,6 @@
 """The entry point that allocates nothing (rdk_verify_sample_static): its outputs against rdk_verify_sample's on the
 same inputs, bit for bit, on two calls in a row of which the second is smaller (the scratch array keeps the first
-call's contents), and the refusal of a batch beyond the fixed scratch size."""
+call's contents), the largest batches it takes, and the refusal of a batch beyond the fixed scratch size."""
 import numpy as np
 import pytest
 import torch
@@ -71,3 +71,32 @@ def test_static_scratch_entry_point_refuses_large_batches():
                                             ctypes.c_void_p(acc.data_ptr()), None, None, ctypes.c_void_p(ids.data_ptr()),
                                             None, None, None)
     assert rc == 6                               # RDK_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("N,B,gamma", [(4, 209696, 4), (4, 209696, 0), (4, 116484, 4), (128256, 2759, 1)])
+def test_scratch_limit_is_that_of_the_block_sums(N, B, gamma):
+    """The largest batches the 4 MiB hold: 12 bytes per row and 1024 ids and the statistics partials, with a per-sequence scan
+    as without.  A workspace sized for gamma = 0 serves a scan too."""
+    import ctypes
+    from paper_2506_03206_amd import rdk
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(N + B)
+    p = torch.softmax(torch.randn((B, N), generator=g, device=dev), 1)
+    q = torch.softmax(torch.randn((B, N), generator=g, device=dev), 1)
+    ref = rdk.rdk_verify_sample(p, q, seed=11, offset=3, gamma=gamma)
+    out = rdk.VerifyOutputs(B, N, gamma, dev)
+    rdk.rdk_verify_sample_static(p, q, seed=11, offset=3, gamma=gamma, outputs=out)
+    small = rdk.VerifyOutputs(B, N, gamma, dev)
+    d = rdk.VerifyDesc(B=B, N=N, gamma=0, sample_draft=1, seed=0, offset=0)
+    need = ctypes.c_size_t()
+    assert rdk.lib().rdk_verify_workspace_bytes(ctypes.byref(d), ctypes.byref(need)) == 0
+    assert need.value - 256 <= 4 << 20
+    small.ws = torch.empty(need.value, dtype=torch.uint8, device=dev)
+    rdk.rdk_verify_sample(p, q, seed=11, offset=3, gamma=gamma, outputs=small)
+    for name in FIELDS[: None if gamma else 5]:
+        assert torch.equal(getattr(out, name), getattr(ref, name)), name
+        assert torch.equal(getattr(small, name), getattr(ref, name)), name
+    if B != 116484:                                    # (there the records would not fit beside the sums)
+        d.B += 1                                       # one row more and the sums do not fit
+        assert rdk.lib().rdk_verify_workspace_bytes(ctypes.byref(d), ctypes.byref(need)) == 0 and need.value - 256 > 4 << 20
