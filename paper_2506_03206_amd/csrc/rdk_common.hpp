@@ -4,6 +4,8 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "rdk.h"
 
 namespace rdk {
@@ -59,6 +61,24 @@ rdk_status_t hip_fail(hipError_t e, const char *what);
         hipError_t e_ = hipGetLastError();                              \
         if (e_ != hipSuccess) return ::rdk::hip_fail(e_, name);         \
     } while (0)
+
+// Dynamic LDS above the default limit has to be granted to a kernel on every device it is launched on.  One object per kernel
+// asks once per device; a refusal is reported, and the next call asks again.
+class LdsGrant {
+    std::atomic<uint64_t> granted_{0};   // bit d: device d (a device beyond the word is asked every time)
+
+public:
+    rdk_status_t operator()(const void *kernel, size_t bytes)
+    {
+        int dev = 0;
+        RDK_HIP(hipGetDevice(&dev));
+        const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+        if (granted_.load(std::memory_order_relaxed) & bit) return RDK_OK;
+        RDK_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+        granted_.fetch_or(bit, std::memory_order_relaxed);
+        return RDK_OK;
+    }
+};
 
 // A 64-bit number that no other call of this process uses (see scan_sequence).
 uint64_t call_nonce();

@@ -1110,19 +1110,20 @@ constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 64;
 // 13.8, from 8192 ids on down 11.6 against 13.7; 48000 ids, logits: 20.4 against 21.6, 8000 ids: 12.5 against 20.9).
 constexpr int kRowShortN = 24 * 1024, kRowShortLogitN = 48 * 1024;
 
-// LDS a workgroup may use on the current device (asked once).
+// LDS a workgroup may use (asked until it is told; the same on every device the library is built for).
 size_t row_lds_limit()
 {
-    static size_t limit = 0;
-    if (!limit) {
+    static std::atomic<size_t> limit{0};
+    size_t l = limit.load(std::memory_order_relaxed);
+    if (!l) {
         int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0)
-            limit = (size_t)v;
-        else
-            limit = 64 * 1024;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess || v <= 0)
+            return 64 * 1024;
+        l = (size_t)v;
+        limit.store(l, std::memory_order_relaxed);
     }
-    return limit;
+    return l;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1184,15 +1185,11 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             // with more positions than compute units the workgroups take turns, and each would add its round trips to the
             // chain of its unit: the scan is a launch of its own then
             if (B <= kComputeUnits) set_scan(fa, seq_rec);
-            // dynamic LDS above the default limit has to be granted once to every instantiation
 #define RDK_ROW_LAUNCH(POW, THREADS)                                                                                         \
     {                                                                                                                       \
-        static bool attr_set = false;                                                                                       \
-        if (!attr_set) {                                                                                                    \
-            RDK_HIP(hipFuncSetAttribute((const void *)taylor_row_kernel<PK, QK, POW, THREADS>,                              \
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds_limit()));                 \
-            attr_set = true;                                                                                                \
-        }                                                                                                                   \
+        static LdsGrant grant;                                                                                              \
+        rc = grant((const void *)taylor_row_kernel<PK, QK, POW, THREADS>, row_lds_limit());                                 \
+        if (rc != RDK_OK) return rc;                                                                                        \
         RDK_TIMED_LAUNCH("taylor_row_kernel", (taylor_row_kernel<PK, QK, POW, THREADS>), dim3((unsigned)B), dim3(THREADS),  \
                          lds_bytes, st, p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.item_lo, h.row_items, h.N, h.n, \
                          vec_p, h.slot_of, fa);                                                                             \

@@ -404,9 +404,9 @@ SlabPlan slab_plan(const KernelHandle &h, int32_t B)
 template <int PK, int QK, bool FIN, int T>
 rdk_status_t launch_one(const SlabArgs &a, const FuseArgs &f, const FinalizeArgs &fin, const DraftArgs &draft, hipStream_t st)
 {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)slab_product_kernel<PK, QK, FIN, T>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
-    RDK_HIP(attr);
+    static LdsGrant grant;
+    const rdk_status_t rc = grant((const void *)slab_product_kernel<PK, QK, FIN, T>, kLdsBytes);
+    if (rc != RDK_OK) return rc;
     RDK_TIMED_LAUNCH("sparse_product_kernel", (slab_product_kernel<PK, QK, FIN, T>), dim3((unsigned)a.B * a.splits), dim3(kSlabThreads),
                      slab_lds_bytes(a.n, FIN ? sparse_blocks(a.t.N) : 0), st, a, f, fin, draft);
     RDK_LAUNCH_CHECK("sparse_product_kernel");
