@@ -4,6 +4,8 @@
 // ctypes, Python attribute reads and one object per argument a call cost 10-15 us of host time before its first launch.
 // Here a call reads tensor pointers, strides and dtypes from the tensor objects themselves, asks the library for the
 // workspace size, and launches; nothing is kept between calls but the workspaces that the Python objects own.
+// Other Python threads run while a call allocates or launches (a launch waits when the queue is full): everything that is
+// taken from Python objects is taken before, and what a call uses is held by it.
 //
 // Every function returns the library's status as an int; argument mistakes that the Python layer used to assert raise
 // AssertionError.  Positional arguments only: rdk.py holds the signatures and defaults.
@@ -81,6 +83,13 @@ int64_t rows(const at::Tensor &t)   // leading dimension of a row-major [B, len]
     return t.stride(0);
 }
 
+struct Rows {   // a [B, len] input
+    void *p;
+    rdk_input_kind_t kind;
+    int64_t ld;
+    Rows(const at::Tensor &t, PyObject *k) : p(ptr(t)), kind(kind_of(t, k)), ld(rows(t)) {}
+};
+
 struct Names {
     PyObject *h, *ws, *draft_ws, *fused_ws, *out_ws, *draft_ids, *accept, *alpha, *resid_mass, *resid_ids, *n_accepted, *out_tokens,
         *cand_ids, *accepted, *token, *B, *N, *gamma;
@@ -116,7 +125,19 @@ const rdk_kernel_t *handle(PyObject *kernel)
     return (const rdk_kernel_t *)PyLong_AsVoidPtr(a.o);
 }
 
+// Runs f without the interpreter lock; f touches no Python object.
+template <class F>
+auto unlocked(const F &f)
+{
+    struct Release {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Release() { PyEval_RestoreThread(state); }
+    } release;
+    return f();
+}
+
 struct Scratch {
+    at::Tensor t;   // held for the call: another thread may put a larger one in its place meanwhile
     void *p;
     size_t bytes;
 };
@@ -128,13 +149,14 @@ Scratch workspace(PyObject *owner, PyObject *name, size_t bytes, const at::Tenso
         Ref a(PyObject_GetAttr(owner, name));
         if (a.o != Py_None) {
             const at::Tensor &t = tensor(a.o, "a workspace is not a tensor");
-            if ((size_t)t.numel() >= bytes) return {ptr(t), (size_t)t.numel()};
+            if ((size_t)t.numel() >= bytes) return {t, ptr(t), (size_t)t.numel()};
         }
     }
-    at::Tensor t = at::empty({(int64_t)bytes}, at::TensorOptions().dtype(at::kByte).device(like.device()));
+    const at::TensorOptions opt = at::TensorOptions().dtype(at::kByte).device(like.device());
+    const at::Tensor t = unlocked([&] { return at::empty({(int64_t)bytes}, opt); });
     Ref w(THPVariable_Wrap(t));
     if (PyObject_SetAttr(owner, name, w.o) != 0) throw PyFail{};
-    return {ptr(t), bytes};
+    return {t, ptr(t), bytes};
 }
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
@@ -213,9 +235,12 @@ PyObject *redistribute_verify(PyObject *const *a)
         out = (float *)ptr(t);
     }
     const VerifyTargets v = verify_targets(o);
-    return status(rdk_redistribute_verify(k, mode, &d, ptr(p), kind_of(p, a[7]), rows(p), ptr(q), kind_of(q, a[8]), rows(q), out, ldo,
-                                          v.draft_ids, v.accept, v.alpha, v.resid_mass, v.resid_ids, v.n_accepted, v.out_tokens,
-                                          w.p, w.bytes, stream()));
+    const Rows pi(p, a[7]), qi(q, a[8]);
+    void *st = stream();
+    return status(unlocked([&] {
+        return rdk_redistribute_verify(k, mode, &d, pi.p, pi.kind, pi.ld, qi.p, qi.kind, qi.ld, out, ldo, v.draft_ids, v.accept, v.alpha,
+                                       v.resid_mass, v.resid_ids, v.n_accepted, v.out_tokens, w.p, w.bytes, st);
+    }));
 }
 
 // p, q_prime, seed, offset, gamma, p_kind, sample, outputs, use_workspace
@@ -232,21 +257,28 @@ PyObject *verify_sample(PyObject *const *a)
         q = (const float *)ptr(t);
     }
     const VerifyTargets v = verify_targets(o);
-    const rdk_input_kind_t kind = kind_of(p, a[5]);
+    const Rows pi(p, a[5]);
+    void *st = stream();
     if (PyObject_IsTrue(a[8]) != 1)
-        return status(rdk_verify_sample_static(&d, ptr(p), kind, rows(p), q, ldq, v.draft_ids, v.accept, v.alpha, v.resid_mass, v.resid_ids,
-                                               v.n_accepted, v.out_tokens, stream()));
+        return status(unlocked([&] {
+            return rdk_verify_sample_static(&d, pi.p, pi.kind, pi.ld, q, ldq, v.draft_ids, v.accept, v.alpha, v.resid_mass, v.resid_ids,
+                                            v.n_accepted, v.out_tokens, st);
+        }));
     Ref ws(PyObject_GetAttr(o, g.out_ws));
     const at::Tensor &w = tensor(ws.o, "the workspace is not a tensor");
-    return status(rdk_verify_sample(&d, ptr(p), kind, rows(p), q, ldq, v.draft_ids, v.accept, v.alpha, v.resid_mass, v.resid_ids,
-                                    v.n_accepted, v.out_tokens, ptr(w), (size_t)w.numel(), stream()));
+    void *wp = ptr(w);
+    const size_t bytes = (size_t)w.numel();
+    return status(unlocked([&] {
+        return rdk_verify_sample(&d, pi.p, pi.kind, pi.ld, q, ldq, v.draft_ids, v.accept, v.alpha, v.resid_mass, v.resid_ids,
+                                 v.n_accepted, v.out_tokens, wp, bytes, st);
+    }));
 }
 
 Scratch kernel_workspace(PyObject *kernel, const rdk_kernel_t *k, int32_t B, const at::Tensor &like, rdk_status_t &rc)
 {
     size_t bytes = 0;
     rc = rdk_workspace_bytes(k, B, &bytes);
-    return rc == RDK_OK ? workspace(kernel, g.ws, bytes, like) : Scratch{nullptr, 0};
+    return rc == RDK_OK ? workspace(kernel, g.ws, bytes, like) : Scratch{at::Tensor(), nullptr, 0};
 }
 
 // kernel, q, q_kind, out
@@ -254,12 +286,15 @@ PyObject *redistribute_exact(PyObject *const *a)
 {
     const rdk_kernel_t *k = handle(a[0]);
     const at::Tensor &q = tensor(a[1], "q is not a tensor"), &out = tensor(a[3], "out is not a tensor");
-    const int64_t ldq = rows(q), ldo = rows(out);
+    const int64_t ldo = rows(out);
+    const Rows qi(q, a[2]);
     const int32_t B = (int32_t)q.size(0);
     rdk_status_t rc;
     const Scratch w = kernel_workspace(a[0], k, B, q, rc);
     if (rc != RDK_OK) return status(rc);
-    return status(rdk_redistribute_exact(k, ptr(q), kind_of(q, a[2]), ldq, B, (float *)ptr(out), ldo, w.p, w.bytes, stream()));
+    float *dst = (float *)ptr(out);
+    void *st = stream();
+    return status(unlocked([&] { return rdk_redistribute_exact(k, qi.p, qi.kind, qi.ld, B, dst, ldo, w.p, w.bytes, st); }));
 }
 
 // kernel, mode, q, q_kind, p, p_kind, out
@@ -268,7 +303,8 @@ PyObject *redistribute_linear(PyObject *const *a)
     const rdk_kernel_t *k = handle(a[0]);
     const rdk_linear_mode_t mode = (rdk_linear_mode_t)int32_of(a[1]);
     const at::Tensor &q = tensor(a[2], "q is not a tensor"), &out = tensor(a[6], "out is not a tensor");
-    const int64_t ldq = rows(q), ldo = rows(out);
+    const int64_t ldo = rows(out);
+    const Rows qi(q, a[3]);
     const int32_t B = (int32_t)q.size(0);
     const void *p = nullptr;
     rdk_input_kind_t pk = RDK_PROB_F32;
@@ -282,8 +318,11 @@ PyObject *redistribute_linear(PyObject *const *a)
     rdk_status_t rc;
     const Scratch w = kernel_workspace(a[0], k, B, q, rc);
     if (rc != RDK_OK) return status(rc);
-    return status(rdk_redistribute_linear(k, mode, p, pk, ldp, ptr(q), kind_of(q, a[3]), ldq, B, (float *)ptr(out), ldo, w.p, w.bytes,
-                                          stream()));
+    float *dst = (float *)ptr(out);
+    void *st = stream();
+    return status(unlocked([&] {
+        return rdk_redistribute_linear(k, mode, p, pk, ldp, qi.p, qi.kind, qi.ld, B, dst, ldo, w.p, w.bytes, st);
+    }));
 }
 
 // kernel, q, seed, offset, q_kind, q_prime, draft_ids, q_draft
@@ -291,7 +330,7 @@ PyObject *sample_draft(PyObject *const *a)
 {
     const rdk_kernel_t *k = handle(a[0]);
     const at::Tensor &q = tensor(a[1], "q is not a tensor");
-    const int64_t ldq = rows(q);
+    const Rows qi(q, a[4]);
     const int32_t B = (int32_t)q.size(0);
     size_t bytes = 0;
     const rdk_status_t rc = rdk_sample_draft_workspace_bytes(k, B, &bytes);
@@ -304,9 +343,13 @@ PyObject *sample_draft(PyObject *const *a)
         ldo = rows(t);
         out = (float *)ptr(t);
     }
-    return status(rdk_sample_draft(k, ptr(q), kind_of(q, a[4]), ldq, B, word(a[2]), word(a[3]),
-                                   (int32_t *)ptr(tensor(a[6], "draft_ids is not a tensor")),
-                                   (float *)ptr(tensor(a[7], "q_draft is not a tensor")), out, ldo, w.p, w.bytes, stream()));
+    const uint64_t seed = word(a[2]), offset = word(a[3]);
+    int32_t *ids = (int32_t *)ptr(tensor(a[6], "draft_ids is not a tensor"));
+    float *qd = (float *)ptr(tensor(a[7], "q_draft is not a tensor"));
+    void *st = stream();
+    return status(unlocked([&] {
+        return rdk_sample_draft(k, qi.p, qi.kind, qi.ld, B, seed, offset, ids, qd, out, ldo, w.p, w.bytes, st);
+    }));
 }
 
 // p, q_prime, C, seed, offset, p_kind, sample, outputs
@@ -322,14 +365,20 @@ PyObject *verify_multi(PyObject *const *a)
     d.seed = word(a[3]);
     d.offset = word(a[4]);
     d.sample_candidates = PyObject_IsTrue(a[6]) == 1 ? 1 : 0;
-    const rdk_input_kind_t kind = kind_of(p, a[5]);
+    const Rows pi(p, a[5]);
     size_t bytes = 0;
-    const rdk_status_t rc = rdk_verify_multi_workspace_bytes(&d, kind, &bytes);
+    const rdk_status_t rc = rdk_verify_multi_workspace_bytes(&d, pi.kind, &bytes);
     if (rc != RDK_OK) return status(rc);
     const Scratch w = workspace(o, g.out_ws, bytes, p);
-    return status(rdk_verify_multi(&d, ptr(p), kind, rows(p), (const float *)ptr(q), rows(q), (int32_t *)device_attr(o, g.cand_ids),
-                                   (int32_t *)device_attr(o, g.accepted), (int32_t *)device_attr(o, g.token),
-                                   (float *)device_attr(o, g.resid_mass), w.p, w.bytes, stream()));
+    const float *qp = (const float *)ptr(q);
+    const int64_t ldq = rows(q);
+    int32_t *cand = (int32_t *)device_attr(o, g.cand_ids), *acc = (int32_t *)device_attr(o, g.accepted),
+            *tok = (int32_t *)device_attr(o, g.token);
+    float *mass = (float *)device_attr(o, g.resid_mass);
+    void *st = stream();
+    return status(unlocked([&] {
+        return rdk_verify_multi(&d, pi.p, pi.kind, pi.ld, qp, ldq, cand, acc, tok, mass, w.p, w.bytes, st);
+    }));
 }
 
 // child_node, accepted, token -> (status, n_accepted, out_tokens)
@@ -342,9 +391,13 @@ PyObject *tree_walk(PyObject *const *a)
     need(acc.numel() == S * nodes && tok.numel() == S * nodes, "accepted and token hold one value per node");
     need(S <= INT32_MAX && nodes <= INT32_MAX && C <= INT32_MAX, "too many trees, nodes or children");
     const at::TensorOptions opt = at::TensorOptions().dtype(at::kInt).device(child.device());
-    at::Tensor n_acc = at::empty({S}, opt), out = at::empty({S, nodes}, opt);   // the walk writes every element
-    const rdk_status_t rc = rdk_tree_walk((int32_t)S, (int32_t)nodes, (int32_t)C, (const int32_t *)ptr(child), (const int32_t *)ptr(acc),
-                                          (const int32_t *)ptr(tok), (int32_t *)ptr(n_acc), (int32_t *)ptr(out), stream());
+    at::Tensor n_acc, out;
+    const rdk_status_t rc = unlocked([&] {
+        n_acc = at::empty({S}, opt);
+        out = at::empty({S, nodes}, opt);   // the walk writes every element
+        return rdk_tree_walk((int32_t)S, (int32_t)nodes, (int32_t)C, (const int32_t *)ptr(child), (const int32_t *)ptr(acc),
+                             (const int32_t *)ptr(tok), (int32_t *)ptr(n_acc), (int32_t *)ptr(out), stream());
+    });
     PyObject *t = PyTuple_New(3);
     if (!t) throw PyFail{};
     PyTuple_SET_ITEM(t, 0, status(rc));

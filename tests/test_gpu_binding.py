@@ -1,0 +1,70 @@
+"""The CPython extension as the rest of a Python program sees it."""
+import sys
+import threading
+import time
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def call_of(name):
+    """One per-step call of the extension, its tensors and workspaces made and used once."""
+    from paper_2506_03206_amd import rdk
+    N, n, B, C = 1300, 300, 4, 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    p = torch.softmax(torch.randn((B, N), generator=g, device="cuda"), 1)
+    kept = torch.arange(0, 4 * n, 4, dtype=torch.int32, device="cuda")
+    q = p[:, kept.long()].contiguous()
+    kern = rdk.rdk_build_kernel(N, kept, rdk.IDENTITY)
+    o, m = rdk.VerifyOutputs(B, N, 2, "cuda"), rdk.MultiOutputs(B, C, "cuda")
+    qp = torch.empty((B, N), device="cuda")
+    ids, qd = torch.empty(B, dtype=torch.int32, device="cuda"), torch.empty(B, device="cuda")
+    child = torch.full((2, 2, C), -1, dtype=torch.int32, device="cuda")
+    f = getattr(rdk.native(), name)
+    args = {
+        "redistribute_verify": (kern, rdk.LINEAR_TAYLOR, p, q, 1, 0, 2, "prob", "prob", True, o, None),
+        "verify_sample": (p, p, 1, 0, 2, "prob", True, o, True),
+        "redistribute_exact": (kern, q, "prob", qp),
+        "redistribute_linear": (kern, rdk.LINEAR_TAYLOR, q, "prob", p, "prob", qp),
+        "sample_draft": (kern, q, 1, 0, "prob", qp, ids, qd),
+        "verify_multi": (p, p, C, 1, 0, "prob", True, m),
+        "tree_walk": (child, m.accepted, m.token),
+    }[name]
+    status = f(*args)
+    assert (status[0] if isinstance(status, tuple) else status) == rdk.OK
+    torch.cuda.synchronize()
+    return lambda: f(*args)
+
+
+@pytest.mark.parametrize("name", ["redistribute_verify", "verify_sample", "redistribute_exact", "redistribute_linear", "sample_draft",
+                                  "verify_multi", "tree_walk"])
+def test_other_threads_run_during_a_call(name):
+    """With the interpreter's own switching out of the way another thread advances only while a call gives it the lock."""
+    call = call_of(name)
+    ticks, stop = [0], [False]
+
+    def tick():
+        while not stop[0]:
+            ticks[0] += 1
+            time.sleep(0)
+
+    interval = sys.getswitchinterval()
+    sys.setswitchinterval(600.0)
+    t = threading.Thread(target=tick, daemon=True)
+    try:
+        t.start()
+        before = ticks[0]
+        for _ in range(2000):
+            call()
+            if ticks[0] != before:
+                break
+        advanced = ticks[0] != before
+    finally:
+        stop[0] = True
+        sys.setswitchinterval(interval)
+    t.join(30)
+    assert advanced
+    torch.cuda.synchronize()
