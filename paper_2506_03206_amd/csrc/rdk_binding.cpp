@@ -14,6 +14,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "rdk.h"
@@ -209,8 +210,8 @@ PyObject *guarded(PyObject *, PyObject *const *args, Py_ssize_t n)
     try {
         return F(args);
     } catch (const PyFail &) {
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (const std::exception &) {   // as torch's own bindings raise it (torch.OutOfMemoryError for a workspace)
+        torch::translate_exception_to_python(std::current_exception());
     }
     return nullptr;
 }

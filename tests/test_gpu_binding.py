@@ -68,3 +68,24 @@ def test_other_threads_run_during_a_call(name):
     t.join(30)
     assert advanced
     torch.cuda.synchronize()
+
+
+def test_out_of_memory_is_raised_as_torch_raises_it():
+    """A workspace that the allocator refuses (a limit set for this process; nothing is launched)."""
+    from paper_2506_03206_amd import rdk
+    N, n, B = 40000, 16000, 1 << 14
+    kept = torch.arange(n, dtype=torch.int32, device="cuda")
+    kern = rdk.rdk_build_kernel(N, kept, rdk.SPARSE_TOPK, k=0, embeddings=torch.ones((N, 4), device="cuda"))
+    q = torch.ones((1, n), device="cuda").expand(B, n)          # the workspace is asked for before the stride is looked at
+    out = torch.ones((1, N), device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
+        with pytest.raises(torch.OutOfMemoryError):
+            rdk.rdk_redistribute_linear(kern, rdk.LINEAR_SPARSE, q, out=out)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    with pytest.raises(rdk.RdkError):
+        rdk.rdk_redistribute_linear(kern, rdk.LINEAR_SPARSE, q, out=out)
