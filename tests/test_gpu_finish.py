@@ -59,3 +59,23 @@ def test_scan_in_graph_replays():
         check_scan(o, gamma)
         ref = rdk.rdk_verify_sample(p, q, seed=5, offset=0, gamma=gamma)
         assert torch.equal(ref.out_tokens, o.out_tokens) and torch.equal(ref.n_accepted, o.n_accepted)
+
+
+@pytest.mark.parametrize("N,B,gamma,kind", [(1300, 1024, 8, "prob"), (1300, 1024, 4, "logit"), (30000, 256, 2, "prob"), (1300, 512, 32, "prob")])
+def test_every_sequence_of_a_large_batch_is_scanned(N, B, gamma, kind):
+    """Rows of a sequence on many compute units at once, forty calls on one workspace: no sequence is left without its scan."""
+    from paper_2506_03206_amd import rdk
+    p, q = rows(N, B, 3)
+    if kind == "logit":
+        p = torch.log(p)
+    o = rdk.VerifyOutputs(B, N, gamma, "cuda")
+    at = torch.arange(gamma + 1, device="cuda")
+    for rep in range(40):
+        o.n_accepted.fill_(-7)
+        o.out_tokens.fill_(-7)
+        rdk.rdk_verify_sample(p, q, seed=9, offset=rep * B, gamma=gamma, p_kind=kind, outputs=o)
+        acc = o.accept.reshape(-1, gamma).to(torch.int32)
+        n = torch.cumprod(acc, 1).sum(1)
+        pad = lambda t: torch.nn.functional.pad(t.reshape(-1, gamma), (0, 1), value=-1)
+        want = torch.where(at < n[:, None], pad(o.draft_ids), torch.where(at == n[:, None], pad(o.resid_ids), -1))
+        assert torch.equal(n.to(torch.int32), o.n_accepted) and torch.equal(want.to(torch.int32), o.out_tokens), rep
