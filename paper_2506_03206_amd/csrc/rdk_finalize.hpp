@@ -455,7 +455,9 @@ __device__ __forceinline__ void finish_row_wide(const FinalizeArgs &a, const Row
 // fetched while it runs, so a row takes the shortest that holds its blocks; above 4096 of them they are read again from memory.
 // Whole calls of 8 positions: draft draw, N = 32000 (500 blocks): 64 registers 14.7 us, 32 13.4, 8 12.6; N = 128256 (2004 blocks):
 // 64 17.8, 32 16.4; N = 250000 (3908 blocks): read again 36.5, 64 24.7.  Fused, N = 32000: 64 17.4, 8 15.4; N = 128256: 64 20.6,
-// 32 19.8.
+// 32 19.8.  The step of 16: draft draw, N = 48000 (752 blocks) 32 registers 14.9 us, 16 14.3; N = 64000 (1000) 15.1, 14.4; fused,
+// N = 48000 17.7, 17.1, bf16 logits 24.0, 23.4.  The step of 40: draft draw, N = 151936 (2376) 64 registers 18.8, 40 17.8;
+// N = 163840 (2560) 20.2, 19.2; fused, N = 151936 23.2, 22.7, bf16 logits 30.5, 29.6.
 template <class F>
 inline void with_block_regs(int nblk, const F &f)
 {
