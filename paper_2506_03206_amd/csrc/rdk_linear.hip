@@ -1105,10 +1105,12 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
 constexpr int kRowSeriesMinN = 4096;   // from here on 1 / (N + p) is taken from its series in p / N (exact to fp32 rounding)
 // Below these batches the two-pass kernels, which split a row over workgroups, fill the chip better.  A longer row takes longer
 // in one workgroup, but gives the split form more to do on a full chip too: over 48000 to 200000 ids the two meet at 80 to 88 rows
-// of probabilities, and at 40 (64000 ids) to 68 (200000) rows of logits, where one line at 64 costs 2.0 us at most.  Calls in GPU time, two passes -> one, probabilities: 64 / 88 / 128 rows of 32000 ids 17.1 -> 16.7 / 18.4 -> 17.0 / 20.3 -> 17.5 us, 64000 ids
-// 20.2 -> 22.4 / 22.9 -> 22.9 / 27.6 -> 23.6, 128256 ids 27.2 -> 31.8 / 35.2 -> 32.4 / 40.0 -> 36.5, 200000 ids 33.5 -> 39.3 / 42.8 ->
-// 42.4 / 52.3 -> 45.5.  bf16 logits, with one more launch in two passes: 48 / 64 / 88 rows of 64000 ids 27.6 -> 25.6 / 29.7 -> 25.6 /
-// 33.5 -> 25.7, 128256 ids 35.7 -> 38.4 / 39.5 -> 38.4 / 49.4 -> 38.7, 200000 ids 42.5 -> 48.0 / 46.5 -> 47.9 / 56.2 -> 48.3 ...
+// of probabilities, and at 40 (64000 ids) to 68 (200000) rows of logits, where one line at 64 costs 2.0 us at most.  Calls in GPU
+// time, two passes -> one, probabilities: 64 / 88 / 128 rows of 32000 ids 17.1 -> 16.7 / 18.4 -> 17.0 / 20.3 -> 17.5 us, 64000 ids
+// 20.2 -> 22.4 / 22.9 -> 22.9 / 27.6 -> 23.6, 128256 ids 27.2 -> 31.8 / 35.2 -> 32.4 / 40.0 -> 36.5, 200000 ids 33.5 -> 39.3 /
+// 42.8 -> 42.4 / 52.3 -> 45.5.  bf16 logits, with one more launch in two passes: 48 / 64 / 88 rows of 64000 ids 27.6 -> 25.6 /
+// 29.7 -> 25.6 / 33.5 -> 25.7, 128256 ids 35.7 -> 38.4 / 39.5 -> 38.4 / 49.4 -> 38.7, 200000 ids 42.5 -> 48.0 / 46.5 -> 47.9 /
+// 56.2 -> 48.3 ...
 constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 64;
 // ... unless the rows are short: at any batch, one launch against three or four.  Probabilities, 4 / 32 / 64 rows of 16000 ids 14.1
 // -> 13.4 / 14.3 -> 14.0 / 15.0 -> 14.4, 24000 ids 14.1 -> 14.0 / 14.8 -> 14.8 / 16.4 -> 15.4, and past the line 32000 ids 13.9 ->
