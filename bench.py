@@ -191,15 +191,18 @@ def run_linear(args, rdk, torch, w, vocab, batch, mode_name, path, steps, warmup
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic.get((w.name, mode_name, path, dominant)),
                 "avg_launch_us": round(avg_s * 1e6, 2),
                 "algorithmic_bytes_per_launch": alg}
-    if dominant == "sparse_product_kernel":
+    gathers = dominant == "sparse_product_kernel" and "q_transpose_kernel" in per_kernel   # the position-minor form
+    if gathers:
         roofline["limited_by"] = "line gathers through the vector L1 (extra.sparse_gather), not HBM: the fraction is the algorithmic HBM bytes over the peak"
+    elif dominant == "sparse_product_kernel":
+        roofline["limited_by"] = "the neighbour table, read out of L2 once per position, not HBM: the fraction is the algorithmic HBM bytes over the peak"
     # whole-step compulsory bytes: fused = read p and q once; two calls = q read, q' written then read, p read (twice for Eq. 3)
     if fused:
         step_bytes = B * esz * (w.N + w.n) + (8 * (w.N - w.n) * kk if mode_name == "sparse" else 0)
     else:
         step_bytes = B * (esz * (w.n + w.N) + 8 * w.N) + (8 * (w.N - w.n) * kk if mode_name == "sparse" else B * esz * w.N)
     res_extra = {}
-    if dominant == "sparse_product_kernel":
+    if gathers:
         # what the kernel is limited by: 128-byte lines gathered from q^T through the vector L1 (one per neighbour and
         # 32 positions), against 64 bytes per clock and compute unit (256 units, 2.4 GHz)
         lines = (w.N - w.n) * kk * ((B + 31) // 32)
