@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librdk_hip.so")
 BINDING = os.path.join(HERE, "_rdk_binding.so")
 CEILINGS = os.path.join(HERE, "ceilings")    # stand-alone microbenchmark of HBM and matrix-instruction rates
-SOURCES = ["rdk_api.hip", "rdk_build.hip", "rdk_linear.hip", "rdk_sparse.hip", "rdk_slab.hip", "rdk_exact.hip", "rdk_verify.hip", "rdk_multi.hip"]
+SOURCES = ["rdk_api.hip", "rdk_build.hip", "rdk_linear.hip", "rdk_sparse.hip", "rdk_slab.hip", "rdk_steps.hip", "rdk_exact.hip", "rdk_verify.hip", "rdk_multi.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-Wall", "-Wno-unused-function",
          # packed fp32 instructions are kept off for every device function
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

@@ -82,8 +82,9 @@ bool kind_ok(rdk_input_kind_t k) { return k == RDK_PROB_F32 || k == RDK_LOGIT_F3
 int32_t nbr_row_len(int32_t k) { return ((k < 1 ? 1 : k) + 15) / 16 * 16; }
 
 struct StorageLayout {
-    size_t kept_ids, slot_of, pruned_ids, chunk_lo, lane_map, item_lo, row_items, body, body2, body3, total;
+    size_t kept_ids, slot_of, pruned_ids, chunk_lo, lane_map, item_lo, row_items, body, body2, body3, steps, total;
     int32_t kk, n_pad, N_pad;
+    StepTable step_table;
     int64_t ldm;
 };
 
@@ -135,6 +136,11 @@ StorageLayout layout_of(const rdk_kernel_desc_t &d)
         case RDK_SPARSE_TOPK:
             L.body = off; off += align_up((size_t)(d.N - d.n) * L.kk * 8 + 512, 256);
             L.body3 = off; off += align_up((size_t)d.n * 4, 256);
+            {
+                size_t step_bytes = 0;
+                L.step_table = step_table_plan(d.N, d.n, d.k, &step_bytes);
+                L.steps = off; off += step_bytes;
+            }
             break;
         case RDK_DENSE_F32:
             L.body = off; off += align_up((size_t)d.n * L.ldm * 4, 256);
@@ -279,6 +285,10 @@ rdk_status_t rdk_build_kernel(const rdk_kernel_desc_t *desc, void *storage, size
             RDK_HIP(hipStreamSynchronize(st));
             if (bad) return RDK_ERR_NOT_STOCHASTIC;
         }
+        h.steps = L.step_table;
+        step_table_place(h.steps, sp + L.steps);
+        rc = launch_step_table(h, st);
+        if (rc != RDK_OK) return rc;
     } else if (d.format == RDK_DENSE_F32 || d.format == RDK_DENSE_BF16) {
         const bool bf16 = d.format == RDK_DENSE_BF16;
         float *M32 = bf16 ? (float *)(ws + build_workspace_bytes(d)) : (float *)(sp + L.body);

@@ -15,6 +15,17 @@ constexpr int kChunk = 1024;     // ids summed by one wavefront step: 64 lanes x
 constexpr int kComputeUnits = 256;   // of an MI355X
 constexpr int kMaxSplits = 64;   // upper bound on workgroups sharing one row
 
+// A second table of a sparse kernel, for the product out of LDS several positions at a time (rdk_steps.hip).  A row is 64
+// consecutive target ids, one per lane; its entries are cut into units of eight steps (one entry of every lane a step), the
+// units of a row stand together and the rows ascend.
+struct StepTable {
+    int P;                   // positions side by side in LDS; 0: there is no such table
+    int rows;                // rows of 64 ids
+    size_t off_body, off_first;
+    char *body;              // the units
+    uint32_t *first;         // [rows + 1] first unit of a row
+};
+
 // Host-side description of a built kernel; every pointer points into the caller's storage blob.
 struct KernelHandle {
     int32_t N, n, k;
@@ -36,6 +47,7 @@ struct KernelHandle {
     const int2 *nbr;            // [N-n, kk] pairs (kept slot, weight as fp32 bits): one 128-byte line per 16 entries
     const float *self_w;        // [n] diagonal weights
     int32_t kk;                 // row length of the two tables: k rounded up to a multiple of 16
+    StepTable steps;
     // dense fp32
     const float *dense;       // [n, ldm]
     int64_t ldm;
@@ -153,6 +165,11 @@ size_t sparse_fused_workspace_bytes(const KernelHandle &h, int32_t B);
 rdk_status_t launch_sparse_fused(const KernelHandle &h, const FusedCall &c, void *ws, hipStream_t st);
 rdk_status_t launch_sparse(const KernelHandle &h, RowInput q, int32_t B, float *out, int64_t ldo, void *ws,
                            hipStream_t st);
+
+// rdk_steps.hip
+StepTable step_table_plan(int32_t N, int32_t n, int32_t k, size_t *bytes);
+void step_table_place(StepTable &t, char *base);
+rdk_status_t launch_step_table(const KernelHandle &h, hipStream_t st);
 
 // rdk_exact.hip
 size_t exact_workspace_bytes(const KernelHandle &h, int32_t B);

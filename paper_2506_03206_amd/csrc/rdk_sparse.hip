@@ -12,7 +12,7 @@
 //   * workgroups are numbered so that each XCD sweeps all id tiles of one position block before moving
 //     on: the 4 MB slab of that block stays in the XCD's own L2;
 //   * results are staged in LDS and leave as full 1 KB row segments.
-#include "rdk_slab.hpp"
+#include "rdk_steps.hpp"
 
 namespace rdk {
 
@@ -511,6 +511,7 @@ template <int QK>
 rdk_status_t run_sparse(const KernelHandle &h, RowInput q, int32_t B, float *out, int64_t ldo, void *ws, hipStream_t st)
 {
     SparseWs w = carve(h, B, ws);
+    if (steps_taken(h, B)) return launch_steps_product(h, q, B, out, ldo, w.qpart, -1, FuseArgs{}, st);
     if (slab_taken(h, B)) return launch_slab_product(h, q, B, out, ldo, w.qpart, -1, FuseArgs{}, FinalizeArgs{}, DraftArgs{}, st);
     rdk_status_t rc = prepare_q<QK>(h, q, B, w, st);
     if (rc != RDK_OK) return rc;
@@ -541,7 +542,8 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     f.part_a = (float *)p; p += per;
     uint64_t *seq_rec = (uint64_t *)p;   // [B, 2]
     rdk_status_t rc;
-    const bool slab = slab_taken(h, B), finishes = slab && slab_finishes(h, B);
+    const bool steps = steps_taken(h, B);
+    const bool slab = !steps && slab_taken(h, B), finishes = slab && slab_finishes(h, B);
     if (PK != RDK_PROB_F32 && !finishes) {
         rc = launch_row_stats<PK>(c.p, h.N, B, p_splits, ppart, st);
         if (rc != RDK_OK) return rc;
@@ -554,12 +556,13 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     fa.nblk = (int)blocks;
     fa.draft_ids = c.draft_ids; fa.accept = c.accept; fa.alpha = c.alpha; fa.resid_mass = c.resid_mass;
     fa.resid_ids = c.resid_ids; fa.n_accepted = c.n_accepted; fa.out_tokens = c.out_tokens;
-    if (slab) {
+    if (steps || slab) {
         f.pstat = ppart; f.p_splits = p_splits;
         f.pmerged = pmerged;
         SoftStat *qrow = w.qpart;
         if (finishes) set_scan(fa, seq_rec);
-        rc = launch_slab_product(h, c.q, B, c.q_prime, c.ldo, qrow, PK, f, fa, DraftArgs{}, st);
+        rc = steps ? launch_steps_product(h, c.q, B, c.q_prime, c.ldo, qrow, PK, f, st)
+                   : launch_slab_product(h, c.q, B, c.q_prime, c.ldo, qrow, PK, f, fa, DraftArgs{}, st);
         if (rc != RDK_OK) return rc;
         if (finishes) return scan_if_left(fa, st);
         typedef QpSparse<RowColumn<QK>> QP;
@@ -598,10 +601,12 @@ rdk_status_t run_sparse_draft(const KernelHandle &h, RowInput q, int32_t B, uint
     f.part_q = (float *)((char *)ws + sparse_workspace_bytes(h, B));
     const DraftArgs da{B, h.N, seed, offset, f.part_q, sparse_blocks(h.N), draft_ids, q_draft};
     rdk_status_t rc;
-    if (slab_taken(h, B)) {
+    const bool steps = steps_taken(h, B);
+    if (steps || slab_taken(h, B)) {
         SoftStat *qrow = w.qpart;
-        rc = launch_slab_product(h, q, B, q_prime, ldo, qrow, -2, f, FinalizeArgs{}, da, st);
-        if (rc != RDK_OK || slab_finishes(h, B)) return rc;
+        rc = steps ? launch_steps_product(h, q, B, q_prime, ldo, qrow, -2, f, st)
+                   : launch_slab_product(h, q, B, q_prime, ldo, qrow, -2, f, FinalizeArgs{}, da, st);
+        if (rc != RDK_OK || (!steps && slab_finishes(h, B))) return rc;
         typedef QpSparse<RowColumn<QK>> QP;
         return launch_draft_finalize<kSubIds, QP>(da, QP{tables_of(h), RowColumn<QK>{q.ptr, q.ld, qrow}}, st);
     }
