@@ -82,7 +82,7 @@ bool kind_ok(rdk_input_kind_t k) { return k == RDK_PROB_F32 || k == RDK_LOGIT_F3
 int32_t nbr_row_len(int32_t k) { return ((k < 1 ? 1 : k) + 15) / 16 * 16; }
 
 struct StorageLayout {
-    size_t kept_ids, slot_of, pruned_ids, chunk_lo, lane_map, item_lo, row_items, body, body2, body3, steps, total;
+    size_t kept_ids, slot_of, pruned_ids, chunk_lo, lane_map, item_lo, row_items, row_masks, body, body2, body3, steps, total;
     int32_t kk, n_pad, N_pad;
     StepTable step_table;
     int64_t ldm;
@@ -129,6 +129,7 @@ StorageLayout layout_of(const rdk_kernel_desc_t &d)
     L.chunk_lo = off; off += align_up((size_t)((d.N + kChunk - 1) / kChunk + 1) * 4, 256);
     L.lane_map = off; off += align_up((size_t)((d.N + kChunk - 1) / kChunk) * kWave * 8, 256);
     L.item_lo = off; off += align_up((size_t)((d.N + kChunk - 1) / kChunk + 1) * 4, 256);
+    L.row_masks = off; off += d.N >= kRowMaskMinN ? align_up((size_t)((d.N + kChunk - 1) / kChunk) * 16 * 8, 256) : 0;
     L.row_items = off; off += align_up((size_t)((d.N + kChunk - 1) / kChunk + d.n / 64 + 1) * 8, 256);
     L.kk = nbr_row_len(d.k);
     L.ldm = ((int64_t)d.N + 3) / 4 * 4;
@@ -259,7 +260,9 @@ rdk_status_t rdk_build_kernel(const rdk_kernel_desc_t *desc, void *storage, size
     if (rc != RDK_OK) return rc;
     uint64_t *lane_map = (uint64_t *)(sp + L.lane_map);
     h.lane_map = lane_map;
-    rc = launch_lane_map(slot_of, chunk_lo, d.N, d.n, lane_map, st);
+    uint64_t *row_masks = d.N >= kRowMaskMinN ? (uint64_t *)(sp + L.row_masks) : nullptr;
+    h.row_masks = row_masks;
+    rc = launch_lane_map(slot_of, chunk_lo, d.N, d.n, lane_map, row_masks, st);
     if (rc != RDK_OK) return rc;
     int32_t *item_lo = (int32_t *)(sp + L.item_lo);
     int2 *row_items = (int2 *)(sp + L.row_items);

@@ -178,8 +178,9 @@ __global__ __launch_bounds__(1024) void row_items_kernel(const int32_t *chunk_lo
     if (threadIdx.x == 0) item_lo[nchunks] = carry;
 }
 
-// Per chunk and lane the kept mask of the lane's 16 ids and the kept ids of the chunk below each of its four groups.
-__global__ void lane_map_kernel(const int32_t *slot_of, const int32_t *chunk_lo, int N, int n, uint64_t *lane_map)
+// Per chunk and lane the kept mask of the lane's 16 ids and the kept ids of the chunk below each of its four groups; row_masks (or
+// null): per chunk and place of a lane's 16 ids the lanes that keep theirs.
+__global__ void lane_map_kernel(const int32_t *slot_of, const int32_t *chunk_lo, int N, int n, uint64_t *lane_map, uint64_t *row_masks)
 {
     const int c = blockIdx.x, l = threadIdx.x;
     const int lo = chunk_lo[c];
@@ -192,8 +193,12 @@ __global__ void lane_map_kernel(const int32_t *slot_of, const int32_t *chunk_lo,
             below = s >= 0 ? s : j0 - (-s - 1);
         }
         rec |= (uint64_t)(below - lo) << (16 + 12 * i);
-        for (int e = 0; e < 4; ++e)
-            if (j0 + e < N && slot_of[j0 + e] >= 0) rec |= (uint64_t)1 << (4 * i + e);
+        for (int e = 0; e < 4; ++e) {
+            const bool kept = j0 + e < N && slot_of[j0 + e] >= 0;
+            if (kept) rec |= (uint64_t)1 << (4 * i + e);
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64(kept);
+            if (row_masks && l == 0) row_masks[16 * c + 4 * i + e] = lanes;
+        }
     }
     lane_map[(int64_t)c * kWave + l] = rec;
 }
@@ -487,11 +492,11 @@ rdk_status_t launch_row_items(const int32_t *chunk_lo, int32_t N, int32_t *item_
     return RDK_OK;
 }
 
-rdk_status_t launch_lane_map(const int32_t *slot_of, const int32_t *chunk_lo, int32_t N, int32_t n, uint64_t *lane_map,
+rdk_status_t launch_lane_map(const int32_t *slot_of, const int32_t *chunk_lo, int32_t N, int32_t n, uint64_t *lane_map, uint64_t *row_masks,
                              hipStream_t st)
 {
     const int nchunks = (N + kChunk - 1) / kChunk;
-    hipLaunchKernelGGL(lane_map_kernel, dim3(nchunks), dim3(kWave), 0, st, slot_of, chunk_lo, N, n, lane_map);
+    hipLaunchKernelGGL(lane_map_kernel, dim3(nchunks), dim3(kWave), 0, st, slot_of, chunk_lo, N, n, lane_map, row_masks);
     RDK_LAUNCH_CHECK("lane_map_kernel");
     return RDK_OK;
 }

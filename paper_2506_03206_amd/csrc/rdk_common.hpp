@@ -12,6 +12,9 @@ namespace rdk {
 
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kChunk = 1024;     // ids summed by one wavefront step: 64 lanes x 4 x float4
+// From this vocabulary on the one-pass form of Eq. 3 takes 1 / (N + p) from its series in p / N (exact to fp32 rounding), and
+// reads which lanes keep their ids as masks (KernelHandle::row_masks).
+constexpr int kRowMaskMinN = 4096;
 constexpr int kComputeUnits = 256;   // of an MI355X
 constexpr int kMaxSplits = 64;   // upper bound on workgroups sharing one row
 
@@ -37,6 +40,9 @@ struct KernelHandle {
     // 256 i + 4 l + e, i, e = 0..3): bit 4 i + e = the id is kept; bits 16 + 12 i .. 27 + 12 i = kept ids of the chunk
     // below id c * kChunk + 256 i + 4 l.  The slot of a kept id follows from these and chunk_lo[c].
     const uint64_t *lane_map;
+    // [ceil(N / kChunk), 16], for N >= kRowMaskMinN (else null): row_masks[16 c + 4 i + e] are the lanes l that keep the id
+    // c * kChunk + 256 i + 4 l + e, the bits of lane_map turned round.
+    const uint64_t *row_masks;
     // The kept slots cut into pieces of at most 64 consecutive slots that never cross a chunk: piece k is
     // row_items[k] = {first slot, chunk | (first slot of the chunk mod 4) << 22 | length << 24}, pieces ascend with the
     // slots, and the pieces of chunk c are item_lo[c] .. item_lo[c + 1] - 1 (item_lo has ceil(N / kChunk) + 1 entries).
@@ -138,7 +144,7 @@ rdk_status_t launch_features_from_scores(const void *z, rdk_input_kind_t kind, i
                                          int64_t ldf, hipStream_t st);
 rdk_status_t launch_chunk_lo(const int32_t *kept_ids, int32_t n, int32_t N, int32_t *chunk_lo, hipStream_t st);
 rdk_status_t launch_row_items(const int32_t *chunk_lo, int32_t N, int32_t *item_lo, int2 *row_items, hipStream_t st);
-rdk_status_t launch_lane_map(const int32_t *slot_of, const int32_t *chunk_lo, int32_t N, int32_t n, uint64_t *lane_map,
+rdk_status_t launch_lane_map(const int32_t *slot_of, const int32_t *chunk_lo, int32_t N, int32_t n, uint64_t *lane_map, uint64_t *row_masks,
                              hipStream_t st);
 rdk_status_t launch_pruned_ids(const int32_t *slot_of, int32_t N, int32_t n, int32_t *pruned_ids, hipStream_t st);
 rdk_status_t launch_build_sparse(const rdk_kernel_desc_t &d, const int32_t *pruned_ids, int2 *nbr, float *self_w,

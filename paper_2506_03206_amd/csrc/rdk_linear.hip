@@ -491,11 +491,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 //   * a kept id needs its own p and q^: while the row streams by, the target values of the kept ids are scattered
 //     into LDS, chunk by chunk in slot order (4 n bytes: one value per drafter slot; the run of every chunk starts
 //     on a 16-byte boundary).
-// The softmax of a logit row is not known while it streams, so step A works relative to the maximum of each chunk:
-// e = exp(z - chunk maximum) goes to LDS for the kept ids, and the chunk keeps power sums of e, from which the sums of
+// The softmax of a logit row is not known while it streams, so step A works relative to a reference of the wavefront's, the
+// largest logit of a chunk before (row_power_chunk): e = exp(z - reference) goes to LDS for the kept ids, and the chunk keeps
+// its reference and power sums of e, from which the sums of
 // p / (N + p) and q^ / (N + p) follow once the scale is known (x = p / N: p / (N + p) = x - x^2 + ..., N / (N + p) = 1 - x +
 // x^2 - ...): over the not-kept ids sum e and e^2, over the kept ids the same and sum q^, q^ e, q^ e^2.  Drafter logits are
-// taken relative to the largest of the chunk's run in the same way.  (Probability rows: e = p, all maxima zero.)  Which
+// taken relative to a reference in the same way.  (Probability rows: e = p, all references zero.)  Which
 // powers: see Powers.
 // Step A streams p, guided by the kernel's lane map (L2-resident, shared by all rows), a wavefront per chunk.  The chunk's
 // run of drafter values is fetched alongside (one contiguous piece of the drafter row); the wavefront reads its own
@@ -508,9 +509,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 // in their order.  HBM traffic: p and q once.
 // What bounds it, measured on MI355X: probability rows, HBM while the row streams and then, with one workgroup on a unit,
 // about 10 us in the steps after it (N = 128256, n = 32064, 256 rows: 38.6 us a call; N = 151936, n = 16384, 1024 rows: 124.8
-// us, 5.5 TB/s); bf16 logit rows, the vector unit in step A (same shape, half the bytes: 124.8 us, 184 before the loads
+// us, 5.5 TB/s); bf16 logit rows, the vector unit in step A (same shape, half the bytes: 92.5 us, 3.8 TB/s; 184 before the loads
 // stayed raw in registers -- a conversion next to a load waits for it, so nothing was ever in flight -- and before the
-// scatter became a block on the execution mask, eight sums were reduced together, and two workgroups shared a unit).
+// scatter became a block on the execution mask, eight sums were reduced together, and two workgroups shared a unit; 125.7
+// before the largest logit of a chunk was done without, the masks of the scatter came by scalar loads, and the kept ids' sums
+// took a slot a lane: 395 vector instructions a chunk of 1024 ids then, 250 now).  The sums of a chunk on the matrix units
+// instead (seven products of 32 cycles) were 10 us slower: the products hold the vector unit's issue.
 // q' of Eq. 3 re-computed from the row constants (the finish step needs the two blocks of the crossings).
 template <int PK, int QK>
 struct QpTaylor {
@@ -702,38 +706,59 @@ __device__ __forceinline__ float wave_sum8(const float (&v)[8])
     return a;
 }
 
-// A chunk of a target row, raw.  Quads need the alignment of one element only (that is all that a global load asks for),
-// and no load depends on a branch: the quads that cross the end of the row or lie past it are put right where they are used.
+// A chunk of a target row, raw, and the raw drafter values of the first kRowAhead rounds of its run of slots [lo, hi): lane l
+// the slots lo + l + 64 r.  Quads need the alignment of one element only (that is all that a global load asks for), and no load
+// depends on a branch: the quads that cross the end of the row or lie past it are put right where they are used, and what lies
+// past the run is left out there.  A chunk past the last one is asked for too (one line per load, never used): the number of
+// loads in flight is then the same on every path, and waiting for the oldest waits for no other.
+constexpr int kRowAhead = 5;
 template <int PK>
 struct PowerChunk {
     typename RawQuad<PK>::type p[4];
     uint64_t map;
+    uint32_t q[kRowAhead];
     int lo, hi;
 };
+// Read-only for the kernel: scalar loads.
+template <class V>
+using ScalarPtr = const __attribute__((address_space(4))) V *;
+template <class V>
+__device__ __forceinline__ ScalarPtr<V> scalar_ptr(const V *p) { return (ScalarPtr<V>)(uintptr_t)p; }
+
+template <int QK>
+__device__ __forceinline__ uint32_t power_q_raw(const void *qr, uint32_t off)
+{
+    return QK == RDK_LOGIT_BF16 ? (uint32_t)*(const uint16_t *)((const char *)qr + off) : *(const uint32_t *)((const char *)qr + off);
+}
+template <int QK>
+__device__ __forceinline__ float power_q_value(uint32_t raw) { return __uint_as_float(QK == RDK_LOGIT_BF16 ? raw << 16 : raw); }
+
 template <int PK>
-__device__ __forceinline__ void power_fetch(const void *pr, const uint64_t *lane_map, const int32_t *chunk_lo, int c, int N,
-                                            PowerChunk<PK> &b)
+__device__ __forceinline__ void power_fetch_p(const void *pr, const uint64_t *lane_map, int c, int N, PowerChunk<PK> &b)
 {
     typedef typename RawQuad<PK>::type Raw;
-    const int lane = lane_id();
+    constexpr uint32_t es = PK == RDK_LOGIT_BF16 ? 2 : 4;
+    const uint32_t lane = (uint32_t)lane_id();
+    const int at = min(c, (N - 1) / kChunk), p0 = min(at * kChunk, N - 4);
+    const char *pb = (const char *)pr + (int64_t)p0 * es;
+    uint32_t most = c == at ? (uint32_t)min(N - 4 - p0, kChunk) * es : 0u;
+    asm("" : "+s"(most));                                  // one minimum per load, not one and a selection
+    b.map = *(const uint64_t *)((const char *)(lane_map + (int64_t)at * kWave) + lane * 8);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t at = (uint32_t)min(c * kChunk + 256 * i + 4 * lane, N - 4) * (PK == RDK_LOGIT_BF16 ? 2u : 4u);
-        b.p[i] = __builtin_nontemporal_load((const Raw *)((const char *)pr + at));
-    }
-    b.map = lane_map[c * kWave + lane];
-    b.lo = chunk_lo[c];
-    b.hi = chunk_lo[c + 1];
+    for (int i = 0; i < 4; ++i) b.p[i] = __builtin_nontemporal_load((const Raw *)(pb + min((4 * lane + 256 * i) * es, most)));
 }
-
-// The raw drafter values of a run [lo, hi) of at most 1024 slots: lane l the quads lo + 4 l + 256 i; what lies past the run
-// is masked on use.
-template <int QK>
-__device__ __forceinline__ void power_q_fetch(const void *qr, int lo, int hi, int n, typename RawQuad<QK>::type (&qv)[4])
+template <int PK, int QK>
+__device__ __forceinline__ void power_fetch_q(const void *qr, int c, int lo, int hi, int N, int n, PowerChunk<PK> &b)
 {
+    constexpr uint32_t qs = QK == RDK_LOGIT_BF16 ? 2 : 4;
+    const int q0 = min(lo, n - 1);
+    const char *qb = (const char *)qr + (int64_t)q0 * qs;
+    uint32_t most = c * kChunk < N ? (uint32_t)(n - 1 - q0) * qs : 0u;
+    asm("" : "+s"(most));
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (lo + 256 * i < hi) qv[i] = raw_quad<QK>(qr, lo + 256 * i + 4 * lane_id(), n);   // the same for all lanes
+    for (int r = 0; r < kRowAhead; ++r) b.q[r] = power_q_raw<QK>(qb, min(((uint32_t)lane_id() + kWave * r) * qs, most));
+    b.lo = lo;
+    b.hi = hi;
 }
 
 // How 1 / (N + p) is taken from power sums.
@@ -743,146 +768,220 @@ enum class Powers {
     Exact,    // smaller vocabularies, probability rows: p^2 is replaced by p^2 / (1 + p / N), which closes the series
 };
 
-// One target value: goes to its slot in LDS (byte address `at`, moved on) in the lanes where the id is kept, into the sums
-// of the ids that are not kept in the others.  The map's bits are shifted out at the top, one per value.  Written as one
-// block on the execution mask: four vector instructions; selecting in the sums and computing the address took eight.
-template <Powers POW>
-__device__ __forceinline__ void power_place(uint32_t &bits, uint32_t &at, float ev, float invN, float &s1, float &s2, float &s3)
+// Four target values of a lane: each goes to its slot in LDS (byte address `at`, moved on) in the lanes where the id is kept,
+// into the sums of the ids that are not kept in the others.  Written on the execution mask: three vector instructions a value
+// with the masks in scalar registers (kept[e]: the lanes whose id e of the quad is kept), four where they are shifted out of the
+// lane's map (bits, at the top), against eight for selecting in the sums and computing the address.
+__device__ __forceinline__ void power_place(const uint64_t *kept, uint32_t &at, const float (&ev)[4], float &s1, float &s2)
 {
-    if (POW == Powers::Series) {
-        asm volatile("v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"
-                     "s_mov_b64 exec, vcc\n\t"
-                     "ds_write_b32 %[at], %[ev]\n\t"
-                     "v_add_u32 %[at], 4, %[at]\n\t"
-                     "s_not_b64 exec, exec\n\t"
-                     "v_add_f32 %[s1], %[ev], %[s1]\n\t"
-                     "v_fmac_f32 %[s2], %[ev], %[ev]\n\t"
-                     "s_mov_b64 exec, -1"
-                     : [m] "+v"(bits), [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2)
-                     : [ev] "v"(ev)
-                     : "vcc", "scc", "memory");
-    } else {
-        const float e2 = POW == Powers::Exact ? ev * ev * __builtin_amdgcn_rcpf(fmaf(ev, invN, 1.0f)) : ev * ev;
-        asm volatile("v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"
-                     "s_mov_b64 exec, vcc\n\t"
-                     "ds_write_b32 %[at], %[ev]\n\t"
-                     "v_add_u32 %[at], 4, %[at]\n\t"
-                     "s_not_b64 exec, exec\n\t"
-                     "v_add_f32 %[s1], %[ev], %[s1]\n\t"
-                     "v_add_f32 %[s2], %[e2], %[s2]\n\t"
-                     "v_fmac_f32 %[s3], %[e2], %[ev]\n\t"
-                     "s_mov_b64 exec, -1"
-                     : [m] "+v"(bits), [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2), [s3] "+v"(s3)
-                     : [ev] "v"(ev), [e2] "v"(e2)
-                     : "vcc", "scc", "memory");
-    }
+#define RDK_PLACE(e, next)                         \
+    "s_mov_b64 exec, %[k" #e "]\n\t"               \
+    "ds_write_b32 %[at], %[e" #e "]\n\t" next      \
+    "s_not_b64 exec, exec\n\t"                     \
+    "v_add_f32 %[s1], %[e" #e "], %[s1]\n\t"       \
+    "v_fmac_f32 %[s2], %[e" #e "], %[e" #e "]\n\t"
+#define RDK_NEXT "v_add_u32 %[at], 4, %[at]\n\t"
+    asm volatile(RDK_PLACE(0, RDK_NEXT) RDK_PLACE(1, RDK_NEXT) RDK_PLACE(2, RDK_NEXT) RDK_PLACE(3, "") "s_mov_b64 exec, -1"
+                 : [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2)
+                 : [e0] "v"(ev[0]), [e1] "v"(ev[1]), [e2] "v"(ev[2]), [e3] "v"(ev[3]), [k0] "s"(kept[0]), [k1] "s"(kept[1]),
+                   [k2] "s"(kept[2]), [k3] "s"(kept[3])
+                 : "scc", "memory");
+#undef RDK_NEXT
+#undef RDK_PLACE
+}
+__device__ __forceinline__ void power_place(uint32_t &bits, uint32_t &at, float ev, float e2, float &s1, float &s2, float &s3)
+{
+    asm volatile("v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"
+                 "s_mov_b64 exec, vcc\n\t"
+                 "ds_write_b32 %[at], %[ev]\n\t"
+                 "v_add_u32 %[at], 4, %[at]\n\t"
+                 "s_not_b64 exec, exec\n\t"
+                 "v_add_f32 %[s1], %[ev], %[s1]\n\t"
+                 "v_add_f32 %[s2], %[e2], %[s2]\n\t"
+                 "v_fmac_f32 %[s3], %[e2], %[ev]\n\t"
+                 "s_mov_b64 exec, -1"
+                 : [m] "+v"(bits), [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2), [s3] "+v"(s3)
+                 : [ev] "v"(ev), [e2] "v"(e2)
+                 : "vcc", "scc", "memory");
 }
 
-// Step A for one chunk: statistics to `stat` (arrays of nchunks floats), e of the kept ids to LDS.
-// lane_stat: which of the statistics the lane writes (-1: none).
-template <int PK, int QK, Powers POW>
-__device__ __forceinline__ void row_power_chunk(const PowerChunk<PK> &b, int c, int lo, int hi, int N,
-                                                const typename RawQuad<QK>::type (&qv)[4], int n, float *pk, const float *zero_quad,
-                                                float *stat, int nchunks, int lane_stat, float invN)
+// v with the value of one lane replaced.
+template <int LANE>
+__device__ __forceinline__ void lane_set(float &v, float to)
 {
-    constexpr bool CUBIC = POW == Powers::Cubic;
-    const int lane = lane_id();
-    float z[4][4];
+    asm("v_writelane_b32 %0, %1, %2" : "+v"(v) : "s"(__builtin_amdgcn_readfirstlane(__float_as_uint(to))), "n"(LANE));
+}
+
+// The target values of a chunk as floats; of a last chunk that does not fill, what lies past the row counts nothing.
+template <int PK>
+__device__ __forceinline__ void power_values(const PowerChunk<PK> &b, int c, int N, float (&z)[4][4])
+{
 #pragma unroll
     for (int i = 0; i < 4; ++i) RawQuad<PK>::to(b.p[i], z[i]);
-    if (N - c * kChunk < kChunk) {                     // the last chunk of a row that does not fill it
+    if (__builtin_expect(N - c * kChunk < kChunk, 0)) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int left = N - (c * kChunk + 256 * i + 4 * lane);   // ids of the row from the lane's quad on
+            const int left = N - (c * kChunk + 256 * i + 4 * lane_id());   // ids of the row from the lane's quad on
             quad_shift(z[i], 4 - left);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (e >= left) z[i][e] = PK == RDK_PROB_F32 ? 0.f : -INFINITY;
         }
     }
-    float mx = 0.f;
+}
+
+// The references of a chunk's weights from its largest logits.
+template <int PK, int QK>
+__device__ __forceinline__ void power_refs(const PowerChunk<PK> &b, int c, int N, const void *qr, float &rp, float &rq)
+{
+    float zm = kLowest, qm = kLowest;
     if (PK != RDK_PROB_F32) {
-        mx = raw_max3(z[0][0], z[0][1], z[0][2]);
-        mx = raw_max3(mx, z[0][3], z[1][0]);
-        mx = raw_max3(mx, z[1][1], z[1][2]);
-        float my = raw_max3(z[1][3], z[2][0], z[2][1]);
-        my = raw_max3(my, z[2][2], z[2][3]);
-        mx = raw_max3(mx, z[3][0], z[3][1]);
-        my = raw_max3(my, z[3][2], z[3][3]);
-        mx = wave_max_scalar(raw_max3(mx, my, kLowest));
+        float z[4][4];
+        power_values<PK>(b, c, N, z);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zm = raw_max3(raw_max3(zm, z[i][0], z[i][1]), z[i][2], z[i][3]);
     }
+    if (QK != RDK_PROB_F32) {
+#pragma unroll
+        for (int r = 0; r < kRowAhead; ++r)
+            qm = lane_id() < b.hi - b.lo - kWave * r ? raw_max(qm, power_q_value<QK>(b.q[r])) : qm;
+        for (int s = b.lo + kWave * kRowAhead + lane_id(); __builtin_expect(s < b.hi, 0); s += kWave)
+            qm = raw_max(qm, power_q_value<QK>(power_q_raw<QK>(qr, (uint32_t)s * (QK == RDK_LOGIT_BF16 ? 2u : 4u))));
+    }
+    if (PK != RDK_PROB_F32) rp = wave_max_scalar(zm);
+    if (QK != RDK_PROB_F32) rq = wave_max_scalar(qm);
+}
+
+// The power sums of a chunk, per lane (n: ids that are not kept, k: kept ones).
+struct PowerSums {
+    float s1n, s2n, s3n, s1k, s2k, s3k, q0, q1, q2, q3;
+};
+
+// Forms them, e of the kept ids to LDS.  Returns what shows a weight beyond its range.
+template <int PK, int QK, Powers POW>
+__device__ __forceinline__ float power_sums(const PowerChunk<PK> &b, int c, int N, const void *qr, int n, float *pk,
+                                            const uint64_t *row_masks, float invN, float rp, float rq,
+                                            PowerSums &v)
+{
+    constexpr bool CUBIC = POW == Powers::Cubic;
+    const int lane = lane_id(), lo = b.lo, hi = b.hi;
     const int run = row_run_start(lo, c);
-    uint32_t bits = __builtin_bitreverse32((uint32_t)b.map);   // the bit of the first id on top
     const uint32_t first = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)pk + 4 * run;
-    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // power sums, in the order of the enumeration; last the third power
-    float s3k = 0.f, q3 = 0.f;
+    uint64_t kept[16];
+    if (POW == Powers::Series) {
+        const ScalarPtr<uint64_t> mk = scalar_ptr(row_masks) + 16 * c;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) kept[i] = mk[i];
+    }
+    float z[4][4];
+    power_values<PK>(b, c, N, z);
+    uint32_t bits = __builtin_bitreverse32((uint32_t)b.map);   // the bit of the first id on top
+    v = PowerSums{};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         uint32_t at = first + 4 * (uint32_t)((b.map >> (16 + 12 * i)) & 0xFFFu);
         float ev[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) ev[e] = to_weight<PK>(z[i][e], mx, 1.f);   // ids beyond N: zero
+        for (int e = 0; e < 4; ++e) ev[e] = to_weight<PK>(z[i][e], rp, 1.f);   // ids beyond N: zero
+        if (POW == Powers::Series) {
+            power_place(kept + 4 * i, at, ev, v.s1n, v.s2n);
+        } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) power_place<POW>(bits, at, ev[e], invN, v[kRowS1n], v[kRowS2n], v[7]);
-    }
-    // over the kept ids, in slot order; the drafter values relative to the largest of the run
-    float qf[4][4], qmx = 0.f;
-    if (lo < hi) {
-        constexpr float none = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
-        float m = kLowest;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (lo + 256 * i < hi) {
-                RawQuad<QK>::to(qv[i], qf[i]);
-                const int left = hi - lo - 4 * (lane + 64 * i);   // slots of the run from the lane's quad on
-                if (hi + 3 > n) quad_shift(qf[i], 4 - (n - lo - 4 * (lane + 64 * i)));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) qf[i][e] = e < left ? qf[i][e] : none;
-                if (QK != RDK_PROB_F32) m = raw_max3(raw_max3(m, qf[i][0], qf[i][1]), qf[i][2], qf[i][3]);
+            for (int e = 0; e < 4; ++e) {
+                const float e2 = POW == Powers::Exact ? ev[e] * ev[e] * __builtin_amdgcn_rcpf(fmaf(ev[e], invN, 1.0f)) : ev[e] * ev[e];
+                power_place(bits, at, ev[e], e2, v.s1n, v.s2n, v.s3n);
             }
         }
-        if (QK != RDK_PROB_F32) qmx = wave_max_scalar(m);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (lo + 256 * i < hi) {
-                const int o = 4 * (lane + 64 * i);
-                const float4 e4 = *(const float4 *)(o < hi - lo ? pk + run + o : zero_quad);   // past the run: zeros
-                const float ee[4] = {e4.x, e4.y, e4.z, e4.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float qe = to_weight<QK>(qf[i][e], qmx, 1.f);
-                    float e2 = ee[e] * ee[e];
-                    if (POW == Powers::Exact) e2 *= __builtin_amdgcn_rcpf(fmaf(ee[e], invN, 1.0f));
-                    v[kRowS1k] += ee[e];
-                    v[kRowS2k] += e2;
-                    v[kRowQ0] += qe;
-                    v[kRowQ1] = fmaf(qe, ee[e], v[kRowQ1]);
-                    v[kRowQ2] = fmaf(qe, e2, v[kRowQ2]);
-                    if (CUBIC) {
-                        s3k = fmaf(e2, ee[e], s3k);
-                        q3 = fmaf(qe * e2, ee[e], q3);
-                    }
-                }
-            }
-        }
-    } else if (QK != RDK_PROB_F32) {
-        qmx = kLowest;
     }
-    float out = wave_sum8(v);
+    // over the kept ids, in slot order, a slot a lane
+    auto add = [&](float qe, float ee) {
+        float e2 = ee * ee;
+        if (POW == Powers::Exact) e2 *= __builtin_amdgcn_rcpf(fmaf(ee, invN, 1.0f));
+        v.s1k += ee;
+        v.s2k += e2;
+        v.q0 += qe;
+        v.q1 = fmaf(qe, ee, v.q1);
+        v.q2 = fmaf(qe, e2, v.q2);
+        if (CUBIC) {
+            v.s3k = fmaf(e2, ee, v.s3k);
+            v.q3 = fmaf(qe * e2, ee, v.q3);
+        }
+    };
+    auto weight = [&](uint32_t raw) { return to_weight<QK>(power_q_value<QK>(raw), rq, 1.f); };
+    auto round = [&](int r, uint32_t raw) {
+        if (lane < hi - lo - kWave * r) add(weight(raw), pk[run + kWave * r + lane]);
+    };
+    // two rounds without a branch: selecting costs less than what a wavefront waits at the ends of short blocks (4 of 102 us).
+    // What a lane past the run reads may be another run's, or lie behind them all (2 x 64 floats at most, less than the layout
+    // holds there), and counts nothing.
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const bool in = lane < hi - lo - kWave * r;
+        const float qe = weight(b.q[r]), ee = pk[run + kWave * r + lane];
+        add(in ? qe : 0.f, in ? ee : 0.f);
+    }
+    if (hi - lo > 2 * kWave) {
+#pragma unroll
+        for (int r = 2; r < kRowAhead; ++r) round(r, b.q[r]);
+    }
+    for (int r = kRowAhead; __builtin_expect(lo + kWave * r < hi, 0); r += 4) {
+        uint32_t more[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            more[j] = power_q_raw<QK>(qr, (uint32_t)min(lo + kWave * (r + j) + lane, n - 1) * (QK == RDK_LOGIT_BF16 ? 2u : 4u));
+        // all there before any is used: a round that is left out would leave its load to be waited for with the next chunk's
+        asm volatile("s_waitcnt vmcnt(0)" : "+v"(more[0]), "+v"(more[1]), "+v"(more[2]), "+v"(more[3]));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) round(r + j, more[j]);
+    }
+    const float q2 = QK == RDK_PROB_F32 ? 0.f : v.q0 * v.q0;
+    return PK == RDK_PROB_F32 ? q2 : q2 + (v.s2n + v.s2k);
+}
+
+// Step A for one chunk: statistics to `stat` (arrays of nchunks floats).  lane_stat: which of them the lane writes (-1: none).
+//
+// A wavefront takes the weights of logits relative to the largest of its first chunk, of target and drafter rows alike,
+// and looks for new references only when a lane's sums show weights well beyond one (or not a number): then the chunk is done
+// again.  The limit lets weights up to 256 pass, exponents up to 8, so the exponents of the values that make up a row's mass stay
+// small and are rounded as finely as below the maximum (resid_mass of 512 rows against 64-bit sums, logits of deviation 2 and
+// 6: 4.4e-8 and 7.6e-8 of it on average, 4.1e-8 and 8.3e-8 with the largest of every chunk); and below the reference nothing is
+// lost that the factor between chunk and row would not take away too.  With a limit of 80 every second wavefront has a chunk to do
+// again (1024 bf16 rows of 151936 ids: 4 us).
+// OWN: the chunk's own references, for rows so short that a wavefront has no use for them after.
+constexpr float kRefLimit = 65536.f;
+template <int PK, int QK, Powers POW, bool OWN>
+__device__ __forceinline__ void row_power_chunk(PowerChunk<PK> &b, int c, int N, const void *qr, int n, float *pk,
+                                                const uint64_t *row_masks, float *stat, int nchunks, int lane_stat, float invN,
+                                                float &rp, float &rq)
+{
+    constexpr bool CUBIC = POW == Powers::Cubic;
+    const int lane = lane_id();
+    PowerSums v;
+    if (OWN) power_refs<PK, QK>(b, c, N, qr, rp, rq);
+    const float most = power_sums<PK, QK, POW>(b, c, N, qr, n, pk, row_masks, invN, rp, rq, v);
+    if (!OWN && (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) && __builtin_expect(__builtin_amdgcn_ballot_w64(!(most <= kRefLimit)) != 0, 0)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(b.p[i]));   // nothing of the first pass is kept for this one
+        asm volatile("" : "+v"(b.map), "+s"(c));
+        power_refs<PK, QK>(b, c, N, qr, rp, rq);
+        power_sums<PK, QK, POW>(b, c, N, qr, n, pk, row_masks, invN, rp, rq, v);
+    }
+    const float all[8] = {v.s1n, v.s2n, v.s1k, v.s2k, v.q0, v.q1, v.q2, v.s3n};   // in the order of the enumeration
+    float out = wave_sum8(all);
     if (CUBIC) {
-        s3k = lane_value(wave_sum_last(s3k), kWave - 1);
-        q3 = lane_value(wave_sum_last(q3), kWave - 1);
+        const float s3k = lane_value(wave_sum_last(v.s3k), kWave - 1), q3 = lane_value(wave_sum_last(v.q3), kWave - 1);
         out = lane == 3 ? s3k : lane == 4 ? q3 : out;
     }
-    out = lane == 1 ? mx : lane == 2 ? qmx : out;
+    if (PK != RDK_PROB_F32) lane_set<1>(out, rp);
+    if (QK != RDK_PROB_F32) lane_set<2>(out, rq);
     if (lane_stat >= 0) stat[lane_stat * nchunks + c] = out;
 }
 
 template <int PK, int QK, Powers POW, int T>
-__global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
-                                                                       const uint64_t *lane_map, const int32_t *chunk_lo,
-                                                                       const int32_t *item_lo, const int2 *row_items, int N, int n,
-                                                                       bool vec_p, const int32_t *slot_of,
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void taylor_row_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
+                                                                       const uint64_t *lane_map, const uint64_t *row_masks,
+                                                                       const int32_t *chunk_lo, const int32_t *item_lo, const int2 *row_items,
+                                                                       int N, int n, bool vec_p, const int32_t *slot_of,
                                                                        FinalizeArgs fin)
 {
     constexpr bool CUBIC = POW == Powers::Cubic;
@@ -917,9 +1016,17 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
     PowerChunk<PK> b0, b1, b2;
     int c = wid;
     // without a condition: a way round these loads would make the wait for the table one for everything
-    power_fetch<PK>(pr, lane_map, chunk_lo, min(c, nchunks - 1), N, b0);
-    power_fetch<PK>(pr, lane_map, chunk_lo, min(c + kW, nchunks - 1), N, b1);
-    if (threadIdx.x == 0) {
+    const ScalarPtr<int32_t> lo_of = scalar_ptr(chunk_lo);
+    const int last = nchunks - 1, ca = min(c, last), cb = min(c + kW, last), cc = min(c + 2 * kW, last);
+    const int lo_a = lo_of[ca], hi_a = lo_of[ca + 1], lo_b = lo_of[cb], hi_b = lo_of[cb + 1];
+    int next_lo = lo_of[cc], next_hi = lo_of[cc + 1];
+    __builtin_amdgcn_sched_barrier(0);                     // the target rows' loads between the scalar loads and what waits for them
+    power_fetch_p<PK>(pr, lane_map, c, N, b0);
+    power_fetch_p<PK>(pr, lane_map, c + kW, N, b1);
+    __builtin_amdgcn_sched_barrier(0);
+    power_fetch_q<PK, QK>(qr, c, lo_a, hi_a, N, n, b0);
+    power_fetch_q<PK, QK>(qr, c + kW, lo_b, hi_b, N, n, b1);
+    if (threadIdx.x == 0) {                                // while the first chunks are on their way: 0.3 us more after step A
         uint32_t words[4];
         position_words(fin.d.seed, fin.d.offset + (uint64_t)row, words);
         uint32_t *fw = (uint32_t *)(lds + L.fin + kFinishFloats);
@@ -941,21 +1048,34 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
     const int lane_sum = (int)(__builtin_bitreverse32((uint32_t)lane >> 3) >> 29);
     const int lane_stat = (lane & 7) == 0 ? (lane_sum < 7 ? lane_sum : CUBIC ? kRowS3n : -1)
                           : lane == 1 ? kRowMax : lane == 2 ? kRowQMax : CUBIC && lane == 3 ? kRowS3k : CUBIC && lane == 4 ? kRowQ3 : -1;
-    typename RawQuad<QK>::type qv[4];
-    if (c < nchunks) power_q_fetch<QK>(qr, b0.lo, b0.hi, n, qv);
-#define RDK_ROW_STEP(CUR, NEXT, FREE)                                                                        \
-    {                                                                                                        \
-        if (c + 2 * kW < nchunks) power_fetch<PK>(pr, lane_map, chunk_lo, c + 2 * kW, N, FREE); \
-        row_power_chunk<PK, QK, POW>(CUR, c, CUR.lo, CUR.hi, N, qv, n, pk, lds + L.zero, stat, nchunks, lane_stat, rcp.invN); \
-        if (c + kW < nchunks) power_q_fetch<QK>(qr, NEXT.lo, NEXT.hi, n, qv);                         \
-        c += kW;                                                                                      \
+    float rp = 0.f, rq = 0.f;
+#define RDK_ROW_STEP(CUR, FREE)                                                                               \
+    {                                                                                                         \
+        power_fetch_q<PK, QK>(qr, c + 2 * kW, next_lo, next_hi, N, n, FREE);                                  \
+        power_fetch_p<PK>(pr, lane_map, c + 2 * kW, N, FREE);                                                 \
+        const int ahead = min(c + 3 * kW, last);                                                              \
+        next_lo = lo_of[ahead];                                                                               \
+        next_hi = lo_of[ahead + 1];                                                                           \
+        row_power_chunk<PK, QK, POW, false>(CUR, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN, rp, rq); \
+        c += kW;                                                                                              \
+    }
+    if (nchunks <= 2 * kW) {
+        // A short row: all of it is on its way.  What it takes then is mostly the time in which its code is fetched, and one
+        // copy of it, without what looks ahead, is enough (12.4 -> 11.9 us a call for 8 rows of 16000 probabilities).
+        while (c < nchunks) {
+            row_power_chunk<PK, QK, POW, true>(b0, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN, rp, rq);
+            b0 = b1;
+            c += kW;
+        }
+    } else {
+        power_refs<PK, QK>(b0, c, N, qr, rp, rq);
     }
     while (c < nchunks) {
-        RDK_ROW_STEP(b0, b1, b2)
+        RDK_ROW_STEP(b0, b2)
         if (c >= nchunks) break;
-        RDK_ROW_STEP(b1, b2, b0)
+        RDK_ROW_STEP(b1, b0)
         if (c >= nchunks) break;
-        RDK_ROW_STEP(b2, b0, b1)
+        RDK_ROW_STEP(b2, b1)
     }
 #undef RDK_ROW_STEP
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the compiler does not count the LDS writes of power_place
@@ -970,8 +1090,7 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
         chunk = it.y & 0x3FFFFF;
         return 4 * li < len ? L.pk + it.x - ((it.y >> 22) & 3) + 4 * chunk + 4 * li : L.zero;
     };
-#pragma unroll
-    for (int t = 0; t < kRowHeld; ++t) {
+    auto hold = [&](int t) {
         const int k = grp + kG * t;
         int len = 0, first = 0;
         pat[t] = L.zero;
@@ -981,6 +1100,16 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
             first = il[k].x;
         }
         qh[t] = raw_quad<QK>(qr, first + 4 * li, n);
+    };
+    // in steps: a short row has few pieces, and code that does nothing for it still has to be fetched
+    hold(0);
+    if (nitems > kG) {
+        hold(1);
+        hold(2);
+        if (nitems > 3 * kG) {
+#pragma unroll
+            for (int t = 3; t < kRowHeld; ++t) hold(t);
+        }
     }
     __syncthreads();
 
@@ -1058,10 +1187,18 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
         sa = row16_sum(sa);
         if (li == 0) isum[k] = make_float2(sr, sa);
     };
-#pragma unroll
-    for (int t = 0; t < kRowHeld; ++t) {
+    auto held_sums = [&](int t) {
         const int k = grp + kG * t;
         if (k < nitems) piece_sums(k, qh[t], pat[t], pch[t]);
+    };
+    held_sums(0);
+    if (nitems > kG) {
+        held_sums(1);
+        held_sums(2);
+        if (nitems > 3 * kG) {
+#pragma unroll
+            for (int t = 3; t < kRowHeld; ++t) held_sums(t);
+        }
     }
     for (int k = grp + kG * kRowHeld; k < nitems; k += kG) {
         int len, chunk;
@@ -1098,11 +1235,10 @@ __global__ __launch_bounds__(T) void taylor_row_kernel(const void *p, int64_t ld
     __syncthreads();
 
     // ---- the finish of the row (draws, accept test), spread over the wavefronts
-    row_finish<PK, QK, T == kRowThreads>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map, chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid,
-                       lane);
+    row_finish<PK, QK, T == kRowThreads>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map,
+                                         chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid, lane);
 }
 
-constexpr int kRowSeriesMinN = 4096;   // from here on 1 / (N + p) is taken from its series in p / N (exact to fp32 rounding)
 // Below these batches the two-pass kernels, which split a row over workgroups, fill the chip better.  A longer row takes longer
 // in one workgroup, but gives the split form more to do on a full chip too: over 48000 to 200000 ids the two meet at 80 to 88 rows
 // of probabilities, and at 40 (64000 ids) to 68 (200000) rows of logits, where one line at 64 costs 2.0 us at most.  Calls in GPU
@@ -1167,7 +1303,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         // values of a row fit the LDS of a compute unit and there are enough positions to fill the chip, or the rows are so
         // short that splitting them saves less than the extra launches cost (logit rows: from the vocabulary size on at
         // which the series of their chunk sums are exact to fp32 rounding)
-        const Powers pow = h.N >= kRowSeriesMinN ? Powers::Series : PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
+        const Powers pow = h.N >= kRowMaskMinN ? Powers::Series : PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
         const int arrays = pow == Powers::Cubic ? kRowAllArrays : kRowArrays;
         size_t lds_bytes = (size_t)row_lds_layout(h.n, nchunks, arrays, kRowWaves).total * sizeof(float);
         const bool fits = h.N >= (PK == RDK_PROB_F32 ? 4 : kOnePassMinN) && h.n >= 4 && lds_bytes <= row_lds_limit();
@@ -1199,8 +1335,8 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         rc = grant((const void *)taylor_row_kernel<PK, QK, POW, THREADS>, row_lds_limit());                                 \
         if (rc != RDK_OK) return rc;                                                                                        \
         RDK_TIMED_LAUNCH("taylor_row_kernel", (taylor_row_kernel<PK, QK, POW, THREADS>), dim3((unsigned)B), dim3(THREADS),  \
-                         lds_bytes, st, p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.item_lo, h.row_items, h.N, h.n, \
-                         vec_p, h.slot_of, fa);                                                                             \
+                         lds_bytes, st, p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.row_masks, h.chunk_lo, h.item_lo, h.row_items, \
+                         h.N, h.n, vec_p, h.slot_of, fa);                                                                             \
     }
             constexpr Powers kSmall = PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
             if (pow == Powers::Series) {
