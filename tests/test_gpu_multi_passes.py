@@ -1,0 +1,35 @@
+"""The passes of a position that rejects several candidates: the blocks that the wavefronts keep (fewer blocks than wavefronts, as
+many, one more) and the others in both directions, ends inside a block, rows at odd strides -- against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity_util import check_multi
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", ["prob", "logit"])
+@pytest.mark.parametrize("N", [9, 1024, 15 * 1024 + 1, 16 * 1024, 16 * 1024 + 3, 35 * 1024 - 1])
+def test_passes_of_several_rejections(N, kind):
+    from paper_2506_03206_amd import rdk
+    B, C, seed, offset = 6, 5, 12, 3
+    rng = np.random.default_rng(N)
+    z = (rng.normal(size=(B, N)) * 2).astype(np.float32)
+    p64 = oracle.probs_from(z, "logit")
+    p32 = p64.astype(np.float32)
+    qp32 = oracle.probs_from(z + rng.normal(size=(B, N)) * 1.5, "logit").astype(np.float32)
+    p64 = p32.astype(np.float64) if kind == "prob" else p64
+    q64 = qp32.astype(np.float64)
+    cand = np.full((B, C), N + 7, np.int32)            # never kept: every round a pass
+    cand[1, 2] = int(np.argmax(p32[1]))                # rounds, and a candidate that may be kept
+    cand[2, 3:] = -1                                   # a list that ends
+    ref = oracle.verify_multi_batch(p64, q64, C, seed, offset, cand_ids=cand)
+    wide = lambda a: torch.nn.functional.pad(torch.from_numpy(np.ascontiguousarray(a)).cuda(), (0, 1), value=float("nan"))[:, :-1]
+    o = rdk.rdk_verify_multi(wide(p32 if kind == "prob" else z), wide(qp32), C, seed, offset, kind,
+                             cand_ids=torch.from_numpy(cand).cuda())
+    check_multi(o, ref, p64, q64, seed, offset, C, min_exact=0.8)
+    even = rdk.rdk_verify_multi(torch.from_numpy(p32 if kind == "prob" else z).cuda(), torch.from_numpy(qp32).cuda(), C, seed, offset,
+                                kind, cand_ids=torch.from_numpy(cand).cuda())
+    check_multi(even, ref, p64, q64, seed, offset, C, min_exact=0.8)
