@@ -1240,19 +1240,20 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
 }
 
 // Below these batches the two-pass kernels, which split a row over workgroups, fill the chip better.  A longer row takes longer
-// in one workgroup, but gives the split form more to do on a full chip too: over 48000 to 200000 ids the two meet at 80 to 88 rows
-// of probabilities, and at 40 (64000 ids) to 68 (200000) rows of logits, where one line at 64 costs 2.0 us at most.  Calls in GPU
-// time, two passes -> one, probabilities: 64 / 88 / 128 rows of 32000 ids 17.1 -> 16.7 / 18.4 -> 17.0 / 20.3 -> 17.5 us, 64000 ids
-// 20.2 -> 22.4 / 22.9 -> 22.9 / 27.6 -> 23.6, 128256 ids 27.2 -> 31.8 / 35.2 -> 32.4 / 40.0 -> 36.5, 200000 ids 33.5 -> 39.3 /
-// 42.8 -> 42.4 / 52.3 -> 45.5.  bf16 logits, with one more launch in two passes: 48 / 64 / 88 rows of 64000 ids 27.6 -> 25.6 /
-// 29.7 -> 25.6 / 33.5 -> 25.7, 128256 ids 35.7 -> 38.4 / 39.5 -> 38.4 / 49.4 -> 38.7, 200000 ids 42.5 -> 48.0 / 46.5 -> 47.9 /
-// 56.2 -> 48.3 ...
-constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 64;
-// ... unless the rows are short: at any batch, one launch against three or four.  Probabilities, 4 / 32 / 64 rows of 16000 ids 14.1
-// -> 13.4 / 14.3 -> 14.0 / 15.0 -> 14.4, 24000 ids 14.1 -> 14.0 / 14.8 -> 14.8 / 16.4 -> 15.4, and past the line 32000 ids 13.9 ->
-// 15.4 / 14.9 -> 16.8.  bf16 logits, 4 / 32 rows of 16000 ids 21.5 -> 14.9 / 21.9 -> 15.3, 48000 ids 21.9 -> 21.3 / 23.9 -> 22.4 (fp32
-// logits 21.2 -> 21.7 / 24.5 -> 23.1), and past the line 64000 ids 22.2 -> 24.2 / 24.9 -> 25.4.
-constexpr int kRowShortN = 24 * 1024, kRowShortLogitN = 48 * 1024;
+// in one workgroup, but gives the split form more to do on a full chip too: over 64000 to 250000 ids the two meet at 72 to 88 rows
+// of probabilities and at 32 to 40 rows of logits.  Calls, two passes -> one, probabilities: 64 / 72 / 80 / 88 rows of 128256 ids
+// 25.7 -> 30.4 / 29.2 -> 30.6 / 30.6 -> 31.0 / 35.5 -> 30.4 us, 64 / 72 / 80 rows of 90000 ids 21.3 -> 24.2 / 22.1 -> 24.5 / 23.1 ->
+// 24.7, of 250000 ids 35.3 -> 43.6 / 38.2 -> 44.0 / 41.2 -> 44.6.  bf16 logits, with one more launch in two passes: 24 / 32 / 48 rows
+// of 64000 ids 24.7 -> 25.5 / 25.4 -> 25.7 / 27.4 -> 25.6, 100000 ids 25.4 -> 26.8 / 27.7 -> 26.9 / 30.7 -> 27.2, 128256 ids 27.9 ->
+// 31.6 / 30.5 -> 31.9 / 34.7 -> 32.2, 250000 ids 33.4 -> 40.8 / 36.5 -> 40.9 / 43.8 -> 41.3 (fp32 logits of 128256 ids, 32 / 64 rows,
+// 31.4 -> 33.0 / 40.3 -> 33.8).
+constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 40;
+// ... unless the rows are short: at any batch, one launch against three or four.  Probabilities, 4 / 32 / 64 rows of 28000 ids 14.8
+// -> 12.2 / 15.4 -> 13.7 / 16.3 -> 14.0 us, 32000 ids 14.2 -> 14.0 / 15.3 -> 14.7 / 17.2 -> 15.0, and past the line 40000 ids 14.6 ->
+// 15.0 / 15.4 -> 15.9.  bf16 logits, 8 rows of 52000 ids 21.7 -> 18.3, and past the
+// line, 4 / 32 rows, 56000 ids 22.5 -> 19.6 / 23.7 -> 20.6, 64000 ids 22.9 -> 23.7 / 25.4 -> 25.7 (fp32 logits: 56000 ids, 11000
+// kept, 20.7 -> 20.0, 20000 kept 21.2 -> 21.4, 64000 ids 22.1 -> 24.6).
+constexpr int kRowShortN = 32 * 1024, kRowShortLogitN = 52 * 1024;
 
 // LDS a workgroup may use (asked until it is told; the same on every device the library is built for).
 size_t row_lds_limit()
