@@ -491,13 +491,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 //   * a kept id needs its own p and q^: while the row streams by, the target values of the kept ids are scattered
 //     into LDS, chunk by chunk in slot order (4 n bytes: one value per drafter slot; the run of every chunk starts
 //     on a 16-byte boundary).
-// The softmax of a logit row is not known while it streams, so step A works relative to a reference of the wavefront's, the
-// largest logit of a chunk before (row_power_chunk): e = exp(z - reference) goes to LDS for the kept ids, and the chunk keeps
-// its reference and power sums of e, from which the sums of
-// p / (N + p) and q^ / (N + p) follow once the scale is known (x = p / N: p / (N + p) = x - x^2 + ..., N / (N + p) = 1 - x +
-// x^2 - ...): over the not-kept ids sum e and e^2, over the kept ids the same and sum q^, q^ e, q^ e^2.  Drafter logits are
-// taken relative to a reference in the same way.  (Probability rows: e = p, all references zero.)  Which
-// powers: see Powers.
+// The softmax of a logit row is not known while it streams, so step A works relative to the largest logit of each chunk:
+// e = exp(z - chunk maximum) goes to LDS for the kept ids, and the chunk keeps its maximum and power sums of e, from which the
+// sums of p / (N + p) and q^ / (N + p) follow once the scale is known (x = p / N: p / (N + p) = x - x^2 + ..., N / (N + p) = 1 -
+// x + x^2 - ...): over the not-kept ids sum e and e^2, over the kept ids the same and sum q^, q^ e, q^ e^2.  Drafter logits are
+// taken relative to the largest of the chunk's run in the same way.  (Probability rows: e = p, no maxima.)  Which powers: see
+// Powers.
 // Step A streams p, guided by the kernel's lane map (L2-resident, shared by all rows), a wavefront per chunk.  The chunk's
 // run of drafter values is fetched alongside (one contiguous piece of the drafter row); the wavefront reads its own
 // scattered target values back in slot order and adds up the kept ids' sums -- those of the row constants cost no pass of
@@ -509,12 +508,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 // in their order.  HBM traffic: p and q once.
 // What bounds it, measured on MI355X: probability rows, HBM while the row streams and then, with one workgroup on a unit,
 // about 10 us in the steps after it (N = 128256, n = 32064, 256 rows: 38.6 us a call; N = 151936, n = 16384, 1024 rows: 124.8
-// us, 5.5 TB/s); bf16 logit rows, the vector unit in step A (same shape, half the bytes: 92.5 us, 3.8 TB/s; 184 before the loads
+// us, 5.5 TB/s); bf16 logit rows, the vector unit in step A (same shape, half the bytes: 96.3 us, 3.6 TB/s; 184 before the loads
 // stayed raw in registers -- a conversion next to a load waits for it, so nothing was ever in flight -- and before the
 // scatter became a block on the execution mask, eight sums were reduced together, and two workgroups shared a unit; 125.7
-// before the largest logit of a chunk was done without, the masks of the scatter came by scalar loads, and the kept ids' sums
-// took a slot a lane: 395 vector instructions a chunk of 1024 ids then, 250 now).  The sums of a chunk on the matrix units
-// instead (seven products of 32 cycles) were 10 us slower: the products hold the vector unit's issue.
+// before the masks of the scatter came by scalar loads, the kept ids' sums took a slot a lane, and both maxima of a chunk were
+// found together: 395 vector instructions per 1024 ids in all then, 301 now).  The sums of a chunk on the matrix units instead
+// (seven products of 32 cycles) were 10 us slower: the products hold the vector unit's issue.
+// A reference that the chunks of a wavefront share until a weight leaves its range does without the maxima (17 instructions, 4
+// us), but weights of up to 256 are then rounded like any others where the largest of a chunk is exactly 1: alpha of rows whose
+// mass lies in a few ids was 5 to 8 % further from 64-bit sums on average.
 // q' of Eq. 3 re-computed from the row constants (the finish step needs the two blocks of the crossings).
 template <int PK, int QK>
 struct QpTaylor {
@@ -667,19 +669,26 @@ __device__ __forceinline__ float raw_max3(float a, float b, float c)
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
-// largest value of the 64 lanes, in a scalar register
-__device__ __forceinline__ float wave_max_scalar(float v)
+// Largest values of two registers over the 64 lanes, in scalar registers: the halves of the wavefront take one each.  The lane
+// exchanges are part of the comparisons (two wait states before each: what it reads through another lane was just written).
+__device__ __forceinline__ void wave_max2(float a, float b, float &ma, float &mb)
 {
-    v = raw_max(v, dpp_move<0xB1>(v));
-    v = raw_max(v, dpp_move<0x4E>(v));
-    v = raw_max(v, dpp_move<0x141>(v));
-    v = raw_max(v, dpp_move<0x140>(v));
     typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    float v = raw_max(__uint_as_float(r.x), __uint_as_float(r.y));
+    r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = raw_max(__uint_as_float(r.x), __uint_as_float(r.y));
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = raw_max(__uint_as_float(r.x), __uint_as_float(r.y));
-    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+    asm("s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+        "s_nop 1\n\t"
+        "v_max_f32_dpp %0, %0, %0 row_mirror row_mask:0xf bank_mask:0xf"
+        : "+v"(v));
+    ma = lane_value(v, 0);
+    mb = lane_value(v, 32);
 }
 
 // Eight sums over the 64 lanes at once: lane l gets the total of v[bit reversal of l / 8].  Values are put side by side
@@ -830,26 +839,34 @@ __device__ __forceinline__ void power_values(const PowerChunk<PK> &b, int c, int
     }
 }
 
-// The references of a chunk's weights from its largest logits.
+// The largest logits of a chunk and of its run of drafter values, which its weights are taken relative to: the largest weight of
+// a chunk is exactly 1, and how far the chunk lies below the row comes in with soft_exp_fine.
 template <int PK, int QK>
-__device__ __forceinline__ void power_refs(const PowerChunk<PK> &b, int c, int N, const void *qr, float &rp, float &rq)
+__device__ __forceinline__ void power_refs(const PowerChunk<PK> &b, const float (&z)[4][4], const void *qr, float &rp, float &rq)
 {
     float zm = kLowest, qm = kLowest;
     if (PK != RDK_PROB_F32) {
-        float z[4][4];
-        power_values<PK>(b, c, N, z);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) zm = raw_max3(raw_max3(zm, z[i][0], z[i][1]), z[i][2], z[i][3]);
+        float zn = raw_max3(z[1][3], z[2][0], z[2][1]);
+        zm = raw_max3(z[0][0], z[0][1], z[0][2]);
+        zm = raw_max3(zm, z[0][3], z[1][0]);
+        zn = raw_max3(zn, z[2][2], z[2][3]);
+        zm = raw_max3(zm, z[1][1], z[1][2]);
+        zn = raw_max3(zn, z[3][0], z[3][1]);
+        zm = raw_max3(zm, z[3][2], z[3][3]);
+        zm = raw_max3(zm, zn, kLowest);
     }
     if (QK != RDK_PROB_F32) {
+        auto take = [&](int r) { qm = lane_id() < b.hi - b.lo - kWave * r ? raw_max(qm, power_q_value<QK>(b.q[r])) : qm; };
+        take(0);
+        take(1);
+        if (b.hi - b.lo > 2 * kWave) {
 #pragma unroll
-        for (int r = 0; r < kRowAhead; ++r)
-            qm = lane_id() < b.hi - b.lo - kWave * r ? raw_max(qm, power_q_value<QK>(b.q[r])) : qm;
+            for (int r = 2; r < kRowAhead; ++r) take(r);
+        }
         for (int s = b.lo + kWave * kRowAhead + lane_id(); __builtin_expect(s < b.hi, 0); s += kWave)
             qm = raw_max(qm, power_q_value<QK>(power_q_raw<QK>(qr, (uint32_t)s * (QK == RDK_LOGIT_BF16 ? 2u : 4u))));
     }
-    if (PK != RDK_PROB_F32) rp = wave_max_scalar(zm);
-    if (QK != RDK_PROB_F32) rq = wave_max_scalar(qm);
+    wave_max2(zm, qm, rp, rq);
 }
 
 // The power sums of a chunk, per lane (n: ids that are not kept, k: kept ones).
@@ -857,11 +874,10 @@ struct PowerSums {
     float s1n, s2n, s3n, s1k, s2k, s3k, q0, q1, q2, q3;
 };
 
-// Forms them, e of the kept ids to LDS.  Returns what shows a weight beyond its range.
+// Forms them, e of the kept ids to LDS.
 template <int PK, int QK, Powers POW>
-__device__ __forceinline__ float power_sums(const PowerChunk<PK> &b, int c, int N, const void *qr, int n, float *pk,
-                                            const uint64_t *row_masks, float invN, float rp, float rq,
-                                            PowerSums &v)
+__device__ __forceinline__ void power_sums(const PowerChunk<PK> &b, const float (&z)[4][4], int c, const void *qr, int n, float *pk,
+                                           const uint64_t *row_masks, float invN, float rp, float rq, PowerSums &v)
 {
     constexpr bool CUBIC = POW == Powers::Cubic;
     const int lane = lane_id(), lo = b.lo, hi = b.hi;
@@ -873,8 +889,6 @@ __device__ __forceinline__ float power_sums(const PowerChunk<PK> &b, int c, int 
 #pragma unroll
         for (int i = 0; i < 16; ++i) kept[i] = mk[i];
     }
-    float z[4][4];
-    power_values<PK>(b, c, N, z);
     uint32_t bits = __builtin_bitreverse32((uint32_t)b.map);   // the bit of the first id on top
     v = PowerSums{};
 #pragma unroll
@@ -934,38 +948,20 @@ __device__ __forceinline__ float power_sums(const PowerChunk<PK> &b, int c, int 
 #pragma unroll
         for (int j = 0; j < 4; ++j) round(r + j, more[j]);
     }
-    const float q2 = QK == RDK_PROB_F32 ? 0.f : v.q0 * v.q0;
-    return PK == RDK_PROB_F32 ? q2 : q2 + (v.s2n + v.s2k);
 }
 
 // Step A for one chunk: statistics to `stat` (arrays of nchunks floats).  lane_stat: which of them the lane writes (-1: none).
-//
-// A wavefront takes the weights of logits relative to the largest of its first chunk, of target and drafter rows alike,
-// and looks for new references only when a lane's sums show weights well beyond one (or not a number): then the chunk is done
-// again.  The limit lets weights up to 256 pass, exponents up to 8, so the exponents of the values that make up a row's mass stay
-// small and are rounded as finely as below the maximum (resid_mass of 512 rows against 64-bit sums, logits of deviation 2 and
-// 6: 4.4e-8 and 7.6e-8 of it on average, 4.1e-8 and 8.3e-8 with the largest of every chunk); and below the reference nothing is
-// lost that the factor between chunk and row would not take away too.  With a limit of 80 every second wavefront has a chunk to do
-// again (1024 bf16 rows of 151936 ids: 4 us).
-// OWN: the chunk's own references, for rows so short that a wavefront has no use for them after.
-constexpr float kRefLimit = 65536.f;
-template <int PK, int QK, Powers POW, bool OWN>
-__device__ __forceinline__ void row_power_chunk(PowerChunk<PK> &b, int c, int N, const void *qr, int n, float *pk,
-                                                const uint64_t *row_masks, float *stat, int nchunks, int lane_stat, float invN,
-                                                float &rp, float &rq)
+template <int PK, int QK, Powers POW>
+__device__ __forceinline__ void row_power_chunk(const PowerChunk<PK> &b, int c, int N, const void *qr, int n, float *pk,
+                                                const uint64_t *row_masks, float *stat, int nchunks, int lane_stat, float invN)
 {
     constexpr bool CUBIC = POW == Powers::Cubic;
     const int lane = lane_id();
+    float z[4][4], rp = 0.f, rq = 0.f;
+    power_values<PK>(b, c, N, z);
+    if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) power_refs<PK, QK>(b, z, qr, rp, rq);
     PowerSums v;
-    if (OWN) power_refs<PK, QK>(b, c, N, qr, rp, rq);
-    const float most = power_sums<PK, QK, POW>(b, c, N, qr, n, pk, row_masks, invN, rp, rq, v);
-    if (!OWN && (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) && __builtin_expect(__builtin_amdgcn_ballot_w64(!(most <= kRefLimit)) != 0, 0)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(b.p[i]));   // nothing of the first pass is kept for this one
-        asm volatile("" : "+v"(b.map), "+s"(c));
-        power_refs<PK, QK>(b, c, N, qr, rp, rq);
-        power_sums<PK, QK, POW>(b, c, N, qr, n, pk, row_masks, invN, rp, rq, v);
-    }
+    power_sums<PK, QK, POW>(b, z, c, qr, n, pk, row_masks, invN, rp, rq, v);
     const float all[8] = {v.s1n, v.s2n, v.s1k, v.s2k, v.q0, v.q1, v.q2, v.s3n};   // in the order of the enumeration
     float out = wave_sum8(all);
     if (CUBIC) {
@@ -1048,7 +1044,6 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
     const int lane_sum = (int)(__builtin_bitreverse32((uint32_t)lane >> 3) >> 29);
     const int lane_stat = (lane & 7) == 0 ? (lane_sum < 7 ? lane_sum : CUBIC ? kRowS3n : -1)
                           : lane == 1 ? kRowMax : lane == 2 ? kRowQMax : CUBIC && lane == 3 ? kRowS3k : CUBIC && lane == 4 ? kRowQ3 : -1;
-    float rp = 0.f, rq = 0.f;
 #define RDK_ROW_STEP(CUR, FREE)                                                                               \
     {                                                                                                         \
         power_fetch_q<PK, QK>(qr, c + 2 * kW, next_lo, next_hi, N, n, FREE);                                  \
@@ -1056,19 +1051,17 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
         const int ahead = min(c + 3 * kW, last);                                                              \
         next_lo = lo_of[ahead];                                                                               \
         next_hi = lo_of[ahead + 1];                                                                           \
-        row_power_chunk<PK, QK, POW, false>(CUR, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN, rp, rq); \
+        row_power_chunk<PK, QK, POW>(CUR, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN);        \
         c += kW;                                                                                              \
     }
     if (nchunks <= 2 * kW) {
         // A short row: all of it is on its way.  What it takes then is mostly the time in which its code is fetched, and one
         // copy of it, without what looks ahead, is enough (12.4 -> 11.9 us a call for 8 rows of 16000 probabilities).
         while (c < nchunks) {
-            row_power_chunk<PK, QK, POW, true>(b0, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN, rp, rq);
+            row_power_chunk<PK, QK, POW>(b0, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN);
             b0 = b1;
             c += kW;
         }
-    } else {
-        power_refs<PK, QK>(b0, c, N, qr, rp, rq);
     }
     while (c < nchunks) {
         RDK_ROW_STEP(b0, b2)
@@ -1119,8 +1112,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
         pm = raw_max(pm, stat[kRowMax * nchunks + cc]);
         qm = raw_max(qm, stat[kRowQMax * nchunks + cc]);
     }
-    pm = PK == RDK_PROB_F32 ? 0.f : wave_max_scalar(pm);
-    qm = QK == RDK_PROB_F32 ? 0.f : wave_max_scalar(qm);
+    wave_max2(pm, qm, pm, qm);
+    if (PK == RDK_PROB_F32) pm = 0.f;
+    if (QK == RDK_PROB_F32) qm = 0.f;
     float t7[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum e, e^2, e^3 over all ids; sum q^ e^k, k = 0..3
     for (int cc = threadIdx.x; cc < nchunks; cc += T) {
         float *sc = stat + cc;
@@ -1243,16 +1237,16 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
 // in one workgroup, but gives the split form more to do on a full chip too: over 64000 to 250000 ids the two meet at 72 to 88 rows
 // of probabilities and at 32 to 40 rows of logits.  Calls, two passes -> one, probabilities: 64 / 72 / 80 / 88 rows of 128256 ids
 // 25.7 -> 30.4 / 29.2 -> 30.6 / 30.6 -> 31.0 / 35.5 -> 30.4 us, 64 / 72 / 80 rows of 90000 ids 21.3 -> 24.2 / 22.1 -> 24.5 / 23.1 ->
-// 24.7, of 250000 ids 35.3 -> 43.6 / 38.2 -> 44.0 / 41.2 -> 44.6.  bf16 logits, with one more launch in two passes: 24 / 32 / 48 rows
-// of 64000 ids 24.7 -> 25.5 / 25.4 -> 25.7 / 27.4 -> 25.6, 100000 ids 25.4 -> 26.8 / 27.7 -> 26.9 / 30.7 -> 27.2, 128256 ids 27.9 ->
-// 31.6 / 30.5 -> 31.9 / 34.7 -> 32.2, 250000 ids 33.4 -> 40.8 / 36.5 -> 40.9 / 43.8 -> 41.3 (fp32 logits of 128256 ids, 32 / 64 rows,
-// 31.4 -> 33.0 / 40.3 -> 33.8).
+// 24.7, of 250000 ids 35.3 -> 43.6 / 38.2 -> 44.0 / 41.2 -> 44.6.  bf16 logits, with one more launch in two passes: 24 / 32 / 40 rows
+// of 100000 ids 28.1 -> 28.7 / 29.9 -> 29.0 / 30.4 -> 29.0, 32 / 40 / 64 rows of 128256 ids 30.7 -> 33.3 / 34.3 -> 33.1 / 40.6 -> 33.6,
+// 32 / 40 rows of 250000 ids 39.2 -> 44.3 / 46.1 -> 44.5 (fp32 logits of 128256 ids, 32 / 40 rows, 33.5 -> 33.9 / 36.3 -> 33.6, of
+// 250000 ids, 40 rows, 47.0 -> 47.9).
 constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 40;
 // ... unless the rows are short: at any batch, one launch against three or four.  Probabilities, 4 / 32 / 64 rows of 28000 ids 14.8
 // -> 12.2 / 15.4 -> 13.7 / 16.3 -> 14.0 us, 32000 ids 14.2 -> 14.0 / 15.3 -> 14.7 / 17.2 -> 15.0, and past the line 40000 ids 14.6 ->
-// 15.0 / 15.4 -> 15.9.  bf16 logits, 8 rows of 52000 ids 21.7 -> 18.3, and past the
-// line, 4 / 32 rows, 56000 ids 22.5 -> 19.6 / 23.7 -> 20.6, 64000 ids 22.9 -> 23.7 / 25.4 -> 25.7 (fp32 logits: 56000 ids, 11000
-// kept, 20.7 -> 20.0, 20000 kept 21.2 -> 21.4, 64000 ids 22.1 -> 24.6).
+// 15.0 / 15.4 -> 15.9.  bf16 logits, 8 rows of 52000 ids 24.0 -> 20.7, and past the line, 4 / 32 rows, 56000 ids 22.8 -> 20.7 / 25.8
+// -> 21.4, 64000 ids 22.7 -> 22.7 / 25.5 -> 23.1 (fp32 logits: 56000 ids, 14000 kept, 22.6 -> 21.7, 20000 kept 24.2 -> 24.5, 64000
+// ids 22.4 -> 22.9).
 constexpr int kRowShortN = 32 * 1024, kRowShortLogitN = 52 * 1024;
 
 // LDS a workgroup may use (asked until it is told; the same on every device the library is built for).
