@@ -1,5 +1,5 @@
 // Alg. 1, step 2 with the top-k sparse kernel, P positions at a time, gathers served out of LDS: the form for larger batches of
-// drafter rows of up to 20288 slots (P = 4 up to 10144, else 2).
+// drafter rows of up to 20320 slots (P = 4 up to 10144, else 2).
 //
 // A workgroup holds the drafter rows of P positions side by side in LDS and streams a table past them that is laid out for it: a
 // row of the table is 64 consecutive target ids, one per lane, and a step is one entry of every lane, so a lane reads its own

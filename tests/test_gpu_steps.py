@@ -1,4 +1,4 @@
-"""The sparse product several positions at a time out of LDS (larger batches, drafter rows of up to 20288 slots) where it can go
+"""The sparse product several positions at a time out of LDS (larger batches, drafter rows of up to 20320 slots) where it can go
 wrong: batches that are no multiple of the positions held together, the edges of the row lengths at which their number changes,
 neighbour counts around the eight entries of a unit, stretches of kept ids, the last row of ids, rows at odd strides."""
 import numpy as np
@@ -27,8 +27,10 @@ SHAPES = [  # N, n, k, gamma, additional sequences, kept ids
     (6000, 4, 4, 1, 0, "spread"),          # the shortest row
     (12000, 10144, 16, 1, 1, "spread"),    # four positions together at most
     (12000, 10145, 8, 1, 0, "spread"),     # two
-    (30000, 20288, 64, 1, 0, "last"),      # the longest row, the most neighbours
-    (30000, 20289, 16, 1, 0, "spread"),    # one slot too many
+    (30000, 20288, 64, 1, 0, "last"),      # a row that ends with a round of banks
+    (30000, 20289, 16, 1, 0, "spread"),    # one slot in the last round of banks
+    (30000, 20320, 64, 1, 0, "last"),      # the longest row, the most neighbours
+    (30000, 20321, 16, 1, 0, "spread"),    # one slot too many: no table, one of the other forms
 ]
 
 
@@ -45,6 +47,9 @@ def test_steps_against_oracle(shape, kind):
     idx, w, sw = idx.astype(np.int32), w.astype(np.float32), sw.astype(np.float32)
     d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
     kern = rdk.rdk_build_kernel(N, d(kept), rdk.SPARSE_TOPK, k=k, sparse=(d(idx), d(w), d(sw)))
+    # a kernel that has this form holds its table beside the pairs
+    table, pairs = 48 * ((N + 255) // 256 * 256) * ((k + 7) // 8 + 0.5), (N - n) * ((k + 15) // 16 * 16) * 8
+    assert (kern.storage.numel() > pairs + table) == (n <= 20320)
     g = torch.Generator(device="cuda")
     g.manual_seed(N)
     wide = lambda x: torch.nn.functional.pad(x, (0, 1), value=float("nan"))[:, :-1]   # an odd row stride
