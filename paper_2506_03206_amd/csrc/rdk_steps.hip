@@ -13,8 +13,9 @@
 // (counters, N = 151936, n = 16384, k = 32, 1024 positions: 0.31-0.33 lines a clock, vector ALU 53 % and LDS 40 % busy), at P = 4
 // the vector ALU is 70 % busy, LDS 45 %.  How far ahead the table is requested hardly matters (one to six units: within 8 %).
 // Measured, position-minor -> this, probabilities / bf16 logits, whole fused calls in us: N = 151936, n = 16384, k = 32, 1024
-// positions 863 / 916 -> 684 / 688; N = 100000, n = 10000, k = 32, 512 positions 307 / 308 -> 177 / 171; N = 32000, n = 8000, k = 16,
-// 1024 positions 122 / 138 -> 87 / 89 and 128 positions 34 / 43 -> 25 / 30; N = 16000, n = 4000, 256 positions 29 / 43 -> 23 / 29.
+// positions 866 / 921 -> 697 / 709 (bf16 702 to 724 on other rows and kept ids); N = 100000, n = 10000, k = 32, 512 positions 302 /
+// 308 -> 169 / 172; N = 32000, n = 8000, k = 16, 1024 positions 119 / 139 -> 85 / 88 and 128 positions 33 / 43 -> 25 / 30; N =
+// 16000, n = 4000, 256 positions 28 / 43 -> 23 / 30.
 // Larger rows would have to come to LDS in windows that take turns, with sums kept between them: measured at n = 16384 with four
 // positions (820-1060 us) and at n = 32064 with two (147 us against 122), the refills, the entries that do not divide evenly
 // over the windows and the kept sums cost more than the lines saved.
@@ -599,11 +600,20 @@ rdk_status_t launch_step_table(const KernelHandle &h, hipStream_t st)
 
 // The table is read once per P positions here, once per position in the product out of LDS one row at a time (rdk_slab.hip), which
 // reads it in 16 neighbours and 8 bytes each, and finishes a row in the same launch where one workgroup holds it.  The line to
-// that form lies at 180 MB of its table reads (fused, probabilities / bf16 logits, one row at a time -> this, us): N = 100000,
-// n = 10000, 16 positions (175 MB) 21.2 / 28.1 -> 22.4 / 28.5; N = 16000, n = 4000, 128 positions (187 MB) 22.4 / 28.7 -> 18.3 / 25.6;
-// N = 64000, n = 16000, 32 positions (187 MB) 24.2 / 30.5 -> 23.4 / 27.4.  A row that is finished in place stays there while every
-// row has a compute unit of its own: N = 8000, n = 2000, 256 positions (187 MB) 18.6 / 21.2 -> 20.5 / 29.0, 384 positions 33.7 /
-// 38.0 -> 22.9 / 30.4.  Beyond 288 MB (where the position-minor form is the other one) this is never the slower.
+// that form lies at 180 MiB of its table reads.  Fused calls, one row at a time -> this, probabilities / bf16 logits, us:
+//   above it  N = 32000, n = 8000, 63 positions (184 MiB) 21.9 / 27.9 -> 19.7 / 24.8; N = 16000, n = 4000, 128 (187) 20.9 / 27.2 ->
+//             18.3 / 24.6; N = 64000, n = 16000, 32 (187) 23.3 / 29.4 -> 22.9 / 26.2; N = 250000, n = 20000, k = 8, 7 (196) 44.1 /
+//             51.1 -> 22.5 / 27.9; N = 100000, n = 20000, 24 (234) 29.3 / 35.2 -> 29.4 / 34.6; N = 100000, n = 10000, 20 (219) 24.8 /
+//             31.2 -> 25.3 / 31.2, the one that loses of fifteen shapes measured
+//   below it  N = 32000, n = 8000, 32 / 40 / 48 positions (93 / 117 / 140 MiB) 16.5 -> 18.7 / 18.0 -> 18.9 / 20.4 -> 19.1 (bf16 22.2 ->
+//             24.2 / 24.3 -> 24.5 / 26.2 -> 24.5); N = 64000, n = 16000, 24 (140) 22.0 / 28.0 -> 23.2 / 27.4; N = 100000, n = 10000, 12 /
+//             16 (131 / 175) 26.4 -> 20.8 / 21.1 -> 22.2; N = 250000, n = 10144, 6 (175) 40.7 / 46.5 -> 25.6 / 31.7
+// What decides is how the positions of a batch divide over the compute units in either form more than the bytes: between 120 MiB
+// and the line this form is already the faster one for most shapes, above the line for all but that one.  A row that is finished in
+// place stays there while every row has a compute unit of its own, which pays for logits: N = 8000, n = 2000, 256 positions (187
+// MiB) 17.8 / 19.8 -> 17.5 / 24.4, N = 12000, n = 3000, 256 positions (281 MiB) 24.2 / 24.8 -> 20.5 / 26.9; with more rows than
+// units, N = 4000, n = 1000, 512 positions (187 MiB), 23.2 / 26.8 -> 19.2 / 25.8.  Beyond 288 MiB (where the position-minor form is
+// the other one) this is never the slower.
 bool steps_taken(const KernelHandle &h, int32_t B)
 {
     if (h.steps.P == 0 || (int64_t)B * (h.N - h.n) * h.kk * 8 <= (int64_t)180 << 20) return false;
