@@ -438,10 +438,12 @@ rdk_status_t launch_kind(int kind, const SlabPlan &p, const SlabArgs &a, const F
 }  // namespace
 
 // The table is read once per position here and once per 32 positions in the position-minor form, which pays with a
-// transposition, a finish and (logits) up to two statistics passes in launches of their own.  The line lies at 288 MB of
-// table reads per call: N = 4000, k = 16, 512 positions (196 MB) 23.0 us against 26.3, N = 16000, 128 positions (196 MB) 22.2
-// against 25.8, N = 128256, 16 positions (197 MB) 27 against 36; N = 8000, 512 positions (393 MB) 32.3 against 30.6.
-// Below 288 MB a byte offset into the table fits 32 bits.
+// transposition, a finish and (logits) up to two statistics passes in launches of their own.  The line lies at 288 MiB of
+// table reads per call.  Kernels with a step table leave this form earlier (rdk_steps.hip), so it parts the two for longer drafter
+// rows; fused calls, this -> position-minor, probabilities / bf16 logits, us: N = 128256, n = 32064, 16 / 24 positions (187 / 281
+// MiB) 25.9 -> 34.0 / 34.8 -> 35.3 (bf16 32.2 -> 45.1 / 40.1 -> 46.7); N = 60000, n = 24000, 48 / 64 (210 / 281) 29.9 -> 32.9 / 33.0 ->
+// 33.3 (bf16 35.3 -> 45.5 / 38.3 -> 46.1); N = 128256, n = 25000, k = 32, 8 / 11 (201 / 277) 27.3 -> 41.7 / 46.7 -> 41.9 (bf16 32.5 ->
+// 54.4 / 52.6 -> 55.1).  Below 288 MiB a byte offset into the table fits 32 bits.
 bool slab_taken(const KernelHandle &h, int32_t B)
 {
     if (h.n > kQuads * 4 * kSlabThreads || slab_lds_bytes(h.n, 0) > kLdsBytes) return false;

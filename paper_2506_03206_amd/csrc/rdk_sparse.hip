@@ -404,9 +404,10 @@ __global__ __launch_bounds__(kThreads) void sparse_product_kernel(SparseArgs a, 
 // Where the finish finds the drafter weight of a slot: in the position-minor copy (SlabColumn), or in the drafter row itself, with
 // the row's maximum and 1 / mass out of the partials that the transposition worked with (PartialColumn) or as the product out
 // of LDS left them (RowColumn).  In the copy every gather touches a line of its own for four useful bytes; a bf16 row of up to
-// kShortRow slots is at most 256 lines, which the vector L1 holds (whole calls, copy -> row: N = 151936, n = 16384, k = 32, 1024
-// positions 923.6 -> 914.9 us, 700: 675.9 -> 643.8; N = 8000, n = 2000, 700 positions 82.3 -> 69.8).  Rows of 128 KB are cold
-// where the copy is in L2 (N = 128256, n = 32064, fp32: 122.7 -> 123.6, draft draw 95.8 -> 96.8).
+// kShortRow slots is at most 256 lines, which the vector L1 holds.  Batches that come to PartialColumn are thousands of positions
+// of a vocabulary with less than 128 KB of pairs, for which there is no step table (whole calls, copy -> row: N = 1024, n = 256, k =
+// 8, 3200 / 8192 positions 62.7 -> 57.4 / 118.9 -> 113.2 us; N = 1500, n = 600, k = 16, 3000 / 6000 positions 77.5 -> 68.6 / 120.5
+// -> 104.6).  Rows of 128 KB are cold where the copy is in L2 (N = 128256, n = 32064, fp32: 122.7 -> 123.6, draft draw 95.8 -> 96.8).
 struct SlabColumn {
     const float *qT;
     const float *zpart;

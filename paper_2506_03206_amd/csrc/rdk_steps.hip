@@ -604,7 +604,7 @@ rdk_status_t launch_step_table(const KernelHandle &h, hipStream_t st)
 //   above it  N = 32000, n = 8000, 63 positions (184 MiB) 21.9 / 27.9 -> 19.7 / 24.8; N = 16000, n = 4000, 128 (187) 20.9 / 27.2 ->
 //             18.3 / 24.6; N = 64000, n = 16000, 32 (187) 23.3 / 29.4 -> 22.9 / 26.2; N = 250000, n = 20000, k = 8, 7 (196) 44.1 /
 //             51.1 -> 22.5 / 27.9; N = 100000, n = 20000, 24 (234) 29.3 / 35.2 -> 29.4 / 34.6; N = 100000, n = 10000, 20 (219) 24.8 /
-//             31.2 -> 25.3 / 31.2, the one that loses of fifteen shapes measured
+//             31.2 -> 25.3 / 31.2, the one that loses of seventeen measured there
 //   below it  N = 32000, n = 8000, 32 / 40 / 48 positions (93 / 117 / 140 MiB) 16.5 -> 18.7 / 18.0 -> 18.9 / 20.4 -> 19.1 (bf16 22.2 ->
 //             24.2 / 24.3 -> 24.5 / 26.2 -> 24.5); N = 64000, n = 16000, 24 (140) 22.0 / 28.0 -> 23.2 / 27.4; N = 100000, n = 10000, 12 /
 //             16 (131 / 175) 26.4 -> 20.8 / 21.1 -> 22.2; N = 250000, n = 10144, 6 (175) 40.7 / 46.5 -> 25.6 / 31.7
