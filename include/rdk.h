@@ -100,7 +100,12 @@ typedef struct {
     int32_t validate;          /* != 0: check kept_ids (and a supplied kernel) on the device, then synchronise */
 } rdk_kernel_desc_t;
 
-/* Bytes of device storage the finished kernel occupies, and of scratch the build needs. */
+/*
+ * Bytes of device storage the finished kernel occupies, and of scratch the build needs.  A top-k kernel takes 8 bytes per
+ * neighbour (k rounded up to 16) and, with n <= 20320 and at least 128 KB of those, holds them a second time in the order that
+ * larger batches read them in: about 48 N (ceil(k / 8) + 1/2) bytes more, whichever batches it is used for (N = 151936, n = 16384,
+ * k = 32: 34.7 MB and 32.8 MB; N = 32000, n = 8000, k = 16: 3.1 MB and 3.8 MB).
+ */
 rdk_status_t rdk_kernel_storage_bytes(const rdk_kernel_desc_t *desc, size_t *storage_bytes,
                                       size_t *build_workspace_bytes);
 
