@@ -876,19 +876,13 @@ struct PowerSums {
 
 // Forms them, e of the kept ids to LDS.
 template <int PK, int QK, Powers POW>
-__device__ __forceinline__ void power_sums(const PowerChunk<PK> &b, const float (&z)[4][4], int c, const void *qr, int n, float *pk,
-                                           const uint64_t *row_masks, float invN, float rp, float rq, PowerSums &v)
+__device__ __forceinline__ void power_sums(const PowerChunk<PK> &b, const float (&z)[4][4], const uint64_t (&kept)[16], int c, const void *qr,
+                                           int n, float *pk, float invN, float rp, float rq, PowerSums &v)
 {
     constexpr bool CUBIC = POW == Powers::Cubic;
     const int lane = lane_id(), lo = b.lo, hi = b.hi;
     const int run = row_run_start(lo, c);
     const uint32_t first = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)pk + 4 * run;
-    uint64_t kept[16];
-    if (POW == Powers::Series) {
-        const ScalarPtr<uint64_t> mk = scalar_ptr(row_masks) + 16 * c;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) kept[i] = mk[i];
-    }
     uint32_t bits = __builtin_bitreverse32((uint32_t)b.map);   // the bit of the first id on top
     v = PowerSums{};
 #pragma unroll
@@ -957,11 +951,17 @@ __device__ __forceinline__ void row_power_chunk(const PowerChunk<PK> &b, int c, 
 {
     constexpr bool CUBIC = POW == Powers::Cubic;
     const int lane = lane_id();
+    uint64_t kept[16];
+    if (POW == Powers::Series) {                       // asked for first: on their way while the maxima are found
+        const ScalarPtr<uint64_t> mk = scalar_ptr(row_masks) + 16 * c;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) kept[i] = mk[i];
+    }
     float z[4][4], rp = 0.f, rq = 0.f;
     power_values<PK>(b, c, N, z);
     if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) power_refs<PK, QK>(b, z, qr, rp, rq);
     PowerSums v;
-    power_sums<PK, QK, POW>(b, z, c, qr, n, pk, row_masks, invN, rp, rq, v);
+    power_sums<PK, QK, POW>(b, z, kept, c, qr, n, pk, invN, rp, rq, v);
     const float all[8] = {v.s1n, v.s2n, v.s1k, v.s2k, v.q0, v.q1, v.q2, v.s3n};   // in the order of the enumeration
     float out = wave_sum8(all);
     if (CUBIC) {
