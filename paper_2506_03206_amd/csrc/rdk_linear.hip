@@ -1235,12 +1235,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
 
 // Below these batches the two-pass kernels, which split a row over workgroups, fill the chip better.  A longer row takes longer
 // in one workgroup, but gives the split form more to do on a full chip too: over 64000 to 250000 ids the two meet at 72 to 88 rows
-// of probabilities and at 32 to 40 rows of logits.  Calls, two passes -> one, probabilities: 64 / 72 / 80 / 88 rows of 128256 ids
+// of probabilities, and of logits at 4 rows of 64000 ids, 28 of 100000, 36 of 128256 and 38 to 50 of 250000.  Calls, two passes -> one, probabilities: 64 / 72 / 80 / 88 rows of 128256 ids
 // 25.7 -> 30.4 / 29.2 -> 30.6 / 30.6 -> 31.0 / 35.5 -> 30.4 us, 64 / 72 / 80 rows of 90000 ids 21.3 -> 24.2 / 22.1 -> 24.5 / 23.1 ->
 // 24.7, of 250000 ids 35.3 -> 43.6 / 38.2 -> 44.0 / 41.2 -> 44.6.  bf16 logits, with one more launch in two passes: 24 / 32 / 40 rows
 // of 100000 ids 28.1 -> 28.7 / 29.9 -> 29.0 / 30.4 -> 29.0, 32 / 40 / 64 rows of 128256 ids 30.7 -> 33.3 / 34.3 -> 33.1 / 40.6 -> 33.6,
 // 32 / 40 rows of 250000 ids 39.2 -> 44.3 / 46.1 -> 44.5 (fp32 logits of 128256 ids, 32 / 40 rows, 33.5 -> 33.9 / 36.3 -> 33.6, of
-// 250000 ids, 40 rows, 47.0 -> 47.9).
+// 250000 ids, 40 / 48 rows, 47.0 -> 47.9 / 47.8 -> 48.4).
 constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 40;
 // ... unless the rows are short: at any batch, one launch against three or four.  Probabilities, 4 / 32 / 64 rows of 28000 ids 14.8
 // -> 12.2 / 15.4 -> 13.7 / 16.3 -> 14.0 us, 32000 ids 14.2 -> 14.0 / 15.3 -> 14.7 / 17.2 -> 15.0, and past the line 40000 ids 14.6 ->
