@@ -177,23 +177,49 @@ __global__ void prep_a_records_kernel(const void *q, int64_t ldq, const SoftStat
 // One wavefront per (128 target ids, 64 positions, one split of the slot blocks), one wavefront per SIMD.  The B
 // operand of the 32x32x16 MFMA wants from lane l = 32 g + c the eight slots 8 g .. 8 g + 7 of column c.  Column c of
 // MFMA e (e = 0..3) is given the target id j0 + 4 c + e, so the lane reads M[s][j0 + 4c .. + 3] for its eight slots
-// s = 16 kb + 8 g + i with eight 16-byte loads of the row-major M -- no packing of M, no LDS -- splits the 32 values
+// s = 16 kb + 8 g + i with eight 16-byte loads of the row-major M -- no packing of M -- splits the 32 values
 // in registers and feeds four MFMA columns; the four results of a lane are again four consecutive ids.  Loads run
 // two slot blocks ahead through a ring of three register sets; the split length is a multiple of three blocks (A is
 // zero beyond n, rows of M are clamped to the last one).  Tiles of 64 ids at two wavefronts per SIMD were slower
 // (0.26 ms against 0.22 ms): every wavefront reads all drafter records of its split.
-constexpr int kSplitWaves = 4;   // wavefronts per workgroup: neighbouring id tiles, walked in step
+//
+// What bounds it: reading M (N = 32000, n = 8000, 64 positions: 1 GB in about 175 us, 5.9 TB/s, where a bare read stream reaches
+// 6.9), and the matrix unit for several row groups.  A lone wavefront has to keep both busy from one instruction stream, so the
+// parts of a pair of columns are taken one unit ahead of their products and every MFMA is followed by five vector instructions
+// and now and then one load: eight loads at once fill the queue of the vector memory pipe, and the wavefront waits there
+// without issuing MFMAs.  The barrier keeps the wavefronts of a workgroup in step: they read neighbouring pieces of the same
+// rows of M, and drift apart otherwise (N = 64000, n = 16000, one position: 680 us a call without it, 640 with it).  The row
+// groups of a tile run side by side on one XCD, whose L2 then reads M once for all of them.
+// Whole calls (product and verification), loads and products in turn -> this: N = 32000, n = 8000, 64 positions 226 -> 211 us;
+// N = 64000, n = 16000, one 713 -> 640; N = 30000, n = 12000, 100 539 -> 481; N = 40000, n = 5000, 256 754 -> 651; N = 5000, n =
+// 1000, five 26.0 -> 24.9.  The drafter records through LDS instead, once per workgroup: 1-2 % slower everywhere.
+constexpr int kSplitWaves = 4;   // wavefronts per workgroup: neighbouring id tiles
 
+// M is loaded non-temporally where it is read once and is larger than the memory-side cache (213 -> 209 us at 1 GB); a smaller one
+// may still lie there from the call before (N = 5000, n = 1000: 26.7 us non-temporally, 24.8 without).
+constexpr size_t kLastLevelBytes = (size_t)256 << 20;
+
+// Issue order of a unit: its 24 MFMAs spread over the vector instructions and loads.
+#define RDK_INTERLEAVE(LOADS)                                                                                        \
+    {                                                                                                                \
+        _Pragma("unroll") for (int i_ = 0; i_ < 24; ++i_) {                                                          \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                                       \
+            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);                                                       \
+            if (i_ * (LOADS) / 24 != (i_ + 1) * (LOADS) / 24) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);     \
+        }                                                                                                            \
+        __builtin_amdgcn_sched_barrier(0);                                                                           \
+    }
+template <bool STREAM>
 __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void exact_f32_split_kernel(
-    const uint16_t *Ap, const float *M, int64_t ldm, int n, int N, int B, int KB, int blocks_per_split, const SoftStat *qstat,
-    float *dst, int64_t ldd, int64_t split_stride, bool scale_here, bool vec_d)
+    const uint16_t *Ap, const float *M, int64_t ldm, int n, int N, int B, int KB, int blocks_per_split, int row_groups,
+    const SoftStat *qstat, float *dst, int64_t ldd, int64_t split_stride, bool scale_here, bool vec_d)
 {
     const int lane = lane_id(), c = lane % 32, g = lane / 32;
-    const int tile = blockIdx.x * kSplitWaves + threadIdx.x / kWave;
-    if (tile * kColSet >= N) return;   // a whole wavefront; the kernel has no barrier
-    const int j0 = tile * kColSet, col = j0 + 4 * c;
-    const int rg = blockIdx.y;
-    const int kb0 = blockIdx.z * blocks_per_split, kb_last = kb0 + blocks_per_split - 1;
+    // the row groups of a tile run at the same time on the same XCD (consecutive workgroups go round the XCDs)
+    const int rg = blockIdx.x / 8 % row_groups, tile_group = blockIdx.x / (8 * row_groups) * 8 + blockIdx.x % 8;
+    if (tile_group * kSplitWaves * kColSet >= N) return;   // a whole workgroup
+    const int j0 = (tile_group * kSplitWaves + threadIdx.x / kWave) * kColSet, col = j0 + 4 * c;
+    const int kb0 = blockIdx.y * blocks_per_split, kb_last = kb0 + blocks_per_split - 1;
     const bool full = col + 3 < N;
     const int lcol = col < N ? col : 0;   // lanes beyond N read column 0 (never stored): no branch around the loads
     f32x16 acc[2][4];
@@ -207,67 +233,83 @@ __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) a_rec[rb] = (const bf16x8 *)Ap + ((int64_t)(rg * 2 + rb) * KB) * 3 * kWave + lane;
 
-    bf16x8 a_ring[kSplitRing][2][3];
+    bf16x8 a_ring[kSplitRing][2][3], parts[2][2][3];
     float4 b_ring[kSplitRing][8];
-#define RDK_LOAD_BLOCK(SLOT, KBI)                                                                                    \
-    {                                                                                                                \
-        const int kb_ = min((KBI), kb_last);                                                                         \
-        _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)                                                             \
-            _Pragma("unroll") for (int pt = 0; pt < 3; ++pt)                                                         \
-                a_ring[SLOT][rb][pt] = a_rec[rb][((int64_t)kb_ * 3 + pt) * kWave];                                   \
-        _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                              \
-            const int s_ = min(kb_ * kSplitStep + 8 * g + i, n - 1);                                                 \
-            b_ring[SLOT][i] = *(const float4 *)(M + (int64_t)s_ * ldm + lcol);                                       \
-        }                                                                                                            \
-        __builtin_amdgcn_sched_barrier(0);                                                                           \
-    }
-    // the four MFMA columns of a block, two at a time: split the eight values of each, then the six part products
-    // smallest first, alternating between the four accumulators involved
-#define RDK_MFMA_BLOCK(SLOT)                                                                                         \
-    {                                                                                                                \
-        _Pragma("unroll") for (int ep = 0; ep < 4; ep += 2) {                                                        \
-            bf16x8 bh_[2], bm_[2], bl_[2];                                                                           \
-            _Pragma("unroll") for (int ee = 0; ee < 2; ++ee) {                                                       \
-                uint32_t h_[8], m_[8], l_[8];                                                                        \
-                _Pragma("unroll") for (int i = 0; i < 8; ++i) {                                                      \
-                    const float4 bv_ = b_ring[SLOT][i];                                                              \
-                    const float x_ = (ep + ee) == 0 ? bv_.x : (ep + ee) == 1 ? bv_.y : (ep + ee) == 2 ? bv_.z : bv_.w; \
-                    split3(x_, h_[i], m_[i], l_[i]);                                                                 \
-                }                                                                                                    \
-                const u32x4 hv_ = {pack_upper(h_[0], h_[1]), pack_upper(h_[2], h_[3]), pack_upper(h_[4], h_[5]), pack_upper(h_[6], h_[7])}; \
-                const u32x4 mv_ = {pack_upper(m_[0], m_[1]), pack_upper(m_[2], m_[3]), pack_upper(m_[4], m_[5]), pack_upper(m_[6], m_[7])}; \
-                const u32x4 lv_ = {pack_upper(l_[0], l_[1]), pack_upper(l_[2], l_[3]), pack_upper(l_[4], l_[5]), pack_upper(l_[6], l_[7])}; \
-                bh_[ee] = __builtin_bit_cast(bf16x8, hv_);                                                           \
-                bm_[ee] = __builtin_bit_cast(bf16x8, mv_);                                                           \
-                bl_[ee] = __builtin_bit_cast(bf16x8, lv_);                                                           \
-            }                                                                                                        \
-            RDK_PART_PRODUCT(SLOT, ep, 1, bm_)                                                                       \
-            RDK_PART_PRODUCT(SLOT, ep, 2, bh_)                                                                       \
-            RDK_PART_PRODUCT(SLOT, ep, 0, bl_)                                                                       \
-            RDK_PART_PRODUCT(SLOT, ep, 1, bh_)                                                                       \
-            RDK_PART_PRODUCT(SLOT, ep, 0, bm_)                                                                       \
-            RDK_PART_PRODUCT(SLOT, ep, 0, bh_)                                                                       \
-        }                                                                                                            \
-    }
-#define RDK_PART_PRODUCT(SLOT, EP, APART, BPART)                                                                     \
-    _Pragma("unroll") for (int ee = 0; ee < 2; ++ee)                                                                 \
-        _Pragma("unroll") for (int rb = 0; rb < 2; ++rb)                                                             \
-            acc[rb][(EP) + ee] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_ring[SLOT][rb][APART], BPART[ee],         \
-                                                                         acc[rb][(EP) + ee], 0, 0, 0);
+    auto load_a = [&](bf16x8 (&slot)[2][3], int kbi) {
+        const int kb = min(kbi, kb_last);
 #pragma unroll
-    for (int t = 0; t < kSplitRing - 1; ++t) RDK_LOAD_BLOCK(t, kb0 + t)
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+            for (int pt = 0; pt < 3; ++pt) slot[rb][pt] = a_rec[rb][((int64_t)kb * 3 + pt) * kWave];
+    };
+    auto load_half = [&](float4 (&slot)[8], int kbi, int half) {
+        const int kb = min(kbi, kb_last);
+#pragma unroll
+        for (int i = 4 * half; i < 4 * half + 4; ++i) {
+            const int s = min(kb * kSplitStep + 8 * g + i, n - 1);
+            const u32x4 *src = (const u32x4 *)(M + (int64_t)s * ldm + lcol);
+            slot[i] = __builtin_bit_cast(float4, STREAM ? __builtin_nontemporal_load(src) : *src);
+        }
+    };
+    // the three parts of the eight values of columns e and e + 1, as operands
+    auto split_pair = [&](bf16x8 (&out)[2][3], const float4 (&slot)[8], int e) {
+#pragma unroll
+        for (int ee = 0; ee < 2; ++ee) {
+            uint32_t h[8], m[8], l[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float x = e + ee == 0 ? slot[i].x : e + ee == 1 ? slot[i].y : e + ee == 2 ? slot[i].z : slot[i].w;
+                split3(x, h[i], m[i], l[i]);
+            }
+            const u32x4 hv = {pack_upper(h[0], h[1]), pack_upper(h[2], h[3]), pack_upper(h[4], h[5]), pack_upper(h[6], h[7])};
+            const u32x4 mv = {pack_upper(m[0], m[1]), pack_upper(m[2], m[3]), pack_upper(m[4], m[5]), pack_upper(m[6], m[7])};
+            const u32x4 lv = {pack_upper(l[0], l[1]), pack_upper(l[2], l[3]), pack_upper(l[4], l[5]), pack_upper(l[6], l[7])};
+            out[ee][0] = __builtin_bit_cast(bf16x8, hv);
+            out[ee][1] = __builtin_bit_cast(bf16x8, mv);
+            out[ee][2] = __builtin_bit_cast(bf16x8, lv);
+        }
+    };
+    // the six part products of two columns, smallest first, alternating between the four accumulators involved
+    auto products = [&](const bf16x8 (&af)[2][3], const bf16x8 (&bf)[2][3], int e) {
+        constexpr int kPart[6][2] = {{1, 1}, {2, 0}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+        for (int x = 0; x < 6; ++x)
+#pragma unroll
+            for (int ee = 0; ee < 2; ++ee)
+#pragma unroll
+                for (int rb = 0; rb < 2; ++rb)
+                    acc[rb][e + ee] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb][kPart[x][0]], bf[ee][kPart[x][1]], acc[rb][e + ee], 0, 0, 0);
+    };
+#pragma unroll
+    for (int t = 0; t < kSplitRing; ++t) {
+        if (t + 1 < kSplitRing) load_a(a_ring[t], kb0 + t);
+        load_half(b_ring[t], kb0 + t, 0);
+        if (t + 1 < kSplitRing) load_half(b_ring[t], kb0 + t, 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    split_pair(parts[0], b_ring[0], 0);
+    __builtin_amdgcn_sched_barrier(0);
+    // A unit is half of a block: the products of two columns, and in their shade the parts of the next two columns and the loads
+    // of the block whose registers fell free last.
     for (int kb = kb0; kb <= kb_last; kb += kSplitRing) {
 #pragma unroll
         for (int t = 0; t < kSplitRing; ++t) {   // ring entries are compile-time constants after unrolling
-            RDK_LOAD_BLOCK((t + kSplitRing - 1) % kSplitRing, kb + t + kSplitRing - 1)
-            RDK_MFMA_BLOCK(t)
+            constexpr int kAhead = kSplitRing - 1;
+            load_a(a_ring[(t + kAhead) % kSplitRing], kb + t + kAhead);
+            load_half(b_ring[(t + kAhead) % kSplitRing], kb + t + kAhead, 1);
+            split_pair(parts[1], b_ring[t], 2);
+            products(a_ring[t], parts[0], 0);
+            RDK_INTERLEAVE(10)
+            load_half(b_ring[t], kb + t + kSplitRing, 0);
+            split_pair(parts[0], b_ring[(t + 1) % kSplitRing], 0);
+            products(a_ring[t], parts[1], 2);
+            RDK_INTERLEAVE(4)
         }
+        __builtin_amdgcn_s_barrier();
     }
-#undef RDK_LOAD_BLOCK
-#undef RDK_MFMA_BLOCK
-#undef RDK_PART_PRODUCT
+#undef RDK_INTERLEAVE
     // D layout of a 32x32 tile: lane l holds column l % 32 and rows 8 * (v / 4) + 4 * (l / 32) + v % 4, v = 0..15
-    float *base = dst + (int64_t)blockIdx.z * split_stride;
+    float *base = dst + (int64_t)blockIdx.y * split_stride;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
@@ -687,16 +729,18 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
             }
         }
         RDK_LAUNCH_CHECK("prep_a_split_kernel");
-        const int tiles = (h.N + kColSet - 1) / kColSet;
-        dim3 grid((tiles + kSplitWaves - 1) / kSplitWaves, row_groups, splits);
+        const int tile_groups = (h.N + kColSet * kSplitWaves - 1) / (kColSet * kSplitWaves);
+        const dim3 grid((tile_groups + 7) / 8 * 8 * row_groups, splits);
+        const bool stream = row_groups == 1 && (size_t)h.n * h.ldm * sizeof(float) > kLastLevelBytes;
+        const auto kernel = stream ? exact_f32_split_kernel<true> : exact_f32_split_kernel<false>;
         if (splits == 1) {
             const bool vec_d = rows_vectorisable(out, ldo, RDK_PROB_F32);
-            RDK_TIMED_LAUNCH("exact_f32_split_kernel", exact_f32_split_kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
-                             h.ldm, h.n, h.N, B, KB, blocks, w.qstat, out, ldo, (int64_t)0, true, vec_d);
+            RDK_TIMED_LAUNCH("exact_f32_split_kernel", kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
+                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, out, ldo, (int64_t)0, true, vec_d);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
         } else {
-            RDK_TIMED_LAUNCH("exact_f32_split_kernel", exact_f32_split_kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
-                             h.ldm, h.n, h.N, B, KB, blocks, w.qstat, w.part, ldd, (int64_t)B * ldd, false, true);
+            RDK_TIMED_LAUNCH("exact_f32_split_kernel", kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
+                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, w.part, ldd, (int64_t)B * ldd, false, true);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
             return launch_reduce(w.part, splits, w.qstat, nullptr, h.N, B, out, ldo, st);
         }

@@ -26,6 +26,17 @@ SHAPES = [  # N, n, B
 @pytest.mark.parametrize("fmt", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_split_product(shape, fmt, kind):
+    check_product(shape, fmt, kind)
+
+
+# The fp32 path's wavefronts (128 ids), workgroups (512 ids, dealt out eight at a time), turns (48 slots) and row groups (64
+# positions) at their edges.
+@pytest.mark.parametrize("shape", [(127, 47, 64), (512, 48, 65), (513, 49, 128), (4095, 96, 1), (4097, 97, 129), (1400, 290, 193)])
+def test_fp32_edges(shape):
+    check_product(shape, "f32", "prob")
+
+
+def check_product(shape, fmt, kind):
     from paper_2506_03206_amd import rdk
     N, n, B = shape
     rng = np.random.default_rng(N + B)
