@@ -124,16 +124,14 @@ __device__ __forceinline__ SoftStat soft_merge(SoftStat a, SoftStat b)
     return r;
 }
 
+// The statistics of the 64 lanes in every lane: each lane's sum is brought to the common maximum once (a tree of soft_merge takes two
+// exponentials and two trips through the LDS crossbar per level, half a microsecond for a lone wavefront).
 __device__ __forceinline__ SoftStat wave_soft_merge(SoftStat v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        SoftStat o;
-        o.m = __shfl_xor(v.m, off, kWave);
-        o.s = __shfl_xor(v.s, off, kWave);
-        v = soft_merge(v, o);
-    }
-    return v;
+    SoftStat r;
+    r.m = wave_max(v.m);
+    r.s = wave_sum(v.s == 0.f ? 0.f : v.s * soft_exp(v.m - r.m));
+    return r;
 }
 
 // ---- typed loads of 4 consecutive elements of a row.  `vec` says the address is 16-byte (fp32)

@@ -147,35 +147,36 @@ __device__ __forceinline__ double lane_partial_sum(const float *part, int nblk, 
     return s;
 }
 
-// Block in which the inclusive prefix of `part` first exceeds thr (-1 if none) and the prefix before it.
-// Lane l owns the per_lane consecutive blocks from l * per_lane.
+// Block in which the inclusive prefix of `part` first exceeds thr (-1 if none) and the prefix before it.  Lane l has added up
+// the per_lane consecutive blocks from l * per_lane (lane_sum); those of the lane in which the threshold is crossed are read again,
+// one per lane: a scan of 64 lanes takes a fifth of the instructions that one lane needs to walk through 32 blocks of its own
+// (N = 128256, 8 positions: fused 18.8 -> 18.1 us a call, draft draw 15.6 -> 14.8; N = 1024, 16 positions 8.63 -> 8.31).  Where rounding leaves no crossing among them it is the last block with a
+// positive sum.
 __device__ __forceinline__ int locate_block(const float *part, int nblk, int per_lane, double lane_sum, double thr,
                                             double &prefix_before)
 {
     const double incl = wave_inclusive_scan(lane_sum);
     const unsigned long long hits = __ballot(incl > thr);
     if (hits == 0ull) return -1;
-    const int src = __ffsll(hits) - 1;
+    const int src = __ffsll(hits) - 1, c0 = src * per_lane, c1 = min(c0 + per_lane, nblk);
+    double before = lane_value(incl - lane_sum, src);
     int blk = -1;
-    double pre = incl - lane_sum;
-    if (lane_id() == src) {
-        const int c0 = src * per_lane;
-        for (int t = 0; t < per_lane && c0 + t < nblk; ++t) {
-            const double v = (double)part[c0 + t];
-            if (pre + v > thr) {
-                blk = c0 + t;
-                break;
-            }
-            pre += v;
+    for (int c = c0; c < c1; c += kWave) {
+        const double x = c + lane_id() < c1 ? (double)part[c + lane_id()] : 0.0;
+        const double to = before + wave_inclusive_scan(x);
+        const unsigned long long over = __ballot(to > thr), some = __ballot(x > 0.0);
+        if (over != 0ull || some != 0ull) {
+            const int at = over != 0ull ? __ffsll(over) - 1 : 63 - __clzll(some);
+            blk = c + at;
+            prefix_before = lane_value(to - x, at);
         }
+        if (over != 0ull) break;
+        before = lane_value(to, kWave - 1);
     }
-    blk = lane_value(blk, src);
-    prefix_before = lane_value(pre, src);
     return blk;
 }
 
-// The same on partials that the lanes already hold in registers (at most kRegBlocks per lane): saves the
-// dependent re-read.  v[t] = partial of block lane * per_lane + t (0 beyond nblk); R = blocks a lane can hold.
+// The block sums of a lane, v[t] = that of block lane * per_lane + t (0 beyond nblk); R = blocks a lane can hold.
 // A lane's blocks are consecutive in memory, so the lanes of one load are per_lane words apart and every load
 // instruction touches up to 64 cache lines.  When the row, the blocks per lane and the block count all are multiples
 // of four words, groups of four blocks are read by one unconditional 16-byte load each (a group is then wholly inside
@@ -209,29 +210,6 @@ __device__ __forceinline__ double sum_partials(const float (&v)[R])
 #pragma unroll
     for (int t = 0; t < R; ++t) s += (double)v[t];
     return s;
-}
-
-template <int R>
-__device__ __forceinline__ int locate_block_regs(const float (&v)[R], int nblk, int per_lane, double lane_sum, double thr,
-                                                 double &prefix_before)
-{
-    const double incl = wave_inclusive_scan(lane_sum);
-    const unsigned long long hits = __ballot(incl > thr);
-    if (hits == 0ull) return -1;
-    const int src = __ffsll(hits) - 1;
-    const int c0 = lane_id() * per_lane;
-    int blk = -1;
-    double pre = incl - lane_sum;
-#pragma unroll
-    for (int t = 0; t < R; ++t) {
-        const double x = (double)v[t];
-        const bool here = blk < 0 && t < per_lane && c0 + t < nblk && pre + x > thr;
-        if (here) blk = c0 + t;
-        if (blk < 0) pre += x;
-    }
-    blk = lane_value(blk, src);
-    prefix_before = lane_value(pre, src);
-    return blk;
 }
 
 // Element (i, e) of a lane's block registers: sub-block i, component e, both run-time values.
@@ -331,8 +309,7 @@ __global__ __launch_bounds__(kFinalizeRows * kWave) void bonus_finalize_kernel(F
     if (R > 0.0) {
         const double thr = word_to_unit(words[3]) * R;
         double before = 0.0;
-        const int blk = in_regs ? locate_block_regs(v, a.nblk, per_lane, lane_r, thr, before)
-                                : locate_block(part, a.nblk, per_lane, lane_r, thr, before);
+        const int blk = locate_block(part, a.nblk, per_lane, lane_r, thr, before);
         if (blk >= 0) {
             const int base = blk * BLOCK;
             float4 w[SUB];
@@ -359,18 +336,24 @@ __global__ __launch_bounds__(kFinalizeRows * kWave) void bonus_finalize_kernel(F
 // the residual sums and the residual's block, wavefront 2 alpha (and the two values of a draft the caller supplied).  Every
 // wavefront of the workgroup calls it.
 //   REGS               block sums a lane keeps in registers (one kind per wavefront)
+//   setup              hands out where q' comes from and the softmax maximum and 1 / normaliser of a logit target row (0 and 1 for
+//                      probabilities); called once the block sums are asked for, so that what it reads comes with them
 //   part_q, _r, _a     the row's a.nblk block sums of q', max(0, p - q') and min(p, q') (LDS or memory)
-//   m, inv             softmax maximum and 1 / normaliser of a logit target row (0 and 1 for probabilities)
 struct WideScratch {   // LDS
     double d[2];       // alpha, residual mass
     int i[2];          // the drafted id, the residual id
     float f[2];        // q' and p at the draft
 };
 
-template <int KIND, int REGS, class Row>
-__device__ __forceinline__ void finish_row_wide(const FinalizeArgs &a, const Row &qrow, int64_t row, const void *pr, float m, float inv,
-                                                const float *part_q, const float *part_r, const float *part_a, WideScratch &sh,
-                                                int wid, int lane)
+template <class Row>
+struct FinishSetup {
+    Row row;
+    float m, inv;
+};
+
+template <int KIND, int REGS, class Setup>
+__device__ __forceinline__ void finish_row_wide(const FinalizeArgs &a, const Setup &setup, int64_t row, const void *pr, const float *part_q,
+                                                const float *part_r, const float *part_a, WideScratch &sh, int wid, int lane)
 {
     const rdk_verify_desc_t &d = a.d;
     const int N = d.N;
@@ -381,56 +364,58 @@ __device__ __forceinline__ void finish_row_wide(const FinalizeArgs &a, const Row
     uint32_t words[4] = {0u, 0u, 0u, 0u};
     int blk = -1;                // the block of this wavefront's draw (-1: nothing to draw) and the threshold inside it
     double thr_local = 0.0;
-    // 1. one kind of block sums per wavefront
     if (wid < 3) {
+        // 1. one kind of block sums per wavefront
         const float *part = wid == 0 ? part_q : wid == 1 ? part_r : part_a;
         const bool wanted = wid == 0 ? draw_draft : true;
         float v[REGS];
         double lane_s = 0.0;
         if (wanted && in_regs) load_partials(part, a.nblk, per_lane, v);
+        const auto given = setup();
+        const auto &qrow = given.row;
+        const float m = given.m, inv = given.inv;
         position_words(d.seed, d.offset + (uint64_t)row, words);   // while the sums are on their way
         if (wanted) lane_s = in_regs ? sum_partials(v) : lane_partial_sum(part, a.nblk, per_lane);
         const double T = wanted ? wave_sum(lane_s) : 0.0;
         if (wid < 2 && wanted && T > 0.0) {
             const double thr = word_to_unit(words[wid == 0 ? 0 : 2]) * T;
             double before = 0.0;
-            blk = in_regs ? locate_block_regs(v, a.nblk, per_lane, lane_s, thr, before)
-                          : locate_block(part, a.nblk, per_lane, lane_s, thr, before);
+            blk = locate_block(part, a.nblk, per_lane, lane_s, thr, before);
             thr_local = thr - before;
         }
         if (lane == 0 && wid >= 1) sh.d[2 - wid] = T;   // wavefront 1: residual mass -> [1], wavefront 2: alpha -> [0]
-    }
-    // 2. the block of the draft (wavefront 0) and of the residual draw (wavefront 1), one id per lane; the two values of
-    //    a caller's draft (wavefront 2)
-    if (wid < 2) {
-        int tok = -1;
-        if (blk >= 0) {
-            const int base = blk * 64, id = base + lane;
-            typename Row::Pending1 t;
-            qrow.template stage1<0>(t, id);
-            float pv = pfill;
-            if (id < N) pv = load1<KIND>(pr, id);
-            qrow.template stage1<1>(t, id);
-            qrow.template stage1<2>(t, id);
-            const float wq = qrow.result1(t, id);
-            const float pw = to_weight<KIND>(pv, m, inv);
-            tok = search_block1(wid == 0 ? wq : fmaxf(pw - wq, 0.f), base, thr_local);
-            if (wid == 0 && tok >= 0) {
-                const float qd = lane_value(wq, tok - base), pd = lane_value(pw, tok - base);
+        // 2. the block of the draft (wavefront 0) and of the residual draw (wavefront 1), one id per lane; the two values of
+        //    a caller's draft (wavefront 2)
+        if (wid < 2) {
+            int tok = -1;
+            if (blk >= 0) {
+                const int base = blk * 64, id = base + lane;
+                typename std::decay<decltype(qrow)>::type::Pending1 t;
+                qrow.template stage1<0>(t, id);
+                float pv = pfill;
+                if (id < N) pv = load1<KIND>(pr, id);
+                qrow.template stage1<1>(t, id);
+                qrow.template stage1<2>(t, id);
+                const float wq = qrow.result1(t, id);
+                const float pw = to_weight<KIND>(pv, m, inv);
+                tok = search_block1(wid == 0 ? wq : fmaxf(pw - wq, 0.f), base, thr_local);
+                if (wid == 0 && tok >= 0) {
+                    const float qd = lane_value(wq, tok - base), pd = lane_value(pw, tok - base);
+                    if (lane == 0) {
+                        sh.f[0] = qd;
+                        sh.f[1] = pd;
+                    }
+                }
+            }
+            if (lane == 0) sh.i[wid] = tok;
+        } else if (!draw_draft) {
+            const int32_t dtok = a.draft_ids[row];
+            if (dtok >= 0 && dtok < N) {
+                const float pd = to_weight<KIND>(load1<KIND>(pr, dtok), m, inv), qd = qrow.load1(dtok);
                 if (lane == 0) {
                     sh.f[0] = qd;
                     sh.f[1] = pd;
                 }
-            }
-        }
-        if (lane == 0) sh.i[wid] = tok;
-    } else if (wid == 2 && !draw_draft) {
-        const int32_t dtok = a.draft_ids[row];
-        if (dtok >= 0 && dtok < N) {
-            const float pd = to_weight<KIND>(load1<KIND>(pr, dtok), m, inv), qd = qrow.load1(dtok);
-            if (lane == 0) {
-                sh.f[0] = qd;
-                sh.f[1] = pd;
             }
         }
     }
@@ -476,15 +461,16 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
     const int64_t row = xcd_row(blockIdx.x, a.d.B);
     const void *pr = row_ptr<KIND>(a.p, a.ldp, row);
-    float m = 0.f, inv = 1.f;
-    if (KIND != RDK_PROB_F32) {
-        const SoftStat rs = merged_row_stat<KIND>(a.pstat, a.p_splits, row);
-        m = rs.m;
-        inv = 1.0f / rs.s;
-    }
-    const typename QP::Row qrow = qp.row(row);
-    finish_row_wide<KIND, REGS>(a, qrow, row, pr, m, inv, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, sh,
-                              wid, lane);
+    auto setup = [&]() {
+        FinishSetup<typename QP::Row> r{qp.row(row), 0.f, 1.f};
+        if (KIND != RDK_PROB_F32) {
+            const SoftStat rs = merged_row_stat<KIND>(a.pstat, a.p_splits, row);
+            r.m = rs.m;
+            r.inv = 1.0f / rs.s;
+        }
+        return r;
+    };
+    finish_row_wide<KIND, REGS>(a, setup, row, pr, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, sh, wid, lane);
 }
 
 // ---- The finish of one row by eight wavefronts, for block sums over 1024 ids (Alg. 4, steps 2 and 4-6 for one position).
@@ -540,8 +526,7 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
         double thr = 0.0, before = 0.0;
         if (wid < 2 && wanted && T > 0.0) {
             thr = word_to_unit(words[wid == 0 ? 0 : 2]) * T;
-            blk = in_regs ? locate_block_regs(v, nblk, per_lane, lane_s, thr, before)
-                          : locate_block(part, nblk, per_lane, lane_s, thr, before);
+            blk = locate_block(part, nblk, per_lane, lane_s, thr, before);
         }
         if (lane == 0) {
             if (wid < 2) {
@@ -713,8 +698,7 @@ __device__ __forceinline__ void draft_row(const DraftArgs &a, const Row &qrow, i
     double thr = 0.0, before = 0.0;
     if (Q > 0.0) {
         thr = word_to_unit(words[0]) * Q;
-        blk = in_regs ? locate_block_regs(vq, a.nblk, per_lane, lane_q, thr, before)
-                      : locate_block(pq, a.nblk, per_lane, lane_q, thr, before);
+        blk = locate_block(pq, a.nblk, per_lane, lane_q, thr, before);
     }
     int32_t dtok = -1;
     float qd = 0.f;

@@ -65,6 +65,7 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, 
 template <int KIND>
 __device__ __forceinline__ SoftStat merged_row_stat(const SoftStat *stat, int splits, int64_t row)
 {
+    if (splits == 1) return stat[row];
     SoftStat v;
     v.m = KIND == RDK_PROB_F32 ? 0.f : -INFINITY;
     v.s = 0.f;

@@ -12,7 +12,7 @@
 // the chain of dependent reads of one position.  Where one workgroup holds a whole row it also takes the softmax statistics
 // of the target row and finishes the row, so that the call is one launch: N = 1024, n = 256, 16 positions 20.4 -> 8.7 us,
 // with bf16 logits 29.5 -> 10.1; N = 4000, k = 16, 8 positions 20.8 -> 11.8; N = 128256, 8 positions over 32 workgroups each
-// 34.4 -> 19.2, with bf16 logits 44.9 -> 25.5.
+// 34.4 -> 18.1, with bf16 logits 44.9 -> 22.4.
 #include "rdk_slab.hpp"
 
 namespace rdk {
@@ -22,7 +22,7 @@ namespace {
 constexpr int kSlabThreads = 1024;
 constexpr int kSlabWaves = kSlabThreads / kWave;
 constexpr int kTile = 256;                          // target ids of a wavefront's tile at most
-constexpr int kQuads = 10;                          // quads of slots a thread holds while LDS is filled
+constexpr int kQuads = 9;                           // quads of slots a thread holds while LDS is filled
 constexpr size_t kLdsBytes = (size_t)160 * 1024;    // of a compute unit
 constexpr int kFinishRegs = 8;                      // block sums a lane keeps in registers in the finish
 constexpr int kFinishMaxBlocks = kFinishRegs * kWave;
@@ -92,34 +92,67 @@ __device__ __forceinline__ float block_sum(float v, float *red)
 
 __device__ __forceinline__ float max4(float4 v) { return fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)); }
 
-// Fills the slab with the unnormalised drafter weights of row b; qmax = the row maximum (logits), zinv = 1 / mass.  The
-// last barrier inside leaves the slab ready.
+// The drafter row on its way to LDS, a quad per thread and round.  bf16 values stay as they lie in memory until all are there (their
+// maximum is what the workgroup waits for first, so they are also asked for before the pairs: one sequence of 8 drafts at N =
+// 128256 24.4 -> 23.4 us a call; rows of fp32 lost 0.3 us by either).
 template <int QK>
-__device__ __forceinline__ void slab_fill(const SlabArgs &a, int b, float *slab, float *red, float &qmax, float &zinv)
-{
-    const float fill = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
-    const void *qr = row_ptr<QK>(a.q, a.ldq, b);
-    float4 raw[kQuads];
+struct SlabRow {
+    static constexpr bool kPacked = QK == RDK_LOGIT_BF16;
+    typedef typename std::conditional<kPacked, uint2, float4>::type Quad;
+    Quad quad[kQuads];
+
+    __device__ __forceinline__ void request(const SlabArgs &a, const void *qr)
+    {
+        const float fill = QK == RDK_PROB_F32 ? 0.f : -INFINITY;
 #pragma unroll
-    for (int v = 0; v < kQuads; ++v) {
-        const int s = (int)(threadIdx.x + v * kSlabThreads) * 4;
-        raw[v] = make_float4(fill, fill, fill, fill);
-        if (s < a.n) raw[v] = load4<QK>(qr, s, a.n, a.vec_q, fill);
+        for (int v = 0; v < kQuads; ++v) {
+            const int s = slot(v);
+            if constexpr (kPacked) {
+                if (v * kSlabThreads * 4 >= a.n) continue;           // behind the end of the row: not looked at either
+                const uint16_t *r = (const uint16_t *)qr + s;
+                constexpr uint32_t kNone = 0xFF80u;                  // -infinity
+                quad[v] = make_uint2(kNone | kNone << 16, kNone | kNone << 16);
+                if (a.vec_q && s + 3 < a.n) quad[v] = *(const uint2 *)r;
+                else if (s < a.n)
+                    quad[v] = make_uint2(r[0] | (s + 1 < a.n ? r[1] : kNone) << 16, (s + 2 < a.n ? r[2] : kNone) | (s + 3 < a.n ? r[3] : kNone) << 16);
+            } else {
+                quad[v] = make_float4(fill, fill, fill, fill);
+                if (s < a.n) quad[v] = load4<QK>(qr, s, a.n, a.vec_q, fill);
+            }
+        }
     }
+    static __device__ __forceinline__ int slot(int v) { return (int)(threadIdx.x + v * kSlabThreads) * 4; }
+    __device__ __forceinline__ float4 values(int v) const
+    {
+        if constexpr (kPacked)
+            return make_float4(__uint_as_float(quad[v].x << 16), __uint_as_float(quad[v].x & 0xFFFF0000u), __uint_as_float(quad[v].y << 16),
+                               __uint_as_float(quad[v].y & 0xFFFF0000u));
+        else
+            return quad[v];
+    }
+};
+
+// Fills the slab with the unnormalised drafter weights of the requested row of n slots; qmax = the row maximum (logits), zinv = 1 /
+// mass.  The last barrier inside leaves the slab ready.
+template <int QK>
+__device__ __forceinline__ void slab_fill(int n, const SlabRow<QK> &row, float *slab, float *red, float &qmax, float &zinv)
+{
     qmax = 0.f;
     if (QK != RDK_PROB_F32) {
         float m = -INFINITY;
 #pragma unroll
-        for (int v = 0; v < kQuads; ++v) m = fmaxf(m, max4(raw[v]));
+        for (int v = 0; v < kQuads; ++v)
+            if (!SlabRow<QK>::kPacked || v * kSlabThreads * 4 < n) m = fmaxf(m, max4(row.values(v)));
         qmax = block_max(m, red);
     }
     float z = 0.f;
 #pragma unroll
     for (int v = 0; v < kQuads; ++v) {
-        const int s = (int)(threadIdx.x + v * kSlabThreads) * 4;
-        if (s < a.n) {
-            const float4 w = make_float4(to_weight<QK>(raw[v].x, qmax, 1.f), to_weight<QK>(raw[v].y, qmax, 1.f),
-                                         to_weight<QK>(raw[v].z, qmax, 1.f), to_weight<QK>(raw[v].w, qmax, 1.f));
+        const int s = SlabRow<QK>::slot(v);
+        if (s < n) {
+            const float4 x = row.values(v);
+            const float4 w = make_float4(to_weight<QK>(x.x, qmax, 1.f), to_weight<QK>(x.y, qmax, 1.f), to_weight<QK>(x.z, qmax, 1.f),
+                                         to_weight<QK>(x.w, qmax, 1.f));
             z += (w.x + w.y) + (w.z + w.w);
             *(float4 *)(slab + s) = w;
         }
@@ -214,6 +247,9 @@ __global__ __launch_bounds__(kSlabThreads) void slab_product_kernel(SlabArgs a, 
         next_lo = pruned_below(a.t.slot_of, (t + kSlabWaves) * T, N, a.n);
         next_hi = pruned_below(a.t.slot_of, (t + kSlabWaves) * T + T, N, a.n);
     };
+    const void *qr = row_ptr<QK>(a.q, a.ldq, b);
+    SlabRow<QK> qraw;
+    if (SlabRow<QK>::kPacked) qraw.request(a, qr);
     if (tile < t_end) {
         const int lo = pruned_below(a.t.slot_of, tile * T, N, a.n), hi = pruned_below(a.t.slot_of, tile * T + T, N, a.n);
         begin_tile(tile, lo, hi);
@@ -221,13 +257,17 @@ __global__ __launch_bounds__(kSlabThreads) void slab_product_kernel(SlabArgs a, 
         if (lo < hi) request(ev_a, c_a, lo, 0, hi);
     }
 
+    SoftStat pstat{-INFINITY, 0.f};   // this lane's partial of the target row's statistics
+    static_assert(kMaxSplits <= kWave, "one partial per lane");
+    if (FUSE && PKIND != RDK_PROB_F32 && !FIN && lane < f.p_splits) pstat = f.pstat[(int64_t)b * f.p_splits + lane];
+    if (!SlabRow<QK>::kPacked) qraw.request(a, qr);
+
     float qmax, zinv;
-    slab_fill<QK>(a, b, slab, red, qmax, zinv);
+    slab_fill<QK>(a.n, qraw, slab, red, qmax, zinv);
     if (!FIN && split == 0 && threadIdx.x == 0) a.qrow[b] = SoftStat{qmax, zinv};
     float pm = 0.f, pinv = 1.f;
     if (FUSE && PKIND != RDK_PROB_F32) {
-        const SoftStat rs = FIN ? row_soft_stat<PKIND>(pr, N, f.vec_p, red + 2 * kSlabWaves)
-                                : merged_row_stat<PKIND>(f.pstat, f.p_splits, b);
+        const SoftStat rs = FIN ? row_soft_stat<PKIND>(pr, N, f.vec_p, red + 2 * kSlabWaves) : wave_soft_merge(pstat);
         pm = rs.m;
         pinv = 1.0f / rs.s;
         if (!FIN && split == 0 && threadIdx.x == 0) f.pmerged[b] = rs;
@@ -367,7 +407,8 @@ __global__ __launch_bounds__(kSlabThreads) void slab_product_kernel(SlabArgs a, 
         __syncthreads();
         WideScratch &sh = *(WideScratch *)red;               // the reductions are over
         const SparseRow<LdsColumn> row{a.t.slot_of, a.t.nbr, a.t.self_w, a.t.kk, N, LdsColumn{slab, zinv}};
-        if (FUSE) finish_row_wide<PKIND, kFinishRegs>(fin, row, b, pr, pm, pinv, blocks, blocks + nblk, blocks + 2 * nblk, sh, wid, lane);
+        auto setup = [&]() { return FinishSetup<SparseRow<LdsColumn>>{row, pm, pinv}; };
+        if (FUSE) finish_row_wide<PKIND, kFinishRegs>(fin, setup, b, pr, blocks, blocks + nblk, blocks + 2 * nblk, sh, wid, lane);
         else if (wid == 0) draft_row<kSubIds, kFinishRegs, 3>(draft, row, b, blocks);
     }
 }
