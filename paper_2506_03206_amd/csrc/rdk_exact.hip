@@ -505,13 +505,17 @@ __global__ __launch_bounds__(kPrepThreads) void prep_a_bf16_kernel(const void *q
 // column blocks (32 target ids each) of the workgroup's column group, i.e. RB x 4 accumulator tiles of
 // 32 x 32 fp32.  The kept slots are walked in stages of 64 (four MFMA steps):
 //   * A records come straight from global memory (L2-resident: every workgroup walks the slots at the same pace),
-//   * the 16 B records of a stage are fetched once per workgroup, parked in LDS (double buffered) and read by all
+//   * the 16 B records of a stage are fetched once per workgroup, parked in LDS (three buffers in turn) and read by all
 //     wavefronts: the vector memory pipe of a CU could not feed every wavefront its own copy;
 //   * requests run two (A) and three (B) stages ahead of the MFMAs; large batches use one wavefront per SIMD with
 //     the whole register file (accumulators in the AGPR half), which halves the LDS reads per MFMA.
+// With requests in one go at the head of a stage, and the stage's LDS writes, barrier and first reads at its end, the matrix pipe was
+// busy 70 % of the clocks; spread between the MFMAs, with the barrier in mid-stage, 81 % (N = 256000, n = 32000, 512 positions: 11.55 ->
+// 9.89 M clocks, at 1.60 -> 1.51 GHz: 7114 -> 6755 us a call of two).  The clock follows the power from here on.
 // M is streamed from HBM exactly once when all positions fit one row of workgroups (B <= 512).
-// A small vocabulary has fewer column groups than the chip has compute units: the slots are split over blockIdx.z then, in
-// whole turns of six stages, and the partial products go to `out` without their scale (split_stride apart).
+// Where there are fewer column groups than the chip has compute units, be it in the whole call or in its last round, the slots are
+// split over blockIdx.z, in whole turns of six stages, and the partial products of the groups from group0 on go to `out` without
+// their scale (split_stride apart).
 // A record of M: read exactly once per launch, so it is loaded non-temporally and leaves the L2 to the A records,
 // which every workgroup of an XCD reads again.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
@@ -522,14 +526,14 @@ __device__ __forceinline__ f16x8 load_once(const f16x8 *p)
 }
 
 template <int W, int RB, bool SPLIT>
-__global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, const uint16_t *Mp, int KB, int KB_split, int N,
-                                                            int B, const float *out_scale, float *out, int64_t ldo,
+__global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, const uint16_t *Mp, int KB, int KB_split, int group0,
+                                                            int N, int B, const float *out_scale, float *out, int64_t ldo,
                                                             int64_t split_stride)
 {
     constexpr int RPW = 16 / W;   // B records a wavefront fetches per stage
-    __shared__ f16x8 bbuf[2][16][64];
-    const int wid = threadIdx.x / kWave, lane = lane_id();
-    const int jb0 = blockIdx.x * kColBlocksPerWg;
+    __shared__ f16x8 bbuf[3][16][64];
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    const int jb0 = (group0 + blockIdx.x) * kColBlocksPerWg;
     const int rb0 = (blockIdx.y * W + wid) * RB;
     const int n_jb = (N + kColBlock - 1) / kColBlock;
     const int kb_first = blockIdx.z * KB_split;
@@ -543,16 +547,16 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
 
-    const f16x8 *a_ptr[RB];
+    const f16x8 *a_ptr[RB];   // the same for every lane, which adds its own place in a record
 #pragma unroll
-    for (int r = 0; r < RB; ++r) a_ptr[r] = (const f16x8 *)Ap + ((int64_t)(rb0 + r) * KB + kb_first) * 64 + lane;
+    for (int r = 0; r < RB; ++r) a_ptr[r] = (const f16x8 *)Ap + ((int64_t)(rb0 + r) * KB + kb_first) * 64;
     const f16x8 *b_src[RPW];
     int b_rec[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
         b_rec[i] = wid * RPW + i;                               // record = jb * 4 + kb within the stage
         const int jb = min(jb0 + b_rec[i] / 4, n_jb - 1);       // surplus column blocks recompute the last one
-        b_src[i] = (const f16x8 *)Mp + ((int64_t)jb * KB + kb_first + b_rec[i] % 4) * 64 + lane;
+        b_src[i] = (const f16x8 *)Mp + ((int64_t)jb * KB + kb_first + b_rec[i] % 4) * 64;
     }
     // Loads return to a wavefront in issue order, so every load inherits the latency of the slowest one before
     // it.  The B records come from HBM: they are requested three stages ahead and kept in a ring of registers.
@@ -565,58 +569,66 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) a_even[r][kb] = a_ptr[r][kb * 64];
+        for (int r = 0; r < RB; ++r) a_even[r][kb] = a_ptr[r][kb * 64 + lane];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
-        for (int i = 0; i < RPW; ++i) b_ring[t][i] = load_once(b_src[i] + (int64_t)min(t, stages - 1) * 4 * 64);
+        for (int i = 0; i < RPW; ++i) b_ring[t][i] = load_once(b_src[i] + (int64_t)min(t, stages - 1) * 4 * 64 + lane);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
+    for (int kb = 0; kb < (RB > 1 ? 3 : 4); ++kb)
 #pragma unroll
-        for (int r = 0; r < RB; ++r) a_odd[r][kb] = a_ptr[r][((int64_t)min(1, stages - 1) * 4 + kb) * 64];
+        for (int r = 0; r < RB; ++r) a_odd[r][kb] = a_ptr[r][((int64_t)min(1, stages - 1) * 4 + kb) * 64 + lane];
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < RPW; ++i) bbuf[0][b_rec[i]][lane] = b_ring[0][i];
     __syncthreads();
+    f16x8 bq[4];   // B fragments are read from LDS two MFMA groups ahead
+    bq[0] = bbuf[0][0][lane];
+    bq[1] = bbuf[0][4][lane];
 
-    // One stage.  SLOT = s % 3 is the ring entry free for the B request three stages ahead.  ACUR holds the A
-    // records of this stage; as soon as the MFMAs of one slot block are issued, its registers take the request
-    // for the same block TWO stages ahead (even and odd stages own one register set each), so twice as many A
-    // bytes are in flight as with whole-stage double buffering.  All indices are clamped: no branches.
-#define RDK_STAGE(SLOT, ACUR)                                                                                        \
+    // One stage: sixteen groups f = kb * 4 + c of RB MFMAs, and between the MFMAs of a group at most one request of each kind, so
+    // that it is issued while an MFMA runs.  The registers of slot block kb fall free with its last group; they take the request
+    // for the same block TWO stages ahead during the next slot block (those of the last one during the next stage: APREV), so
+    // even and odd stages own one register set each.  SLOT = s % 3 is the ring entry free for the B request three stages ahead, and
+    // the LDS buffer of this stage.  The next stage's B records go to LDS in the third slot block, the barrier that makes
+    // them visible stands before the last one, and the first two fragments of the next stage are read behind it: no wavefront
+    // waits for LDS between two stages.  All indices are clamped: no branches.
+#define RDK_STAGE(SLOT, ACUR, APREV)                                                                                 \
     {                                                                                                                \
-        const int cur = s & 1;                                                                                       \
-        const int64_t sa = min(s + 2, stages - 1), sb = min(s + 3, stages - 1);                                      \
-        _Pragma("unroll") for (int i = 0; i < RPW; ++i) b_ring[SLOT][i] = load_once(b_src[i] + sb * 4 * 64);         \
+        const int64_t sp = (int64_t)min(s + 1, stages - 1) * 256, sa = (int64_t)min(s + 2, stages - 1) * 256;        \
+        const int64_t sb = (int64_t)min(s + 3, stages - 1) * 256;                                                    \
+        if (RB == 1) _Pragma("unroll") for (int i = 0; i < RPW; ++i) b_ring[SLOT][i] = load_once(b_src[i] + sb + lane); \
         __builtin_amdgcn_sched_barrier(0);                                                                           \
-        f16x8 bq[3];                        /* B fragments are read from LDS two MFMA groups ahead */               \
-        bq[0] = bbuf[cur][0][lane];                                                                                  \
-        bq[1] = bbuf[cur][4][lane];                                                                                  \
-        _Pragma("unroll") for (int f = 0; f < 16; ++f) {     /* f = kb * 4 + c */                                    \
-            const int kb = f / 4, c = f % 4;                                                                         \
-            if (f + 2 < 16) bq[(f + 2) % 3] = bbuf[cur][((f + 2) % 4) * 4 + (f + 2) / 4][lane];                      \
-            _Pragma("unroll") for (int r = 0; r < RB; ++r)                                                           \
-                acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ACUR[r][kb], bq[f % 3], acc[r][c], 0, 0, 0);     \
-            if (c == 3) {                                                                                            \
+        _Pragma("unroll") for (int f = 0; f < 16; ++f) {                                                             \
+            const int kb = f / 4, c = f % 4, nf = (f + 2) % 16;                                                      \
+            if (f == 12) __syncthreads();                                                                            \
+            _Pragma("unroll") for (int r = 0; r < RB; ++r) {                                                         \
+                acc[r][c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ACUR[r][kb], bq[f % 4], acc[r][c], 0, 0, 0);     \
                 __builtin_amdgcn_sched_barrier(0);                                                                   \
-                _Pragma("unroll") for (int r = 0; r < RB; ++r) ACUR[r][kb] = a_ptr[r][(sa * 4 + kb) * 64];           \
+                if (r == 0) bq[(f + 2) % 4] = bbuf[f + 2 < 16 ? SLOT : (SLOT + 1) % 3][(nf % 4) * 4 + nf / 4][lane]; \
+                if (RB == 1 && c == 3) ACUR[0][kb] = a_ptr[0][sa + kb * 64 + lane];                                  \
+                if (RB > 1 && r == RB / 4 && c < RB) {                                                                   \
+                    if (kb == 0) APREV[c][3] = a_ptr[c][sp + 3 * 64 + lane];                                         \
+                    else ACUR[c][(kb + 3) % 4] = a_ptr[c][sa + (kb - 1) * 64 + lane];                                \
+                }                                                                                                    \
+                if (RB > 1 && r == RB / 2 && c == 2 && kb < RPW) b_ring[SLOT][kb % RPW] = load_once(b_src[kb % RPW] + sb + lane); \
+                if (r == RB - 1 && kb == 2)                                                                          \
+                    _Pragma("unroll") for (int i = c; i < RPW; i += 4) bbuf[(SLOT + 1) % 3][b_rec[i]][lane] = b_ring[(SLOT + 1) % 3][i]; \
                 __builtin_amdgcn_sched_barrier(0);                                                                   \
             }                                                                                                        \
         }                                                                                                            \
-        _Pragma("unroll") for (int i = 0; i < RPW; ++i) bbuf[cur ^ 1][b_rec[i]][lane] = b_ring[(SLOT + 1) % 3][i];   \
-        __syncthreads();                                                                                             \
         ++s;                                                                                                         \
     }
     // the number of stages is a multiple of six (the slot count is padded for it): six stages of straight-line code
     for (int s = 0; s < stages;) {
-        RDK_STAGE(0, a_even)
-        RDK_STAGE(1, a_odd)
-        RDK_STAGE(2, a_even)
-        RDK_STAGE(0, a_odd)
-        RDK_STAGE(1, a_even)
-        RDK_STAGE(2, a_odd)
+        RDK_STAGE(0, a_even, a_odd)
+        RDK_STAGE(1, a_odd, a_even)
+        RDK_STAGE(2, a_even, a_odd)
+        RDK_STAGE(0, a_odd, a_even)
+        RDK_STAGE(1, a_even, a_odd)
+        RDK_STAGE(2, a_odd, a_even)
     }
 #undef RDK_STAGE
     // D layout of the 32x32 tile: lane l holds column l % 32 and rows 8 * (v / 4) + 4 * (l / 32) + v % 4, v = 0..15
@@ -629,7 +641,9 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int b = (rb0 + r) * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
-                if (b < B) out[(int64_t)b * ldo + j] = SPLIT ? acc[r][c][v] : acc[r][c][v] * out_scale[b];
+                if (b >= B) continue;
+                if (SPLIT) out[(int64_t)b * ldo + j - group0 * (kColBlocksPerWg * kColBlock)] = acc[r][c][v];
+                else out[(int64_t)b * ldo + j] = acc[r][c][v] * out_scale[b];
             }
         }
 }
@@ -640,27 +654,52 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 // N = 16000, 256 positions 76.8 -> 70.9.  Two workgroups to a unit were slower (36.1 and 88.1 us at 128 and 256 positions).
 // Small vocabularies take the smallest workgroups at any batch, several rows of them: M comes out of the caches again
 // (N = 4000, 512 positions, one row of the largest workgroups split seven ways 46.2 us, four rows 33.3).
+// Up to 64 positions a workgroup has 64 rows: with 128, half of them padding, the vector memory pipe brings as many bytes of A as
+// of M.  128 rows -> 64, two calls with q' kept: N = 50000, n = 20000, 8 positions 460 -> 396 us, N = 20000, n = 6000, 30 90.5 ->
+// 74.4, N = 8000, n = 2000, 8 28.2 -> 24.5, N = 110000, n = 20000, 64 896 -> 827.
+// With more workgroups than the chip holds, the ones that are left for a last round would have it to themselves.  Up to half of the
+// compute units they are split as above, in a launch of their own: N = 40000, n = 15000, 200 positions (57 of 313 left) 440 -> 350
+// us, 480 769 -> 577, N = 100000, n = 15000, 512 (14 of 782) 1646 -> 1415; with 213 of 469 left there is nothing to split, and 248
+// of the smallest ones of 1016 still draw as many bytes from HBM as the full chip (887 us, split 905).
 constexpr int kSmallGroups = 64;
 struct Bf16Shape {
     int W, RB, B_pad, groups, KB, KB_split, splits;
+    int whole, tail_split, tail_splits;   // groups of full rounds; slot blocks and number of the splits of the ones after them
 };
+
+// Cuts KB slot blocks into at most `want` splits of whole turns.
+void split_turns(int KB, int want, int *KB_split, int *splits)
+{
+    const int turns = KB / 24;
+    if (want > turns) want = turns;
+    if (want < 1) want = 1;
+    const int per = (turns + want - 1) / want;
+    *KB_split = per * 24;
+    *splits = (turns + per - 1) / per;
+}
+
+
 Bf16Shape bf16_shape(const KernelHandle &h, int B)
 {
     Bf16Shape s;
     s.groups = ((h.N + kColBlock - 1) / kColBlock + kColBlocksPerWg - 1) / kColBlocksPerWg;
-    if (B <= 128 || s.groups <= kSmallGroups) { s.W = 4; s.RB = 1; }
+    if (B <= 64) { s.W = 2; s.RB = 1; }
+    else if (B <= 128 || s.groups <= kSmallGroups) { s.W = 4; s.RB = 1; }
     else if (B <= 256) { s.W = 8; s.RB = 1; }
     else { s.W = 4; s.RB = 4; }   // one wavefront per SIMD with all 512 registers: half the LDS reads per MFMA
     const int rows = s.W * s.RB * 32;
     s.B_pad = (B + rows - 1) / rows * rows;
     s.KB = h.n_pad / kKStep;
-    const int turns = s.KB / 24;
-    int want = kComputeUnits / (s.groups * (s.B_pad / rows));
-    if (want > turns) want = turns;
-    if (want < 1) want = 1;
-    const int per = (turns + want - 1) / want;
-    s.KB_split = per * 24;
-    s.splits = (turns + per - 1) / per;
+    split_turns(s.KB, kComputeUnits / (s.groups * (s.B_pad / rows)), &s.KB_split, &s.splits);
+    s.whole = s.groups;
+    s.tail_split = s.KB;
+    s.tail_splits = 1;
+    const int resident = (s.W <= 4 && s.RB == 1 ? 3 : 1) * kComputeUnits;   // LDS holds three of them, the registers one of the others
+    const int tail = s.groups % resident;
+    if (rows == s.B_pad && s.groups > resident && tail > 0 && tail * 2 <= kComputeUnits) {
+        split_turns(s.KB, resident / tail, &s.tail_split, &s.tail_splits);
+        if (s.tail_splits > 1) s.whole = s.groups - tail;
+    }
     return s;
 }
 
@@ -756,15 +795,19 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
         RDK_TIMED_LAUNCH("prep_a_bf16_kernel", (prep_a_bf16_kernel<QK>), dim3(B_pad), dim3(kPrepThreads), 0, st, q.ptr, q.ld, h.row_sum, h.n, KB, B, w.A, w.out_scale);
     }
     RDK_LAUNCH_CHECK("prep_a_bf16_kernel");
-    const dim3 grid(c.groups, B_pad / (c.W * c.RB * 32), c.splits);
-    const bool split = c.splits > 1;
-    float *dst = split ? w.part : out;
-    const int64_t ldd = split ? padded(h.N) : ldo, stride = split ? (int64_t)B * ldd : 0;
-    {
 #define RDK_BF16_LAUNCH(W, RB, SPLIT)                                                                                              \
-    RDK_TIMED_LAUNCH("exact_bf16_kernel", (exact_bf16_kernel<W, RB, SPLIT>), grid, dim3(W * 64), 0, st, w.A, h.packed, KB, c.KB_split, \
+    RDK_TIMED_LAUNCH("exact_bf16_kernel", (exact_bf16_kernel<W, RB, SPLIT>), grid, dim3(W * 64), 0, st, w.A, h.packed, KB, per, group0, \
                      h.N, B, w.out_scale, dst, ldd, stride)
-        if (c.W == 4 && c.RB == 1) {
+    const auto product = [&](int group0, int groups, int per, int splits) {
+        const dim3 grid(groups, B_pad / (c.W * c.RB * 32), splits);
+        const bool split = splits > 1;
+        const int j0 = group0 * kColBlocksPerWg * kColBlock;
+        float *dst = split ? w.part : out;
+        const int64_t ldd = split ? padded(h.N - j0) : ldo, stride = split ? (int64_t)B * ldd : 0;
+        if (c.W == 2) {
+            if (split) RDK_BF16_LAUNCH(2, 1, true);
+            else RDK_BF16_LAUNCH(2, 1, false);
+        } else if (c.W == 4 && c.RB == 1) {
             if (split) RDK_BF16_LAUNCH(4, 1, true);
             else RDK_BF16_LAUNCH(4, 1, false);
         } else if (c.W == 8) {
@@ -774,11 +817,12 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
             if (split) RDK_BF16_LAUNCH(4, 4, true);
             else RDK_BF16_LAUNCH(4, 4, false);
         }
+        RDK_LAUNCH_CHECK("exact_bf16_kernel");
+        return split ? launch_reduce(w.part, splits, nullptr, w.out_scale, h.N - j0, B, out + j0, ldo, st) : RDK_OK;
+    };
 #undef RDK_BF16_LAUNCH
-    }
-    RDK_LAUNCH_CHECK("exact_bf16_kernel");
-    if (split) return launch_reduce(w.part, c.splits, nullptr, w.out_scale, h.N, B, out, ldo, st);
-    return RDK_OK;
+    const rdk_status_t rc = product(0, c.whole, c.KB_split, c.splits);
+    return rc == RDK_OK && c.whole < c.groups ? product(c.whole, c.groups - c.whole, c.tail_split, c.tail_splits) : rc;
 }
 
 }  // namespace
@@ -809,7 +853,13 @@ size_t exact_workspace_bytes(const KernelHandle &h, int32_t B)
         // a full one (its rows, 128 to 512, grow with B).
         const size_t splits = std::min<size_t>(c.KB / 24, kComputeUnits / c.groups), full = (size_t)c.W * c.RB * 32 * (kComputeUnits / c.groups);
         const size_t rows = splits > 1 ? std::min(B * splits, full) : 0;
-        bytes += align_up(rows * padded(h.N) * sizeof(float), 256);
+        size_t partials = rows * padded(h.N);
+        for (int b : {std::min(B, 64), std::min(B, 128), std::min(B, 256), std::min(B, 512)}) {   // the largest batches of each shape that has a tail
+            const Bf16Shape t = bf16_shape(h, b);
+            if (t.whole < t.groups)
+                partials = std::max(partials, (size_t)t.tail_splits * b * padded(h.N - t.whole * kColBlocksPerWg * kColBlock));
+        }
+        bytes += align_up(partials * sizeof(float), 256);
     }
     return bytes;
 }

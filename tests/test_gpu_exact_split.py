@@ -36,6 +36,15 @@ def test_fp32_edges(shape):
     check_product(shape, "f32", "prob")
 
 
+# Column groups (128 ids) beyond whole rounds of the chip (256 workgroups, 768 of the smaller ones) have their slots split: one group
+# and a ragged one, 128 groups (the most that are split), one more, a single turn of slots (nothing to split), and the batches
+# at which the workgroup changes.
+@pytest.mark.parametrize("shape", [(98305, 800, 3), (98500, 400, 64), (98305, 800, 65), (98500, 400, 128), (32897, 1153, 129),
+                                   (33001, 1200, 256), (49152, 800, 300), (49153, 800, 260), (33001, 384, 200), (33030, 3100, 512)])
+def test_bf16_tail(shape):
+    check_product(shape, "bf16", "prob")
+
+
 def check_product(shape, fmt, kind):
     from paper_2506_03206_amd import rdk
     N, n, B = shape
