@@ -134,77 +134,30 @@ __device__ __forceinline__ SoftStat wave_soft_merge(SoftStat v)
     return r;
 }
 
-// ---- typed loads of 4 consecutive elements of a row.  `vec` says the address is 16-byte (fp32)
-// or 8-byte (bf16) aligned and all four are in range; otherwise elements are read one by one and
-// those at or beyond `len` come back as `fill`.
+// ---- typed loads of 4 consecutive elements of a row; those at or beyond `len` come back as `fill`.
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
-template <int KIND>
-__device__ __forceinline__ float4 load4(const void *row, int64_t i, int64_t len, bool vec, float fill)
-{
-    float4 v;
-    if (KIND == RDK_LOGIT_BF16) {
-        const uint16_t *r = (const uint16_t *)row;
-        if (vec && i + 3 < len) {
-            uint2 raw = *(const uint2 *)(r + i);
-            v.x = __uint_as_float(raw.x << 16);
-            v.y = __uint_as_float(raw.x & 0xFFFF0000u);
-            v.z = __uint_as_float(raw.y << 16);
-            v.w = __uint_as_float(raw.y & 0xFFFF0000u);
-        } else {
-            v.x = i + 0 < len ? bf16_to_f32(r[i + 0]) : fill;
-            v.y = i + 1 < len ? bf16_to_f32(r[i + 1]) : fill;
-            v.z = i + 2 < len ? bf16_to_f32(r[i + 2]) : fill;
-            v.w = i + 3 < len ? bf16_to_f32(r[i + 3]) : fill;
-        }
-    } else {
-        const float *r = (const float *)row;
-        if (vec && i + 3 < len) {
-            v = *(const float4 *)(r + i);
-        } else {
-            v.x = i + 0 < len ? r[i + 0] : fill;
-            v.y = i + 1 < len ? r[i + 1] : fill;
-            v.z = i + 2 < len ? r[i + 2] : fill;
-            v.w = i + 3 < len ? r[i + 3] : fill;
-        }
-    }
-    return v;
-}
+// Four consecutive elements, which may lie at any multiple of the element's size: the vector memory pipe reads 16 bytes from any
+// address (a row of an odd number of ids starts anywhere), and single loads are left for the quad that crosses the row's end.
+// Single loads for all of such a row, before, now: ten tree nodes of N = 256987 277 -> 111 us a call, 56 of N = 102359 165 -> 63,
+// fused Eq. 3 at N = 55393, 44 positions 22.8 -> 16.8, fused sparse at N = 4797, 336 fp32 logits 32.7 -> 28.3.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 
-// The same without any check: the caller knows the four elements are in range and the address is aligned.
-// STREAM marks the load non-temporal: for data that is read once and should not displace what the caches hold.
+// Without any check: the caller knows the four elements are in range.  STREAM marks the load non-temporal: for data that is read
+// once and should not displace what the caches hold.
 template <int KIND, bool STREAM = false>
 __device__ __forceinline__ float4 load4_full(const void *row, int64_t i)
 {
-    typedef float f32x4_t __attribute__((ext_vector_type(4)));
-    typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
     if (KIND == RDK_LOGIT_BF16) {
-        const u32x2_t *src = (const u32x2_t *)((const uint16_t *)row + i);
-        const u32x2_t raw = STREAM ? __builtin_nontemporal_load(src) : *src;
+        const u32x2_any *src = (const u32x2_any *)((const uint16_t *)row + i);
+        const u32x2_any raw = STREAM ? __builtin_nontemporal_load(src) : *src;
         return make_float4(__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xFFFF0000u), __uint_as_float(raw.y << 16),
                            __uint_as_float(raw.y & 0xFFFF0000u));
     }
-    const f32x4_t *src = (const f32x4_t *)((const float *)row + i);
-    const f32x4_t v = STREAM ? __builtin_nontemporal_load(src) : *src;
+    const f32x4_any *src = (const f32x4_any *)((const float *)row + i);
+    const f32x4_any v = STREAM ? __builtin_nontemporal_load(src) : *src;
     return make_float4(v.x, v.y, v.z, v.w);
-}
-
-// The 16 elements a lane holds of one chunk of kChunk ids (ids base + i*256 + lane*4 .. +3, i = 0..3).  A chunk that
-// lies wholly inside the row of a vectorisable input is read by four loads behind ONE wavefront-uniform
-// branch; per-load range checks cost a dozen scalar and exec-mask instructions each and made the streaming
-// kernels issue-bound.  The loads are non-temporal unless STREAM is false: every user reads its rows once per
-// launch, and batches are larger than the caches.
-template <int KIND, bool STREAM = true>
-__device__ __forceinline__ void load_chunk(const void *row, int64_t base, int64_t len, bool vec, float fill, float4 (&v)[4])
-{
-    const int64_t first = base + lane_id() * 4;
-    if (vec && base + kChunk <= len) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = load4_full<KIND, STREAM>(row, first + i * 256);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = load4<KIND>(row, first + i * 256, len, vec, fill);
-    }
 }
 
 template <int KIND>
@@ -212,6 +165,32 @@ __device__ __forceinline__ float load1(const void *row, int64_t i)
 {
     if (KIND == RDK_LOGIT_BF16) return bf16_to_f32(((const uint16_t *)row)[i]);
     return ((const float *)row)[i];
+}
+
+template <int KIND>
+__device__ __forceinline__ float4 load4(const void *row, int64_t i, int64_t len, float fill)
+{
+    if (i + 3 < len) return load4_full<KIND>(row, i);
+    return make_float4(i + 0 < len ? load1<KIND>(row, i + 0) : fill, i + 1 < len ? load1<KIND>(row, i + 1) : fill,
+                       i + 2 < len ? load1<KIND>(row, i + 2) : fill, i + 3 < len ? load1<KIND>(row, i + 3) : fill);
+}
+
+// The 16 elements a lane holds of one chunk of kChunk ids (ids base + i*256 + lane*4 .. +3, i = 0..3).  A chunk that
+// lies wholly inside the row is read by four loads behind ONE wavefront-uniform
+// branch; per-load range checks cost a dozen scalar and exec-mask instructions each and made the streaming
+// kernels issue-bound.  The loads are non-temporal unless STREAM is false: every user reads its rows once per
+// launch, and batches are larger than the caches.
+template <int KIND, bool STREAM = true>
+__device__ __forceinline__ void load_chunk(const void *row, int64_t base, int64_t len, float fill, float4 (&v)[4])
+{
+    const int64_t first = base + lane_id() * 4;
+    if (base + kChunk <= len) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = load4_full<KIND, STREAM>(row, first + i * 256);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = load4<KIND>(row, first + i * 256, len, fill);
+    }
 }
 
 // Four consecutive raw values as they lie in memory: the conversion of bf16 waits until they are used, or every load would
@@ -255,11 +234,8 @@ __device__ __forceinline__ const void *row_ptr(const void *base, int64_t ld, int
     return (const void *)((const float *)base + b * ld);
 }
 
-inline bool rows_vectorisable(const void *base, int64_t ld, rdk_input_kind_t kind)
-{
-    if (kind == RDK_LOGIT_BF16) return ((uintptr_t)base % 8 == 0) && (ld % 4 == 0);
-    return ((uintptr_t)base % 16 == 0) && (ld % 4 == 0);
-}
+// Four consecutive floats to any address of a float.
+__device__ __forceinline__ void store4(float *dst, float a, float b, float c, float d) { *(f32x4_any *)dst = f32x4_any{a, b, c, d}; }
 
 // Turns a raw element into the weight the method works with: probabilities pass through, logits
 // become exp(z - m) * inv (inv = 1 / sum exp for a normalised softmax, 1 for an unnormalised one).

@@ -212,7 +212,7 @@ constexpr size_t kLastLevelBytes = (size_t)256 << 20;
 template <bool STREAM>
 __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void exact_f32_split_kernel(
     const uint16_t *Ap, const float *M, int64_t ldm, int n, int N, int B, int KB, int blocks_per_split, int row_groups,
-    const SoftStat *qstat, float *dst, int64_t ldd, int64_t split_stride, bool scale_here, bool vec_d)
+    const SoftStat *qstat, float *dst, int64_t ldd, int64_t split_stride, bool scale_here)
 {
     const int lane = lane_id(), c = lane % 32, g = lane / 32;
     // the row groups of a tile run at the same time on the same XCD (consecutive workgroups go round the XCDs)
@@ -319,8 +319,8 @@ __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_pe
             const float sc = scale_here ? inv_mass(qstat[b].s) : 1.f;
             const float o[4] = {acc[rb][0][v] * sc, acc[rb][1][v] * sc, acc[rb][2][v] * sc, acc[rb][3][v] * sc};
             float *drow = base + (int64_t)b * ldd + col;
-            if (full && vec_d) {
-                *(float4 *)drow = make_float4(o[0], o[1], o[2], o[3]);
+            if (full) {
+                store4(drow, o[0], o[1], o[2], o[3]);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_pe
 // latency once per partial (fp32 path, N = 8000, n = 2000, fourteen splits: 8 positions 40.4 -> 31.5 us a call, 64: 46.3 -> 37.2).
 __global__ __launch_bounds__(256) void exact_reduce_kernel(const float *part, int64_t ldd, int64_t split_stride, int splits,
                                                            const SoftStat *qstat, const float *out_scale, int N, int B, float *out,
-                                                           int64_t ldo, bool vec_o)
+                                                           int64_t ldo)
 {
     for (int b = blockIdx.y; b < B; b += gridDim.y) {   // positions beyond the grid's second dimension are looped over
         const float sc = out_scale ? out_scale[b] : inv_mass(qstat[b].s);
@@ -354,8 +354,8 @@ __global__ __launch_bounds__(256) void exact_reduce_kernel(const float *part, in
         }
         float *dst = out + (int64_t)b * ldo + j;
         const float o[4] = {s.x * sc, s.y * sc, s.z * sc, s.w * sc};
-        if (vec_o && j + 3 < N) {
-            *(float4 *)dst = make_float4(o[0], o[1], o[2], o[3]);
+        if (j + 3 < N) {
+            store4(dst, o[0], o[1], o[2], o[3]);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -735,8 +735,7 @@ rdk_status_t launch_reduce(const float *part, int splits, const SoftStat *qstat,
                            int64_t ldo, hipStream_t st)
 {
     RDK_TIMED_LAUNCH("exact_reduce_kernel", exact_reduce_kernel, dim3((N + 1023) / 1024, B < 32768 ? B : 32768), dim3(256), 0, st, part,
-                     padded(N), (int64_t)B * padded(N), splits, qstat, out_scale, N, B, out, ldo,
-                     rows_vectorisable(out, ldo, RDK_PROB_F32));
+                     padded(N), (int64_t)B * padded(N), splits, qstat, out_scale, N, B, out, ldo);
     RDK_LAUNCH_CHECK("exact_reduce_kernel");
     return RDK_OK;
 }
@@ -773,13 +772,12 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
         const bool stream = row_groups == 1 && (size_t)h.n * h.ldm * sizeof(float) > kLastLevelBytes;
         const auto kernel = stream ? exact_f32_split_kernel<true> : exact_f32_split_kernel<false>;
         if (splits == 1) {
-            const bool vec_d = rows_vectorisable(out, ldo, RDK_PROB_F32);
             RDK_TIMED_LAUNCH("exact_f32_split_kernel", kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
-                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, out, ldo, (int64_t)0, true, vec_d);
+                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, out, ldo, (int64_t)0, true);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
         } else {
             RDK_TIMED_LAUNCH("exact_f32_split_kernel", kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
-                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, w.part, ldd, (int64_t)B * ldd, false, true);
+                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, w.part, ldd, (int64_t)B * ldd, false);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
             return launch_reduce(w.part, splits, w.qstat, nullptr, h.N, B, out, ldo, st);
         }

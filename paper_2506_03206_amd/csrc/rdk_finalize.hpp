@@ -23,7 +23,6 @@ struct FinalizeArgs {
     rdk_verify_desc_t d;
     const void *p;
     int64_t ldp;
-    bool vec_p;
     const SoftStat *pstat;   // [B, p_splits] (logit p only)
     int p_splits;
     const float *part_q, *part_r, *part_a;   // [B, nblk]
@@ -104,11 +103,9 @@ struct QpMemory {
     static constexpr int kStages = 1;
     const float *q;
     int64_t ldq;
-    bool vec;
     int N;
     struct Row {
         const float *qr;
-        bool vec;
         int N;
         struct Pending {
             float4 v;
@@ -116,12 +113,12 @@ struct QpMemory {
         template <int K>
         __device__ __forceinline__ void stage(Pending &t, int64_t idx) const
         {
-            t.v = rdk::load4<RDK_PROB_F32>(qr, idx, N, vec, 0.f);
+            t.v = rdk::load4<RDK_PROB_F32>(qr, idx, N, 0.f);
         }
         __device__ __forceinline__ float4 result(Pending &t, int64_t) const { return t.v; }
         __device__ __forceinline__ float load1(int j) const { return qr[j]; }
     };
-    __device__ __forceinline__ Row row(int64_t b) const { return Row{q + b * ldq, vec, N}; }
+    __device__ __forceinline__ Row row(int64_t b) const { return Row{q + b * ldq, N}; }
 };
 
 // Runs step K of the policy on the SUB records of one block (nothing when the block is not wanted).
@@ -314,7 +311,7 @@ __global__ __launch_bounds__(kFinalizeRows * kWave) void bonus_finalize_kernel(F
             const int base = blk * BLOCK;
             float4 w[SUB];
 #pragma unroll
-            for (int i = 0; i < SUB; ++i) w[i] = load4<KIND>(pr, base + i * 256 + lane * 4, d.N, a.vec_p, pfill);
+            for (int i = 0; i < SUB; ++i) w[i] = load4<KIND>(pr, base + i * 256 + lane * 4, d.N, pfill);
 #pragma unroll
             for (int i = 0; i < SUB; ++i)
                 w[i] = make_float4(to_weight<KIND>(w[i].x, m, inv), to_weight<KIND>(w[i].y, m, inv), to_weight<KIND>(w[i].z, m, inv),
@@ -496,7 +493,7 @@ constexpr int kFinishFloats = 64;
 template <int KIND, bool SCAN, class Quads>
 __device__ __forceinline__ void finish_row_quarters(float *scratch, const float *sq, const float *sr, const float *sa, int nblk,
                                                     const FinalizeArgs &fin, int64_t row, const void *pr, float pm, float pinv,
-                                                    int N, bool vec_p, const Quads &quads, const uint32_t (&words)[4], int wid,
+                                                    int N, const Quads &quads, const uint32_t (&words)[4], int wid,
                                                     int lane)
 {
     constexpr int kBlock = 1024;
@@ -546,7 +543,7 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
     int last_pos = -1;
     if (factive) {
         typename Quads::Token t = quads.begin(fblk, fq, fidx);
-        const float4 pl = load4<KIND>(pr, fidx, N, vec_p, KIND == RDK_PROB_F32 ? 0.f : -INFINITY);
+        const float4 pl = load4<KIND>(pr, fidx, N, KIND == RDK_PROB_F32 ? 0.f : -INFINITY);
         pv4[0] = to_weight<KIND>(pl.x, pm, pinv); pv4[1] = to_weight<KIND>(pl.y, pm, pinv);
         pv4[2] = to_weight<KIND>(pl.z, pm, pinv); pv4[3] = to_weight<KIND>(pl.w, pm, pinv);
         quads.end(t, fidx, pv4, qp4);
@@ -663,7 +660,7 @@ __global__ __launch_bounds__(8 * kWave) void verify_finalize_quarters_kernel(Fin
     const typename QP::Row qrow = qp.row(row);
     const PolicyQuads<typename QP::Row, QP::kStages> quads{qrow};
     finish_row_quarters<KIND, true>(scratch, a.part_q + row * a.nblk, a.part_r + row * a.nblk, a.part_a + row * a.nblk, a.nblk, a, row, pr,
-                              m, inv, d.N, a.vec_p, quads, words, wid, lane);
+                              m, inv, d.N, quads, words, wid, lane);
 }
 
 // ---- Draft draw alone (Alg. 4 step 2 on the drafter's side, before a target row exists): one wavefront per row,

@@ -49,7 +49,7 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 template <int QK>
-__device__ __forceinline__ void stage_chunk(float *lds, const void *qr, bool vec_q, int n, float qm, const int32_t *kept, int lo,
+__device__ __forceinline__ void stage_chunk(float *lds, const void *qr, int n, float qm, const int32_t *kept, int lo,
                                             int hi, int base, float4 (&qd)[4])
 {
     const int lane = lane_id();
@@ -61,7 +61,7 @@ __device__ __forceinline__ void stage_chunk(float *lds, const void *qr, bool vec
     // the same answer for the whole wavefront.  Then the sweep over the run is uniform too: lanes past its end are
     // sent to the last quad of the row (they repeat what its own lane stores), and no load or store sits behind a
     // per-lane branch.
-    if (vec_q && ((hi + 3) & ~3) <= n) {
+    if (((hi + 3) & ~3) <= n) {
         const int last_quad = (n & ~3) - 4;
         for (int s0 = lo & ~3; s0 < hi; s0 += 4 * kWave) {
             const int s = min(s0 + lane * 4, last_quad);
@@ -85,7 +85,7 @@ __device__ __forceinline__ void stage_chunk(float *lds, const void *qr, bool vec
                 if (s + 1 < n) kv.y = kept[s + 1];
                 if (s + 2 < n) kv.z = kept[s + 2];
             }
-            const float4 qv = load4<QK>(qr, s, n, vec_q, QK == RDK_PROB_F32 ? 0.f : -INFINITY);
+            const float4 qv = load4<QK>(qr, s, n, QK == RDK_PROB_F32 ? 0.f : -INFINITY);
             const int ke[4] = {kv.x, kv.y, kv.z, kv.w};
             const float qe[4] = {qv.x, qv.y, qv.z, qv.w};
 #pragma unroll
@@ -112,7 +112,7 @@ template <int PK, int QK, bool KEEP_P>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void taylor_stats_kernel(
     const void *p, int64_t ldp, const void *q, int64_t ldq,
                                                                 const int32_t *kept, const int32_t *chunk_lo, int N, int n,
-                                                                int splits, bool vec_p, bool vec_q, LinearWs w)
+                                                                int splits, LinearWs w)
 {
     __shared__ __attribute__((aligned(16))) float qchunk[kWaves][kChunk + kWave];
     const int64_t row = blockIdx.x / splits;
@@ -143,13 +143,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     for (; c < c_end; c += kWaves) {
         const int base = c * kChunk;
         float4 pv[4], qd[4];
-        load_chunk<PK, !KEEP_P>(pr, base, N, vec_p, pfill, pv);
+        load_chunk<PK, !KEEP_P>(pr, base, N, pfill, pv);
         const int lo_now = lo, hi_now = hi;
         if (c + kWaves < c_end) {
             lo = chunk_lo[c + kWaves];
             hi = chunk_lo[c + kWaves + 1];
         }
-        stage_chunk<QK>(qchunk[wid], qr, vec_q, n, qm, kept, lo_now, hi_now, base, qd);
+        stage_chunk<QK>(qchunk[wid], qr, n, qm, kept, lo_now, hi_now, base, qd);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const float pe[4] = {to_weight<PK>(pv[i].x, pm, pinv), to_weight<PK>(pv[i].y, pm, pinv),
@@ -197,7 +197,7 @@ constexpr int kOnePassMinN = 1024;
 template <int PK, int QK, bool KEEP_P>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void taylor_stats_onepass_kernel(
     const void *p, int64_t ldp, const void *q, int64_t ldq, const int32_t *kept, const int32_t *chunk_lo, int N, int n,
-    int splits, bool vec_p, bool vec_q, LinearWs w)
+    int splits, LinearWs w)
 {
     static_assert(PK != RDK_PROB_F32, "probabilities need no normaliser: the two-pass kernel serves them");
     __shared__ __attribute__((aligned(16))) float qchunk[kWaves][kChunk + kWave];
@@ -221,13 +221,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     for (; c < c_end; c += kWaves) {
         const int base = c * kChunk;
         float4 pv[4], qd[4];
-        load_chunk<PK, !KEEP_P>(pr, base, N, vec_p, -INFINITY, pv);
+        load_chunk<PK, !KEEP_P>(pr, base, N, -INFINITY, pv);
         const int lo_now = lo, hi_now = hi;
         if (c + kWaves < c_end) {
             lo = chunk_lo[c + kWaves];
             hi = chunk_lo[c + kWaves + 1];
         }
-        stage_chunk<QK>(qchunk[wid], qr, vec_q, n, qm, kept, lo_now, hi_now, base, qd);
+        stage_chunk<QK>(qchunk[wid], qr, n, qm, kept, lo_now, hi_now, base, qd);
         float cm = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; ++i) cm = fmaxf(cm, fmaxf(fmaxf(pv[i].x, pv[i].y), fmaxf(pv[i].z, pv[i].w)));
@@ -284,7 +284,6 @@ struct TaylorArgs {
     int64_t ldp, ldq;
     const int32_t *slot_of, *kept, *chunk_lo;
     int N, n, splits;
-    bool vec_p, vec_q;
     bool onepass;   // the first pass was the one-pass kernel: tpart holds its eight-word records
     LinearWs w;
 };
@@ -294,7 +293,6 @@ struct TaylorRow {
     const void *pr, *qr;
     const int32_t *slot_of;
     int N;
-    bool vec_p;
     float pm, pinv, qm, inv_zq, theta, inv_S, fN, nzs, ths;   // nzs = N / (Zq S), ths = theta / S
 
     // Eq. 3 for one id: qh = unnormalised drafter weight of the id (0 if it is not kept), pe = its target weight
@@ -313,7 +311,7 @@ struct TaylorRow {
     __device__ __forceinline__ void stage(Pending &t, int64_t idx) const
     {
         if (K == 0) {
-            t.pv = rdk::load4<PK>(pr, idx, N, vec_p, PK == RDK_PROB_F32 ? 0.f : -INFINITY);
+            t.pv = rdk::load4<PK>(pr, idx, N, PK == RDK_PROB_F32 ? 0.f : -INFINITY);
             t.sv = make_int4(-1, -1, -1, -1);
             if (idx + 3 < N) {
                 t.sv = *(const int4 *)(slot_of + idx);
@@ -358,7 +356,6 @@ __device__ __forceinline__ TaylorRow<PK, QK> make_taylor_row(const TaylorArgs &a
     r.qr = row_ptr<QK>(a.q, a.ldq, row);
     r.slot_of = a.slot_of;
     r.N = a.N;
-    r.vec_p = a.vec_p;
     r.pm = 0.f;
     r.pinv = 1.f;
     if (PK != RDK_PROB_F32) {
@@ -408,7 +405,7 @@ __device__ __forceinline__ TaylorRow<PK, QK> make_taylor_row(const TaylorArgs &a
 // is decided at run time, so that the sums do not depend on it by a single bit.
 template <int PK, int QK, bool FUSE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void taylor_write_kernel(
-    TaylorArgs a, bool vec_o, float *out, int64_t ldo, float *part_q,
+    TaylorArgs a, float *out, int64_t ldo, float *part_q,
                                                                 float *part_r, float *part_a)
 {
     __shared__ __attribute__((aligned(16))) float qchunk[kWaves][kChunk + kWave];
@@ -430,15 +427,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     for (; c < c_end; c += kWaves) {
         const int base = c * kChunk;
         float4 pv[4], qd[4];
-        load_chunk<PK>(tr.pr, base, a.N, a.vec_p, pfill, pv);
+        load_chunk<PK>(tr.pr, base, a.N, pfill, pv);
         const int lo_now = lo, hi_now = hi;
         if (c + kWaves < c_end) {
             lo = a.chunk_lo[c + kWaves];
             hi = a.chunk_lo[c + kWaves + 1];
         }
-        stage_chunk<QK>(qchunk[wid], tr.qr, a.vec_q, a.n, tr.qm, a.kept, lo_now, hi_now, base, qd);
+        stage_chunk<QK>(qchunk[wid], tr.qr, a.n, tr.qm, a.kept, lo_now, hi_now, base, qd);
         float sq = 0.f, sr = 0.f, sa = 0.f;
-        const bool full_o = vec_o && base + kChunk <= a.N;   // the whole chunk is stored with 16-byte stores
+        const bool full_o = base + kChunk <= a.N;   // the whole chunk is stored with 16-byte stores
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t idx = (int64_t)base + i * 256 + lane * 4;
@@ -453,7 +450,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
             }
             if (orow) {
                 if (full_o) {
-                    *(float4 *)(orow + idx) = make_float4(oe[0], oe[1], oe[2], oe[3]);
+                    store4(orow + idx, oe[0], oe[1], oe[2], oe[3]);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -630,13 +627,12 @@ template <int PK, int QK, bool SCAN, class RCP>
 __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, int l_sum_r, int l_sum_a,
                                            const FinalizeArgs &fin, int64_t row, int nchunks,
                                            const void *pr, float pm, float pinv, const void *qr, float qm,
-                                           const uint64_t *lane_map, const int32_t *chunk_lo, const int32_t *slot_of, int N,
-                                           bool vec_p, float nzs, float ths, const RCP &rcp, int wid, int lane)
+                                           const uint64_t *lane_map, const int32_t *chunk_lo, const int32_t *slot_of, int N, float nzs, float ths, const RCP &rcp, int wid, int lane)
 {
     const uint32_t *fw = (const uint32_t *)(lds + l_fin + kFinishFloats);
     const uint32_t words[4] = {fw[0], fw[1], fw[2], fw[3]};
     const Eq3Quads<QK, RCP> quads{lane_map, chunk_lo, slot_of, qr, qm, nzs, ths, rcp, N};
-    finish_row_quarters<PK, SCAN>(lds + l_fin, lds + l_sum_q, lds + l_sum_r, lds + l_sum_a, nchunks, fin, row, pr, pm, pinv, N, vec_p,
+    finish_row_quarters<PK, SCAN>(lds + l_fin, lds + l_sum_q, lds + l_sum_r, lds + l_sum_a, nchunks, fin, row, pr, pm, pinv, N,
                             quads, words, wid, lane);
 }
 
@@ -977,7 +973,7 @@ template <int PK, int QK, Powers POW, int T>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void taylor_row_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
                                                                        const uint64_t *lane_map, const uint64_t *row_masks,
                                                                        const int32_t *chunk_lo, const int32_t *item_lo, const int2 *row_items,
-                                                                       int N, int n, bool vec_p, const int32_t *slot_of,
+                                                                       int N, int n, const int32_t *slot_of,
                                                                        FinalizeArgs fin)
 {
     constexpr bool CUBIC = POW == Powers::Cubic;
@@ -1230,7 +1226,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
 
     // ---- the finish of the row (draws, accept test), spread over the wavefronts
     row_finish<PK, QK, T == kRowThreads>(lds, L.fin, L.sum_q, L.sum_r, L.sum_a, fin, row, nchunks, pr, pm, pinv, qr, qm, lane_map,
-                                         chunk_lo, slot_of, N, vec_p, nzs, ths, rcp, wid, lane);
+                                         chunk_lo, slot_of, N, nzs, ths, rcp, wid, lane);
 }
 
 // Below these batches the two-pass kernels, which split a row over workgroups, fill the chip better.  A longer row takes longer
@@ -1312,11 +1308,10 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
                 halves = 2 * align_up(half_bytes, 2048) <= row_lds_limit();
                 if (halves) lds_bytes = half_bytes;
             }
-            const bool vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
             if (q.kind != RDK_LOGIT_BF16 && ((uintptr_t)q.ptr % 4 != 0)) return RDK_ERR_ALIGN;
             FinalizeArgs fa{};                // the block sums stay in the workgroup's LDS
             fa.d = c->d;
-            fa.p = p.ptr; fa.ldp = p.ld; fa.vec_p = vec_p;
+            fa.p = p.ptr; fa.ldp = p.ld;
             fa.pstat = w.pstat; fa.p_splits = w.p_splits;
             fa.nblk = nchunks;
             fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
@@ -1331,7 +1326,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         if (rc != RDK_OK) return rc;                                                                                        \
         RDK_TIMED_LAUNCH("taylor_row_kernel", (taylor_row_kernel<PK, QK, POW, THREADS>), dim3((unsigned)B), dim3(THREADS),  \
                          lds_bytes, st, p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.row_masks, h.chunk_lo, h.item_lo, h.row_items, \
-                         h.N, h.n, vec_p, h.slot_of, fa);                                                                             \
+                         h.N, h.n, h.slot_of, fa);                                                                             \
     }
             constexpr Powers kSmall = PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
             if (pow == Powers::Series) {
@@ -1359,16 +1354,13 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     TaylorArgs a;
     a.p = p.ptr; a.q = q.ptr; a.ldp = p.ld; a.ldq = q.ld;
     a.slot_of = h.slot_of; a.kept = h.kept_ids; a.chunk_lo = h.chunk_lo; a.N = h.N; a.n = h.n; a.splits = w.t_splits;
-    a.vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
-    a.vec_q = rows_vectorisable(q.ptr, q.ld, q.kind);
     a.onepass = onepass;
     a.w = w;
-    const bool vec_o = out ? rows_vectorisable(out, ldo, RDK_PROB_F32) : false;
     // first pass: one-pass or two-pass statistics; in the fused call (c != NULL) it leaves the target rows cacheable
     const dim3 grid((unsigned)B * w.t_splits);
 #define RDK_LAUNCH_STATS(KERNEL)                                                                                         \
     RDK_TIMED_LAUNCH("taylor_stats_kernel", KERNEL, grid, dim3(kThreads), 0, st, p.ptr, p.ld, q.ptr, q.ld, h.kept_ids,  \
-                     h.chunk_lo, h.N, h.n, w.t_splits, a.vec_p, a.vec_q, w)
+                     h.chunk_lo, h.N, h.n, w.t_splits, w)
     bool launched = false;
     if constexpr (PK != RDK_PROB_F32) {
         if (onepass) {
@@ -1385,7 +1377,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     RDK_LAUNCH_CHECK("taylor_stats_kernel");
     if (!c) {
         {
-            RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, false>), grid, dim3(kThreads), 0, st, a, vec_o,
+            RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, false>), grid, dim3(kThreads), 0, st, a,
                              out, ldo, (float *)nullptr, (float *)nullptr, (float *)nullptr);
         }
         RDK_LAUNCH_CHECK("taylor_write_kernel");
@@ -1393,13 +1385,13 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     }
     float *part_q = (float *)fused_ws, *part_r = (float *)(fused_ws + per), *part_a = (float *)(fused_ws + 2 * per);
     {
-        RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, true>), grid, dim3(kThreads), 0, st, a, vec_o, out,
+        RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, true>), grid, dim3(kThreads), 0, st, a, out,
                          ldo, part_q, part_r, part_a);
     }
     RDK_LAUNCH_CHECK("taylor_write_kernel");
     FinalizeArgs fa{};
     fa.d = c->d;
-    fa.p = p.ptr; fa.ldp = p.ld; fa.vec_p = a.vec_p;
+    fa.p = p.ptr; fa.ldp = p.ld;
     fa.pstat = w.pstat; fa.p_splits = w.p_splits;
     fa.part_q = part_q; fa.part_r = part_r; fa.part_a = part_a;
     fa.nblk = nchunks;

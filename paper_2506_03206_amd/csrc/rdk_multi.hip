@@ -28,10 +28,8 @@ struct MultiArgs {
     rdk_multi_desc_t d;
     const void *p;
     int64_t ldp;
-    bool vec_p;
     const float *q;
     int64_t ldq;
-    bool vec_q;
     const SoftStat *pstat;   // [B, p_splits] (logit p only)
     int p_splits;
     int32_t *cand_ids, *accepted, *token;
@@ -59,7 +57,6 @@ struct MultiRow {
     const void *pr;
     const float *qr;
     int N;
-    bool vec_p, vec_q;
     float m, inv, pfill;
 
     // sum of the weights of one block, from its values in registers
@@ -91,9 +88,9 @@ struct MultiRow {
         for (int k = first + wid; k < nblk; k += kMultiWaves) {
             const int c = back ? nblk - 1 - (k - first) : k;
             float4 pv[4], qv[4];
-            if (RESID) load_chunk<KIND, false>(pr, (int64_t)c * kChunk, N, vec_p, pfill, pv);
+            if (RESID) load_chunk<KIND, false>(pr, (int64_t)c * kChunk, N, pfill, pv);
             if (WITH_Q) {
-                load_chunk<RDK_PROB_F32, false>(qr, (int64_t)c * kChunk, N, vec_q, 0.f, qv);
+                load_chunk<RDK_PROB_F32, false>(qr, (int64_t)c * kChunk, N, 0.f, qv);
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -118,10 +115,10 @@ struct MultiRow {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t idx = (int64_t)b * kChunk + i * 256 + lane * 4;
-            const float4 q4 = load4<RDK_PROB_F32>(qr, idx, N, vec_q, 0.f);
+            const float4 q4 = load4<RDK_PROB_F32>(qr, idx, N, 0.f);
             float4 p4 = make_float4(0.f, 0.f, 0.f, 0.f);
             if (RESID) {
-                const float4 raw = load4<KIND>(pr, idx, N, vec_p, pfill);
+                const float4 raw = load4<KIND>(pr, idx, N, pfill);
                 p4 = make_float4(to_weight<KIND>(raw.x, m, inv), to_weight<KIND>(raw.y, m, inv), to_weight<KIND>(raw.z, m, inv),
                                  to_weight<KIND>(raw.w, m, inv));
             }
@@ -150,8 +147,6 @@ __global__ __launch_bounds__(kMultiThreads) void verify_multi_kernel(MultiArgs a
     r.pr = row_ptr<KIND>(a.p, a.ldp, row);
     r.qr = a.q + row * a.ldq;
     r.N = N;
-    r.vec_p = a.vec_p;
-    r.vec_q = a.vec_q;
     r.m = 0.f;
     r.inv = 1.f;
     if (KIND != RDK_PROB_F32) {
@@ -214,8 +209,8 @@ __global__ __launch_bounds__(kMultiThreads) void verify_multi_kernel(MultiArgs a
         wb = cb + 1.f;
         if (wid < nblk) {
             if (!any_pass) {
-                load_chunk<KIND, false>(r.pr, (int64_t)wid * kChunk, N, r.vec_p, r.pfill, hp);
-                load_chunk<RDK_PROB_F32, false>(r.qr, (int64_t)wid * kChunk, N, r.vec_q, 0.f, hq);
+                load_chunk<KIND, false>(r.pr, (int64_t)wid * kChunk, N, r.pfill, hp);
+                load_chunk<RDK_PROB_F32, false>(r.qr, (int64_t)wid * kChunk, N, 0.f, hq);
             }
             r.template block_sum<true>(hp, hq, wa, wb, blk + wid);
         }
@@ -322,8 +317,8 @@ rdk_status_t launch_verify_multi(const rdk_multi_desc_t &d, RowInput p, const fl
 {
     MultiArgs a{};
     a.d = d;
-    a.p = p.ptr; a.ldp = p.ld; a.vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
-    a.q = q_prime; a.ldq = ldq; a.vec_q = rows_vectorisable(q_prime, ldq, RDK_PROB_F32);
+    a.p = p.ptr; a.ldp = p.ld;
+    a.q = q_prime; a.ldq = ldq;
     a.cand_ids = cand_ids; a.accepted = accepted; a.token = token; a.resid_mass = resid_mass;
     switch (p.kind) {
         case RDK_PROB_F32: return run_multi<RDK_PROB_F32>(a, p, ws, st);

@@ -9,7 +9,7 @@ namespace rdk {
 constexpr int kStatThreads = 256;
 
 template <int KIND>
-__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, int64_t ld, int64_t len, int splits, bool vec,
+__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, int64_t ld, int64_t len, int splits,
                                                                  SoftStat *out)
 {
     constexpr int kWaves = kStatThreads / kWave;
@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, 
     st.s = 0.f;
     for (int c = c_begin + wid; c < c_end; c += kWaves) {
         float4 v[4];   // kept cacheable: the kernels that follow read the same rows again
-        load_chunk<KIND, false>(xr, (int64_t)c * kChunk, len, vec, KIND == RDK_PROB_F32 ? 0.f : -INFINITY, v);
+        load_chunk<KIND, false>(xr, (int64_t)c * kChunk, len, KIND == RDK_PROB_F32 ? 0.f : -INFINITY, v);
         if (KIND == RDK_PROB_F32) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) st.s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
@@ -84,7 +84,7 @@ inline rdk_status_t launch_row_stats(RowInput x, int64_t len, int32_t B, int spl
 {
     {
         RDK_TIMED_LAUNCH("row_stats_kernel", (row_stats_kernel<KIND>), dim3((unsigned)B * splits), dim3(kStatThreads), 0, st,
-                         x.ptr, x.ld, len, splits, rows_vectorisable(x.ptr, x.ld, x.kind), out);
+                         x.ptr, x.ld, len, splits, out);
     }
     RDK_LAUNCH_CHECK("row_stats_kernel");
     return RDK_OK;

@@ -41,7 +41,6 @@ inline size_t slab_lds_bytes(int n, int nblk_finish)
 struct SlabArgs {
     const void *q;
     int64_t ldq;
-    bool vec_q;
     SparseTables t;
     const int32_t *pruned_ids, *kept_ids;
     int n, B;
@@ -49,7 +48,6 @@ struct SlabArgs {
     SoftStat *qrow;
     float *out;
     int64_t ldo;
-    bool vec_o;
 };
 
 __device__ __forceinline__ void wave_lds_sync()
@@ -112,12 +110,12 @@ struct SlabRow {
                 const uint16_t *r = (const uint16_t *)qr + s;
                 constexpr uint32_t kNone = 0xFF80u;                  // -infinity
                 quad[v] = make_uint2(kNone | kNone << 16, kNone | kNone << 16);
-                if (a.vec_q && s + 3 < a.n) quad[v] = *(const uint2 *)r;
+                if (s + 3 < a.n) quad[v] = make_uint2(((const u32x2_any *)r)->x, ((const u32x2_any *)r)->y);
                 else if (s < a.n)
                     quad[v] = make_uint2(r[0] | (s + 1 < a.n ? r[1] : kNone) << 16, (s + 2 < a.n ? r[2] : kNone) | (s + 3 < a.n ? r[3] : kNone) << 16);
             } else {
                 quad[v] = make_float4(fill, fill, fill, fill);
-                if (s < a.n) quad[v] = load4<QK>(qr, s, a.n, a.vec_q, fill);
+                if (s < a.n) quad[v] = load4<QK>(qr, s, a.n, fill);
             }
         }
     }
@@ -162,14 +160,14 @@ __device__ __forceinline__ void slab_fill(int n, const SlabRow<QK> &row, float *
 
 // Softmax maximum and normaliser of a whole logit target row, by the workgroup (the row comes from L2 a second time later).
 template <int KIND>
-__device__ __forceinline__ SoftStat row_soft_stat(const void *pr, int N, bool vec, float *red)
+__device__ __forceinline__ SoftStat row_soft_stat(const void *pr, int N, float *red)
 {
     float m = -INFINITY;
-    for (int j = threadIdx.x * 4; j < N; j += kSlabThreads * 4) m = fmaxf(m, max4(load4<KIND>(pr, j, N, vec, -INFINITY)));
+    for (int j = threadIdx.x * 4; j < N; j += kSlabThreads * 4) m = fmaxf(m, max4(load4<KIND>(pr, j, N, -INFINITY)));
     m = block_max(m, red);
     float s = 0.f;
     for (int j = threadIdx.x * 4; j < N; j += kSlabThreads * 4) {
-        const float4 x = load4<KIND>(pr, j, N, vec, -INFINITY);
+        const float4 x = load4<KIND>(pr, j, N, -INFINITY);
         s += (soft_exp(x.x - m) + soft_exp(x.y - m)) + (soft_exp(x.z - m) + soft_exp(x.w - m));
     }
     return SoftStat{m, block_sum(s, red + kSlabWaves)};
@@ -238,7 +236,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_product_kernel(SlabArgs a, 
         u_lo = lo;
         u_hi = hi;
         if (FUSE) {
-            if (T == 256) praw = load4<PKIND>(pr, t * T + 4 * lane, N, f.vec_p, pfill);
+            if (T == 256) praw = load4<PKIND>(pr, t * T + 4 * lane, N, pfill);
             else praw.x = t * T + lane < N ? load1<PKIND>(pr, t * T + lane) : pfill;
         }
         const int s = min(min(t * T, N) - lo + lane, a.n - 1);
@@ -267,7 +265,7 @@ __global__ __launch_bounds__(kSlabThreads) void slab_product_kernel(SlabArgs a, 
     if (!FIN && split == 0 && threadIdx.x == 0) a.qrow[b] = SoftStat{qmax, zinv};
     float pm = 0.f, pinv = 1.f;
     if (FUSE && PKIND != RDK_PROB_F32) {
-        const SoftStat rs = FIN ? row_soft_stat<PKIND>(pr, N, f.vec_p, red + 2 * kSlabWaves) : wave_soft_merge(pstat);
+        const SoftStat rs = FIN ? row_soft_stat<PKIND>(pr, N, red + 2 * kSlabWaves) : wave_soft_merge(pstat);
         pm = rs.m;
         pinv = 1.0f / rs.s;
         if (!FIN && split == 0 && threadIdx.x == 0) f.pmerged[b] = rs;
@@ -291,9 +289,9 @@ __global__ __launch_bounds__(kSlabThreads) void slab_product_kernel(SlabArgs a, 
         wave_lds_sync();   // the next tile is staged over this one
         if (a.out != nullptr) {
             float *dst = a.out + (int64_t)b * a.ldo + jl;
-            if (T == 256 && a.vec_o && jl + 3 < N) {
-                const f32x4 v = {qv[0], qv[1], qv[2], qv[3]};
-                __builtin_nontemporal_store(v, (f32x4 *)dst);
+            if (T == 256 && jl + 3 < N) {
+                const f32x4_any v = {qv[0], qv[1], qv[2], qv[3]};
+                __builtin_nontemporal_store(v, (f32x4_any *)dst);
             } else {
 #pragma unroll
                 for (int e = 0; e < (T == 256 ? 4 : 1); ++e)
@@ -498,13 +496,13 @@ rdk_status_t launch_slab_product(const KernelHandle &h, RowInput q, int32_t B, f
 {
     const SlabPlan p = slab_plan(h, B);
     SlabArgs a{};
-    a.q = q.ptr; a.ldq = q.ld; a.vec_q = rows_vectorisable(q.ptr, q.ld, q.kind);
+    a.q = q.ptr; a.ldq = q.ld;
     a.t = tables_of(h);
     a.pruned_ids = h.pruned_ids; a.kept_ids = h.kept_ids;
     a.n = h.n; a.B = B;
     a.splits = p.splits; a.tiles = p.tiles; a.tiles_per_split = p.tiles_per_split;
     a.qrow = qrow;
-    a.out = out; a.ldo = ldo; a.vec_o = out ? rows_vectorisable(out, ldo, RDK_PROB_F32) : false;
+    a.out = out; a.ldo = ldo;
     switch (q.kind) {
         case RDK_PROB_F32: return launch_kind<RDK_PROB_F32>(kind, p, a, f, fin, draft, st);
         case RDK_LOGIT_F32: return launch_kind<RDK_LOGIT_F32>(kind, p, a, f, fin, draft, st);

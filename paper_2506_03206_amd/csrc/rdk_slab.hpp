@@ -113,7 +113,6 @@ struct QpSparse {
 struct FuseArgs {
     const void *p;
     int64_t ldp;
-    bool vec_p;
     const SoftStat *pstat;             // softmax statistics of logit target rows, p_splits partials per row
     int p_splits;
     SoftStat *pmerged;                 // [B]: the merged pair of each row, written by the product out of LDS

@@ -66,7 +66,7 @@ __device__ __forceinline__ float oct_sum(float v)
 // threads per row, eight tiles of 64 slots each, all loads of a workgroup requested before the first is used).
 template <int QK>
 __global__ __launch_bounds__(kPrepThreads) void q_transpose_kernel(const void *q, int64_t ldq, int n, int B,
-                                                                   const SoftStat *qpart, int q_splits, bool vec, float *zpart,
+                                                                   const SoftStat *qpart, int q_splits, float *zpart,
                                                                    int zt, float *qT, const SoftStat *pstat, int p_splits,
                                                                    SoftStat *pmerged)
 {
@@ -114,8 +114,8 @@ __global__ __launch_bounds__(kPrepThreads) void q_transpose_kernel(const void *q
             if (b < B) {
                 const void *qr = row_ptr<QK>(q, ldq, b);
                 const int s = g0 + t * kTSlots + part * 4;   // the eight threads of a row read 128 contiguous bytes per load
-                raw[t][0] = load4<QK>(qr, s, n, vec, fill);
-                raw[t][1] = load4<QK>(qr, s + 32, n, vec, fill);
+                raw[t][0] = load4<QK>(qr, s, n, fill);
+                raw[t][1] = load4<QK>(qr, s + 32, n, fill);
             }
         }
         float z = 0.f;
@@ -187,7 +187,6 @@ struct SparseArgs {
     int tiles, per_xcd, total_work;
     float *out;
     int64_t ldo;
-    bool vec_o;
 };
 
 // Number of pruned ids below target id j (j may be N).
@@ -327,10 +326,10 @@ __global__ __launch_bounds__(kThreads) void sparse_product_kernel(SparseArgs a, 
             // streamed past the caches' replacement order: the L2 of this XCD should keep the drafter slab instead
             if (b >= a.B)
                 praw[rr] = make_float4(pfill, pfill, pfill, pfill);
-            else if (f.vec_p && whole_tile)
+            else if (whole_tile)
                 praw[rr] = load4_full<PKIND, true>(row_ptr<PKIND>(f.p, f.ldp, b), jl);
             else
-                praw[rr] = load4<PKIND>(row_ptr<PKIND>(f.p, f.ldp, b), jl, a.N, f.vec_p, pfill);
+                praw[rr] = load4<PKIND>(row_ptr<PKIND>(f.p, f.ldp, b), jl, a.N, pfill);
         }
     }
     // Eq. 1: the row sums of the four rows this wavefront finishes, from the partials of the transposition (asked for now)
@@ -354,9 +353,9 @@ __global__ __launch_bounds__(kThreads) void sparse_product_kernel(SparseArgs a, 
                              jl + 2 < a.N ? sv.z * inv_z : 0.f, jl + 3 < a.N ? sv.w * inv_z : 0.f};
         if (WRITE_Q) {
             float *o = a.out + b * a.ldo + jl;
-            if (a.vec_o && whole_tile) {
-                const f32x4 v = {qv[0], qv[1], qv[2], qv[3]};
-                __builtin_nontemporal_store(v, (f32x4 *)o);
+            if (whole_tile) {
+                const f32x4_any v = {qv[0], qv[1], qv[2], qv[3]};
+                __builtin_nontemporal_store(v, (f32x4_any *)o);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -486,7 +485,7 @@ SparseArgs make_args(const KernelHandle &h, const SparseWs &w, int32_t B, float 
     a.tiles = (h.N + kTileIds - 1) / kTileIds;
     a.total_work = pbs * a.tiles;
     a.per_xcd = (a.total_work + 7) / 8;
-    a.out = out; a.ldo = ldo; a.vec_o = out ? rows_vectorisable(out, ldo, RDK_PROB_F32) : false;
+    a.out = out; a.ldo = ldo;
     return a;
 }
 
@@ -501,7 +500,7 @@ rdk_status_t prepare_q(const KernelHandle &h, RowInput q, int32_t B, const Spars
     const int pbs = (B + kPosBlock - 1) / kPosBlock;
     {
         RDK_TIMED_LAUNCH("q_transpose_kernel", (q_transpose_kernel<QK>), dim3(w.zt, pbs), dim3(kPrepThreads), 0, st,
-                         q.ptr, q.ld, h.n, B, w.qpart, w.q_splits, rows_vectorisable(q.ptr, q.ld, q.kind), w.zpart, w.zt, w.qT, pstat, p_splits,
+                         q.ptr, q.ld, h.n, B, w.qpart, w.q_splits, w.zpart, w.zt, w.qT, pstat, p_splits,
                          pmerged);
     }
     RDK_LAUNCH_CHECK("q_transpose_kernel");
@@ -532,7 +531,7 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     SparseWs w = carve(h, B, ws);
     char *p = (char *)ws + sparse_workspace_bytes(h, B);
     FuseArgs f{};
-    f.p = c.p.ptr; f.ldp = c.p.ld; f.vec_p = rows_vectorisable(c.p.ptr, c.p.ld, c.p.kind);
+    f.p = c.p.ptr; f.ldp = c.p.ld;
     const int p_splits = row_splits(B, h.N, kStatThreads / kWave);
     SoftStat *ppart = (SoftStat *)p; p += align_up((size_t)B * kMaxSplits * sizeof(SoftStat), 256);   // partials per split
     SoftStat *pmerged = (SoftStat *)p; p += align_up((size_t)B * sizeof(SoftStat), 256);              // one per row
@@ -551,7 +550,7 @@ rdk_status_t run_sparse_fused(const KernelHandle &h, const FusedCall &c, void *w
     }
     FinalizeArgs fa{};
     fa.d = c.d;
-    fa.p = c.p.ptr; fa.ldp = c.p.ld; fa.vec_p = f.vec_p;
+    fa.p = c.p.ptr; fa.ldp = c.p.ld;
     fa.pstat = pmerged; fa.p_splits = 1;
     fa.part_q = f.part_q; fa.part_r = f.part_r; fa.part_a = f.part_a;
     fa.nblk = (int)blocks;

@@ -52,7 +52,7 @@ VerifyWs carve(const rdk_verify_desc_t &d, void *ws, size_t ws_bytes)
 // ------------------------------------------------------------------------------------------------
 template <int KIND, bool HAS_Q>
 __global__ __launch_bounds__(kStreamThreads) void verify_stream_kernel(const void *p, int64_t ldp, const float *q, int64_t ldq,
-                                                                       int N, int splits, bool vec_p, bool vec_q, VerifyWs w)
+                                                                       int N, int splits, VerifyWs w)
 {
     const int64_t row = blockIdx.x / splits;
     const int split = blockIdx.x % splits;
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kStreamThreads) void verify_stream_kernel(const voi
 
     for (int c = c_begin + wid; c < c_end; c += kWavesPerBlock) {
         float4 pv[4], qv[4];
-        load_chunk<KIND>(pr, (int64_t)c * kChunk, N, vec_p, pfill, pv);
-        if (HAS_Q) load_chunk<RDK_PROB_F32>(qr, (int64_t)c * kChunk, N, vec_q, 0.f, qv);
+        load_chunk<KIND>(pr, (int64_t)c * kChunk, N, pfill, pv);
+        if (HAS_Q) load_chunk<RDK_PROB_F32>(qr, (int64_t)c * kChunk, N, 0.f, qv);
         float sq = 0.f, sr = 0.f, sa = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -165,7 +165,7 @@ __device__ __forceinline__ void row_stat_chunk(const typename RawQuad<KIND>::typ
 
 template <int KIND, int T>
 __global__ __launch_bounds__(T) void verify_row_kernel(const void *p, int64_t ldp, const float *q, int64_t ldq, int N,
-                                                                 int nchunks, bool vec_p, bool vec_q, FinalizeArgs fin)
+                                                                 int nchunks, FinalizeArgs fin)
 {
     constexpr int kRowWaves = T / kWave;
     __shared__ __attribute__((aligned(16))) float sums[3][kRowMaxChunks];   // of q', max(0, p - q'), min(p, q') per chunk
@@ -240,9 +240,9 @@ __global__ __launch_bounds__(T) void verify_row_kernel(const void *p, int64_t ld
         }
     }
     __syncthreads();
-    const QpMemory::Row qrow{qr, vec_q, N};
+    const QpMemory::Row qrow{qr, N};
     const PolicyQuads<QpMemory::Row, QpMemory::kStages> quads{qrow};
-    finish_row_quarters<KIND, true>(scratch, sums[0], sums[1], sums[2], nchunks, fin, row, pr, pm, pinv, N, vec_p, quads, words, wid, lane);
+    finish_row_quarters<KIND, true>(scratch, sums[0], sums[1], sums[2], nchunks, fin, row, pr, pm, pinv, N, quads, words, wid, lane);
 }
 
 }  // namespace
@@ -313,11 +313,9 @@ rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, 
                         int32_t *out_tokens, void *ws, size_t ws_bytes, hipStream_t st)
 {
     VerifyWs w = carve(d, ws, ws_bytes);
-    const bool vec_p = rows_vectorisable(p.ptr, p.ld, p.kind);
-    const bool vec_q = HAS_Q ? rows_vectorisable(q, ldq, RDK_PROB_F32) : false;
     FinalizeArgs fa{};
     fa.d = d;
-    fa.p = p.ptr; fa.ldp = p.ld; fa.vec_p = vec_p;
+    fa.p = p.ptr; fa.ldp = p.ld;
     fa.pstat = w.pstat; fa.p_splits = w.stat_splits;
     fa.part_q = w.part_q; fa.part_r = w.part_r; fa.part_a = w.part_a;
     fa.nblk = w.nchunks;
@@ -329,10 +327,10 @@ rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, 
             // more rows than compute units: workgroups of half the size, two on a unit (512 rows of 1000 ids 14.1 -> 9.1 us)
             if (d.B <= kComputeUnits)
                 RDK_TIMED_LAUNCH("verify_stream_kernel", (verify_row_kernel<KIND, 1024>), dim3((unsigned)d.B), dim3(1024), 0, st, p.ptr, p.ld,
-                                 q, ldq, d.N, w.nchunks, vec_p, vec_q, fa);
+                                 q, ldq, d.N, w.nchunks, fa);
             else
                 RDK_TIMED_LAUNCH("verify_stream_kernel", (verify_row_kernel<KIND, 512>), dim3((unsigned)d.B), dim3(512), 0, st, p.ptr, p.ld, q,
-                                 ldq, d.N, w.nchunks, vec_p, vec_q, fa);
+                                 ldq, d.N, w.nchunks, fa);
             RDK_LAUNCH_CHECK("verify_row_kernel");
             return scan_if_left(fa, st);
         }
@@ -344,16 +342,16 @@ rdk_status_t run_verify(const rdk_verify_desc_t &d, RowInput p, const float *q, 
     }
     {
         RDK_TIMED_LAUNCH("verify_stream_kernel", (verify_stream_kernel<KIND, HAS_Q>), dim3((unsigned)d.B * splits),
-                         dim3(kStreamThreads), 0, st, p.ptr, p.ld, q, ldq, d.N, splits, vec_p, vec_q, w);
+                         dim3(kStreamThreads), 0, st, p.ptr, p.ld, q, ldq, d.N, splits, w);
     }
     RDK_LAUNCH_CHECK("verify_stream_kernel");
-    QpMemory qp{q, ldq, vec_q, d.N};
+    QpMemory qp{q, ldq, d.N};
     return launch_finalize<KIND, 1024, HAS_Q, QpMemory>(fa, qp, w.seq_rec, st);
 }
 
 // Sums of each 1024-id block of materialised rows (the draft draw from a q' that sits in memory).
 __global__ __launch_bounds__(kStreamThreads) void row_block_sums_kernel(const float *q, int64_t ldq, int N, int nchunks, int splits,
-                                                                        bool vec_q, float *part_q)
+                                                                        float *part_q)
 {
     const int64_t row = blockIdx.x / splits;
     const int split = blockIdx.x % splits;
@@ -363,7 +361,7 @@ __global__ __launch_bounds__(kStreamThreads) void row_block_sums_kernel(const fl
     const int wid = threadIdx.x / kWave, lane = lane_id();
     for (int c = c_begin + wid; c < c_end; c += kWavesPerBlock) {
         float4 qv[4];
-        load_chunk<RDK_PROB_F32>(qr, (int64_t)c * kChunk, N, vec_q, 0.f, qv);
+        load_chunk<RDK_PROB_F32>(qr, (int64_t)c * kChunk, N, 0.f, qv);
         float sq = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) sq += (qv[i].x + qv[i].y) + (qv[i].z + qv[i].w);
@@ -381,13 +379,12 @@ rdk_status_t launch_draft_from_rows(const float *q_prime, int64_t ldq, int32_t B
 {
     const int nchunks = chunks_of(N);
     const int splits = row_splits(B, N, kWavesPerBlock);
-    const bool vec_q = rows_vectorisable(q_prime, ldq, RDK_PROB_F32);
     float *part_q = (float *)ws;
     RDK_TIMED_LAUNCH("row_block_sums_kernel", row_block_sums_kernel, dim3((unsigned)B * splits), dim3(kStreamThreads), 0, st,
-                     q_prime, ldq, N, nchunks, splits, vec_q, part_q);
+                     q_prime, ldq, N, nchunks, splits, part_q);
     RDK_LAUNCH_CHECK("row_block_sums_kernel");
     DraftArgs a{B, N, seed, offset, part_q, nchunks, draft_ids, q_draft};
-    return launch_draft_finalize<1024, QpMemory>(a, QpMemory{q_prime, ldq, vec_q, N}, st);
+    return launch_draft_finalize<1024, QpMemory>(a, QpMemory{q_prime, ldq, N}, st);
 }
 
 size_t verify_sums_bytes(const rdk_verify_desc_t &d)
