@@ -211,15 +211,20 @@ constexpr size_t kLastLevelBytes = (size_t)256 << 20;
     }
 template <bool STREAM>
 __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void exact_f32_split_kernel(
-    const uint16_t *Ap, const float *M, int64_t ldm, int n, int N, int B, int KB, int blocks_per_split, int row_groups,
+    const uint16_t *Ap, const float *M, int64_t ldm, int n, int N, int B, int KB, int blocks_per_split, int row_groups, int splits,
     const SoftStat *qstat, float *dst, int64_t ldd, int64_t split_stride, bool scale_here)
 {
     const int lane = lane_id(), c = lane % 32, g = lane / 32;
-    // the row groups of a tile run at the same time on the same XCD (consecutive workgroups go round the XCDs)
-    const int rg = blockIdx.x / 8 % row_groups, tile_group = blockIdx.x / (8 * row_groups) * 8 + blockIdx.x % 8;
-    if (tile_group * kSplitWaves * kColSet >= N) return;   // a whole workgroup
+    // The row groups of a tile run at the same time on the same XCD: consecutive workgroups go round the XCDs, so each XCD is given a
+    // share of the list of (split, tile, row group) of its own, equal ones, because all workgroups are to be resident at once.  (Whole
+    // tiles dealt out to the XCDs left some of them with more workgroups than compute units: N = 10729, n = 2067, 235 positions
+    // 122 us a call, this way 88.)
+    const int tile_groups = (N + kSplitWaves * kColSet - 1) / (kSplitWaves * kColSet), share = gridDim.x / 8;
+    const int item = row_groups > 1 ? blockIdx.x % 8 * share + blockIdx.x / 8 : blockIdx.x;
+    const int rg = item % row_groups, tile_group = item / row_groups % tile_groups, split = item / row_groups / tile_groups;
+    if (split >= splits) return;   // a whole workgroup
     const int j0 = (tile_group * kSplitWaves + threadIdx.x / kWave) * kColSet, col = j0 + 4 * c;
-    const int kb0 = blockIdx.y * blocks_per_split, kb_last = kb0 + blocks_per_split - 1;
+    const int kb0 = split * blocks_per_split, kb_last = kb0 + blocks_per_split - 1;
     const bool full = col + 3 < N;
     const int lcol = col < N ? col : 0;   // lanes beyond N read column 0 (never stored): no branch around the loads
     f32x16 acc[2][4];
@@ -309,7 +314,7 @@ __global__ __launch_bounds__(kSplitWaves * kWave) __attribute__((amdgpu_waves_pe
     }
 #undef RDK_INTERLEAVE
     // D layout of a 32x32 tile: lane l holds column l % 32 and rows 8 * (v / 4) + 4 * (l / 32) + v % 4, v = 0..15
-    float *base = dst + (int64_t)blockIdx.y * split_stride;
+    float *base = dst + (int64_t)split * split_stride;
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
@@ -768,16 +773,16 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
         }
         RDK_LAUNCH_CHECK("prep_a_split_kernel");
         const int tile_groups = (h.N + kColSet * kSplitWaves - 1) / (kColSet * kSplitWaves);
-        const dim3 grid((tile_groups + 7) / 8 * 8 * row_groups, splits);
+        const dim3 grid((tile_groups * row_groups * splits + 7) / 8 * 8);
         const bool stream = row_groups == 1 && (size_t)h.n * h.ldm * sizeof(float) > kLastLevelBytes;
         const auto kernel = stream ? exact_f32_split_kernel<true> : exact_f32_split_kernel<false>;
         if (splits == 1) {
             RDK_TIMED_LAUNCH("exact_f32_split_kernel", kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
-                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, out, ldo, (int64_t)0, true);
+                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, splits, w.qstat, out, ldo, (int64_t)0, true);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
         } else {
             RDK_TIMED_LAUNCH("exact_f32_split_kernel", kernel, grid, dim3(kSplitWaves * kWave), 0, st, Ap, h.dense,
-                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, w.qstat, w.part, ldd, (int64_t)B * ldd, false);
+                             h.ldm, h.n, h.N, B, KB, blocks, row_groups, splits, w.qstat, w.part, ldd, (int64_t)B * ldd, false);
             RDK_LAUNCH_CHECK("exact_f32_split_kernel");
             return launch_reduce(w.part, splits, w.qstat, nullptr, h.N, B, out, ldo, st);
         }
