@@ -577,9 +577,9 @@ rdk_status_t rdk_verify_multi(const rdk_multi_desc_t *desc, const void *p, rdk_i
     if (!q_prime || !cand_ids || !accepted || !token || !workspace) return RDK_ERR_NULL;
     if (ldq < desc->N) return RDK_ERR_SHAPE;
     if (!aligned16(q_prime) || !aligned16(workspace)) return RDK_ERR_ALIGN;
-    if (workspace_bytes < multi_workspace_bytes(*desc, p_kind)) return RDK_ERR_WORKSPACE;
+    if (workspace_bytes < multi_least_bytes(*desc, p_kind)) return RDK_ERR_WORKSPACE;
     RowInput pi{p, p_kind, ldp};
-    return launch_verify_multi(*desc, pi, q_prime, ldq, cand_ids, accepted, token, resid_mass, workspace, (hipStream_t)stream);
+    return launch_verify_multi(*desc, pi, q_prime, ldq, cand_ids, accepted, token, resid_mass, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 rdk_status_t rdk_tree_walk(int32_t S, int32_t nodes, int32_t C, const int32_t *child_node, const int32_t *accepted,

@@ -11,7 +11,7 @@
 //   r_i(j) = max(0, ca * p(j) - cb * q'(j))   with  (ca, cb) = (1, 0)  and  (ca, cb) <- (ca, cb + 1) / Z,
 // Z = sum_j max(0, ca * p(j) - (cb + 1) * q'(j)) being the mass that the rejection leaves.  One workgroup owns one
 // position: every rejection costs one pass over the two rows (HBM-bound: 8 bytes per id), whose 1024-id block sums
-// stay in LDS; they give Z (added in fp64) and, after the last rejection, the block of the final draw, which is then
+// stay in LDS (a few long rows: a launch of its own, multi_in_rounds); they give Z (added in fp64) and, after the last rejection, the block of the final draw, which is then
 // re-read and scanned in fp64.  The candidates are drawn the same way from the block sums of q'.
 #include "rdk_finalize.hpp"
 
@@ -252,6 +252,123 @@ __global__ __launch_bounds__(kMultiThreads) void verify_multi_kernel(MultiArgs a
     }
 }
 
+// ---- A few long rows: one launch per round, every block of 1024 ids on a wavefront of its own
+//
+// A position that is verified by one workgroup goes through its rows at what one compute unit draws from memory (about 60 GB/s),
+// once per rejection, while a small batch leaves the rest of the chip idle.  Here a round of all positions is a launch: its
+// wavefronts add up the block sums of the round before (the same bits everywhere), take the position's decision, each for
+// itself, and the ones whose position goes on sum their block for the next round.  Sums and decisions are handed on in
+// two buffers that change places with every launch; launch C + 1 is the last, positions that are done leave at once.
+struct MultiState {
+    float wa, wb;   // coefficients of the pass that left the block sums
+    int32_t phase;
+};
+enum { kMultiRunning = 0, kMultiLeaf = 1, kMultiDone = 2 };
+
+struct MultiRounds {
+    MultiState *state[2];   // [B]
+    float *blk[2];          // [B, nblk]
+};
+
+constexpr int kRoundThreads = 256;
+
+template <int KIND>
+__global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(MultiArgs a, MultiRounds s, int round)
+{
+    const int64_t row = blockIdx.y;
+    const int N = a.d.N, C = a.d.C;
+    const int nblk = (N + kChunk - 1) / kChunk;
+    const int per_lane = ((nblk + kWave - 1) / kWave + 3) & ~3;
+    const int c = blockIdx.x * (kRoundThreads / kWave) + threadIdx.x / kWave;   // this wavefront's block
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0, drawing = blockIdx.x == 0 && threadIdx.x < kWave;
+    if (round == 0 && blockIdx.x == 0 && a.resid_mass && threadIdx.x < C) a.resid_mass[row * C + threadIdx.x] = 0.f;
+    const MultiState was = round == 0 ? MultiState{1.f, 0.f, kMultiRunning} : s.state[(round - 1) & 1][row];
+    MultiState *now = s.state[round & 1] + row;
+    if (was.phase == kMultiDone) {
+        if (first) *now = was;
+        return;
+    }
+    const int cand = round < C ? a.cand_ids[row * C + round] : -1;
+    MultiRow<KIND> r;
+    r.pr = row_ptr<KIND>(a.p, a.ldp, row);
+    r.qr = a.q + row * a.ldq;
+    r.N = N;
+    r.m = 0.f;
+    r.inv = 1.f;
+    r.pfill = KIND == RDK_PROB_F32 ? 0.f : -INFINITY;
+    // asked for before the decision that needs them is taken
+    float4 pv[4], qv[4];
+    const bool leaf = round == 0 && cand < 0;   // no candidates at all: t ~ p
+    if (c < nblk && (leaf || cand >= 0)) {
+        load_chunk<KIND, false>(r.pr, (int64_t)c * kChunk, N, r.pfill, pv);
+        if (!leaf) {
+            load_chunk<RDK_PROB_F32, false>(r.qr, (int64_t)c * kChunk, N, 0.f, qv);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+    const bool valid = cand >= 0 && cand < N;   // a candidate beyond the vocabulary is never kept
+    const float praw = valid ? load1<KIND>(r.pr, cand) : 0.f, qx = valid ? r.qr[cand] : 0.f;
+    if (KIND != RDK_PROB_F32) {
+        const SoftStat rs = merged_row_stat<KIND>(a.pstat, a.p_splits, row);
+        r.m = rs.m;
+        r.inv = 1.0f / rs.s;
+    }
+    const float *blk = s.blk[(round + 1) & 1] + row * nblk;
+    float ca = 1.f, cb = 0.f;
+    double lane_sum = 0.0, Z = 0.0;
+    if (round > 0) {
+        lane_sum = lane_partial_sum(blk, nblk, per_lane);
+        Z = wave_sum(lane_sum);
+        ca = Z > 0.0 ? (float)((double)was.wa / Z) : 0.f;
+        cb = Z > 0.0 ? (float)((double)was.wb / Z) : 0.f;
+        if (first && was.phase == kMultiRunning && a.resid_mass) a.resid_mass[row * C + round - 1] = (float)Z;
+    }
+    MultiState next{ca, cb + 1.f, kMultiRunning};
+    if (leaf) {
+        next = MultiState{1.f, 0.f, kMultiLeaf};
+    } else if (was.phase == kMultiLeaf || cand < 0) {   // every candidate was rejected, or there was none
+        if (drawing) {
+            const int t = r.template draw<true>(blk, nblk, per_lane, lane_sum, Z, multi_unit(a.d.seed, a.d.offset + (uint64_t)row, 2 * C), was.wa, was.wb);
+            if (first) {
+                a.accepted[row] = C;
+                a.token[row] = t;
+            }
+        }
+        next.phase = kMultiDone;
+    } else {
+        const float px = valid ? to_weight<KIND>(praw, r.m, r.inv) : 0.f;
+        const float rho = fmaxf(px * ca - qx * cb, 0.f);
+        if (multi_unit(a.d.seed, a.d.offset + (uint64_t)row, C + round) * (double)qx < (double)rho) {
+            if (first) {
+                a.accepted[row] = round;
+                a.token[row] = cand;
+            }
+            next.phase = kMultiDone;
+        }
+    }
+    if (first) *now = next;
+    if (next.phase != kMultiDone && c < nblk) r.template block_sum<true>(pv, qv, next.wa, next.wb, s.blk[round & 1] + row * nblk + c);
+}
+
+// Which batches go a launch a round: a launch costs 4 to 5 us whether or not a position still needs it, a round of a position in one
+// workgroup 10 us per 100000 ids, and from about 100 positions on the chip is busy either way.  Calls of tree product and
+// verification, C = 4, one workgroup a position -> rounds: N = 60001, 16 positions 36.4 -> 35.5 us, 100 44.9 -> 47.0; N = 102359, 4
+// 35.3 -> 31.3, 40 49.4 -> 43.4, 100 70.3 -> 67.4; N = 128256, 16 55.8 -> 39.0, 128 106.3 -> 105.7, 256 160 -> 174; N = 256987, 4 76.5 ->
+// 42.8, 100 183 -> 151; N = 30001, 4 22.1 -> 28.8.  Candidates drawn here stay with the one workgroup.
+constexpr int kRoundIds = 20000, kRoundRows = 96;
+bool multi_in_rounds(const rdk_multi_desc_t &d)
+{
+    return !d.sample_candidates && d.B <= kRoundRows && d.N >= kRoundIds * (d.C + 1);
+}
+
+size_t multi_stat_bytes(const rdk_multi_desc_t &d, rdk_input_kind_t p_kind)
+{
+    if (p_kind == RDK_PROB_F32) return 256;
+    return align_up((size_t)d.B * row_splits(d.B, d.N, kStatThreads / kWave) * sizeof(SoftStat), 256);
+}
+
 // Walk through verified token trees: one thread per tree follows, from the root, the candidate that the verification
 // of each node kept, and emits that node's token; it stops at the first node that kept none (integer work only).
 __global__ void tree_walk_kernel(int S, int nodes, int C, const int32_t *child_node, const int32_t *accepted,
@@ -275,13 +392,28 @@ __global__ void tree_walk_kernel(int S, int nodes, int C, const int32_t *child_n
 }
 
 template <int KIND>
-rdk_status_t run_multi(MultiArgs a, RowInput p, void *ws, hipStream_t st)
+rdk_status_t run_multi(MultiArgs a, RowInput p, void *ws, size_t ws_bytes, hipStream_t st)
 {
     if (KIND != RDK_PROB_F32) {
         a.p_splits = row_splits(a.d.B, a.d.N, kStatThreads / kWave);
         a.pstat = (SoftStat *)ws;
         rdk_status_t rc = launch_row_stats<KIND>(p, a.d.N, a.d.B, a.p_splits, (SoftStat *)ws, st);
         if (rc != RDK_OK) return rc;
+    }
+    if (multi_in_rounds(a.d) && ws_bytes >= multi_workspace_bytes(a.d, p.kind)) {
+        const int nblk = (a.d.N + kChunk - 1) / kChunk, waves = kRoundThreads / kWave;
+        char *at = (char *)ws + multi_stat_bytes(a.d, p.kind);
+        MultiRounds s;
+        for (int i = 0; i < 2; ++i) {
+            s.state[i] = (MultiState *)at; at += align_up((size_t)a.d.B * sizeof(MultiState), 256);
+            s.blk[i] = (float *)at; at += align_up((size_t)a.d.B * nblk * sizeof(float), 256);
+        }
+        for (int round = 0; round <= a.d.C; ++round) {
+            RDK_TIMED_LAUNCH("verify_multi_kernel", (verify_multi_round_kernel<KIND>), dim3((nblk + waves - 1) / waves, (unsigned)a.d.B),
+                             dim3(kRoundThreads), 0, st, a, s, round);
+            RDK_LAUNCH_CHECK("verify_multi_kernel");
+        }
+        return RDK_OK;
     }
     {
         RDK_TIMED_LAUNCH("verify_multi_kernel", (verify_multi_kernel<KIND>), dim3((unsigned)a.d.B), dim3(kMultiThreads), 0, st, a);
@@ -295,10 +427,16 @@ rdk_status_t run_multi(MultiArgs a, RowInput p, void *ws, hipStream_t st)
 int multi_max_ids() { return kMultiMaxBlocks * kChunk; }
 int multi_max_candidates() { return kMultiMaxCandidates; }
 
+size_t multi_least_bytes(const rdk_multi_desc_t &d, rdk_input_kind_t p_kind) { return multi_stat_bytes(d, p_kind); }
+
 size_t multi_workspace_bytes(const rdk_multi_desc_t &d, rdk_input_kind_t p_kind)
 {
-    if (p_kind == RDK_PROB_F32) return 256;
-    return align_up((size_t)d.B * row_splits(d.B, d.N, kStatThreads / kWave) * sizeof(SoftStat), 256);
+    size_t bytes = multi_stat_bytes(d, p_kind);
+    if (multi_in_rounds(d)) {
+        const size_t nblk = (d.N + kChunk - 1) / kChunk;
+        bytes += 2 * (align_up((size_t)d.B * sizeof(MultiState), 256) + align_up((size_t)d.B * nblk * sizeof(float), 256));
+    }
+    return bytes;
 }
 
 rdk_status_t launch_tree_walk(int32_t S, int32_t nodes, int32_t C, const int32_t *child_node, const int32_t *accepted,
@@ -313,7 +451,8 @@ rdk_status_t launch_tree_walk(int32_t S, int32_t nodes, int32_t C, const int32_t
 }
 
 rdk_status_t launch_verify_multi(const rdk_multi_desc_t &d, RowInput p, const float *q_prime, int64_t ldq, int32_t *cand_ids,
-                                 int32_t *accepted, int32_t *token, float *resid_mass, void *ws, hipStream_t st)
+                                 int32_t *accepted, int32_t *token, float *resid_mass, void *ws, size_t ws_bytes,
+                                 hipStream_t st)
 {
     MultiArgs a{};
     a.d = d;
@@ -321,9 +460,9 @@ rdk_status_t launch_verify_multi(const rdk_multi_desc_t &d, RowInput p, const fl
     a.q = q_prime; a.ldq = ldq;
     a.cand_ids = cand_ids; a.accepted = accepted; a.token = token; a.resid_mass = resid_mass;
     switch (p.kind) {
-        case RDK_PROB_F32: return run_multi<RDK_PROB_F32>(a, p, ws, st);
-        case RDK_LOGIT_F32: return run_multi<RDK_LOGIT_F32>(a, p, ws, st);
-        case RDK_LOGIT_BF16: return run_multi<RDK_LOGIT_BF16>(a, p, ws, st);
+        case RDK_PROB_F32: return run_multi<RDK_PROB_F32>(a, p, ws, ws_bytes, st);
+        case RDK_LOGIT_F32: return run_multi<RDK_LOGIT_F32>(a, p, ws, ws_bytes, st);
+        case RDK_LOGIT_BF16: return run_multi<RDK_LOGIT_BF16>(a, p, ws, ws_bytes, st);
     }
     return RDK_ERR_DTYPE;
 }
