@@ -11,8 +11,9 @@
 //   r_i(j) = max(0, ca * p(j) - cb * q'(j))   with  (ca, cb) = (1, 0)  and  (ca, cb) <- (ca, cb + 1) / Z,
 // Z = sum_j max(0, ca * p(j) - (cb + 1) * q'(j)) being the mass that the rejection leaves.  One workgroup owns one
 // position: every rejection costs one pass over the two rows (HBM-bound: 8 bytes per id), whose 1024-id block sums
-// stay in LDS (a few long rows: a launch of its own, multi_in_rounds); they give Z (added in fp64) and, after the last rejection, the block of the final draw, which is then
-// re-read and scanned in fp64.  The candidates are drawn the same way from the block sums of q'.
+// stay in LDS (long rows, up to one per compute unit: a launch of its own, multi_in_rounds); they give Z (added in fp64) and, after the
+// last rejection, the block of the final draw, which is then re-read and scanned in fp64.  The candidates are drawn the same way
+// from the block sums of q'.
 #include "rdk_finalize.hpp"
 
 namespace rdk {
@@ -252,11 +253,11 @@ __global__ __launch_bounds__(kMultiThreads) void verify_multi_kernel(MultiArgs a
     }
 }
 
-// ---- A few long rows: one launch per round, every block of 1024 ids on a wavefront of its own
+// ---- Long rows, up to one per compute unit: one launch per round, one or two blocks of 1024 ids on a wavefront
 //
 // A position that is verified by one workgroup goes through its rows at what one compute unit draws from memory (about 60 GB/s),
-// once per rejection, while a small batch leaves the rest of the chip idle.  Here a round of all positions is a launch: its
-// wavefronts add up the block sums of the round before (the same bits everywhere), take the position's decision, each for
+// once per rejection, while the units of a small batch, or of positions that are done, stand idle.  Here a round of all positions is a
+// launch: its wavefronts add up the block sums of the round before (the same bits everywhere), take the position's decision, each for
 // itself, and the ones whose position goes on sum their block for the next round.  Sums and decisions are handed on in
 // two buffers that change places with every launch; launch C + 1 is the last, positions that are done leave at once.
 struct MultiState {
@@ -273,13 +274,14 @@ struct MultiRounds {
 constexpr int kRoundThreads = 256;
 
 template <int KIND>
-__global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(MultiArgs a, MultiRounds s, int round)
+__global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(MultiArgs a, MultiRounds s, int round, bool early)
 {
     const int64_t row = blockIdx.y;
     const int N = a.d.N, C = a.d.C;
     const int nblk = (N + kChunk - 1) / kChunk;
     const int per_lane = ((nblk + kWave - 1) / kWave + 3) & ~3;
-    const int c = blockIdx.x * (kRoundThreads / kWave) + threadIdx.x / kWave;   // this wavefront's block
+    const int c0 = blockIdx.x * (kRoundThreads / kWave) + threadIdx.x / kWave;   // this wavefront's first block
+    const int stride = gridDim.x * (kRoundThreads / kWave);
     const bool first = blockIdx.x == 0 && threadIdx.x == 0, drawing = blockIdx.x == 0 && threadIdx.x < kWave;
     if (round == 0 && blockIdx.x == 0 && a.resid_mass && threadIdx.x < C) a.resid_mass[row * C + threadIdx.x] = 0.f;
     const MultiState was = round == 0 ? MultiState{1.f, 0.f, kMultiRunning} : s.state[(round - 1) & 1][row];
@@ -296,10 +298,9 @@ __global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(Multi
     r.m = 0.f;
     r.inv = 1.f;
     r.pfill = KIND == RDK_PROB_F32 ? 0.f : -INFINITY;
-    // asked for before the decision that needs them is taken
     float4 pv[4], qv[4];
     const bool leaf = round == 0 && cand < 0;   // no candidates at all: t ~ p
-    if (c < nblk && (leaf || cand >= 0)) {
+    auto ask = [&](int c) {
         load_chunk<KIND, false>(r.pr, (int64_t)c * kChunk, N, r.pfill, pv);
         if (!leaf) {
             load_chunk<RDK_PROB_F32, false>(r.qr, (int64_t)c * kChunk, N, 0.f, qv);
@@ -307,7 +308,8 @@ __global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(Multi
 #pragma unroll
             for (int i = 0; i < 4; ++i) qv[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-    }
+    };
+    if (early && c0 < nblk && (leaf || cand >= 0)) ask(c0);   // before the decision that needs them is taken
     const bool valid = cand >= 0 && cand < N;   // a candidate beyond the vocabulary is never kept
     const float praw = valid ? load1<KIND>(r.pr, cand) : 0.f, qx = valid ? r.qr[cand] : 0.f;
     if (KIND != RDK_PROB_F32) {
@@ -349,18 +351,28 @@ __global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(Multi
         }
     }
     if (first) *now = next;
-    if (next.phase != kMultiDone && c < nblk) r.template block_sum<true>(pv, qv, next.wa, next.wb, s.blk[round & 1] + row * nblk + c);
+    if (next.phase == kMultiDone) return;
+    for (int c = c0; c < nblk; c += stride) {
+        if (c != c0 || !early) ask(c);
+        r.template block_sum<true>(pv, qv, next.wa, next.wb, s.blk[round & 1] + row * nblk + c);
+    }
 }
 
 // Which batches go a launch a round: a launch costs 4 to 5 us whether or not a position still needs it, a round of a position in one
-// workgroup 10 us per 100000 ids, and from about 100 positions on the chip is busy either way.  Calls of tree product and
-// verification, C = 4, one workgroup a position -> rounds: N = 60001, 16 positions 36.4 -> 35.5 us, 100 44.9 -> 47.0; N = 102359, 4
-// 35.3 -> 31.3, 40 49.4 -> 43.4, 100 70.3 -> 67.4; N = 128256, 16 55.8 -> 39.0, 128 106.3 -> 105.7, 256 160 -> 174; N = 256987, 4 76.5 ->
-// 42.8, 100 183 -> 151; N = 30001, 4 22.1 -> 28.8.  Candidates drawn here stay with the one workgroup.
-constexpr int kRoundIds = 20000, kRoundRows = 96;
+// workgroup 10 us per 100000 ids, and with more positions than compute units others take the place of those that are done.  Calls of
+// tree product and verification, one workgroup a position -> rounds: N = 60001, C = 4, 16 positions 36.4 -> 35.5 us, 100
+// 44.9 -> 47.0; N = 128256, C = 4, 16 55.8 -> 39.0, 128 112.8 -> 95.8, 256 178 -> 172, 384 231.7 -> 232.0; N = 256987, C = 4, 4 76.5 -> 42.8;
+// N = 260000, C = 2, 256 fp32 logits 423 -> 406; N = 100000, C = 4, 128 79.5 -> 70.4, 256 114 -> 114; N = 100000, C = 3, 240 bf16 145 -> 142, 384 174 -> 180; N = 60000,
+// C = 2, 128 47.6 -> 46.6, 256 67.7 -> 69.2; N = 30001, 4 22.1 -> 28.8.  Candidates drawn here stay with the one workgroup.
+// Up to 32 positions a wavefront has one block and asks for it before it knows whether its position goes on; a larger batch pays
+// for what positions that are done have read, and for the dispatch of its workgroups: two blocks a wavefront, read once the
+// decision is taken (asked for early -> this: N = 128256, 64 positions 67.7 -> 64.5, N = 200000, 96 rows of bf16 logits 154 -> 144, 32
+// positions 48 either way; four blocks a wavefront 65.9 and 144).
+constexpr int kRoundIds = 20000, kRoundRows = kComputeUnits, kRoundEarlyRows = 32;
+constexpr int kRoundManyIds = 25000, kRoundManyRows = 128;
 bool multi_in_rounds(const rdk_multi_desc_t &d)
 {
-    return !d.sample_candidates && d.B <= kRoundRows && d.N >= kRoundIds * (d.C + 1);
+    return !d.sample_candidates && d.B <= kRoundRows && d.N >= (d.B > kRoundManyRows ? kRoundManyIds : kRoundIds) * (d.C + 1);
 }
 
 size_t multi_stat_bytes(const rdk_multi_desc_t &d, rdk_input_kind_t p_kind)
@@ -408,9 +420,11 @@ rdk_status_t run_multi(MultiArgs a, RowInput p, void *ws, size_t ws_bytes, hipSt
             s.state[i] = (MultiState *)at; at += align_up((size_t)a.d.B * sizeof(MultiState), 256);
             s.blk[i] = (float *)at; at += align_up((size_t)a.d.B * nblk * sizeof(float), 256);
         }
+        const bool early = a.d.B <= kRoundEarlyRows;
+        const int per = waves * (early ? 1 : 2);
         for (int round = 0; round <= a.d.C; ++round) {
-            RDK_TIMED_LAUNCH("verify_multi_kernel", (verify_multi_round_kernel<KIND>), dim3((nblk + waves - 1) / waves, (unsigned)a.d.B),
-                             dim3(kRoundThreads), 0, st, a, s, round);
+            RDK_TIMED_LAUNCH("verify_multi_kernel", (verify_multi_round_kernel<KIND>), dim3((nblk + per - 1) / per, (unsigned)a.d.B),
+                             dim3(kRoundThreads), 0, st, a, s, round, early);
             RDK_LAUNCH_CHECK("verify_multi_kernel");
         }
         return RDK_OK;

@@ -35,15 +35,17 @@ def test_passes_of_several_rejections(N, kind):
     check_multi(even, ref, p64, q64, seed, offset, C, min_exact=0.8)
 
 
-# Few long rows: a launch a round.  Ends inside a block, the fewest ids for one and for four candidates, one block in the last workgroup.
+# Long rows: a launch a round up to 256 positions, one block a wavefront up to 32, two beyond.  Ends inside a block, the fewest ids for
+# one and for four candidates, one block in the last workgroup.
 @pytest.mark.parametrize("kind", ["prob", "logit"])
-@pytest.mark.parametrize("N,C", [(40000, 1), (60001, 2), (100000, 4), (127 * 1024 + 1, 4)])
+@pytest.mark.parametrize("N,C", [(40000, 1), (60001, 2), (99999, 3), (100000, 4), (127 * 1024 + 1, 4)])
 def test_a_launch_a_round(N, C, kind):
     from paper_2506_03206_amd import rdk
-    B, seed, offset = 97, 5, 9
-    rng = np.random.default_rng(N + C)
-    z = torch.from_numpy((rng.normal(size=(B, N)) * 2).astype(np.float32)).cuda()
-    qp = torch.softmax(z + torch.from_numpy(rng.normal(size=(B, N)).astype(np.float32)).cuda(), 1)
+    B, seed, offset = 257, 5, 9
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + C)
+    z = torch.randn((B, N), generator=gen, device="cuda").mul_(2)
+    qp = torch.softmax(z + torch.randn((B, N), generator=gen, device="cuda"), 1)
     p = torch.softmax(z, 1) if kind == "prob" else z
     cand = np.full((B, C), N + 7, np.int32)            # never kept: every round a pass
     best = torch.softmax(z, 1).argmax(1).cpu().numpy()
@@ -53,10 +55,11 @@ def test_a_launch_a_round(N, C, kind):
     cand[4] = -1                                       # a leaf
     cd = torch.from_numpy(cand).cuda()
     whole = rdk.rdk_verify_multi(p, qp, C, seed, offset, kind, cand_ids=cd)          # a workgroup a position
-    part = rdk.rdk_verify_multi(p[:96], qp[:96], C, seed, offset, kind, cand_ids=cd[:96].contiguous())
-    assert torch.equal(whole.accepted[:96], part.accepted) and torch.equal(whole.token[:96], part.token)
-    # the same blocks in the same order, but for the statistics of logit rows, which are cut by the size of the batch
-    torch.testing.assert_close(part.resid_mass, whole.resid_mass[:96], rtol=0 if kind == "prob" else 1e-5, atol=0)
+    for m in (32, 33, 128, 129, 256):
+        part = rdk.rdk_verify_multi(p[:m], qp[:m], C, seed, offset, kind, cand_ids=cd[:m].contiguous())
+        assert torch.equal(whole.accepted[:m], part.accepted) and torch.equal(whole.token[:m], part.token)
+        # the same blocks in the same order, but for the statistics of logit rows, which are cut by the size of the batch
+        torch.testing.assert_close(part.resid_mass, whole.resid_mass[:m], rtol=0 if kind == "prob" else 1e-5, atol=0)
     n = 6
     p64 = p[:n].cpu().numpy().astype(np.float64) if kind == "prob" else oracle.probs_from(z[:n].cpu().numpy(), "logit")
     q64 = qp[:n].cpu().numpy().astype(np.float64)
