@@ -231,16 +231,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         float cm = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; ++i) cm = fmaxf(cm, fmaxf(fmaxf(pv[i].x, pv[i].y), fmaxf(pv[i].z, pv[i].w)));
-        cm = wave_max(cm);                                       // finite: a chunk holds at least one id
+        cm = wave_max(cm);
         if (cm > m) {                                            // the same decision in all lanes
             const float f = soft_exp(m - cm), f2 = f * f, f3 = f2 * f;   // 0 on the first chunk (m = -inf)
             s1 *= f; s2 *= f2; s3 *= f3;
             q1 *= f; q2 *= f2; q3 *= f3;
             m = cm;
         }
+        const float ref = m > -INFINITY ? m : 0.f;               // only masked ids so far: their weights are 0 against any reference
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float pe[4] = {soft_exp(pv[i].x - m), soft_exp(pv[i].y - m), soft_exp(pv[i].z - m), soft_exp(pv[i].w - m)};
+            const float pe[4] = {soft_exp(pv[i].x - ref), soft_exp(pv[i].y - ref), soft_exp(pv[i].z - ref), soft_exp(pv[i].w - ref)};
             const float qe[4] = {qd[i].x, qd[i].y, qd[i].z, qd[i].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {

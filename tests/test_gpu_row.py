@@ -92,3 +92,20 @@ def test_rows_masked_with_the_lowest_finite_value(N, B, kind):
     rdk.rdk_timing_select(None)
     assert rdk.rdk_timing_read("taylor_row_kernel")[0] == ((N, B) != (60001, 6))
     check_verify_outputs(out, ref, p64, ref_qp, 9, 4, 2, "logit", min_exact=0.6)
+
+
+@pytest.mark.parametrize("N,B", [(60001, 6), (33001, 70)])
+def test_two_passes_over_chunks_of_masked_ids(N, B):
+    """q' of rows in which a wavefront's first chunk, and every chunk of one, is masked with -inf."""
+    from paper_2506_03206_amd import rdk
+    rng = np.random.default_rng(N)
+    kept = np.sort(rng.choice(N, size=N // 4, replace=False)).astype(np.int32)
+    zp = (rng.normal(size=(B, N)) * 2).astype(np.float32)
+    zq = (zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept]
+    zp[0, :3072] = -np.inf
+    zp[1, 1024:] = -np.inf
+    kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
+    got = rdk.rdk_redistribute_linear(kern, rdk.LINEAR_TAYLOR, torch.from_numpy(zq).cuda(), "logit", p=torch.from_numpy(zp).cuda(),
+                                      p_kind="logit").cpu().numpy().astype(np.float64)
+    ref = oracle.redistribute_batch("taylor", oracle.probs_from(zq, "logit"), kept, N, p=oracle.probs_from(zp, "logit"))
+    assert (np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-7).all()
