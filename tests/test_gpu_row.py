@@ -101,7 +101,7 @@ def test_two_passes_over_chunks_of_masked_ids(N, B):
     rng = np.random.default_rng(N)
     kept = np.sort(rng.choice(N, size=N // 4, replace=False)).astype(np.int32)
     zp = (rng.normal(size=(B, N)) * 2).astype(np.float32)
-    zq = (zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept]
+    zq = np.ascontiguousarray((zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept])
     zp[0, :3072] = -np.inf
     zp[1, 1024:] = -np.inf
     kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
