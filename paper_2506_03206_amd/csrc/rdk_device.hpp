@@ -227,6 +227,20 @@ __device__ __forceinline__ void quad_shift(float (&v)[4], int past)
     v[0] = two ? v[2] : v[0]; v[1] = two ? v[3] : v[1];
 }
 
+// The lane's four values of quad i of chunk c; ids beyond N come back as `fill`.
+template <int KIND>
+__device__ __forceinline__ void row_quad_values(const typename RawQuad<KIND>::type raw, int c, int i, int N, float fill, float (&v)[4])
+{
+    RawQuad<KIND>::to(raw, v);
+    if (N - c * kChunk < kChunk) {                                        // the same for the whole wavefront
+        const int left = N - (c * kChunk + 256 * i + 4 * lane_id());      // ids of the row from the lane's quad on
+        quad_shift(v, 4 - left);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e >= left) v[e] = fill;
+    }
+}
+
 template <int KIND>
 __device__ __forceinline__ const void *row_ptr(const void *base, int64_t ld, int64_t b)
 {

@@ -480,6 +480,199 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 }
 
 // ------------------------------------------------------------------------------------------------
+// Eq. 3 of a whole row by one workgroup, q' written: both passes above, and the statistics of logit rows, in one launch.  A
+// wavefront holds its chunks (one, or two sixteen chunks apart) of the target row and of the drafter row in id order in registers
+// from the first sum to the store.  The kept ids of a quad own consecutive slots, so their drafter values are one 16-byte load at
+// the slot that lane_map gives, and three selects a value put them in their places.  The sums are those of taylor_stats_kernel, with
+// the row's own maximum and normaliser (no series).
+// What bounds it: the chain of a launch, two dependent reads, one barrier (three for logits) and the stores.
+constexpr int kWholeThreads = 1024;
+constexpr int kWholeHeld = 2;                                                       // chunks of a wavefront
+constexpr int kWholeMaxN = kWholeHeld * (kWholeThreads / kWave) * kChunk;
+
+// Totals over the workgroup of M values of every wavefront, the same bits in each; at: M * waves floats of LDS, used once.
+template <int M>
+__device__ __forceinline__ void whole_totals(float (&v)[M], float *at, int wid, int lane, int waves)
+{
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = wave_sum(v[m]);
+    if (lane == 0) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) at[m * waves + wid] = v[m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = wave_sum(lane < waves ? at[m * waves + lane] : 0.f);
+}
+
+template <int PK, int QK, bool FUSE>
+__global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
+                                                                     const uint64_t *lane_map, const int32_t *chunk_lo, int N, int n,
+                                                                     float *out, int64_t ldo, LinearWs w, float *part_q, float *part_r,
+                                                                     float *part_a)
+{
+    __shared__ float lds[7 * kWholeThreads / kWave];
+    const int64_t row = blockIdx.x;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    const int waves = blockDim.x / kWave, nchunks = (N + kChunk - 1) / kChunk;
+    const void *pr = row_ptr<PK>(p, ldp, row);
+    const void *qr = row_ptr<QK>(q, ldq, row);
+    constexpr float kNoLogit = -INFINITY;
+    uint64_t map[kWholeHeld];
+    int lo[kWholeHeld], hi[kWholeHeld];
+    typename RawQuad<PK>::type praw[kWholeHeld][4];
+    typename RawQuad<QK>::type qraw[kWholeHeld][4];
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+        map[t] = lane_map[c * kWave + lane];
+        lo[t] = chunk_lo[c];
+        hi[t] = chunk_lo[c + 1];
+    }
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) praw[t][i] = raw_quad<PK>(pr, c * kChunk + 256 * i + 4 * lane, N);
+    }
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        if (wid + t * waves >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qraw[t][i] = raw_quad<QK>(qr, lo[t] + (int)((map[t] >> (16 + 12 * i)) & 0xFFFu), n);
+    }
+    // the values in id order; ids that are not kept, and those beyond N, have no weight
+    float pv[kWholeHeld][4][4], qv[kWholeHeld][4][4];
+    float pm = kNoLogit, qm = kNoLogit;
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            row_quad_values<PK>(praw[t][i], c, i, N, PK == RDK_PROB_F32 ? 0.f : kNoLogit, pv[t][i]);
+            float v[4];
+            RawQuad<QK>::to(qraw[t][i], v);
+            if (hi[t] > n - 4) quad_shift(v, lo[t] + (int)((map[t] >> (16 + 12 * i)) & 0xFFFu) - (n - 4));   // the row's last quad
+            const uint32_t kb = (uint32_t)map[t] >> (4 * i);
+            const bool b0 = kb & 1, b1 = kb & 2, b2 = kb & 4, b3 = kb & 8;
+            const float s1 = b0 ? v[1] : v[0], s2 = b0 ? v[2] : v[1], s3 = b0 ? v[3] : v[2];
+            const float r2 = b1 ? s2 : s1, r3 = b1 ? s3 : s2;
+            const float none = QK == RDK_PROB_F32 ? 0.f : kNoLogit;
+            qv[t][i][0] = b0 ? v[0] : none;
+            qv[t][i][1] = b1 ? s1 : none;
+            qv[t][i][2] = b2 ? r2 : none;
+            qv[t][i][3] = b3 ? (b2 ? r3 : r2) : none;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (PK != RDK_PROB_F32) pm = fmaxf(pm, pv[t][i][e]);
+                if (QK != RDK_PROB_F32) qm = fmaxf(qm, qv[t][i][e]);
+            }
+        }
+    }
+    float *red = lds;
+    if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) {
+        if (PK != RDK_PROB_F32) pm = wave_max(pm);
+        if (QK != RDK_PROB_F32) qm = wave_max(qm);
+        if (lane == 0) {
+            red[wid] = pm;
+            red[waves + wid] = qm;
+        }
+        __syncthreads();
+        if (PK != RDK_PROB_F32) pm = wave_max(lane < waves ? red[lane] : kNoLogit);
+        if (QK != RDK_PROB_F32) qm = wave_max(lane < waves ? red[waves + lane] : kNoLogit);
+        red += 2 * waves;
+    }
+    float z[1] = {0.f};
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        if (wid + t * waves >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (PK != RDK_PROB_F32) {
+                    pv[t][i][e] = soft_exp(pv[t][i][e] - pm);
+                    z[0] += pv[t][i][e];
+                }
+                if (QK != RDK_PROB_F32) qv[t][i][e] = (map[t] >> (4 * i + e)) & 1 ? soft_exp(qv[t][i][e] - qm) : 0.f;
+            }
+    }
+    float pinv = 1.f;
+    if (PK != RDK_PROB_F32) {
+        whole_totals(z, red, wid, lane, waves);
+        pinv = 1.0f / z[0];
+        red += waves;
+    }
+    const float fN = (float)N;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};   // sum q^, sum q^ p, sum q^ / (N + p), sum p / (N + p)
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        if (wid + t * waves >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (PK != RDK_PROB_F32) pv[t][i][e] *= pinv;
+                const float pe = pv[t][i][e], qh = qv[t][i][e], r = __builtin_amdgcn_rcpf(fN + pe);
+                s[0] += qh;
+                s[1] += qh * pe;
+                s[2] += qh * r;
+                s[3] += pe * r;
+            }
+    }
+    whole_totals(s, red, wid, lane, waves);
+    const float inv_zq = inv_mass(s[0]), theta = s[1] * inv_zq, inv_S = inv_mass(s[2] * fN * inv_zq + theta * s[3]);
+    const float nzs = fN * inv_zq * inv_S, ths = theta * inv_S;
+    if (FUSE && threadIdx.x == 0) {   // what make_taylor_row reads: a single split
+        *(float4 *)(w.tpart + row * 4) = make_float4(s[0], s[1], s[2] * fN, s[3]);
+        if (PK != RDK_PROB_F32) w.pstat[row] = SoftStat{pm, z[0]};
+        if (QK != RDK_PROB_F32) w.qstat[row] = SoftStat{qm, s[0]};
+    }
+    float *orow = out + row * ldo;
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+        float sq = 0.f, sr = 0.f, sa = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int id = c * kChunk + 256 * i + 4 * lane;
+            float o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (nzs * qv[t][i][e] + ths * pv[t][i][e]) * __builtin_amdgcn_rcpf(fN + pv[t][i][e]);
+            if ((c + 1) * kChunk <= N) {
+                store4(orow + id, o[0], o[1], o[2], o[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (id + e < N) orow[id + e] = o[e];
+            }
+            if (FUSE) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {   // beyond N both weights are zero, and so is q'
+                    sq += o[e];
+                    sr += fmaxf(pv[t][i][e] - o[e], 0.f);
+                    sa += fminf(pv[t][i][e], o[e]);
+                }
+            }
+        }
+        if (FUSE) {
+            sq = wave_sum(sq);
+            sr = wave_sum(sr);
+            sa = wave_sum(sa);
+            if (lane == 0) {
+                part_q[row * nchunks + c] = sq;
+                part_r[row * nchunks + c] = sr;
+                part_a[row * nchunks + c] = sa;
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // Eq. 3 and the verification sums in ONE pass over the target row (the fused call when q' is not asked for).  The two-pass
 // kernels above read p twice because the row constants (theta, sum of pt) are only known after the whole row has been seen.
 // Here one workgroup owns one position and keeps what the second step needs on chip:
@@ -1278,6 +1471,18 @@ __global__ __launch_bounds__(kThreads) void tli_scatter_kernel(const void *q, in
     }
 }
 
+// Whether q' of a row is written by one workgroup (taylor_whole_kernel): rows that its wavefronts hold, and, of those with two chunks
+// for most wavefronts, from 64 positions on; fewer leave the chip to the form that splits a row.  One call of the redistribution
+// alone, two passes -> one launch, probabilities / bf16 logits, us: N = 1001, 64 rows 7.5 -> 4.1; N = 4000, 4 rows 6.6 / 11.6 -> 4.0 / 5.1,
+// 256 8.0 / 13.0 -> 4.7 / 5.9; N = 16000, 64 8.4 / 13.2 -> 6.0 / 9.4, 512 23.2 / 29.9 -> 17.2 / 21.4; N = 20003, 4 7.0 / 12.2 -> 5.5 / 9.7, 256
+// 16.0 / 23.3 -> 11.1 / 13.5, 1024 51.1 / 54.8 -> 44.8 / 46.1; N = 32000, 4 6.8 / 11.7 -> 7.3 / 13.0 (not taken), 64 9.3 / 14.1 -> 8.7 /
+// 14.3, 256 22.8 / 29.2 -> 14.6 / 18.6, 1024 85.9 / 73.6 -> 66.4 / 73.9.  Beyond 1024 rows, where nothing was measured, the two passes.
+constexpr int kWholeAnyBatchN = 24 * kChunk, kWholeLeastRows = 64, kWholeMostRows = 4 * kComputeUnits;
+bool taylor_in_one(const KernelHandle &h, int32_t B)
+{
+    return h.N >= 4 && h.n >= 4 && h.N <= (B < kWholeLeastRows ? kWholeAnyBatchN : kWholeMaxN) && B <= kWholeMostRows;
+}
+
 // c == nullptr: plain Eq. 3 into `out`.  Otherwise the fused call: verification sums per block, then the finish.
 template <int PK, int QK>
 rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B, float *out, int64_t ldo, void *ws,
@@ -1342,6 +1547,35 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             return scan_if_left(fa, st);
         }
     }
+    float *part_q = (float *)fused_ws, *part_r = (float *)(fused_ws + per), *part_a = (float *)(fused_ws + 2 * per);
+    TaylorArgs a;
+    a.p = p.ptr; a.q = q.ptr; a.ldp = p.ld; a.ldq = q.ld;
+    a.slot_of = h.slot_of; a.kept = h.kept_ids; a.chunk_lo = h.chunk_lo; a.N = h.N; a.n = h.n; a.splits = w.t_splits;
+    a.onepass = false;
+    auto finish = [&]() {
+        a.w = w;
+        FinalizeArgs fa{};
+        fa.d = c->d;
+        fa.p = p.ptr; fa.ldp = p.ld;
+        fa.pstat = w.pstat; fa.p_splits = w.p_splits;
+        fa.part_q = part_q; fa.part_r = part_r; fa.part_a = part_a;
+        fa.nblk = nchunks;
+        fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
+        fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
+        return launch_finalize<PK, 1024, true, QpTaylor<PK, QK>>(fa, QpTaylor<PK, QK>{a}, seq_rec, st);
+    };
+    if (out && taylor_in_one(h, B)) {   // q' has the same bits in the call that only writes it and in the fused one
+        const int waves = nchunks < kWholeThreads / kWave ? nchunks : kWholeThreads / kWave;
+        w.p_splits = a.splits = 1;
+#define RDK_WHOLE_LAUNCH(FUSE)                                                                                               \
+    RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), 0, st, p.ptr, \
+                     p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.N, h.n, out, ldo, w, part_q, part_r, part_a)
+        if (c) RDK_WHOLE_LAUNCH(true);
+        else RDK_WHOLE_LAUNCH(false);
+#undef RDK_WHOLE_LAUNCH
+        RDK_LAUNCH_CHECK("taylor_write_kernel");
+        return c ? finish() : RDK_OK;
+    }
     // logit target rows of a large vocabulary: the first pass of Eq. 3 also delivers the softmax statistics
     const bool onepass = PK != RDK_PROB_F32 && h.N >= kOnePassMinN;
     if (PK != RDK_PROB_F32 && !onepass) {
@@ -1352,9 +1586,6 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         rc = launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
         if (rc != RDK_OK) return rc;
     }
-    TaylorArgs a;
-    a.p = p.ptr; a.q = q.ptr; a.ldp = p.ld; a.ldq = q.ld;
-    a.slot_of = h.slot_of; a.kept = h.kept_ids; a.chunk_lo = h.chunk_lo; a.N = h.N; a.n = h.n; a.splits = w.t_splits;
     a.onepass = onepass;
     a.w = w;
     // first pass: one-pass or two-pass statistics; in the fused call (c != NULL) it leaves the target rows cacheable
@@ -1384,21 +1615,12 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         RDK_LAUNCH_CHECK("taylor_write_kernel");
         return RDK_OK;
     }
-    float *part_q = (float *)fused_ws, *part_r = (float *)(fused_ws + per), *part_a = (float *)(fused_ws + 2 * per);
     {
         RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, true>), grid, dim3(kThreads), 0, st, a, out,
                          ldo, part_q, part_r, part_a);
     }
     RDK_LAUNCH_CHECK("taylor_write_kernel");
-    FinalizeArgs fa{};
-    fa.d = c->d;
-    fa.p = p.ptr; fa.ldp = p.ld;
-    fa.pstat = w.pstat; fa.p_splits = w.p_splits;
-    fa.part_q = part_q; fa.part_r = part_r; fa.part_a = part_a;
-    fa.nblk = nchunks;
-    fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
-    fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
-    return launch_finalize<PK, 1024, true, QpTaylor<PK, QK>>(fa, QpTaylor<PK, QK>{a}, seq_rec, st);
+    return finish();
 }
 
 template <int QK>

@@ -122,20 +122,6 @@ struct RowPair {
     typename RawQuad<RDK_PROB_F32>::type q[4];
 };
 
-// The lane's four values of quad i of chunk c; ids beyond N come back as `fill`.
-template <int KIND>
-__device__ __forceinline__ void row_quad_values(const typename RawQuad<KIND>::type raw, int c, int i, int N, float fill, float (&v)[4])
-{
-    RawQuad<KIND>::to(raw, v);
-    if (N - c * kChunk < kChunk) {                                        // the same for the whole wavefront
-        const int left = N - (c * kChunk + 256 * i + 4 * lane_id());      // ids of the row from the lane's quad on
-        quad_shift(v, 4 - left);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e >= left) v[e] = fill;
-    }
-}
-
 template <int KIND>
 __device__ __forceinline__ void row_fetch(const void *row, int c, int N, typename RawQuad<KIND>::type (&v)[4])
 {

@@ -1,0 +1,76 @@
+"""Eq. 3 with q' written by one workgroup per row where it can go wrong: ends inside a quad and on a chunk, a second chunk for one
+wavefront and for all, the last quads of the drafter row, chunks without kept ids and with nothing but, rows at odd strides, both
+sides of the lines to the two passes -- against the oracle, and the fused call against the one that only writes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2506_03206_amd import synth
+from parity_util import check_verify_outputs
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # N, n, B, gamma, which ids are kept, one launch
+    (4, 4, 2, 1, "any", True),
+    (5, 3, 2, 1, "any", False),              # a drafter row without a whole quad
+    (1023, 5, 3, 3, "tail", True),
+    (1025, 1024, 3, 3, "first", True),       # every id of the first chunk, none of the second
+    (3001, 2999, 260, 4, "any", True),
+    (16 * 1024, 4001, 4, 2, "any", True),
+    (16 * 1024 + 1, 5003, 4, 2, "tail", True),
+    (24 * 1024, 6001, 63, 1, "any", True),
+    (24 * 1024 + 1, 6001, 63, 1, "any", False),
+    (24 * 1024 + 1, 6002, 64, 4, "tail", True),
+    (32 * 1024, 9001, 64, 2, "any", True),
+    (32 * 1024 + 1, 9001, 64, 2, "any", False),
+    (700, 130, 1024, 4, "any", True),
+    (700, 130, 1025, 5, "any", False),
+]
+
+
+@pytest.mark.parametrize("kinds", ["prob prob", "logit logit", "bf16 bf16", "prob bf16", "bf16 prob"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_rows_written_in_one_launch(shape, kinds):
+    from paper_2506_03206_amd import rdk
+    N, n, B, gamma, where, one = shape
+    rng = np.random.default_rng(N + n)
+    if where == "first":
+        kept = np.arange(n)
+    elif where == "tail":                    # runs that end with the drafter row, one slot and two in the last quads
+        kept = np.concatenate([np.sort(rng.choice(N - 8, size=n - 3, replace=False)), [N - 6, N - 2, N - 1]])
+    else:
+        kept = np.sort(rng.choice(N, size=n, replace=False))
+    kept = kept.astype(np.int32)
+    zp = (rng.normal(size=(B, N)) * 2).astype(np.float32)
+    zq = (zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept]
+    if N > 3072:
+        zp[0, 1024:2048] = -np.inf           # a chunk of masked ids
+    zp[1, : N // 2] = np.finfo(np.float32).min
+    rows, p64, dev = [], [], []
+    for z, kind in zip((zp, zq), kinds.split()):
+        if kind == "bf16":
+            z = synth.bf16_round(np.maximum(z, -1e38))
+        if kind == "prob":
+            z = oracle.probs_from(z, "logit").astype(np.float32)
+        rows.append("prob" if kind == "prob" else "logit")
+        p64.append(oracle.probs_from(z, rows[-1]))
+        t = torch.from_numpy(np.ascontiguousarray(z)).cuda().to(torch.bfloat16 if kind == "bf16" else torch.float32)
+        dev.append(torch.nn.functional.pad(t, (0, 1), value=float("nan"))[:, :-1])
+    kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
+    held = torch.full((B, N + 3), 7.0, device="cuda")
+    rdk.rdk_timing_select("taylor_stats_kernel")
+    rdk.rdk_redistribute_linear(kern, rdk.LINEAR_TAYLOR, dev[1], rows[1], p=dev[0], p_kind=rows[0], out=held[:, :N])
+    torch.cuda.synchronize()
+    rdk.rdk_timing_select(None)
+    assert rdk.rdk_timing_read("taylor_stats_kernel")[0] == (0 if one else 1)
+    assert bool((held[:, N:] == 7.0).all())  # nothing behind a row is written
+    got = held[:, :N].cpu().numpy().astype(np.float64)
+    ref = oracle.redistribute_batch("taylor", p64[1], kept, N, p=p64[0])
+    # fp32 terms and sums of at most 2**15 terms in a tree; a softmax term carries its logit's rounding (2**-24 of a difference of 15)
+    assert (np.abs(got - ref) <= 1e-5 * np.abs(ref) + 1e-7).all()
+    qp = torch.empty((B, N), device="cuda")
+    out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, dev[0], dev[1], 9, 4, gamma, rows[0], rows[1], q_prime=qp)
+    assert torch.equal(qp, held[:, :N])      # the same bits in both calls
+    want = oracle.verify_batch(p64[0], ref, 9, 4, gamma=gamma)
+    check_verify_outputs(out, want, p64[0], ref, 9, 4, gamma, rows[0], min_exact=0.6)
