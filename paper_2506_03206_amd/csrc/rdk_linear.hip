@@ -480,199 +480,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 }
 
 // ------------------------------------------------------------------------------------------------
-// Eq. 3 of a whole row by one workgroup, q' written: both passes above, and the statistics of logit rows, in one launch.  A
-// wavefront holds its chunks (one, or two sixteen chunks apart) of the target row and of the drafter row in id order in registers
-// from the first sum to the store.  The kept ids of a quad own consecutive slots, so their drafter values are one 16-byte load at
-// the slot that lane_map gives, and three selects a value put them in their places.  The sums are those of taylor_stats_kernel, with
-// the row's own maximum and normaliser (no series).
-// What bounds it: the chain of a launch, two dependent reads, one barrier (three for logits) and the stores.
-constexpr int kWholeThreads = 1024;
-constexpr int kWholeHeld = 2;                                                       // chunks of a wavefront
-constexpr int kWholeMaxN = kWholeHeld * (kWholeThreads / kWave) * kChunk;
-
-// Totals over the workgroup of M values of every wavefront, the same bits in each; at: M * waves floats of LDS, used once.
-template <int M>
-__device__ __forceinline__ void whole_totals(float (&v)[M], float *at, int wid, int lane, int waves)
-{
-#pragma unroll
-    for (int m = 0; m < M; ++m) v[m] = wave_sum(v[m]);
-    if (lane == 0) {
-#pragma unroll
-        for (int m = 0; m < M; ++m) at[m * waves + wid] = v[m];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < M; ++m) v[m] = wave_sum(lane < waves ? at[m * waves + lane] : 0.f);
-}
-
-template <int PK, int QK, bool FUSE>
-__global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
-                                                                     const uint64_t *lane_map, const int32_t *chunk_lo, int N, int n,
-                                                                     float *out, int64_t ldo, LinearWs w, float *part_q, float *part_r,
-                                                                     float *part_a)
-{
-    __shared__ float lds[7 * kWholeThreads / kWave];
-    const int64_t row = blockIdx.x;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-    const int waves = blockDim.x / kWave, nchunks = (N + kChunk - 1) / kChunk;
-    const void *pr = row_ptr<PK>(p, ldp, row);
-    const void *qr = row_ptr<QK>(q, ldq, row);
-    constexpr float kNoLogit = -INFINITY;
-    uint64_t map[kWholeHeld];
-    int lo[kWholeHeld], hi[kWholeHeld];
-    typename RawQuad<PK>::type praw[kWholeHeld][4];
-    typename RawQuad<QK>::type qraw[kWholeHeld][4];
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        const int c = wid + t * waves;
-        if (c >= nchunks) break;
-        map[t] = lane_map[c * kWave + lane];
-        lo[t] = chunk_lo[c];
-        hi[t] = chunk_lo[c + 1];
-    }
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        const int c = wid + t * waves;
-        if (c >= nchunks) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) praw[t][i] = raw_quad<PK>(pr, c * kChunk + 256 * i + 4 * lane, N);
-    }
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        if (wid + t * waves >= nchunks) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qraw[t][i] = raw_quad<QK>(qr, lo[t] + (int)((map[t] >> (16 + 12 * i)) & 0xFFFu), n);
-    }
-    // the values in id order; ids that are not kept, and those beyond N, have no weight
-    float pv[kWholeHeld][4][4], qv[kWholeHeld][4][4];
-    float pm = kNoLogit, qm = kNoLogit;
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        const int c = wid + t * waves;
-        if (c >= nchunks) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            row_quad_values<PK>(praw[t][i], c, i, N, PK == RDK_PROB_F32 ? 0.f : kNoLogit, pv[t][i]);
-            float v[4];
-            RawQuad<QK>::to(qraw[t][i], v);
-            if (hi[t] > n - 4) quad_shift(v, lo[t] + (int)((map[t] >> (16 + 12 * i)) & 0xFFFu) - (n - 4));   // the row's last quad
-            const uint32_t kb = (uint32_t)map[t] >> (4 * i);
-            const bool b0 = kb & 1, b1 = kb & 2, b2 = kb & 4, b3 = kb & 8;
-            const float s1 = b0 ? v[1] : v[0], s2 = b0 ? v[2] : v[1], s3 = b0 ? v[3] : v[2];
-            const float r2 = b1 ? s2 : s1, r3 = b1 ? s3 : s2;
-            const float none = QK == RDK_PROB_F32 ? 0.f : kNoLogit;
-            qv[t][i][0] = b0 ? v[0] : none;
-            qv[t][i][1] = b1 ? s1 : none;
-            qv[t][i][2] = b2 ? r2 : none;
-            qv[t][i][3] = b3 ? (b2 ? r3 : r2) : none;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (PK != RDK_PROB_F32) pm = fmaxf(pm, pv[t][i][e]);
-                if (QK != RDK_PROB_F32) qm = fmaxf(qm, qv[t][i][e]);
-            }
-        }
-    }
-    float *red = lds;
-    if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) {
-        if (PK != RDK_PROB_F32) pm = wave_max(pm);
-        if (QK != RDK_PROB_F32) qm = wave_max(qm);
-        if (lane == 0) {
-            red[wid] = pm;
-            red[waves + wid] = qm;
-        }
-        __syncthreads();
-        if (PK != RDK_PROB_F32) pm = wave_max(lane < waves ? red[lane] : kNoLogit);
-        if (QK != RDK_PROB_F32) qm = wave_max(lane < waves ? red[waves + lane] : kNoLogit);
-        red += 2 * waves;
-    }
-    float z[1] = {0.f};
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        if (wid + t * waves >= nchunks) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (PK != RDK_PROB_F32) {
-                    pv[t][i][e] = soft_exp(pv[t][i][e] - pm);
-                    z[0] += pv[t][i][e];
-                }
-                if (QK != RDK_PROB_F32) qv[t][i][e] = (map[t] >> (4 * i + e)) & 1 ? soft_exp(qv[t][i][e] - qm) : 0.f;
-            }
-    }
-    float pinv = 1.f;
-    if (PK != RDK_PROB_F32) {
-        whole_totals(z, red, wid, lane, waves);
-        pinv = 1.0f / z[0];
-        red += waves;
-    }
-    const float fN = (float)N;
-    float s[4] = {0.f, 0.f, 0.f, 0.f};   // sum q^, sum q^ p, sum q^ / (N + p), sum p / (N + p)
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        if (wid + t * waves >= nchunks) break;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (PK != RDK_PROB_F32) pv[t][i][e] *= pinv;
-                const float pe = pv[t][i][e], qh = qv[t][i][e], r = __builtin_amdgcn_rcpf(fN + pe);
-                s[0] += qh;
-                s[1] += qh * pe;
-                s[2] += qh * r;
-                s[3] += pe * r;
-            }
-    }
-    whole_totals(s, red, wid, lane, waves);
-    const float inv_zq = inv_mass(s[0]), theta = s[1] * inv_zq, inv_S = inv_mass(s[2] * fN * inv_zq + theta * s[3]);
-    const float nzs = fN * inv_zq * inv_S, ths = theta * inv_S;
-    if (FUSE && threadIdx.x == 0) {   // what make_taylor_row reads: a single split
-        *(float4 *)(w.tpart + row * 4) = make_float4(s[0], s[1], s[2] * fN, s[3]);
-        if (PK != RDK_PROB_F32) w.pstat[row] = SoftStat{pm, z[0]};
-        if (QK != RDK_PROB_F32) w.qstat[row] = SoftStat{qm, s[0]};
-    }
-    float *orow = out + row * ldo;
-#pragma unroll
-    for (int t = 0; t < kWholeHeld; ++t) {
-        const int c = wid + t * waves;
-        if (c >= nchunks) break;
-        float sq = 0.f, sr = 0.f, sa = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int id = c * kChunk + 256 * i + 4 * lane;
-            float o[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (nzs * qv[t][i][e] + ths * pv[t][i][e]) * __builtin_amdgcn_rcpf(fN + pv[t][i][e]);
-            if ((c + 1) * kChunk <= N) {
-                store4(orow + id, o[0], o[1], o[2], o[3]);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (id + e < N) orow[id + e] = o[e];
-            }
-            if (FUSE) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {   // beyond N both weights are zero, and so is q'
-                    sq += o[e];
-                    sr += fmaxf(pv[t][i][e] - o[e], 0.f);
-                    sa += fminf(pv[t][i][e], o[e]);
-                }
-            }
-        }
-        if (FUSE) {
-            sq = wave_sum(sq);
-            sr = wave_sum(sr);
-            sa = wave_sum(sa);
-            if (lane == 0) {
-                part_q[row * nchunks + c] = sq;
-                part_r[row * nchunks + c] = sr;
-                part_a[row * nchunks + c] = sa;
-            }
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
 // Eq. 3 and the verification sums in ONE pass over the target row (the fused call when q' is not asked for).  The two-pass
 // kernels above read p twice because the row constants (theta, sum of pt) are only known after the whole row has been seen.
 // Here one workgroup owns one position and keeps what the second step needs on chip:
@@ -828,6 +635,211 @@ __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, i
     const Eq3Quads<QK, RCP> quads{lane_map, chunk_lo, slot_of, qr, qm, nzs, ths, rcp, N};
     finish_row_quarters<PK, SCAN>(lds + l_fin, lds + l_sum_q, lds + l_sum_r, lds + l_sum_a, nchunks, fin, row, pr, pm, pinv, N,
                             quads, words, wid, lane);
+}
+
+// ------------------------------------------------------------------------------------------------
+// Eq. 3 of a whole row by one workgroup, q' written: both passes above, and the statistics of logit rows, in one launch.  A
+// wavefront holds its chunks (one, or two sixteen chunks apart) of the target row and of the drafter row in id order in registers
+// from the first sum to the store.  The kept ids of a quad own consecutive slots, so their drafter values are one 16-byte load at
+// the slot that lane_map gives, and three selects a value put them in their places.  The sums are those of taylor_stats_kernel, with
+// the row's own maximum and normaliser (no series).
+// What bounds it: the chain of a launch, two dependent reads, one barrier (three for logits) and the stores.
+constexpr int kWholeThreads = 1024, kFinishWaves = 8;   // of a workgroup at most; at least where it finishes its row
+constexpr int kWholeHeld = 2;                                                       // chunks of a wavefront
+constexpr int kWholeMaxN = kWholeHeld * (kWholeThreads / kWave) * kChunk;
+
+// Totals over the workgroup of M values of every wavefront, the same bits in each; at: M * waves floats of LDS, used once.
+template <int M>
+__device__ __forceinline__ void whole_totals(float (&v)[M], float *at, int wid, int lane, int waves)
+{
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = wave_sum(v[m]);
+    if (lane == 0) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) at[m * waves + wid] = v[m];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = wave_sum(lane < waves ? at[m * waves + lane] : 0.f);
+}
+
+struct WholeRcp {
+    float fN;
+    __device__ __forceinline__ float operator()(float pe) const { return __builtin_amdgcn_rcpf(fN + pe); }
+};
+
+// FUSE: the sums of every chunk go to LDS and the row is finished (q' is written only if it is asked for).
+template <int PK, int QK, bool FUSE>
+__global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
+                                                                     const uint64_t *lane_map, const int32_t *chunk_lo,
+                                                                     const int32_t *slot_of, int N, int n, float *out, int64_t ldo,
+                                                                     FinalizeArgs fin)
+{
+    __shared__ float lds[7 * kWholeThreads / kWave];
+    __shared__ __attribute__((aligned(16))) float sums[3][FUSE ? kWholeMaxN / kChunk : 1];   // of q', max(0, p - q'), min(p, q') per chunk
+    __shared__ __attribute__((aligned(16))) float scratch[FUSE ? kFinishFloats : 1];
+    const int64_t row = blockIdx.x;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
+    const int waves = blockDim.x / kWave, nchunks = (N + kChunk - 1) / kChunk;
+    const void *pr = row_ptr<PK>(p, ldp, row);
+    const void *qr = row_ptr<QK>(q, ldq, row);
+    constexpr float kNoLogit = -INFINITY;
+    uint64_t map[kWholeHeld];
+    int lo[kWholeHeld], hi[kWholeHeld];
+    typename RawQuad<PK>::type praw[kWholeHeld][4];
+    typename RawQuad<QK>::type qraw[kWholeHeld][4];
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+        map[t] = lane_map[c * kWave + lane];
+        lo[t] = chunk_lo[c];
+        hi[t] = chunk_lo[c + 1];
+    }
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) praw[t][i] = raw_quad<PK>(pr, c * kChunk + 256 * i + 4 * lane, N);
+    }
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        if (wid + t * waves >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qraw[t][i] = raw_quad<QK>(qr, lo[t] + (int)((map[t] >> (16 + 12 * i)) & 0xFFFu), n);
+    }
+    // the values in id order; ids that are not kept, and those beyond N, have no weight
+    float pv[kWholeHeld][4][4], qv[kWholeHeld][4][4];
+    float pm = kNoLogit, qm = kNoLogit;
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            row_quad_values<PK>(praw[t][i], c, i, N, PK == RDK_PROB_F32 ? 0.f : kNoLogit, pv[t][i]);
+            float v[4];
+            RawQuad<QK>::to(qraw[t][i], v);
+            if (hi[t] > n - 4) quad_shift(v, lo[t] + (int)((map[t] >> (16 + 12 * i)) & 0xFFFu) - (n - 4));   // the row's last quad
+            const uint32_t kb = (uint32_t)map[t] >> (4 * i);
+            const bool b0 = kb & 1, b1 = kb & 2, b2 = kb & 4, b3 = kb & 8;
+            const float s1 = b0 ? v[1] : v[0], s2 = b0 ? v[2] : v[1], s3 = b0 ? v[3] : v[2];
+            const float r2 = b1 ? s2 : s1, r3 = b1 ? s3 : s2;
+            const float none = QK == RDK_PROB_F32 ? 0.f : kNoLogit;
+            qv[t][i][0] = b0 ? v[0] : none;
+            qv[t][i][1] = b1 ? s1 : none;
+            qv[t][i][2] = b2 ? r2 : none;
+            qv[t][i][3] = b3 ? (b2 ? r3 : r2) : none;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (PK != RDK_PROB_F32) pm = fmaxf(pm, pv[t][i][e]);
+                if (QK != RDK_PROB_F32) qm = fmaxf(qm, qv[t][i][e]);
+            }
+        }
+    }
+    float *red = lds;
+    if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) {
+        if (PK != RDK_PROB_F32) pm = wave_max(pm);
+        if (QK != RDK_PROB_F32) qm = wave_max(qm);
+        if (lane == 0) {
+            red[wid] = pm;
+            red[waves + wid] = qm;
+        }
+        __syncthreads();
+        if (PK != RDK_PROB_F32) pm = wave_max(lane < waves ? red[lane] : kNoLogit);
+        if (QK != RDK_PROB_F32) qm = wave_max(lane < waves ? red[waves + lane] : kNoLogit);
+        red += 2 * waves;
+    }
+    float z[1] = {0.f};
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        if (wid + t * waves >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (PK != RDK_PROB_F32) {
+                    pv[t][i][e] = soft_exp(pv[t][i][e] - pm);
+                    z[0] += pv[t][i][e];
+                }
+                if (QK != RDK_PROB_F32) qv[t][i][e] = (map[t] >> (4 * i + e)) & 1 ? soft_exp(qv[t][i][e] - qm) : 0.f;
+            }
+    }
+    float pinv = 1.f;
+    if (PK != RDK_PROB_F32) {
+        whole_totals(z, red, wid, lane, waves);
+        pinv = 1.0f / z[0];
+        red += waves;
+    }
+    const float fN = (float)N;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};   // sum q^, sum q^ p, sum q^ / (N + p), sum p / (N + p)
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        if (wid + t * waves >= nchunks) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (PK != RDK_PROB_F32) pv[t][i][e] *= pinv;
+                const float pe = pv[t][i][e], qh = qv[t][i][e], r = __builtin_amdgcn_rcpf(fN + pe);
+                s[0] += qh;
+                s[1] += qh * pe;
+                s[2] += qh * r;
+                s[3] += pe * r;
+            }
+    }
+    whole_totals(s, red, wid, lane, waves);
+    const float inv_zq = inv_mass(s[0]), theta = s[1] * inv_zq, inv_S = inv_mass(s[2] * fN * inv_zq + theta * s[3]);
+    const float nzs = fN * inv_zq * inv_S, ths = theta * inv_S;
+    float *orow = out ? out + row * ldo : nullptr;
+#pragma unroll
+    for (int t = 0; t < kWholeHeld; ++t) {
+        const int c = wid + t * waves;
+        if (c >= nchunks) break;
+        float sq = 0.f, sr = 0.f, sa = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int id = c * kChunk + 256 * i + 4 * lane;
+            float o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (nzs * qv[t][i][e] + ths * pv[t][i][e]) * __builtin_amdgcn_rcpf(fN + pv[t][i][e]);
+            if (FUSE && !orow) {
+            } else if ((c + 1) * kChunk <= N) {
+                store4(orow + id, o[0], o[1], o[2], o[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (id + e < N) orow[id + e] = o[e];
+            }
+            if (FUSE) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {   // beyond N both weights are zero, and so is q'
+                    sq += o[e];
+                    sr += fmaxf(pv[t][i][e] - o[e], 0.f);
+                    sa += fminf(pv[t][i][e], o[e]);
+                }
+            }
+        }
+        if (FUSE) {
+            sq = wave_sum(sq);
+            sr = wave_sum(sr);
+            sa = wave_sum(sa);
+            if (lane == 0) {
+                sums[0][c] = sq;
+                sums[1][c] = sr;
+                sums[2][c] = sa;
+            }
+        }
+    }
+    if (FUSE) {
+        uint32_t words[4];
+        position_words(fin.d.seed, fin.d.offset + (uint64_t)row, words);
+        __syncthreads();
+        const WholeRcp rcp{fN};
+        const Eq3Quads<QK, WholeRcp> quads{lane_map, chunk_lo, slot_of, qr, qm, nzs, ths, rcp, N};
+        finish_row_quarters<PK, true>(scratch, sums[0], sums[1], sums[2], nchunks, fin, row, pr, pm, pinv, N, quads, words, wid, lane);
+    }
 }
 
 // Stands in for the maximum of nothing, where -inf would make the weight of a masked id exp(-inf + inf).  Nothing finite lies
@@ -1483,6 +1495,20 @@ bool taylor_in_one(const KernelHandle &h, int32_t B)
     return h.N >= 4 && h.n >= 4 && h.N <= (B < kWholeLeastRows ? kWholeAnyBatchN : kWholeMaxN) && B <= kWholeMostRows;
 }
 
+// The same for the fused call without q', beside taylor_row_kernel.  That one reads the tables of a kernel, keeps the kept target
+// values in LDS and goes through the kept slots again; this one holds everything in registers and has less to do after its sums, but
+// every id carries a drafter value, and beyond 8192 ids its sixteen wavefronts fill a compute unit.  Fused calls, taylor_row_kernel
+// -> this, probabilities / fp32 logits, us: N = 1001, 64 positions 11.5 / 22.3 (logits below 1024 ids: four launches) -> 8.4 / 9.4, 1024
+// 21.9 / 27.6 -> 17.7 / 20.5; N = 4000, 4 11.0 / 11.3 -> 8.0 / 8.8, 512 13.7 / 14.8 -> 10.5 / 13.2, 1024 23.0 / 25.0 -> 18.9 / 22.2; N = 8003, 64
+// 11.6 / 12.8 -> 9.0 / 11.0, 512 14.6 / 16.0 -> 13.3 / 16.3, 1024 24.3 / 26.8 -> 22.4 / 27.2; N = 16000, 64 12.5 / 14.3 -> 10.9 / 14.4, 256 13.5 /
+// 15.1 -> 12.7 / 16.1, 512 17.7 / 19.8 -> 23.7 / 28.9; N = 24576, 4 13.2 / 14.5 -> 11.6 / 15.7, 256 16.2 / 17.9 -> 15.5 / 19.9.
+bool taylor_finished_in_one(const KernelHandle &h, int32_t B, rdk_input_kind_t p_kind)
+{
+    const bool side_by_side = B <= kComputeUnits;   // a compute unit for every row
+    if (h.N <= kFinishWaves * kChunk) return p_kind == RDK_PROB_F32 || side_by_side || h.N <= kFinishWaves / 2 * kChunk;
+    return p_kind == RDK_PROB_F32 && side_by_side && h.N <= kWholeAnyBatchN;
+}
+
 // c == nullptr: plain Eq. 3 into `out`.  Otherwise the fused call: verification sums per block, then the finish.
 template <int PK, int QK>
 rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B, float *out, int64_t ldo, void *ws,
@@ -1495,6 +1521,28 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     const size_t per = align_up((size_t)B * nchunks * sizeof(float), 256);
     char *fused_ws = (char *)ws + taylor_workspace_bytes(h, B);
     uint64_t *seq_rec = (uint64_t *)(fused_ws + 3 * per);
+    if (taylor_in_one(h, B) && (out || taylor_finished_in_one(h, B, p.kind))) {
+        // q' has the same bits in the call that only writes it and in the fused one
+        FinalizeArgs fa{};
+        int waves = nchunks < kWholeThreads / kWave ? nchunks : kWholeThreads / kWave;
+        if (c) {
+            fa.d = c->d;
+            fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
+            fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
+            set_scan(fa, seq_rec);
+            if (waves < kFinishWaves) waves = kFinishWaves;
+        }
+        // timed as the kernel whose calls it takes
+        const char *name = out || (PK != RDK_PROB_F32 && h.N < kOnePassMinN) ? "taylor_write_kernel" : "taylor_row_kernel";
+#define RDK_WHOLE_LAUNCH(FUSE)                                                                                                \
+    RDK_TIMED_LAUNCH(name, (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), 0, st, p.ptr, \
+                     p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.slot_of, h.N, h.n, out, ldo, fa)
+        if (c) RDK_WHOLE_LAUNCH(true);
+        else RDK_WHOLE_LAUNCH(false);
+#undef RDK_WHOLE_LAUNCH
+        RDK_LAUNCH_CHECK("taylor_write_kernel");
+        return c ? scan_if_left(fa, st) : RDK_OK;
+    }
     {
         // the fused call without q': one pass over the target rows, one workgroup per position, when the kept target
         // values of a row fit the LDS of a compute unit and there are enough positions to fill the chip, or the rows are so
@@ -1547,35 +1595,6 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             return scan_if_left(fa, st);
         }
     }
-    float *part_q = (float *)fused_ws, *part_r = (float *)(fused_ws + per), *part_a = (float *)(fused_ws + 2 * per);
-    TaylorArgs a;
-    a.p = p.ptr; a.q = q.ptr; a.ldp = p.ld; a.ldq = q.ld;
-    a.slot_of = h.slot_of; a.kept = h.kept_ids; a.chunk_lo = h.chunk_lo; a.N = h.N; a.n = h.n; a.splits = w.t_splits;
-    a.onepass = false;
-    auto finish = [&]() {
-        a.w = w;
-        FinalizeArgs fa{};
-        fa.d = c->d;
-        fa.p = p.ptr; fa.ldp = p.ld;
-        fa.pstat = w.pstat; fa.p_splits = w.p_splits;
-        fa.part_q = part_q; fa.part_r = part_r; fa.part_a = part_a;
-        fa.nblk = nchunks;
-        fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
-        fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
-        return launch_finalize<PK, 1024, true, QpTaylor<PK, QK>>(fa, QpTaylor<PK, QK>{a}, seq_rec, st);
-    };
-    if (out && taylor_in_one(h, B)) {   // q' has the same bits in the call that only writes it and in the fused one
-        const int waves = nchunks < kWholeThreads / kWave ? nchunks : kWholeThreads / kWave;
-        w.p_splits = a.splits = 1;
-#define RDK_WHOLE_LAUNCH(FUSE)                                                                                               \
-    RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), 0, st, p.ptr, \
-                     p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.N, h.n, out, ldo, w, part_q, part_r, part_a)
-        if (c) RDK_WHOLE_LAUNCH(true);
-        else RDK_WHOLE_LAUNCH(false);
-#undef RDK_WHOLE_LAUNCH
-        RDK_LAUNCH_CHECK("taylor_write_kernel");
-        return c ? finish() : RDK_OK;
-    }
     // logit target rows of a large vocabulary: the first pass of Eq. 3 also delivers the softmax statistics
     const bool onepass = PK != RDK_PROB_F32 && h.N >= kOnePassMinN;
     if (PK != RDK_PROB_F32 && !onepass) {
@@ -1586,6 +1605,9 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         rc = launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
         if (rc != RDK_OK) return rc;
     }
+    TaylorArgs a;
+    a.p = p.ptr; a.q = q.ptr; a.ldp = p.ld; a.ldq = q.ld;
+    a.slot_of = h.slot_of; a.kept = h.kept_ids; a.chunk_lo = h.chunk_lo; a.N = h.N; a.n = h.n; a.splits = w.t_splits;
     a.onepass = onepass;
     a.w = w;
     // first pass: one-pass or two-pass statistics; in the fused call (c != NULL) it leaves the target rows cacheable
@@ -1615,12 +1637,21 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         RDK_LAUNCH_CHECK("taylor_write_kernel");
         return RDK_OK;
     }
+    float *part_q = (float *)fused_ws, *part_r = (float *)(fused_ws + per), *part_a = (float *)(fused_ws + 2 * per);
     {
         RDK_TIMED_LAUNCH("taylor_write_kernel", (taylor_write_kernel<PK, QK, true>), grid, dim3(kThreads), 0, st, a, out,
                          ldo, part_q, part_r, part_a);
     }
     RDK_LAUNCH_CHECK("taylor_write_kernel");
-    return finish();
+    FinalizeArgs fa{};
+    fa.d = c->d;
+    fa.p = p.ptr; fa.ldp = p.ld;
+    fa.pstat = w.pstat; fa.p_splits = w.p_splits;
+    fa.part_q = part_q; fa.part_r = part_r; fa.part_a = part_a;
+    fa.nblk = nchunks;
+    fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
+    fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
+    return launch_finalize<PK, 1024, true, QpTaylor<PK, QK>>(fa, QpTaylor<PK, QK>{a}, seq_rec, st);
 }
 
 template <int QK>

@@ -74,3 +74,31 @@ def test_rows_written_in_one_launch(shape, kinds):
     assert torch.equal(qp, held[:, :N])      # the same bits in both calls
     want = oracle.verify_batch(p64[0], ref, 9, 4, gamma=gamma)
     check_verify_outputs(out, want, p64[0], ref, 9, 4, gamma, rows[0], min_exact=0.6)
+
+
+# The fused call without q': both sides of the lines to the kernel that keeps the kept values in LDS, whose forms for small
+# vocabularies are left to more positions than this one takes.
+@pytest.mark.parametrize("kind", ["prob", "logit", "bf16"])
+@pytest.mark.parametrize("N,n,B,gamma", [(1001, 1000, 5, 1), (1023, 131, 1026, 3), (1025, 131, 1026, 3), (4096, 900, 257, 1),
+                                         (4097, 900, 257, 1), (8192, 2000, 256, 4), (8193, 2000, 6, 3), (3001, 700, 1026, 2)])
+def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
+    from paper_2506_03206_amd import rdk
+    rng = np.random.default_rng(N + B)
+    kept = np.sort(rng.choice(N, size=n, replace=False)).astype(np.int32)
+    zp = (rng.normal(size=(B, N)) * 2).astype(np.float32)
+    zq = np.ascontiguousarray((zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept])
+    zp[0, : N // 2], zp[1], zq[2] = -np.inf, 1.5, -2.0             # masked ids, uniform rows
+    if kind == "bf16":
+        zp, zq = synth.bf16_round(zp), synth.bf16_round(zq)
+    pk = "prob" if kind == "prob" else "logit"
+    if kind == "prob":
+        zp, zq = [oracle.probs_from(x, "logit").astype(np.float32) for x in (zp, zq)]
+    dt = torch.bfloat16 if kind == "bf16" else torch.float32
+    wide = lambda a: torch.nn.functional.pad(torch.from_numpy(np.ascontiguousarray(a)).cuda().to(dt), (0, 1), value=float("nan"))[:, :-1]
+    kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
+    p64, q64 = oracle.probs_from(zp, pk), oracle.probs_from(zq, pk)
+    ref = oracle.redistribute_batch("taylor", q64, kept, N, p=p64)
+    want = oracle.verify_batch(p64, ref, 9, 4, gamma=gamma)
+    for _ in range(2):                       # the records of the scan are as they were after a call
+        out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, wide(zp), wide(zq), 9, 4, gamma, pk, pk)
+        check_verify_outputs(out, want, p64, ref, 9, 4, gamma, pk, min_exact=0.6)
