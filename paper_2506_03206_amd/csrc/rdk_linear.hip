@@ -751,6 +751,7 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
         if (QK != RDK_PROB_F32) qm = wave_max(lane < waves ? red[waves + lane] : kNoLogit);
         red += 2 * waves;
     }
+    if (!(qm > kNoLogit)) qm = 0.f;   // a drafter row of masked ids has no mass
     float z[1] = {0.f};
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
@@ -825,6 +826,10 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             sq = wave_sum(sq);
             sr = wave_sum(sr);
             sa = wave_sum(sa);
+            if (!orow) {   // a row with a NaN or an infinity has one in theta, which the minima and maxima above would hide
+                sr += ths * 0.f;
+                sa += ths * 0.f;
+            }
             if (lane == 0) {
                 sums[0][c] = sq;
                 sums[1][c] = sr;

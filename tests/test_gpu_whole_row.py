@@ -102,3 +102,30 @@ def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
     for _ in range(2):                       # the records of the scan are as they were after a call
         out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, wide(zp), wide(zq), 9, 4, gamma, pk, pk)
         check_verify_outputs(out, want, p64, ref, 9, 4, gamma, pk, min_exact=0.6)
+
+
+@pytest.mark.parametrize("N", [3000, 8000])
+@pytest.mark.parametrize("keep", [False, True])
+def test_rows_without_mass_and_with_nan(N, keep):
+    """A drafter row of masked ids (or of zeros) drafts nothing and leaves the whole target row; NaN stays visible."""
+    from paper_2506_03206_amd import rdk
+    kern = rdk.rdk_build_kernel(N, torch.arange(0, N, 4, dtype=torch.int32, device="cuda"), rdk.IDENTITY)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    z = torch.randn((6, N), generator=gen, device="cuda")
+    for kind in ("logit", "prob"):
+        p, q = (z, z[:, ::4]) if kind == "logit" else (torch.softmax(z, 1), torch.softmax(z, 1)[:, ::4])
+        p, q = p.clone(), q.clone().contiguous()
+        q[1] = -float("inf") if kind == "logit" else 0.0
+        p[2, 7] = float("nan")
+        q[3, 5] = float("nan")
+        p[4, 9] = float("inf")
+        qp = torch.empty((6, N), device="cuda") if keep else None
+        o = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, p, q, 3, 0, 3, kind, kind, q_prime=qp)
+        assert int(o.draft_ids[1]) == -1 and float(o.alpha[1]) == 0.0 and int(o.resid_ids[1]) >= 0
+        assert abs(float(o.resid_mass[1]) - 1.0) < 1e-5        # fp32 sum of a row that adds up to one
+        assert (o.draft_ids[2:5] == -1).all() and (o.draft_ids[[0, 5]] >= 0).all()
+        if keep:
+            assert not qp[1].any() and qp[2:5].isnan().any(1).all()
+        else:
+            assert o.alpha[2:5].isnan().all() and o.resid_mass[2:5].isnan().all()
