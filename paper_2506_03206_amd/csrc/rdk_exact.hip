@@ -141,16 +141,24 @@ __global__ __launch_bounds__(kPrepThreads) void prep_a_split_kernel(const void *
     if (threadIdx.x == 0 && b < B) qstat[b] = SoftStat{qm, z};
 }
 
-// The same for long rows, statistics given: a thread per 16 bytes of the records, in their order.  Workgroups that own a row
-// write 16 bytes of a 128-byte line each, three times per eight slots, which costs more than the launch for the statistics from
-// about 5000 slots on (one launch against two, a call of 16 positions: n = 2000 29.7 us against 32.4, 4000 56.9 : 58.4,
-// 5000 76.2 : 76.3, 8000 198.3 : 196.1).
-constexpr int kPrepRowMax = 4096;
+// The same for long rows: a thread per 16 bytes of the records, in their order.  Workgroups that own a row write 16 bytes of a
+// 128-byte line each, three times per eight slots.  The records of logits need the row's maximum: that costs more than the
+// launch for it from about 5000 slots on (one launch against two, a call of 16 positions: n = 2000 29.7 us against 32.4, 4000 56.9 :
+// 58.4, 5000 76.2 : 76.3, 8000 198.3 : 196.1).  Those of probabilities need nothing of their row, whose mass is taken by the first B
+// workgroups of the same launch: one workgroup a row -> this, the product's calls, n = 2000, one position 24.0 -> 23.8, 256 52.9 ->
+// 51.9, n = 4000, one 49.0 -> 45.6, 256 158.9 -> 154.8; n = 600 either way the same.  With a launch for the mass: n = 6000, 5 positions
+// 80.0 -> 76.9, n = 12001, 256 1414 -> 1405.
+constexpr int kPrepRowMax = 4096, kPrepRowMaxProb = 2048;
 template <int QK>
-__global__ void prep_a_records_kernel(const void *q, int64_t ldq, const SoftStat *qstat, int n, int B, int KB, int64_t records,
-                                    uint16_t *Ap)
+__global__ __launch_bounds__(kStatThreads) void prep_a_records_kernel(const void *q, int64_t ldq, SoftStat *qstat, int n, int B, int KB,
+                                                                      int64_t records, uint16_t *Ap)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int mass_rows = QK == RDK_PROB_F32 ? B : 0;
+    if ((int)blockIdx.x < mass_rows) {
+        row_stats<QK>(row_ptr<QK>(q, ldq, blockIdx.x), n, 0, (n + kChunk - 1) / kChunk, qstat + blockIdx.x);
+        return;
+    }
+    const int64_t idx = (int64_t)(blockIdx.x - mass_rows) * blockDim.x + threadIdx.x;
     if (idx >= records * kWave) return;
     const int l = (int)(idx % kWave);
     const int64_t rec = idx / kWave;
@@ -162,10 +170,12 @@ __global__ void prep_a_records_kernel(const void *q, int64_t ldq, const SoftStat
     if (b < B) {
         const void *qr = row_ptr<QK>(q, ldq, b);
         const float qm = QK == RDK_PROB_F32 ? 0.f : qstat[b].m;
+        const int s = kb * kSplitStep + g * 8;
+        if (s < n) {
+            float v[8];
+            load8<QK>(qr, s, n, QK == RDK_PROB_F32 ? 0.f : -INFINITY, v);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int s = kb * kSplitStep + g * 8 + e;
-            if (s < n) split3(to_weight<QK>(load1<QK>(qr, s), qm, 1.f), h[e], m[e], lo[e]);
+            for (int e = 0; e < 8; ++e) split3(to_weight<QK>(v[e], qm, 1.f), h[e], m[e], lo[e]);
         }
     }
     uint4 *dst = (uint4 *)(Ap + ((rec * 3) * kWave + l) * 8);
@@ -761,14 +771,15 @@ rdk_status_t run_exact(const KernelHandle &h, RowInput q, int32_t B, float *out,
         w.part = (float *)p;
         const int64_t ldd = padded(h.N);
         {
-            if (h.n <= kPrepRowMax) {
+            if (h.n <= (QK == RDK_PROB_F32 ? kPrepRowMaxProb : kPrepRowMax)) {
                 RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_split_kernel<QK>), dim3(row_groups * kRowGroup), dim3(kPrepThreads), 0, st,
                                  q.ptr, q.ld, w.qstat, h.n, B, KB, Ap);
             } else {
-                const rdk_status_t rc = launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
+                const rdk_status_t rc = QK == RDK_PROB_F32 ? RDK_OK : launch_row_stats<QK>(q, h.n, B, 1, w.qstat, st);
                 if (rc != RDK_OK) return rc;
-                RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_records_kernel<QK>), dim3((unsigned)((records * kWave + 255) / 256)),
-                                 dim3(256), 0, st, q.ptr, q.ld, w.qstat, h.n, B, KB, records, Ap);
+                const int64_t threads = records * kWave;
+                RDK_TIMED_LAUNCH("prep_a_split_kernel", (prep_a_records_kernel<QK>),
+                                 dim3((unsigned)((threads + kStatThreads - 1) / kStatThreads + (QK == RDK_PROB_F32 ? B : 0))), dim3(kStatThreads), 0, st, q.ptr, q.ld, w.qstat, h.n, B, KB, records, Ap);
             }
         }
         RDK_LAUNCH_CHECK("prep_a_split_kernel");

@@ -8,17 +8,11 @@ namespace rdk {
 
 constexpr int kStatThreads = 256;
 
+// The statistics of the chunks c_begin .. c_end - 1 of one row, by a workgroup of kStatThreads.
 template <int KIND>
-__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, int64_t ld, int64_t len, int splits,
-                                                                 SoftStat *out)
+__device__ __forceinline__ void row_stats(const void *xr, int64_t len, int c_begin, int c_end, SoftStat *to)
 {
     constexpr int kWaves = kStatThreads / kWave;
-    const int64_t row = blockIdx.x / splits;
-    const int split = blockIdx.x % splits;
-    const int nchunks = (int)((len + kChunk - 1) / kChunk);
-    const int cpw = (nchunks + splits - 1) / splits;
-    const int c_begin = split * cpw, c_end = min(nchunks, c_begin + cpw);
-    const void *xr = row_ptr<KIND>(x, ld, row);
     const int wid = threadIdx.x / kWave, lane = lane_id();
     SoftStat st;
     st.m = KIND == RDK_PROB_F32 ? 0.f : -INFINITY;
@@ -57,8 +51,20 @@ __global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, 
             if (KIND == RDK_PROB_F32) r.s += sh[i].s;
             else r = soft_merge(r, sh[i]);
         }
-        out[row * splits + split] = r;
+        *to = r;
     }
+}
+
+template <int KIND>
+__global__ __launch_bounds__(kStatThreads) void row_stats_kernel(const void *x, int64_t ld, int64_t len, int splits,
+                                                                 SoftStat *out)
+{
+    const int64_t row = blockIdx.x / splits;
+    const int split = blockIdx.x % splits;
+    const int nchunks = (int)((len + kChunk - 1) / kChunk);
+    const int cpw = (nchunks + splits - 1) / splits;
+    const int c_begin = split * cpw;
+    row_stats<KIND>(row_ptr<KIND>(x, ld, row), len, c_begin, min(nchunks, c_begin + cpw), out + row * splits + split);
 }
 
 // Merge the partials of one row; every lane of the calling wave receives (m, s).

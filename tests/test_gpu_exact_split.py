@@ -36,6 +36,15 @@ def test_fp32_edges(shape):
     check_product(shape, "f32", "prob")
 
 
+# Drafter rows brought into operand form by a workgroup each and by a thread per record: both sides of the line (2048 slots of
+# probabilities, 4096 of logits), ends inside eight slots, one chunk of 1024 and a single slot more.
+@pytest.mark.parametrize("kind", ["prob", "logit"])
+@pytest.mark.parametrize("shape", [(700, 2048, 65), (700, 2049, 65), (513, 3077, 1), (700, 4096, 33), (700, 4097, 129)])
+def test_fp32_drafter_rows(shape, kind):
+    N, n, B = shape
+    check_product((N + n, n, B), "f32", kind)
+
+
 # Column groups (128 ids) beyond whole rounds of the chip (256 workgroups, 768 of the smaller ones) have their slots split: one group
 # and a ragged one, 128 groups (the most that are split), one more, a single turn of slots (nothing to split), and the batches
 # at which the workgroup changes.
