@@ -488,13 +488,27 @@ __global__ __launch_bounds__(4 * kWave) void verify_finalize_wide_kernel(Finaliz
 //   quads          where q' comes from: begin() issues the loads that need no target value, end() hands out q' of four
 //                  ids given their target weights, at() q' of one id
 //   SCAN           whether the per-sequence scan follows (scan_sequence)
+//   held           called by every thread with the two blocks once they are known: where the target weights and q' of both lie in
+//                  LDS (block by block, 256 quads of either), put there by the wavefronts that hold them, or null
 constexpr int kFinishFloats = 64;
+constexpr int kHeldQuads = 4 * 256;
 
-template <int KIND, bool SCAN, class Quads>
+struct NotHeld {
+    __device__ __forceinline__ const float4 *operator()(int, int) const { return nullptr; }
+};
+
+// Four quads of a lane, in the order of finish_row_quarters' quarters.
+__device__ __forceinline__ void hold_block(float4 *to, const float (&v)[4][4], int lane)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) to[i * kWave + lane] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
+}
+
+template <int KIND, bool SCAN, class Quads, class Held = NotHeld>
 __device__ __forceinline__ void finish_row_quarters(float *scratch, const float *sq, const float *sr, const float *sa, int nblk,
                                                     const FinalizeArgs &fin, int64_t row, const void *pr, float pm, float pinv,
                                                     int N, const Quads &quads, const uint32_t (&words)[4], int wid,
-                                                    int lane)
+                                                    int lane, const Held &held = Held{})
 {
     constexpr int kBlock = 1024;
     double *fd = (double *)scratch;                   // [0..1] local thresholds, [2] alpha, [3] residual mass, [4..11] quarter totals
@@ -534,6 +548,7 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
         }
     }
     __syncthreads();
+    const float4 *in_lds = held(fi[0], fi[1]);
     const int fb = wid >> 2, fq = wid & 3;            // which of the two blocks, which quarter of it
     const int fblk = wid < 8 ? fi[fb] : -1;
     const bool factive = fblk >= 0;
@@ -542,11 +557,17 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
     double l0 = 0.0, l1 = 0.0, l2 = 0.0, l3 = 0.0, incl = 0.0;
     int last_pos = -1;
     if (factive) {
-        typename Quads::Token t = quads.begin(fblk, fq, fidx);
-        const float4 pl = load4<KIND>(pr, fidx, N, KIND == RDK_PROB_F32 ? 0.f : -INFINITY);
-        pv4[0] = to_weight<KIND>(pl.x, pm, pinv); pv4[1] = to_weight<KIND>(pl.y, pm, pinv);
-        pv4[2] = to_weight<KIND>(pl.z, pm, pinv); pv4[3] = to_weight<KIND>(pl.w, pm, pinv);
-        quads.end(t, fidx, pv4, qp4);
+        if (in_lds) {
+            const float4 pl = in_lds[fb * 512 + fq * kWave + lane], ql = in_lds[fb * 512 + 256 + fq * kWave + lane];
+            pv4[0] = pl.x; pv4[1] = pl.y; pv4[2] = pl.z; pv4[3] = pl.w;
+            qp4[0] = ql.x; qp4[1] = ql.y; qp4[2] = ql.z; qp4[3] = ql.w;
+        } else {
+            typename Quads::Token t = quads.begin(fblk, fq, fidx);
+            const float4 pl = load4<KIND>(pr, fidx, N, KIND == RDK_PROB_F32 ? 0.f : -INFINITY);
+            pv4[0] = to_weight<KIND>(pl.x, pm, pinv); pv4[1] = to_weight<KIND>(pl.y, pm, pinv);
+            pv4[2] = to_weight<KIND>(pl.z, pm, pinv); pv4[3] = to_weight<KIND>(pl.w, pm, pinv);
+            quads.end(t, fidx, pv4, qp4);
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) wv4[e] = fb == 0 ? qp4[e] : fmaxf(pv4[e] - qp4[e], 0.f);
         l0 = (double)wv4[0]; l1 = l0 + (double)wv4[1]; l2 = l1 + (double)wv4[2]; l3 = l2 + (double)wv4[3];
