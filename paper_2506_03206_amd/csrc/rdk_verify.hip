@@ -184,8 +184,9 @@ __global__ __launch_bounds__(T) void verify_row_kernel(const void *p, int64_t ld
         st = wave_soft_merge(st);
         if (lane == 0) sh_stat[wid] = st;
         __syncthreads();
-        st = sh_stat[0];
-        for (int i = 1; i < kRowWaves; ++i) st = soft_merge(st, sh_stat[i]);
+        // a lane for every wavefront: one after the other took 1 us of a call (bf16 logits, N = 1024, 64 rows 9.7 -> 8.75 us, N = 20003,
+        // 256 rows 14.7 -> 13.3, N = 32000, 64 rows 14.2 -> 13.1)
+        st = wave_soft_merge(lane < kRowWaves ? sh_stat[lane] : SoftStat{-INFINITY, 0.f});
         pm = st.m;
         pinv = 1.0f / st.s;
     }
