@@ -286,6 +286,8 @@ rdk_status_t rdk_sample_draft(const rdk_kernel_t *kernel, const void *q, rdk_inp
  * Outputs (device): accepted [B] = index of the kept candidate, or C; token [B] = the emitted id (-1 when the last
  * residual is empty); resid_mass [B, C] (optional) = sum_j max(0, r(j) - q'_b(j)) after each rejection, 0 for rounds
  * that were not reached.  p [B, ldp] of kind p_kind, q_prime [B, ldq] fp32; 1 <= C <= 16, N <= 2 097 152.
+ * A call with less workspace than it asks for, but enough for the softmax partials of logit rows, takes a form that is slower for few
+ * long rows, with the same results.
  * Errors: RDK_ERR_NULL, RDK_ERR_SHAPE (B, N, C, strides), RDK_ERR_DTYPE, RDK_ERR_ALIGN (rows not 16-byte aligned),
  * RDK_ERR_UNSUPPORTED (N or C above the limits), RDK_ERR_WORKSPACE, RDK_ERR_HIP.
  */

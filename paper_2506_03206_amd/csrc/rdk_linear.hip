@@ -641,8 +641,10 @@ __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, i
 // Eq. 3 of a whole row by one workgroup, q' written: both passes above, and the statistics of logit rows, in one launch.  A
 // wavefront holds its chunks (one, or two sixteen chunks apart) of the target row and of the drafter row in id order in registers
 // from the first sum to the store.  The kept ids of a quad own consecutive slots, so their drafter values are one 16-byte load at
-// the slot that lane_map gives, and three selects a value put them in their places.  The sums are those of taylor_stats_kernel, with
-// the row's own maximum and normaliser (no series).
+// the slot that lane_map gives, and three selects a value put them in their places.  The terms are those of taylor_stats_kernel, with
+// the row's own maximum and normaliser (no series), and the drafter row's mass is not needed at all.  Against 64-bit sums, 120 sets
+// of rows of 1000 to 32768 ids, mean relative error of q' with two passes -> this: probabilities 8.8e-8 -> 7.7e-8, fp32 logits 9.7e-8 ->
+// 8.2e-8, bf16 logits 9.9e-8 -> 8.2e-8; of alpha and the residual mass 0 to 15 % less as well.
 // What bounds it: the chain of a launch, two dependent reads, one barrier (three for logits) and the stores.
 constexpr int kWholeThreads = 1024, kFinishWaves = 8;   // of a workgroup at most; at least where it finishes its row
 constexpr int kWholeHeld = 2;                                                       // chunks of a wavefront
@@ -675,10 +677,10 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
                                                                      const int32_t *slot_of, int N, int n, float *out, int64_t ldo,
                                                                      FinalizeArgs fin)
 {
-    __shared__ float lds[7 * kWholeThreads / kWave];
+    __shared__ float lds[6 * kWholeThreads / kWave];
     __shared__ __attribute__((aligned(16))) float sums[3][FUSE ? kWholeMaxN / kChunk : 1];   // of q', max(0, p - q'), min(p, q') per chunk
     __shared__ __attribute__((aligned(16))) float scratch[FUSE ? kFinishFloats : 1];
-    __shared__ float4 blocks[FUSE ? kHeldQuads : 1];   // the two blocks that the draws fall into
+    extern __shared__ float4 blocks[];   // FUSE: the two blocks that the draws fall into
     const int64_t row = blockIdx.x;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
     const int waves = blockDim.x / kWave, nchunks = (N + kChunk - 1) / kChunk;
@@ -775,7 +777,7 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
         red += waves;
     }
     const float fN = (float)N;
-    float s[4] = {0.f, 0.f, 0.f, 0.f};   // sum q^, sum q^ p, sum q^ / (N + p), sum p / (N + p)
+    float s[3] = {0.f, 0.f, 0.f};   // sum q^ p, sum q^ / (N + p), sum p / (N + p)
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
         if (wid + t * waves >= nchunks) break;
@@ -785,15 +787,15 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             for (int e = 0; e < 4; ++e) {
                 if (PK != RDK_PROB_F32) pv[t][i][e] *= pinv;
                 const float pe = pv[t][i][e], qh = qv[t][i][e], r = __builtin_amdgcn_rcpf(fN + pe);
-                s[0] += qh;
-                s[1] += qh * pe;
-                s[2] += qh * r;
-                s[3] += pe * r;
+                s[0] += qh * pe;
+                s[1] += qh * r;
+                s[2] += pe * r;
             }
     }
     whole_totals(s, red, wid, lane, waves);
-    const float inv_zq = inv_mass(s[0]), theta = s[1] * inv_zq, inv_S = inv_mass(s[2] * fN * inv_zq + theta * s[3]);
-    const float nzs = fN * inv_zq * inv_S, ths = theta * inv_S;
+    // with the drafter row's mass Z, theta = s0 / Z and S = (N s1 + s0 s2) / Z: Z cancels in N / (Z S) and in theta / S
+    const float T = fmaf(s[1], fN, s[0] * s[2]);
+    const float nzs = T > 0.f ? fN / T : 0.f, ths = T > 0.f ? s[0] / T : s[0] * 0.f;   // a row without mass gives the zero row
     float *orow = out ? out + row * ldo : nullptr;
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
@@ -828,7 +830,7 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             sq = wave_sum(sq);
             sr = wave_sum(sr);
             sa = wave_sum(sa);
-            if (!orow) {   // a row with a NaN or an infinity has one in theta, which the minima and maxima above would hide
+            if (!orow) {   // a row with a NaN or an infinity has a NaN in sum q^ p, which the minima and maxima above would hide
                 sr += ths * 0.f;
                 sa += ths * 0.f;
             }
@@ -1557,11 +1559,17 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
         }
         // timed as the kernel whose calls it takes
         const char *name = out || (PK != RDK_PROB_F32 && h.N < kOnePassMinN) ? "taylor_write_kernel" : "taylor_row_kernel";
-#define RDK_WHOLE_LAUNCH(FUSE)                                                                                                \
-    RDK_TIMED_LAUNCH(name, (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), 0, st, p.ptr, \
-                     p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.slot_of, h.N, h.n, out, ldo, fa)
-        if (c) RDK_WHOLE_LAUNCH(true);
-        else RDK_WHOLE_LAUNCH(false);
+#define RDK_WHOLE_LAUNCH(FUSE, LDS)                                                                                           \
+    RDK_TIMED_LAUNCH(name, (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), LDS, st, p.ptr, p.ld, q.ptr, \
+                     q.ld, h.lane_map, h.chunk_lo, h.slot_of, h.N, h.n, out, ldo, fa)
+        if (c) {
+            static LdsGrant grant;
+            rc = grant((const void *)taylor_whole_kernel<PK, QK, true>, kHeldQuads * sizeof(float4));
+            if (rc != RDK_OK) return rc;
+            RDK_WHOLE_LAUNCH(true, kHeldQuads * sizeof(float4));
+        } else {
+            RDK_WHOLE_LAUNCH(false, 0);
+        }
 #undef RDK_WHOLE_LAUNCH
         RDK_LAUNCH_CHECK("taylor_write_kernel");
         return c ? scan_if_left(fa, st) : RDK_OK;
