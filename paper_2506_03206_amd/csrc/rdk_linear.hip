@@ -1522,16 +1522,19 @@ bool taylor_in_one(const KernelHandle &h, int32_t B)
 
 // The same for the fused call without q', beside taylor_row_kernel.  That one reads the tables of a kernel, keeps the kept target
 // values in LDS and goes through the kept slots again; this one holds everything in registers and has less to do after its sums, but
-// every id carries a drafter value, and beyond 8192 ids its sixteen wavefronts fill a compute unit.  Fused calls, taylor_row_kernel
-// -> this, probabilities / fp32 logits, us: N = 1001, 64 positions 11.5 / 22.3 (logits below 1024 ids: four launches) -> 8.4 / 9.4, 1024
-// 21.9 / 27.6 -> 17.7 / 20.5; N = 4000, 4 11.0 / 11.3 -> 8.0 / 8.8, 512 13.7 / 14.8 -> 10.5 / 13.2, 1024 23.0 / 25.0 -> 18.9 / 22.2; N = 8003, 64
-// 11.6 / 12.8 -> 9.0 / 11.0, 512 14.6 / 16.0 -> 13.3 / 16.3, 1024 24.3 / 26.8 -> 22.4 / 27.2; N = 16000, 64 12.5 / 14.3 -> 10.9 / 14.4, 256 13.5 /
-// 15.1 -> 12.7 / 16.1, 512 17.7 / 19.8 -> 23.7 / 28.9; N = 24576, 4 13.2 / 14.5 -> 11.6 / 15.7, 256 16.2 / 17.9 -> 15.5 / 19.9.
+// every id carries a drafter value (and the exponential of one), and beyond 8192 ids its wavefronts leave no room for a second
+// row on a compute unit.  Fused calls, taylor_row_kernel -> this, probabilities / fp32 logits, us: N = 1001, 64 positions 11.5 / 22.3
+// (logits below 1024 ids: four launches) -> 7.5 / 8.8, 1024 21.9 / 27.6 -> 17.5 / 20; N = 8003, 4 10.8 / 11.7 -> 7.8 / 9.8, 512 14.1 / 15.7 ->
+// 11.9 / 15.2, 1024 24.3 / 26.8 -> 22 / 27; N = 12000, 16 11.9 / 13.2 -> 9.4 / 12.0, 256 13.3 / 14.6 -> 10.6 / 13.2, 384 16.0 / 18.1 -> 17.3 /
+// 22.5; N = 14003, 16 12.2 / 13.4 -> 10.1 / 14.3; N = 20003, 64 13.3 / 14.7 -> 10.9 / 14.9; N = 32003, 4 13.5 / 15.2 -> 12.5 / 17.9, 256 17.6 /
+// 19.6 -> 16.9 / 22.6.
+constexpr int kWholeLogitN = 12 * kChunk;
 bool taylor_finished_in_one(const KernelHandle &h, int32_t B, rdk_input_kind_t p_kind)
 {
-    const bool side_by_side = B <= kComputeUnits;   // a compute unit for every row
-    if (h.N <= kFinishWaves * kChunk) return p_kind == RDK_PROB_F32 || side_by_side || h.N <= kFinishWaves / 2 * kChunk;
-    return p_kind == RDK_PROB_F32 && side_by_side && h.N <= kWholeAnyBatchN;
+    if (h.N < 4 || h.n < 4 || B > kWholeMostRows) return false;
+    const bool prob = p_kind == RDK_PROB_F32;
+    if (B <= kComputeUnits) return h.N <= (prob ? kWholeMaxN : kWholeLogitN);
+    return h.N <= (prob || B <= 2 * kComputeUnits ? kFinishWaves : kFinishWaves / 2) * kChunk;
 }
 
 // c == nullptr: plain Eq. 3 into `out`.  Otherwise the fused call: verification sums per block, then the finish.
@@ -1546,7 +1549,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     const size_t per = align_up((size_t)B * nchunks * sizeof(float), 256);
     char *fused_ws = (char *)ws + taylor_workspace_bytes(h, B);
     uint64_t *seq_rec = (uint64_t *)(fused_ws + 3 * per);
-    if (taylor_in_one(h, B) && (out || taylor_finished_in_one(h, B, p.kind))) {
+    if (out ? taylor_in_one(h, B) : taylor_finished_in_one(h, B, p.kind)) {
         // q' has the same bits in the call that only writes it and in the fused one
         FinalizeArgs fa{};
         int waves = nchunks < kWholeThreads / kWave ? nchunks : kWholeThreads / kWave;

@@ -80,7 +80,9 @@ def test_rows_written_in_one_launch(shape, kinds):
 # vocabularies are left to more positions than this one takes.
 @pytest.mark.parametrize("kind", ["prob", "logit", "bf16"])
 @pytest.mark.parametrize("N,n,B,gamma", [(1001, 1000, 5, 1), (1023, 131, 1026, 3), (1025, 131, 1026, 3), (4096, 900, 257, 1),
-                                         (4097, 900, 257, 1), (8192, 2000, 256, 4), (8193, 2000, 6, 3), (3001, 700, 1026, 2)])
+                                         (4097, 900, 257, 1), (8192, 2000, 256, 4), (8193, 2000, 6, 3), (8192, 2000, 513, 3),
+                                         (8193, 2000, 257, 1), (12288, 3000, 5, 1), (12289, 3000, 256, 2), (32768, 8000, 3, 3),
+                                         (3001, 700, 1026, 2)])
 def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
     from paper_2506_03206_amd import rdk
     rng = np.random.default_rng(N + B)
