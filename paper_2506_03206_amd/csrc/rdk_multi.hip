@@ -360,10 +360,11 @@ __global__ __launch_bounds__(kRoundThreads) void verify_multi_round_kernel(Multi
 
 // Which batches go a launch a round: a launch costs 4 to 5 us whether or not a position still needs it, a round of a position in one
 // workgroup 10 us per 100000 ids, and with more positions than compute units others take the place of those that are done.  Calls of
-// tree product and verification, one workgroup a position -> rounds: N = 60001, C = 4, 16 positions 36.4 -> 35.5 us, 100
-// 44.9 -> 47.0; N = 128256, C = 4, 16 55.8 -> 39.0, 128 112.8 -> 95.8, 256 178 -> 172, 384 231.7 -> 232.0; N = 256987, C = 4, 4 76.5 -> 42.8;
-// N = 260000, C = 2, 256 fp32 logits 423 -> 406; N = 100000, C = 4, 128 79.5 -> 70.4, 256 114 -> 114; N = 100000, C = 3, 240 bf16 145 -> 142, 384 174 -> 180; N = 60000,
-// C = 2, 128 47.6 -> 46.6, 256 67.7 -> 69.2; N = 30001, 4 22.1 -> 28.8.  Candidates drawn here stay with the one workgroup.
+// tree product and verification, one workgroup a position -> rounds: N = 60001, C = 4, 16 positions 36.4 -> 35.5 us, 100 44.9 ->
+// 47.0; N = 128256, C = 4, 16 55.8 -> 39.0, 128 112.8 -> 95.8, 256 178 -> 172, 384 231.7 -> 232.0; N = 256987, C = 4, 4 76.5 -> 42.8;
+// N = 260000, C = 2, 256 fp32 logits 423 -> 406; N = 100000, C = 4, 128 79.5 -> 70.4, 256 114 -> 114; N = 100000, C = 3, 240 bf16 145 ->
+// 142, 384 174 -> 180; N = 60000, C = 2, 128 47.6 -> 46.6, 256 67.7 -> 69.2; N = 30001, 4 22.1 -> 28.8.  Candidates drawn here stay with
+// the one workgroup.
 // Up to 32 positions a wavefront has one block and asks for it before it knows whether its position goes on; a larger batch pays
 // for what positions that are done have read, and for the dispatch of its workgroups: two blocks a wavefront, read once the
 // decision is taken (asked for early -> this: N = 128256, 64 positions 67.7 -> 64.5, N = 200000, 96 rows of bf16 logits 154 -> 144, 32
