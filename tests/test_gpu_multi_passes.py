@@ -66,3 +66,30 @@ def test_a_launch_a_round(N, C, kind):
     ref = oracle.verify_multi_batch(p64, q64, C, seed, offset, cand_ids=cand[:n])
     few = rdk.rdk_verify_multi(p[:n], qp[:n], C, seed, offset, kind, cand_ids=cd[:n].contiguous())
     check_multi(few, ref, p64, q64, seed, offset, C, min_exact=0.8)
+
+
+def test_rounds_in_a_graph():
+    """Replays on other candidates, with eager calls between them, against the eager call."""
+    from paper_2506_03206_amd import rdk
+    N, C, B = 60001, 2, 40
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    z = torch.randn((B, N), generator=gen, device="cuda").mul_(2)
+    p, qp = torch.softmax(z, 1), torch.softmax(z + torch.randn((B, N), generator=gen, device="cuda"), 1)
+    cand = torch.randint(0, N, (B, C), generator=gen, device="cuda", dtype=torch.int32)
+    o = rdk.MultiOutputs(B, C, "cuda")
+    rdk.rdk_verify_multi(p, qp, C, 5, 9, cand_ids=cand, outputs=o)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rdk.rdk_verify_multi(p, qp, C, 5, 9, cand_ids=cand, outputs=o)
+    for rep in range(3):
+        cand.copy_(torch.topk(qp, C + rep, dim=1).indices[:, rep:].int())
+        cand[rep::5, 1:] = -1
+        cand[rep + 1::7] = -1
+        o.token.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = rdk.rdk_verify_multi(p, qp, C, 5, 9, cand_ids=cand)
+        for name in ("accepted", "token", "resid_mass"):
+            assert torch.equal(getattr(o, name), getattr(ref, name)), name

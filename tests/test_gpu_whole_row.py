@@ -131,3 +131,38 @@ def test_rows_without_mass_and_with_nan(N, keep):
             assert not qp[1].any() and qp[2:5].isnan().any(1).all()
         else:
             assert o.alpha[2:5].isnan().all() and o.resid_mass[2:5].isnan().all()
+
+
+@pytest.mark.parametrize("N,B,keep", [(3000, 20, False), (3000, 20, True), (20001, 640, True), (8000, 512, False)])
+def test_graph_replays_of_rows_in_one_launch(N, B, keep):
+    """Replays on other rows, with eager calls between them, against the eager call; every sequence is scanned."""
+    from paper_2506_03206_amd import rdk
+    kern = rdk.rdk_build_kernel(N, torch.arange(1, N, 3, dtype=torch.int32, device="cuda"), rdk.IDENTITY)
+    gamma = 4
+
+    def rows(seed):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        z = torch.randn((B, N), generator=gen, device="cuda")
+        return torch.softmax(2 * z, 1), torch.softmax(2 * z + torch.randn((B, N), generator=gen, device="cuda"), 1)[:, 1::3].contiguous()
+    p, q = rows(0)
+    o, qp = rdk.VerifyOutputs(B, N, gamma, "cuda"), torch.empty((B, N), device="cuda") if keep else None
+    call = lambda out, held: rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, p, q, 5, 0, gamma, q_prime=held, outputs=out)
+    call(o, qp)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(o, qp)
+    for rep in range(3):
+        p2, q2 = rows(10 + rep)
+        p.copy_(p2)
+        q.copy_(q2)
+        o.n_accepted.fill_(-7)
+        o.out_tokens.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        ref, held = rdk.VerifyOutputs(B, N, gamma, "cuda"), torch.empty((B, N), device="cuda") if keep else None
+        call(ref, held)
+        for name in ("draft_ids", "accept", "alpha", "resid_mass", "resid_ids", "n_accepted", "out_tokens"):
+            assert torch.equal(getattr(o, name), getattr(ref, name)), name
+        assert (o.n_accepted >= 0).all() and (not keep or torch.equal(qp, held))
