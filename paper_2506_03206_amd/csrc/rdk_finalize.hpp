@@ -147,8 +147,9 @@ __device__ __forceinline__ double lane_partial_sum(const float *part, int nblk, 
 // Block in which the inclusive prefix of `part` first exceeds thr (-1 if none) and the prefix before it.  Lane l has added up
 // the per_lane consecutive blocks from l * per_lane (lane_sum); those of the lane in which the threshold is crossed are read again,
 // one per lane: a scan of 64 lanes takes a fifth of the instructions that one lane needs to walk through 32 blocks of its own
-// (N = 128256, 8 positions: fused 18.8 -> 18.1 us a call, draft draw 15.6 -> 14.8; N = 1024, 16 positions 8.63 -> 8.31).  Where rounding leaves no crossing among them it is the last block with a
-// positive sum.
+// (N = 128256, 8 positions: fused 18.8 -> 18.1 us a call, draft draw 15.6 -> 14.8; N = 1024, 16 positions 8.63 -> 8.31).  Only
+// blocks with mass can be crossed: the scan adds in another order for every lane, so a lane behind the last block may hold an ulp
+// more than that block.  Where rounding leaves no crossing among them it is the last block with a positive sum.
 __device__ __forceinline__ int locate_block(const float *part, int nblk, int per_lane, double lane_sum, double thr,
                                             double &prefix_before)
 {
@@ -161,7 +162,7 @@ __device__ __forceinline__ int locate_block(const float *part, int nblk, int per
     for (int c = c0; c < c1; c += kWave) {
         const double x = c + lane_id() < c1 ? (double)part[c + lane_id()] : 0.0;
         const double to = before + wave_inclusive_scan(x);
-        const unsigned long long over = __ballot(to > thr), some = __ballot(x > 0.0);
+        const unsigned long long over = __ballot(x > 0.0 && to > thr), some = __ballot(x > 0.0);
         if (over != 0ull || some != 0ull) {
             const int at = over != 0ull ? __ffsll(over) - 1 : 63 - __clzll(some);
             blk = c + at;
