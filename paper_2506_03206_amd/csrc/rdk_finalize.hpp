@@ -223,7 +223,14 @@ __device__ __forceinline__ float pick(const float4 (&w)[SUB], int i, int e)
     return r;
 }
 
-// Smallest id of the block whose inclusive prefix of weights exceeds thr_local; if rounding leaves none,
+// Which of a lane's four ids the threshold crosses, given that it crosses one: excl = the prefix before them, l0 .. l2 their own
+// first sums.  Like a block (locate_block), an id is crossed only if it has a weight: the sums beside it may differ by an ulp.
+__device__ __forceinline__ int crossed_id(float w0, float w1, float w2, double l0, double l1, double l2, double excl, double thr)
+{
+    return w0 > 0.f && excl + l0 > thr ? 0 : w1 > 0.f && excl + l1 > thr ? 1 : w2 > 0.f && excl + l2 > thr ? 2 : 3;
+}
+
+// Smallest id of the block with a positive weight whose inclusive prefix of weights exceeds thr_local; if rounding leaves none,
 // the last id of the block with a positive weight.  wv[i] = weights of ids base + i*256 + lane*4 .. +3.
 template <int SUB>
 __device__ __forceinline__ int search_block(const float4 (&wv)[SUB], int base, double thr_local)
@@ -237,10 +244,10 @@ __device__ __forceinline__ int search_block(const float4 (&wv)[SUB], int base, d
         const double l0 = (double)wv[i].x, l1 = l0 + (double)wv[i].y, l2 = l1 + (double)wv[i].z, l3 = l2 + (double)wv[i].w;
         const double incl = wave_inclusive_scan(l3);
         const double excl = carried + (incl - l3);
-        const unsigned long long hits = __ballot(excl + l3 > thr_local);
+        const unsigned long long hits = __ballot(l3 > 0.0 && excl + l3 > thr_local);
         if (hits != 0ull) {
             const int src = __ffsll(hits) - 1;
-            const int e = (excl + l0 > thr_local) ? 0 : (excl + l1 > thr_local) ? 1 : (excl + l2 > thr_local) ? 2 : 3;
+            const int e = crossed_id(wv[i].x, wv[i].y, wv[i].z, l0, l1, l2, excl, thr_local);
             return lane_value(idx + e, src);
         }
         const int mine = wv[i].w > 0.f ? 3 : wv[i].z > 0.f ? 2 : wv[i].y > 0.f ? 1 : wv[i].x > 0.f ? 0 : -1;
@@ -258,7 +265,7 @@ __device__ __forceinline__ int search_block(const float4 (&wv)[SUB], int base, d
 __device__ __forceinline__ int search_block1(float w, int base, double thr_local)
 {
     const double incl = wave_inclusive_scan((double)w);
-    const unsigned long long hits = __ballot(incl > thr_local);
+    const unsigned long long hits = __ballot(w > 0.f && incl > thr_local);
     if (hits != 0ull) return base + (__ffsll(hits) - 1);
     const unsigned long long pos = __ballot(w > 0.f);
     return pos != 0ull ? base + (63 - __clzll(pos)) : -1;
@@ -584,10 +591,10 @@ __device__ __forceinline__ void finish_row_quarters(float *scratch, const float 
         for (int i = 0; i < fq; ++i) carried += fd[4 + 4 * fb + i];
         const double thr_local = fd[fb];
         const double excl = carried + (incl - l3);
-        const unsigned long long hits = __ballot(excl + l3 > thr_local);
+        const unsigned long long hits = __ballot(l3 > 0.0 && excl + l3 > thr_local);
         int hit = -1;
         if (hits != 0ull) {
-            const int e = (excl + l0 > thr_local) ? 0 : (excl + l1 > thr_local) ? 1 : (excl + l2 > thr_local) ? 2 : 3;
+            const int e = crossed_id(wv4[0], wv4[1], wv4[2], l0, l1, l2, excl, thr_local);
             hit = lane_value((int)fidx + e, __ffsll(hits) - 1);
         }
         const int cand = hit >= 0 ? hit : last_pos;

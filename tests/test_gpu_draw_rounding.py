@@ -1,5 +1,5 @@
-"""Draws whose threshold lies on a step of the prefix sums, where fp64 sums taken in another order differ by an ulp: the block that is
-picked carries mass and lies in the row."""
+"""Draws whose threshold lies on a step of the prefix sums, where fp64 sums taken in another order differ by an ulp: the block and
+the id that are picked carry mass and lie in the row."""
 import numpy as np
 import pytest
 import torch
@@ -18,6 +18,17 @@ def uniform(call, seed):
     return float(oracle.uniforms(seed, 0)[{"draft": 0, "residual": 2, "bonus": 3, "fused": 2}[call]])
 
 
+def with_rest(row, block, rest):
+    """The rest of the total, with the blocks of three other lanes, in floats that add up to it exactly."""
+    for i in range(3):
+        f = np.float32(rest)
+        f = np.nextafter(f, np.float32(0)) if float(f) > rest else f
+        row[(4 + 4 * i) * block] = f
+        rest -= float(f)
+    assert rest == 0.0
+    return row
+
+
 def row_between_blocks(u, block):
     """A lane owns four blocks, of sums 1, 0, 3/4 ulp and 1/2 ulp, and the threshold u * total is 1 + ulp: added up one after the
     other they are 1 + 2 ulp, a scan over the lanes has reached 1 + ulp at the last of them, and 1 + 2 ulp three lanes later, where
@@ -28,14 +39,7 @@ def row_between_blocks(u, block):
         return None
     row = np.zeros(N, np.float32)
     row[0], row[2 * block + 5], row[3 * block + 9] = 1.0, 0.75 * ULP, 0.5 * ULP
-    rest = total - (1.0 + 2 * ULP)               # the rest of the total lies with other lanes, in floats that add up to it exactly
-    for i in range(3):
-        f = np.float32(rest)
-        f = np.nextafter(f, np.float32(0)) if float(f) > rest else f
-        row[(4 + 4 * i) * block] = f
-        rest -= float(f)
-    assert rest == 0.0
-    return row, [2 * block + 5, 3 * block + 9]
+    return with_rest(row, block, total - (1.0 + 2 * ULP)), [2 * block + 5, 3 * block + 9]
 
 
 def rows(call, make, count):
@@ -75,4 +79,25 @@ def draw(call, row, seed):
 @pytest.mark.parametrize("call", list(BLOCK))
 def test_threshold_between_two_orders_of_the_block_sums(call):
     for seed, row, ids in rows(call, row_between_blocks, 3):
+        assert draw(call, row, seed) in ids
+
+
+def row_between_ids(u, block):
+    """Ids 0, 4, 8 and 12 (0 to 3 in blocks of 64) of the first block weigh 1 and three times 1/4 ulp, and the threshold is 1: their
+    own prefixes are rounded to 1, those of the empty places that follow to 1 + ulp.  The next id with a weight is drawn, or, with
+    sums that don't round, the second."""
+    step = 1 if block == 64 else 4
+    total = next((float(t) for t in (1.0 / u, np.nextafter(1.0 / u, 0), np.nextafter(1.0 / u, 4)) if u * t == 1.0), 0.0)
+    if not 1.01 < total < 1.99:
+        return None
+    row = np.zeros(N, np.float32)
+    row[0], row[step], row[2 * step], row[3 * step] = 1.0, 0.25 * ULP, 0.25 * ULP, 0.25 * ULP
+    row[50 * step + 1 if step > 1 else 50] = 2.0 ** -8
+    return with_rest(row, block, total - (1.0 + 2.0 ** -8)), [step, 2 * step, 3 * step, 50 * step + 1 if step > 1 else 50]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", list(BLOCK))
+def test_threshold_between_two_orders_of_a_block(call):
+    for seed, row, ids in rows(call, row_between_ids, 3):
         assert draw(call, row, seed) in ids
