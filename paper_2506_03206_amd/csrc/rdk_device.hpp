@@ -110,6 +110,10 @@ __device__ __forceinline__ float soft_exp_fine(float x)
 // then returns the zero row (no token can be drafted from it; verification falls back on the target row alone).
 __device__ __forceinline__ float inv_mass(float z) { return z > 0.f ? 1.0f / z : 0.f; }
 
+// What the weights of a drafter row of logits are formed against: its maximum, or 0 if all of its ids are masked.  Their weights are
+// exp(-inf) = 0 then, where -inf for both would make them NaN, and the row is one without mass like any other.
+__device__ __forceinline__ float weight_reference(float row_max) { return row_max > -INFINITY ? row_max : 0.f; }
+
 // ---- softmax statistics (running maximum m and sum of exp(z - m)), merged pairwise
 struct SoftStat {
     float m, s;

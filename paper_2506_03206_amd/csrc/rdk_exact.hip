@@ -71,7 +71,7 @@ __device__ __forceinline__ void load8(const void *qr, int s, int n, float fill, 
     }
 }
 
-// Largest value of a logit row, in every thread (0 for probabilities).
+// What a logit row's weights are formed against, in every thread (0 for probabilities).
 template <int QK>
 __device__ __forceinline__ float prep_row_max(const void *qr, int n, float *sh)
 {
@@ -89,7 +89,7 @@ __device__ __forceinline__ float prep_row_max(const void *qr, int n, float *sh)
     m = sh[0];
     for (int i = 1; i < kPrepWaves; ++i) m = fmaxf(m, sh[i]);
     __syncthreads();
-    return m;
+    return weight_reference(m);
 }
 
 // Sum over the workgroup, in every thread.
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kStatThreads) void prep_a_records_kernel(const void
     for (int e = 0; e < 8; ++e) h[e] = m[e] = lo[e] = 0u;
     if (b < B) {
         const void *qr = row_ptr<QK>(q, ldq, b);
-        const float qm = QK == RDK_PROB_F32 ? 0.f : qstat[b].m;
+        const float qm = QK == RDK_PROB_F32 ? 0.f : weight_reference(qstat[b].m);
         const int s = kb * kSplitStep + g * 8;
         if (s < n) {
             float v[8];

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
         pm = rs.m;
         pinv = 1.0f / rs.s;
     }
-    const float qm = QK == RDK_PROB_F32 ? 0.f : w.qstat[row].m;
+    const float qm = QK == RDK_PROB_F32 ? 0.f : weight_reference(w.qstat[row].m);
     const float pfill = PK == RDK_PROB_F32 ? 0.f : -INFINITY;
     const float fN = (float)N;
     float zq = 0.f, tn = 0.f, an = 0.f, bs = 0.f;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
     const void *pr = row_ptr<PK>(p, ldp, row);
     const void *qr = row_ptr<QK>(q, ldq, row);
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = lane_id();
-    const float qm = QK == RDK_PROB_F32 ? 0.f : w.qstat[row].m;
+    const float qm = QK == RDK_PROB_F32 ? 0.f : weight_reference(w.qstat[row].m);
     float m = -INFINITY;                                         // running maximum, the same in all lanes
     float s1 = 0.f, s2 = 0.f, s3 = 0.f, q0 = 0.f, q1 = 0.f, q2 = 0.f, q3 = 0.f;
     int c = c_begin + wid;
@@ -364,7 +364,7 @@ __device__ __forceinline__ TaylorRow<PK, QK> make_taylor_row(const TaylorArgs &a
         r.pm = rs.m;
         r.pinv = 1.0f / rs.s;
     }
-    r.qm = QK == RDK_PROB_F32 ? 0.f : a.w.qstat[row].m;
+    r.qm = QK == RDK_PROB_F32 ? 0.f : weight_reference(a.w.qstat[row].m);
     // totals of the first pass, summed in split order by every wavefront alike
     r.fN = (float)a.N;
     float zq, tn, an, bs;
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
         if (QK != RDK_PROB_F32) qm = wave_max(lane < waves ? red[waves + lane] : kNoLogit);
         red += 2 * waves;
     }
-    if (!(qm > kNoLogit)) qm = 0.f;   // a drafter row of masked ids has no mass
+    qm = weight_reference(qm);
     float z[1] = {0.f};
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
@@ -1500,7 +1500,7 @@ __global__ __launch_bounds__(kThreads) void tli_scatter_kernel(const void *q, in
 {
     for (int64_t row = blockIdx.y; row < B; row += gridDim.y) {   // positions beyond the grid's second dimension are looped over
         const void *qr = row_ptr<QK>(q, ldq, row);
-        const float qm = qstat[row].m, inv = inv_mass(qstat[row].s);
+        const float qm = QK == RDK_PROB_F32 ? 0.f : weight_reference(qstat[row].m), inv = inv_mass(qstat[row].s);
         for (int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x; j < N; j += (int64_t)gridDim.x * kThreads) {
             const int s = slot_of[j];
             out[row * ldo + j] = s >= 0 ? to_weight<QK>(load1<QK>(qr, s), qm, 1.f) * inv : 0.f;

@@ -141,7 +141,7 @@ __device__ __forceinline__ void slab_fill(int n, const SlabRow<QK> &row, float *
 #pragma unroll
         for (int v = 0; v < kQuads; ++v)
             if (!SlabRow<QK>::kPacked || v * kSlabThreads * 4 < n) m = fmaxf(m, max4(row.values(v)));
-        qmax = block_max(m, red);
+        qmax = weight_reference(block_max(m, red));
     }
     float z = 0.f;
 #pragma unroll

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kPrepThreads) void q_transpose_kernel(const void *q
         m = fmaxf(m, __shfl_xor(m, 1, kWave));
         m = fmaxf(m, __shfl_xor(m, 2, kWave));
         m = fmaxf(m, __shfl_xor(m, 4, kWave));
-        qm = m;
+        qm = weight_reference(m);
     }
     // the row's 512 slots of this workgroup: 8 slots per thread and tile
     float v[kTGroup][8];
@@ -444,7 +444,7 @@ struct PartialColumn {
         if (QK != RDK_PROB_F32) {
             m = -INFINITY;
             for (int i = lane_id(); i < q_splits; i += kWave) m = fmaxf(m, qpart[b * q_splits + i].m);
-            m = wave_max(m);
+            m = weight_reference(wave_max(m));
         }
         return Row{row_ptr<QK>(q, ldq, b), m, row_mass_inv(zpart, zt, b)};
     }

@@ -254,7 +254,7 @@ __device__ __forceinline__ void fill_rows(const char *const (&row)[P], int n, fl
     if (QK != RDK_PROB_F32) {
         __syncthreads();
 #pragma unroll
-        for (int p = 0; p < P; ++p) qm[p] = wave_max(red[lane % kWaves * P + p]);
+        for (int p = 0; p < P; ++p) qm[p] = weight_reference(wave_max(red[lane % kWaves * P + p]));
     }
     float z[P];
 #pragma unroll
