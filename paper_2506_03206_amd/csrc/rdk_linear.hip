@@ -469,6 +469,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
             sq = wave_sum(sq);
             sr = wave_sum(sr);
             sa = wave_sum(sa);
+            sr += tr.ths * 0.f;   // a row with a NaN or an infinity has a NaN in theta, which the minima and maxima above would hide
+            sa += tr.ths * 0.f;
             if (lane == 0) {
                 const int64_t o = row * nchunks + c;
                 part_q[o] = sq;
@@ -830,10 +832,8 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             sq = wave_sum(sq);
             sr = wave_sum(sr);
             sa = wave_sum(sa);
-            if (!orow) {   // a row with a NaN or an infinity has a NaN in sum q^ p, which the minima and maxima above would hide
-                sr += ths * 0.f;
-                sa += ths * 0.f;
-            }
+            sr += ths * 0.f;   // a row with a NaN or an infinity has a NaN in sum q^ p, which the minima and maxima above would hide
+            sa += ths * 0.f;
             if (lane == 0) {
                 sums[0][c] = sq;
                 sums[1][c] = sr;

@@ -106,10 +106,12 @@ def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
         check_verify_outputs(out, want, p64, ref, 9, 4, gamma, pk, min_exact=0.6)
 
 
-@pytest.mark.parametrize("N", [3000, 8000])
+# Rows by one workgroup, and (probabilities, or q' written; the last also for logits) in two passes.
+@pytest.mark.parametrize("N", [3000, 8000, 40000, 60000])
 @pytest.mark.parametrize("keep", [False, True])
 def test_rows_without_mass_and_with_nan(N, keep):
-    """A drafter row of masked ids (or of zeros) drafts nothing and leaves the whole target row; NaN stays visible."""
+    """A drafter row of masked ids (or of zeros) drafts nothing and leaves the whole target row; NaN stays visible, whether q' is
+    written or not."""
     from paper_2506_03206_amd import rdk
     kern = rdk.rdk_build_kernel(N, torch.arange(0, N, 4, dtype=torch.int32, device="cuda"), rdk.IDENTITY)
     gen = torch.Generator(device="cuda")
@@ -129,8 +131,7 @@ def test_rows_without_mass_and_with_nan(N, keep):
         assert (o.draft_ids[2:5] == -1).all() and (o.draft_ids[[0, 5]] >= 0).all()
         if keep:
             assert not qp[1].any() and qp[2:5].isnan().any(1).all()
-        else:
-            assert o.alpha[2:5].isnan().all() and o.resid_mass[2:5].isnan().all()
+        assert o.alpha[2:5].isnan().all() and o.resid_mass[2:5].isnan().all() and (o.resid_ids[2:5] == -1).all()
 
 
 @pytest.mark.parametrize("N,B,keep", [(3000, 20, False), (3000, 20, True), (20001, 640, True), (8000, 512, False)])
