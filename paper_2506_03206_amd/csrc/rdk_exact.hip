@@ -725,14 +725,17 @@ struct ExactWs {
     float *out_scale;  // bf16 path: [B]
 };
 
-// Split of the slot blocks of the fp32 path: as many wavefronts as the chip holds at one per SIMD (1024) but no more,
-// so that they all run side by side (a few left over for a second round would double the time); splits of a whole
-// number of ring turns.  blocks = slot blocks per split.
+// Split of the slot blocks of the fp32 path: as many workgroups as the chip holds at one per compute unit but no more, so that
+// they all run side by side (a few left over would have a second round to themselves); splits of a whole number of ring turns.
+// A workgroup counts whole where its last wavefronts lie beyond N.  Splits counted by wavefronts, which leave up to 64 workgroups over
+// where the 128-id tiles are no multiple of four -> this, the product's calls: N = 13000, n = 5000, 64 positions (260 workgroups -> 234)
+// 110 -> 77 us, N = 5200, n = 2000, 256 (264 -> 220) 65 -> 47, N = 18600, n = 5000, 64 (259 -> 222) 145 -> 91, N = 9849, n = 2954, 8
+// (260 -> 240) 45 -> 31.  blocks = slot blocks per split.
 int split_splits(const KernelHandle &h, int B, int *blocks)
 {
-    const int tiles = ((h.N + kColSet - 1) / kColSet) * ((B + kRowGroup - 1) / kRowGroup);
+    const int groups = ((h.N + kSplitWaves * kColSet - 1) / (kSplitWaves * kColSet)) * ((B + kRowGroup - 1) / kRowGroup);
     const int kb_total = (h.n + kSplitStep - 1) / kSplitStep;
-    int want = 1024 / tiles;
+    int want = kComputeUnits / groups;
     const int maxs = (kb_total + 2 * kSplitRing - 1) / (2 * kSplitRing);    // at least 96 slots per split
     if (want > maxs) want = maxs;
     if (want > 64) want = 64;
