@@ -676,7 +676,13 @@ __global__ __launch_bounds__(W * 64) void exact_bf16_kernel(const uint16_t *Ap, 
 // compute units they are split as above, in a launch of their own: N = 40000, n = 15000, 200 positions (57 of 313 left) 440 -> 350
 // us, 480 769 -> 577, N = 100000, n = 15000, 512 (14 of 782) 1646 -> 1415; with 213 of 469 left there is nothing to split, and 248
 // of the smallest ones of 1016 still draw as many bytes from HBM as the full chip (887 us, split 905).
+// Of the workgroups of four wavefronts the chip holds two on a unit: 65 to 128 positions, unsplit -> split, n = 8000, 8 of 520 groups left
+// 270 -> 229 us, 128 of 640 293 -> 277, 4 of 1028 478 -> 461.  A half round more, one for every unit, takes three quarters as long as
+// a full one.  What is left behind it is split where the rows are long (100 positions, n = 9000: 2 of 770 left 437 -> 417, 62 of 830
+// 445 -> 417, 112 of 880 455 -> 446; n = 16000: 716 -> 640, 736 -> 681, 128 of 896 763 -> 725) or where it is little (n = 5000: 2 of 770
+// left 263 -> 247, 32 of 800 266 -> 258; but n = 4000, 112 of 880 222 -> 225, and n = 8000 383 -> 391, 402 -> 446).
 constexpr int kSmallGroups = 64;
+constexpr int kHalfRoundSlots = 9000, kHalfRoundFewSlots = 7000;
 struct Bf16Shape {
     int W, RB, B_pad, groups, KB, KB_split, splits;
     int whole, tail_split, tail_splits;   // groups of full rounds; slot blocks and number of the splits of the ones after them
@@ -693,7 +699,6 @@ void split_turns(int KB, int want, int *KB_split, int *splits)
     *splits = (turns + per - 1) / per;
 }
 
-
 Bf16Shape bf16_shape(const KernelHandle &h, int B)
 {
     Bf16Shape s;
@@ -709,9 +714,15 @@ Bf16Shape bf16_shape(const KernelHandle &h, int B)
     s.whole = s.groups;
     s.tail_split = s.KB;
     s.tail_splits = 1;
-    const int resident = (s.W <= 4 && s.RB == 1 ? 3 : 1) * kComputeUnits;   // LDS holds three of them, the registers one of the others
-    const int tail = s.groups % resident;
-    if (rows == s.B_pad && s.groups > resident && tail > 0 && tail * 2 <= kComputeUnits) {
+    // workgroups that a compute unit holds: LDS three of two wavefronts, the registers two of four, and one of the others
+    const int resident = (s.RB > 1 || s.W == 8 ? 1 : s.W == 4 ? 2 : 3) * kComputeUnits;
+    int tail = s.groups % resident;
+    bool cut = tail * 2 <= kComputeUnits;
+    if (resident == 2 * kComputeUnits && tail > kComputeUnits) {
+        tail -= kComputeUnits;
+        cut = tail * 2 <= kComputeUnits && (h.n >= kHalfRoundSlots || (tail * 8 <= kComputeUnits && h.n <= kHalfRoundFewSlots));
+    }
+    if (rows == s.B_pad && s.groups > resident && tail > 0 && cut) {
         split_turns(s.KB, resident / tail, &s.tail_split, &s.tail_splits);
         if (s.tail_splits > 1) s.whole = s.groups - tail;
     }
@@ -730,7 +741,7 @@ struct ExactWs {
 // A workgroup counts whole where its last wavefronts lie beyond N.  Splits counted by wavefronts, which leave up to 64 workgroups over
 // where the 128-id tiles are no multiple of four -> this, the product's calls: N = 13000, n = 5000, 64 positions (260 workgroups -> 234)
 // 110 -> 77 us, N = 5200, n = 2000, 256 (264 -> 220) 65 -> 47, N = 18600, n = 5000, 64 (259 -> 222) 145 -> 91, N = 9849, n = 2954, 8
-// (260 -> 240) 45 -> 31.  blocks = slot blocks per split.
+// (260 -> 220) 45 -> 31.  blocks = slot blocks per split.
 int split_splits(const KernelHandle &h, int B, int *blocks)
 {
     const int groups = ((h.N + kSplitWaves * kColSet - 1) / (kSplitWaves * kColSet)) * ((B + kRowGroup - 1) / kRowGroup);
@@ -867,7 +878,7 @@ size_t exact_workspace_bytes(const KernelHandle &h, int32_t B)
         bytes += align_up((size_t)c.B_pad * h.n_pad * 2, 256) + align_up((size_t)B * sizeof(float), 256);
         // A workspace for a batch serves every smaller one, so what is asked for must not fall as B grows: the rows of partial
         // products, splits * B, are at most B times the splits that one row of workgroups can have, and at most those splits of
-        // a full one (its rows, 128 to 512, grow with B).
+        // a full one (its rows, 64 to 512, grow with B).
         const size_t splits = std::min<size_t>(c.KB / 24, kComputeUnits / c.groups), full = (size_t)c.W * c.RB * 32 * (kComputeUnits / c.groups);
         const size_t rows = splits > 1 ? std::min(B * splits, full) : 0;
         size_t partials = rows * padded(h.N);

@@ -45,10 +45,10 @@ def test_fp32_drafter_rows(shape, kind):
     check_product((N + n, n, B), "f32", kind)
 
 
-# Column groups (128 ids) beyond whole rounds of the chip (256 workgroups, 768 of the smaller ones) have their slots split: one group
-# and a ragged one, 128 groups (the most that are split), one more, a single turn of slots (nothing to split), and the batches
+# Column groups (128 ids) beyond whole rounds of the chip (256 workgroups, 768 of the smallest ones, 512 of the next, or those and 256
+# more) have their slots split: one group and a ragged one, 128 groups (the most that are split), one more, a single turn of slots (nothing to split), and the batches
 # at which the workgroup changes.
-@pytest.mark.parametrize("shape", [(98305, 800, 3), (98500, 400, 64), (98305, 800, 65), (98500, 400, 128), (32897, 1153, 129),
+@pytest.mark.parametrize("shape", [(98305, 800, 3), (98500, 400, 64), (98305, 800, 65), (98500, 400, 128), (65537, 800, 65), (81900, 800, 100), (32897, 1153, 129),
                                    (33001, 1200, 256), (49152, 800, 300), (49153, 800, 260), (33001, 384, 200), (33030, 3100, 512)])
 def test_bf16_tail(shape):
     check_product(shape, "bf16", "prob")

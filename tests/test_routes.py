@@ -36,3 +36,33 @@ def test_splits_of_the_fp32_product_run_side_by_side(ask):
         assert len(grid) == 1 and grid[0][0] <= UNITS, shape
         split += 1
     assert split > 300
+
+
+# Column groups (128 ids) of the 16-bit product that are left after whole rounds of the chip, which holds three workgroups of two
+# wavefronts on a compute unit (up to 64 positions), two of four (up to 128) and one of the larger ones: a launch of its own, its
+# slots split over the chip.
+@pytest.mark.parametrize("B,resident", [(64, 3), (65, 2), (128, 2), (129, 1), (256, 1), (257, 1)])
+def test_last_round_of_the_16_bit_product(ask, B, resident):
+    full = resident * UNITS
+    for rounds in (1, 2):
+        for tail in (1, 8, 92, UNITS // 2, UNITS // 2 + 1, full - 1):
+            assert_cut(ask, B, rounds * full + tail, 2000, tail if tail <= UNITS // 2 else 0, full)
+
+
+# Two on a unit, and half a round and some groups left: the ones after the half round, where they are few or the rows long.
+@pytest.mark.parametrize("n,tail,cut", [(2000, 32, True), (7000, 32, True), (7001, 32, False), (2000, 33, False), (8999, 1, False),
+                                        (9000, 1, True), (9000, 128, True), (9000, 129, False)])
+def test_last_half_round_of_the_16_bit_product(ask, n, tail, cut):
+    for rounds in (1, 2):
+        assert_cut(ask, 100, rounds * 2 * UNITS + UNITS + tail, n, tail if cut else 0, 2 * UNITS)
+    assert_cut(ask, 100, UNITS + tail, n, 0, 2 * UNITS)       # all of them run side by side
+
+
+def assert_cut(ask, B, groups, n, tail, full):
+    lines = ["kernel %d %d %d 0" % (DENSE_BF16, groups * 128, n)]
+    lines.append("exact %d %d" % (PROB, B))
+    grids = [x.grid for x in ask(lines)[1].launches if x.kernel.startswith("exact_bf16_kernel")]
+    if tail:
+        assert grids[0] == (groups - tail, 1, 1) and grids[1][:2] == (tail, 1) and 2 <= grids[1][2] <= full // tail, grids
+    else:
+        assert grids == [(groups, 1, 1)], grids
