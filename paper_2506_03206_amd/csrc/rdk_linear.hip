@@ -1512,26 +1512,35 @@ __global__ __launch_bounds__(kThreads) void tli_scatter_kernel(const void *q, in
 // for most wavefronts, from 64 positions on; fewer leave the chip to the form that splits a row.  One call of the redistribution
 // alone, two passes -> one launch, probabilities / bf16 logits, us: N = 1001, 64 rows 7.5 -> 4.1; N = 4000, 4 rows 6.6 / 11.6 -> 4.0 / 5.1,
 // 256 8.0 / 13.0 -> 4.7 / 5.9; N = 16000, 64 8.4 / 13.2 -> 6.0 / 9.4, 512 23.2 / 29.9 -> 17.2 / 21.4; N = 20003, 4 7.0 / 12.2 -> 5.5 / 9.7, 256
-// 16.0 / 23.3 -> 11.1 / 13.5, 1024 51.1 / 54.8 -> 44.8 / 46.1; N = 32000, 4 6.8 / 11.7 -> 7.3 / 13.0 (not taken), 64 9.3 / 14.1 -> 8.7 /
-// 14.3, 256 22.8 / 29.2 -> 14.6 / 18.6, 1024 85.9 / 73.6 -> 66.4 / 73.9.  Beyond 1024 rows, where nothing was measured, the two passes.
-constexpr int kWholeAnyBatchN = 24 * kChunk, kWholeLeastRows = 64, kWholeMostRows = 4 * kComputeUnits;
-bool taylor_in_one(const KernelHandle &h, int32_t B)
+// 16.0 / 23.3 -> 11.1 / 13.5; N = 32000, 4 6.8 / 11.7 -> 7.3 / 13.0 (not taken), 256 22.8 / 29.2 -> 14.6 / 18.6, 1024 76.5 / 70.7 -> 59.8 /
+// 60.3.  The fused call that keeps q' takes the same form, for the same bits, and gains less on a full chip, where the finish of a row
+// holds its registers: between 4 and 1024 rows of 4097 to 32000 ids it was faster at every size measured but one (513 bf16 rows of
+// 32000 ids, +4 %).  Beyond 1024 rows the two meet (redistribution alone / fused with q'): logits at 8192 ids (8192 bf16 rows of 8003
+// ids 154 -> 108 / 225 -> 174, 4096 of 12000 102 -> 75 / 145 -> 173), probabilities not below 32768 (4096 of 32000 363 -> 220 / 398 -> 267);
+// beyond 2048 rows also at two chunks of ids, below which the finish is most of the call (4096 rows of probabilities, 3001 ids 36 -> 21 /
+// 69 -> 55, 1001 20.7 -> 11.0 / 51.5 -> 54.3, 200 16.5 -> 6.1 / 43.2 -> 48.7).
+constexpr int kWholeAnyBatchN = 24 * kChunk, kWholeLeastRows = 64;
+constexpr int kWholeManyRows = 4 * kComputeUnits, kWholeManyLogitN = 8 * kChunk, kWholeMostRows = 8 * kComputeUnits, kWholeMostLeastN = 2 * kChunk;
+bool taylor_in_one(const KernelHandle &h, int32_t B, bool prob)
 {
-    return h.N >= 4 && h.n >= 4 && h.N <= (B < kWholeLeastRows ? kWholeAnyBatchN : kWholeMaxN) && B <= kWholeMostRows;
+    if (h.N < 4 || h.n < 4) return false;
+    if (B <= kWholeManyRows) return h.N <= (B < kWholeLeastRows ? kWholeAnyBatchN : kWholeMaxN);
+    return h.N <= (prob ? kWholeMaxN : kWholeManyLogitN) && (B <= kWholeMostRows || h.N >= kWholeMostLeastN);
 }
 
 // The same for the fused call without q', beside taylor_row_kernel.  That one reads the tables of a kernel, keeps the kept target
 // values in LDS and goes through the kept slots again; this one holds everything in registers and has less to do after its sums, but
 // every id carries a drafter value (and the exponential of one), and beyond 8192 ids its wavefronts leave no room for a second
 // row on a compute unit.  Fused calls, taylor_row_kernel -> this, probabilities / fp32 logits, us: N = 1001, 64 positions 11.5 / 22.3
-// (logits below 1024 ids: four launches) -> 7.5 / 8.8, 1024 21.9 / 27.6 -> 17.5 / 20; N = 8003, 4 10.8 / 11.7 -> 7.8 / 9.8, 512 14.1 / 15.7 ->
-// 11.9 / 15.2, 1024 24.3 / 26.8 -> 22 / 27; N = 12000, 16 11.9 / 13.2 -> 9.4 / 12.0, 256 13.3 / 14.6 -> 10.6 / 13.2, 384 16.0 / 18.1 -> 17.3 /
-// 22.5; N = 14003, 16 12.2 / 13.4 -> 10.1 / 14.3; N = 20003, 64 13.3 / 14.7 -> 10.9 / 14.9; N = 32003, 4 13.5 / 15.2 -> 12.5 / 17.9, 256 17.6 /
-// 19.6 -> 16.9 / 22.6.
+// (logits below 1024 ids: four launches) -> 7.5 / 8.8, 1024 18.8 / 26.0 -> 13.7 / 15.9, 4096 70.9 / 61.4 -> 48.5 / 55.6; N = 4096, 8192 133 /
+// 148 -> 91 / 112; N = 8003, 4 10.8 / 11.7 -> 7.8 / 9.8, 512 14.1 / 15.7 -> 11.9 / 15.2, 4096 77 / 84 -> 58 / 75 (but logits of 8192 ids with
+// 819 kept, 1300 rows +8 %); N = 12000, 16 11.9 / 13.2 -> 9.4 / 12.0, 256 13.3 / 14.6 -> 10.6 / 13.2, 384 16.0 / 18.1 -> 17.3 / 22.5; N = 14003,
+// 16 12.2 / 13.4 -> 10.1 / 14.3; N = 20003, 64 13.3 / 14.7 -> 10.9 / 14.9; N = 32003, 4 13.5 / 15.2 -> 12.5 / 17.9, 256 17.6 / 19.6 -> 16.9 /
+// 22.6.
 constexpr int kWholeLogitN = 12 * kChunk;
 bool taylor_finished_in_one(const KernelHandle &h, int32_t B, rdk_input_kind_t p_kind)
 {
-    if (h.N < 4 || h.n < 4 || B > kWholeMostRows) return false;
+    if (h.N < 4 || h.n < 4) return false;
     const bool prob = p_kind == RDK_PROB_F32;
     if (B <= kComputeUnits) return h.N <= (prob ? kWholeMaxN : kWholeLogitN);
     return h.N <= (prob || B <= 2 * kComputeUnits ? kFinishWaves : kFinishWaves / 2) * kChunk;
@@ -1549,7 +1558,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     const size_t per = align_up((size_t)B * nchunks * sizeof(float), 256);
     char *fused_ws = (char *)ws + taylor_workspace_bytes(h, B);
     uint64_t *seq_rec = (uint64_t *)(fused_ws + 3 * per);
-    if (out ? taylor_in_one(h, B) : taylor_finished_in_one(h, B, p.kind)) {
+    if (out ? taylor_in_one(h, B, PK == RDK_PROB_F32 && QK == RDK_PROB_F32) : taylor_finished_in_one(h, B, p.kind)) {
         // q' has the same bits in the call that only writes it and in the fused one
         FinalizeArgs fa{};
         int waves = nchunks < kWholeThreads / kWave ? nchunks : kWholeThreads / kWave;
@@ -1557,7 +1566,9 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             fa.d = c->d;
             fa.draft_ids = c->draft_ids; fa.accept = c->accept; fa.alpha = c->alpha; fa.resid_mass = c->resid_mass;
             fa.resid_ids = c->resid_ids; fa.n_accepted = c->n_accepted; fa.out_tokens = c->out_tokens;
-            set_scan(fa, seq_rec);
+            // The scan of a sequence by its last row, or, with more than four rows for every compute unit, in a launch of its own: 1024 rows
+            // of 4000 probabilities 2.1 us more than without a scan against 2.5 for the launch, 2048 4.5 : 2.5, 6144 11.2 : 2.6.
+            if (B <= kWholeManyRows) set_scan(fa, seq_rec);
             if (waves < kFinishWaves) waves = kFinishWaves;
         }
         // timed as the kernel whose calls it takes

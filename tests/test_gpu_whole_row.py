@@ -25,7 +25,9 @@ SHAPES = [  # N, n, B, gamma, which ids are kept, one launch
     (32 * 1024, 9001, 64, 2, "any", True),
     (32 * 1024 + 1, 9001, 64, 2, "any", False),
     (700, 130, 1024, 4, "any", True),
-    (700, 130, 1025, 5, "any", False),
+    (700, 130, 1025, 5, "any", True),        # beyond one row for every place on the chip
+    (700, 130, 2049, 3, "any", False),
+    (2048, 500, 2049, 3, "any", True),
 ]
 
 
@@ -81,7 +83,7 @@ def test_rows_written_in_one_launch(shape, kinds):
 @pytest.mark.parametrize("kind", ["prob", "logit", "bf16"])
 @pytest.mark.parametrize("N,n,B,gamma", [(1001, 1000, 5, 1), (1023, 131, 1026, 3), (1025, 131, 1026, 3), (4096, 900, 257, 1),
                                          (4097, 900, 257, 1), (8192, 2000, 256, 4), (8193, 2000, 6, 3), (8192, 2000, 513, 3),
-                                         (8193, 2000, 257, 1), (12288, 3000, 5, 1), (12289, 3000, 256, 2), (32768, 8000, 3, 3),
+                                         (8193, 2000, 257, 1), (12288, 3000, 5, 1), (12289, 3000, 256, 2), (32768, 8000, 3, 3), (600, 200, 1024, 4),
                                          (3001, 700, 1026, 2)])
 def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
     from paper_2506_03206_amd import rdk

@@ -66,3 +66,32 @@ def assert_cut(ask, B, groups, n, tail, full):
         assert grids[0] == (groups - tail, 1, 1) and grids[1][:2] == (tail, 1) and 2 <= grids[1][2] <= full // tail, grids
     else:
         assert grids == [(groups, 1, 1)], grids
+
+
+# Eq. 3 with q' written (alone and fused) and without: rows of one workgroup in one launch, and what takes the others.
+WRITTEN = [(24576, 63, 3), (24577, 63, 0), (24577, 64, 3), (32768, 1024, 3), (32769, 64, 0), (32768, 1025, 1), (8192, 1025, 3),
+           (8193, 1025, 1), (8192, 20000, 3), (200, 2048, 3), (2047, 2049, 0), (2048, 2049, 3), (32768, 5000, 1)]
+FINISHED = [(4096, 1025, 3), (4096, 20000, 3), (5, 20000, 3), (4097, 513, 1), (4097, 1025, 1), (8192, 512, 3), (8192, 3000, 1), (8193, 257, 0),
+            (12288, 256, 3), (12289, 256, 1), (32768, 256, 1), (32769, 256, 0), (32768, 1, 1)]
+
+
+@pytest.mark.parametrize("N,B,kinds", WRITTEN)
+def test_rows_of_eq3_written_in_one_launch(ask, N, B, kinds):
+    """kinds: bit 0 = probabilities, bit 1 = logits take one launch."""
+    lines = ["kernel %d %d %d 0" % (IDENTITY, N, max(4, N // 4))]
+    for kind in (PROB, LOGIT, BF16):
+        lines += ["linear 0 %d %d %d" % (kind, kind, B), "fused 0 %d %d %d 1" % (kind, kind, B)]
+    for i, r in enumerate(ask(lines)[1:]):
+        one = kinds & (1 if i < 2 else 2)
+        names = [x.kernel.split("<")[0] for x in r.launches]
+        assert names == ["taylor_whole_kernel"] if one else "taylor_write_kernel" in names, (i, names)
+
+
+@pytest.mark.parametrize("N,B,kinds", FINISHED)
+def test_rows_of_eq3_finished_in_one_launch(ask, N, B, kinds):
+    lines = ["kernel %d %d %d 0" % (IDENTITY, N, max(4, N // 4))]
+    lines += ["fused 0 %d %d %d 0" % (kind, kind, B) for kind in (PROB, LOGIT, BF16)]
+    for i, r in enumerate(ask(lines)[1:]):
+        one = kinds & (1 if i < 1 else 2)
+        names = [x.kernel.split("<")[0] for x in r.launches]
+        assert names == ["taylor_whole_kernel" if one else "taylor_row_kernel"], (i, names)
