@@ -495,8 +495,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) v
 // e = exp(z - chunk maximum) goes to LDS for the kept ids, and the chunk keeps its maximum and power sums of e, from which the
 // sums of p / (N + p) and q^ / (N + p) follow once the scale is known (x = p / N: p / (N + p) = x - x^2 + ..., N / (N + p) = 1 -
 // x + x^2 - ...): over the not-kept ids sum e and e^2, over the kept ids the same and sum q^, q^ e, q^ e^2.  Drafter logits are
-// taken relative to the largest of the chunk's run in the same way.  (Probability rows: e = p, no maxima.)  Which powers: see
-// Powers.
+// taken relative to the largest of the chunk's run in the same way.  (Probability rows: e = p, no maxima.)  The
+// form is for N >= 4096, where the next power, (p / N)^2, is 2^-24 of the first at most.
 // Step A streams p, guided by the kernel's lane map (L2-resident, shared by all rows), a wavefront per chunk.  The chunk's
 // run of drafter values is fetched alongside (one contiguous piece of the drafter row); the wavefront reads its own
 // scattered target values back in slot order and adds up the kept ids' sums -- those of the row constants cost no pass of
@@ -531,6 +531,9 @@ constexpr int kRowThreads = 1024;
 constexpr int kRowWaves = kRowThreads / kWave;
 constexpr int kRowHeld = 10;                   // pieces per group whose drafter values are requested ahead of the row constants
 
+// What step A leaves behind per chunk (arrays in LDS).
+enum { kRowS1n = 0, kRowS2n, kRowS1k, kRowS2k, kRowQ0, kRowQ1, kRowQ2, kRowMax, kRowQMax, kRowScale, kRowArrays };
+
 struct RowLds {      // offsets in floats into the dynamic LDS block
     int pk, zero, blk, red, items, item_lo, sum_q, sum_r, sum_a, fin, total;
 };
@@ -542,8 +545,8 @@ __host__ __device__ inline int row_run_start(int lo, int c) { return (lo & ~3) +
 // Upper bound on the number of pieces (the size of the kernel's table): one per chunk and one per 64 slots.
 __host__ __device__ inline int row_max_items(int n, int nchunks) { return nchunks + n / 64 + 1; }
 
-// arrays: how many floats step A leaves behind per chunk; waves: wavefronts of the workgroup.
-__host__ __device__ inline RowLds row_lds_layout(int n, int nchunks, int arrays, int waves)
+// waves: wavefronts of the workgroup.
+__host__ __device__ inline RowLds row_lds_layout(int n, int nchunks, int waves)
 {
     RowLds L;
     int off = 0;
@@ -551,7 +554,7 @@ __host__ __device__ inline RowLds row_lds_layout(int n, int nchunks, int arrays,
     // (their values are masked)
     L.pk = off; off += ((n + 3) & ~3) + 4 * nchunks + 4;
     L.zero = off; off += 4;                            // a quad of zeros for the lanes past the end of a piece
-    L.blk = off; off += (arrays * nchunks + 3) & ~3;   // what step A leaves behind per chunk
+    L.blk = off; off += (kRowArrays * nchunks + 3) & ~3;   // what step A leaves behind per chunk
     L.red = off; off += waves * 8;                     // what the wavefronts hand to each other between the steps
     const int mi = (row_max_items(n, nchunks) + 1) & ~1;
     // the kernel's table of pieces; the sums of a piece (max(0, p - q') and min(p, q')) take the place of its entry
@@ -567,16 +570,12 @@ __host__ __device__ inline RowLds row_lds_layout(int n, int nchunks, int arrays,
     return L;
 }
 
-// 1 / (N + p) for 0 <= p <= 1.  For a large vocabulary the first two terms of the series in p / N are exact to fp32
-// rounding (the next term is (p / N)^2 <= 2^-24 of the result for N >= 4096) and cost one multiply-add instead of a
+// 1 / (N + p) for 0 <= p <= 1, N >= 4096 (kRowMaskMinN): the first two terms of the series in p / N are exact to fp32
+// rounding (the next term is (p / N)^2 <= 2^-24 of the result) and cost one multiply-add instead of a
 // reciprocal, which the vector unit issues at a quarter of the rate.
-template <bool SERIES>
 struct RowRcp {
-    float fN, invN, invN2;
-    __device__ __forceinline__ float operator()(float p) const
-    {
-        return SERIES ? fmaf(-p, invN2, invN) : __builtin_amdgcn_rcpf(fN + p);
-    }
+    float invN, invN2;
+    __device__ __forceinline__ float operator()(float p) const { return fmaf(-p, invN2, invN); }
 };
 
 // q' of Eq. 3 for the finish of a row inside the one-pass kernels (finish_row_quarters): the drafter values of the kept ids
@@ -870,17 +869,6 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
 // Stands in for the maximum of nothing, where -inf would make the weight of a masked id exp(-inf + inf).  Nothing finite lies
 // below it: rows masked with the lowest finite value of their type keep their own maximum, and with it their weights.
 constexpr float kLowest = -FLT_MAX;
-// The statistics of a chunk (arrays in LDS); the third powers only where the series needs them.
-enum { kRowS1n = 0, kRowS2n, kRowS1k, kRowS2k, kRowQ0, kRowQ1, kRowQ2, kRowMax, kRowQMax, kRowScale, kRowArrays, kRowS3n = kRowArrays, kRowS3k, kRowQ3, kRowAllArrays };
-
-// sum over the 64 lanes, valid in the lanes 48..63
-__device__ __forceinline__ float wave_sum_last(float v)
-{
-    v = row16_sum(v);
-    v += dpp_move<0x142, 0xa>(v);
-    v += dpp_move<0x143, 0xc>(v);
-    return v;
-}
 
 // The larger of two values, neither of them a NaN that anybody would miss (fmaxf spends an instruction per operand on
 // quieting NaNs).
@@ -997,17 +985,10 @@ __device__ __forceinline__ void power_fetch_q(const void *qr, int c, int lo, int
     b.hi = hi;
 }
 
-// How 1 / (N + p) is taken from power sums.
-enum class Powers {
-    Series,   // N >= 4096: up to the second power, exact to fp32 rounding (the next term is (p / N)^2 <= 2^-24 of the first)
-    Cubic,    // smaller vocabularies, logit rows: up to the third (N >= 1024: the next one is 2^-30)
-    Exact,    // smaller vocabularies, probability rows: p^2 is replaced by p^2 / (1 + p / N), which closes the series
-};
-
 // Four target values of a lane: each goes to its slot in LDS (byte address `at`, moved on) in the lanes where the id is kept,
 // into the sums of the ids that are not kept in the others.  Written on the execution mask: three vector instructions a value
-// with the masks in scalar registers (kept[e]: the lanes whose id e of the quad is kept), four where they are shifted out of the
-// lane's map (bits, at the top), against eight for selecting in the sums and computing the address.
+// with the masks in scalar registers (kept[e]: the lanes whose id e of the quad is kept), against four where they are shifted out of
+// the lane's map and eight for selecting in the sums and computing the address.
 __device__ __forceinline__ void power_place(const uint64_t *kept, uint32_t &at, const float (&ev)[4], float &s1, float &s2)
 {
 #define RDK_PLACE(e, next)                         \
@@ -1024,21 +1005,6 @@ __device__ __forceinline__ void power_place(const uint64_t *kept, uint32_t &at, 
                  : "scc", "memory");
 #undef RDK_NEXT
 #undef RDK_PLACE
-}
-__device__ __forceinline__ void power_place(uint32_t &bits, uint32_t &at, float ev, float e2, float &s1, float &s2, float &s3)
-{
-    asm volatile("v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"
-                 "s_mov_b64 exec, vcc\n\t"
-                 "ds_write_b32 %[at], %[ev]\n\t"
-                 "v_add_u32 %[at], 4, %[at]\n\t"
-                 "s_not_b64 exec, exec\n\t"
-                 "v_add_f32 %[s1], %[ev], %[s1]\n\t"
-                 "v_add_f32 %[s2], %[e2], %[s2]\n\t"
-                 "v_fmac_f32 %[s3], %[e2], %[ev]\n\t"
-                 "s_mov_b64 exec, -1"
-                 : [m] "+v"(bits), [at] "+v"(at), [s1] "+v"(s1), [s2] "+v"(s2), [s3] "+v"(s3)
-                 : [ev] "v"(ev), [e2] "v"(e2)
-                 : "vcc", "scc", "memory");
 }
 
 // v with the value of one lane replaced.
@@ -1098,19 +1064,17 @@ __device__ __forceinline__ void power_refs(const PowerChunk<PK> &b, const float 
 
 // The power sums of a chunk, per lane (n: ids that are not kept, k: kept ones).
 struct PowerSums {
-    float s1n, s2n, s3n, s1k, s2k, s3k, q0, q1, q2, q3;
+    float s1n, s2n, s1k, s2k, q0, q1, q2;
 };
 
 // Forms them, e of the kept ids to LDS.
-template <int PK, int QK, Powers POW>
+template <int PK, int QK>
 __device__ __forceinline__ void power_sums(const PowerChunk<PK> &b, const float (&z)[4][4], const uint64_t (&kept)[16], int c, const void *qr,
-                                           int n, float *pk, float invN, float rp, float rq, PowerSums &v)
+                                           int n, float *pk, float rp, float rq, PowerSums &v)
 {
-    constexpr bool CUBIC = POW == Powers::Cubic;
     const int lane = lane_id(), lo = b.lo, hi = b.hi;
     const int run = row_run_start(lo, c);
     const uint32_t first = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)pk + 4 * run;
-    uint32_t bits = __builtin_bitreverse32((uint32_t)b.map);   // the bit of the first id on top
     v = PowerSums{};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1118,29 +1082,16 @@ __device__ __forceinline__ void power_sums(const PowerChunk<PK> &b, const float 
         float ev[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) ev[e] = to_weight<PK>(z[i][e], rp, 1.f);   // ids beyond N: zero
-        if (POW == Powers::Series) {
-            power_place(kept + 4 * i, at, ev, v.s1n, v.s2n);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float e2 = POW == Powers::Exact ? ev[e] * ev[e] * __builtin_amdgcn_rcpf(fmaf(ev[e], invN, 1.0f)) : ev[e] * ev[e];
-                power_place(bits, at, ev[e], e2, v.s1n, v.s2n, v.s3n);
-            }
-        }
+        power_place(kept + 4 * i, at, ev, v.s1n, v.s2n);
     }
     // over the kept ids, in slot order, a slot a lane
     auto add = [&](float qe, float ee) {
-        float e2 = ee * ee;
-        if (POW == Powers::Exact) e2 *= __builtin_amdgcn_rcpf(fmaf(ee, invN, 1.0f));
+        const float e2 = ee * ee;
         v.s1k += ee;
         v.s2k += e2;
         v.q0 += qe;
         v.q1 = fmaf(qe, ee, v.q1);
         v.q2 = fmaf(qe, e2, v.q2);
-        if (CUBIC) {
-            v.s3k = fmaf(e2, ee, v.s3k);
-            v.q3 = fmaf(qe * e2, ee, v.q3);
-        }
     };
     auto weight = [&](uint32_t raw) { return to_weight<QK>(power_q_value<QK>(raw), rq, 1.f); };
     auto round = [&](int r, uint32_t raw) {
@@ -1172,46 +1123,37 @@ __device__ __forceinline__ void power_sums(const PowerChunk<PK> &b, const float 
 }
 
 // Step A for one chunk: statistics to `stat` (arrays of nchunks floats).  lane_stat: which of them the lane writes (-1: none).
-template <int PK, int QK, Powers POW>
+template <int PK, int QK>
 __device__ __forceinline__ void row_power_chunk(const PowerChunk<PK> &b, int c, int N, const void *qr, int n, float *pk,
-                                                const uint64_t *row_masks, float *stat, int nchunks, int lane_stat, float invN)
+                                                const uint64_t *row_masks, float *stat, int nchunks, int lane_stat)
 {
-    constexpr bool CUBIC = POW == Powers::Cubic;
-    const int lane = lane_id();
-    uint64_t kept[16];
-    if (POW == Powers::Series) {                       // asked for first: on their way while the maxima are found
-        const ScalarPtr<uint64_t> mk = scalar_ptr(row_masks) + 16 * c;
+    uint64_t kept[16];                                 // asked for first: on their way while the maxima are found
+    const ScalarPtr<uint64_t> mk = scalar_ptr(row_masks) + 16 * c;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) kept[i] = mk[i];
-    }
+    for (int i = 0; i < 16; ++i) kept[i] = mk[i];
     float z[4][4], rp = 0.f, rq = 0.f;
     power_values<PK>(b, c, N, z);
     if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) power_refs<PK, QK>(b, z, qr, rp, rq);
     PowerSums v;
-    power_sums<PK, QK, POW>(b, z, kept, c, qr, n, pk, invN, rp, rq, v);
-    const float all[8] = {v.s1n, v.s2n, v.s1k, v.s2k, v.q0, v.q1, v.q2, v.s3n};   // in the order of the enumeration
+    power_sums<PK, QK>(b, z, kept, c, qr, n, pk, rp, rq, v);
+    const float all[8] = {v.s1n, v.s2n, v.s1k, v.s2k, v.q0, v.q1, v.q2, 0.f};   // in the order of the enumeration
     float out = wave_sum8(all);
-    if (CUBIC) {
-        const float s3k = lane_value(wave_sum_last(v.s3k), kWave - 1), q3 = lane_value(wave_sum_last(v.q3), kWave - 1);
-        out = lane == 3 ? s3k : lane == 4 ? q3 : out;
-    }
     if (PK != RDK_PROB_F32) lane_set<1>(out, rp);
     if (QK != RDK_PROB_F32) lane_set<2>(out, rq);
     if (lane_stat >= 0) stat[lane_stat * nchunks + c] = out;
 }
 
-template <int PK, int QK, Powers POW, int T>
+template <int PK, int QK, int T>
 __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void taylor_row_kernel(const void *p, int64_t ldp, const void *q, int64_t ldq,
                                                                        const uint64_t *lane_map, const uint64_t *row_masks,
                                                                        const int32_t *chunk_lo, const int32_t *item_lo, const int2 *row_items,
                                                                        int N, int n, const int32_t *slot_of,
                                                                        FinalizeArgs fin)
 {
-    constexpr bool CUBIC = POW == Powers::Cubic;
     constexpr int kW = T / kWave, kG = T / 16;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int nchunks = (N + kChunk - 1) / kChunk;
-    const RowLds L = row_lds_layout(n, nchunks, CUBIC ? kRowAllArrays : kRowArrays, kW);
+    const RowLds L = row_lds_layout(n, nchunks, kW);
     float *pk = lds + L.pk, *stat = lds + L.blk;
     int2 *il = (int2 *)(lds + L.items);
     int *ilo = (int *)(lds + L.item_lo);
@@ -1221,8 +1163,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
     const void *pr = row_ptr<PK>(p, ldp, row);
     const void *qr = row_ptr<QK>(q, ldq, row);
     const float fN = (float)N;
-    RowRcp<POW == Powers::Series> rcp;
-    rcp.fN = fN;
+    RowRcp rcp;
     rcp.invN = 1.0f / fN;
     rcp.invN2 = rcp.invN * rcp.invN;
 
@@ -1267,10 +1208,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
     }
     __syncthreads();
 
-    // ---- step A.  A lane of every eight writes one of the eight sums, the lanes 1 to 4 what else a chunk leaves behind.
+    // ---- step A.  A lane of every eight writes one of the seven sums, the lanes 1 and 2 what else a chunk leaves behind.
     const int lane_sum = (int)(__builtin_bitreverse32((uint32_t)lane >> 3) >> 29);
-    const int lane_stat = (lane & 7) == 0 ? (lane_sum < 7 ? lane_sum : CUBIC ? kRowS3n : -1)
-                          : lane == 1 ? kRowMax : lane == 2 ? kRowQMax : CUBIC && lane == 3 ? kRowS3k : CUBIC && lane == 4 ? kRowQ3 : -1;
+    const int lane_stat = (lane & 7) == 0 ? (lane_sum < 7 ? lane_sum : -1) : lane == 1 ? kRowMax : lane == 2 ? kRowQMax : -1;
 #define RDK_ROW_STEP(CUR, FREE)                                                                               \
     {                                                                                                         \
         power_fetch_q<PK, QK>(qr, c + 2 * kW, next_lo, next_hi, N, n, FREE);                                  \
@@ -1278,14 +1218,14 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
         const int ahead = min(c + 3 * kW, last);                                                              \
         next_lo = lo_of[ahead];                                                                               \
         next_hi = lo_of[ahead + 1];                                                                           \
-        row_power_chunk<PK, QK, POW>(CUR, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN);        \
+        row_power_chunk<PK, QK>(CUR, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat);                    \
         c += kW;                                                                                              \
     }
     if (nchunks <= 2 * kW) {
         // A short row: all of it is on its way.  What it takes then is mostly the time in which its code is fetched, and one
         // copy of it, without what looks ahead, is enough (12.4 -> 11.9 us a call for 8 rows of 16000 probabilities).
         while (c < nchunks) {
-            row_power_chunk<PK, QK, POW>(b0, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat, rcp.invN);
+            row_power_chunk<PK, QK>(b0, c, N, qr, n, pk, row_masks, stat, nchunks, lane_stat);
             b0 = b1;
             c += kW;
         }
@@ -1342,10 +1282,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
     wave_max2(pm, qm, pm, qm);
     if (PK == RDK_PROB_F32) pm = 0.f;
     if (QK == RDK_PROB_F32) qm = 0.f;
-    float t7[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // sum e, e^2, e^3 over all ids; sum q^ e^k, k = 0..3
+    float t5[5] = {0.f, 0.f, 0.f, 0.f, 0.f};   // sum e, e^2 over all ids; sum q^ e^k, k = 0..2
     for (int cc = threadIdx.x; cc < nchunks; cc += T) {
         float *sc = stat + cc;
-        const float f = PK == RDK_PROB_F32 ? 1.f : soft_exp_fine(sc[kRowMax * nchunks] - pm), f2 = f * f, f3 = f2 * f;   // shared by 1024 ids
+        const float f = PK == RDK_PROB_F32 ? 1.f : soft_exp_fine(sc[kRowMax * nchunks] - pm), f2 = f * f;   // shared by 1024 ids
         const float fq = QK == RDK_PROB_F32 ? 1.f : soft_exp_fine(sc[kRowQMax * nchunks] - qm);
         const float s1n = sc[kRowS1n * nchunks] * f, s2n = sc[kRowS2n * nchunks] * f2;
         const float s1k = sc[kRowS1k * nchunks] * f, s2k = sc[kRowS2k * nchunks] * f2;
@@ -1354,33 +1294,27 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
         sc[kRowS1k * nchunks] = s1k; sc[kRowS2k * nchunks] = s2k;
         sc[kRowQ0 * nchunks] = q0; sc[kRowQ1 * nchunks] = q1; sc[kRowQ2 * nchunks] = q2;
         sc[kRowScale * nchunks] = f;
-        t7[0] += s1n + s1k; t7[1] += s2n + s2k;
-        t7[3] += q0; t7[4] += q1; t7[5] += q2;
-        if (CUBIC) {
-            const float s3n = sc[kRowS3n * nchunks] * f3, s3k = sc[kRowS3k * nchunks] * f3, q3 = sc[kRowQ3 * nchunks] * f3 * fq;
-            sc[kRowS3n * nchunks] = s3n; sc[kRowS3k * nchunks] = s3k; sc[kRowQ3 * nchunks] = q3;
-            t7[2] += s3n + s3k;
-            t7[6] += q3;
-        }
+        t5[0] += s1n + s1k; t5[1] += s2n + s2k;
+        t5[2] += q0; t5[3] += q1; t5[4] += q2;
     }
     {
-        const float v8[8] = {t7[0], t7[1], t7[2], t7[3], t7[4], t7[5], t7[6], 0.f};
+        const float v8[8] = {t5[0], t5[1], t5[2], t5[3], t5[4], 0.f, 0.f, 0.f};
         const float v = wave_sum8(v8);
         if ((lane & 7) == 0) lds[L.red + wid * 8 + lane_sum] = v;
     }
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < 7; ++j) t7[j] = 0.f;
+    for (int j = 0; j < 5; ++j) t5[j] = 0.f;
     for (int i = 0; i < kW; ++i) {
-        const float4 a4 = *(const float4 *)(lds + L.red + i * 8), b4 = *(const float4 *)(lds + L.red + i * 8 + 4);
-        t7[0] += a4.x; t7[1] += a4.y; t7[2] += a4.z; t7[3] += a4.w;
-        t7[4] += b4.x; t7[5] += b4.y; t7[6] += b4.z;
+        const float4 a4 = *(const float4 *)(lds + L.red + i * 8);
+        t5[0] += a4.x; t5[1] += a4.y; t5[2] += a4.z; t5[3] += a4.w;
+        t5[4] += lds[L.red + i * 8 + 4];
     }
-    const float pinv = PK == RDK_PROB_F32 ? 1.f : 1.0f / t7[0];   // the row maximum itself contributes e = 1: never zero
-    const float c1 = pinv / fN, c2 = c1 * c1, c3 = c2 * c1;
-    const float zq = t7[3], tn = t7[4] * pinv;
-    const float an = t7[3] - t7[4] * c1 + t7[5] * c2 - t7[6] * c3;     // sum q^ N / (N + p)
-    const float bs = t7[0] * c1 - t7[1] * c2 + t7[2] * c3;             // sum p / (N + p)
+    const float pinv = PK == RDK_PROB_F32 ? 1.f : 1.0f / t5[0];   // the row maximum itself contributes e = 1: never zero
+    const float c1 = pinv / fN, c2 = c1 * c1;
+    const float zq = t5[2], tn = t5[3] * pinv;
+    const float an = t5[2] - t5[3] * c1 + t5[4] * c2;                  // sum q^ N / (N + p)
+    const float bs = t5[0] * c1 - t5[1] * c2;                          // sum p / (N + p)
     const float inv_zq = inv_mass(zq);
     const float theta = tn * inv_zq;
     const float inv_S = inv_mass(an * inv_zq + theta * bs);
@@ -1438,14 +1372,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
         if (li == 0) {
             const float *sc = stat + cc;
             const float s1n = sc[kRowS1n * nchunks];
-            float a_nk = s1n * c1 - sc[kRowS2n * nchunks] * c2;                   // sum p / (N + p), not-kept ids
-            float a_k = sc[kRowS1k * nchunks] * c1 - sc[kRowS2k * nchunks] * c2;   //                  kept ids
+            const float a_nk = s1n * c1 - sc[kRowS2n * nchunks] * c2;                   // sum p / (N + p), not-kept ids
+            const float a_k = sc[kRowS1k * nchunks] * c1 - sc[kRowS2k * nchunks] * c2;   //                  kept ids
             float aq = sc[kRowQ0 * nchunks] - sc[kRowQ1 * nchunks] * c1 + sc[kRowQ2 * nchunks] * c2;
-            if (CUBIC) {
-                a_nk += sc[kRowS3n * nchunks] * c3;
-                a_k += sc[kRowS3k * nchunks] * c3;
-                aq -= sc[kRowQ3 * nchunks] * c3;
-            }
             aq *= rcp.invN;                                            // sum q^ / (N + p), kept ids
             const float ta = ths * a_nk;                               // sum of q' (= sum of min(p, q')) over the not-kept ids
             lds[L.sum_q + cc] = ths * (a_nk + a_k) + nzs * aq;
@@ -1469,12 +1398,10 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4, 4))) void 
 // 32 / 40 rows of 250000 ids 39.2 -> 44.3 / 46.1 -> 44.5 (fp32 logits of 128256 ids, 32 / 40 rows, 33.5 -> 33.9 / 36.3 -> 33.6, of
 // 250000 ids, 40 / 48 rows, 47.0 -> 47.9 / 47.8 -> 48.4).
 constexpr int kRowMinBatch = 88, kRowMinBatchLogit = 40;
-// ... unless the rows are short: at any batch, one launch against three or four.  Probabilities, 4 / 32 / 64 rows of 28000 ids 14.8
-// -> 12.2 / 15.4 -> 13.7 / 16.3 -> 14.0 us, 32000 ids 14.2 -> 14.0 / 15.3 -> 14.7 / 17.2 -> 15.0, and past the line 40000 ids 14.6 ->
-// 15.0 / 15.4 -> 15.9.  bf16 logits, 8 rows of 52000 ids 24.0 -> 20.7, and past the line, 4 / 32 rows, 56000 ids 22.8 -> 20.7 / 25.8
-// -> 21.4, 64000 ids 22.7 -> 22.7 / 25.5 -> 23.1 (fp32 logits: 56000 ids, 14000 kept, 22.6 -> 21.7, 20000 kept 24.2 -> 24.5, 64000
-// ids 22.4 -> 22.9).
-constexpr int kRowShortN = 32 * 1024, kRowShortLogitN = 52 * 1024;
+// ... unless logit rows are short: at any batch, one launch against three or four.  bf16 logits, 8 rows of 52000 ids 24.0 -> 20.7, and
+// past the line, 4 / 32 rows, 56000 ids 22.8 -> 20.7 / 25.8 -> 21.4, 64000 ids 22.7 -> 22.7 / 25.5 -> 23.1 (fp32 logits: 56000 ids,
+// 14000 kept, 22.6 -> 21.7, 20000 kept 24.2 -> 24.5, 64000 ids 22.4 -> 22.9).  (Short rows of probabilities are taylor_whole_kernel's.)
+constexpr int kRowShortLogitN = 52 * 1024;
 
 // LDS a workgroup may use (asked until it is told; the same on every device the library is built for).
 size_t row_lds_limit()
@@ -1591,23 +1518,20 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
     {
         // the fused call without q': one pass over the target rows, one workgroup per position, when the kept target
         // values of a row fit the LDS of a compute unit and there are enough positions to fill the chip, or the rows are so
-        // short that splitting them saves less than the extra launches cost (logit rows: from the vocabulary size on at
-        // which the series of their chunk sums are exact to fp32 rounding)
-        const Powers pow = h.N >= kRowMaskMinN ? Powers::Series : PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
-        const int arrays = pow == Powers::Cubic ? kRowAllArrays : kRowArrays;
-        size_t lds_bytes = (size_t)row_lds_layout(h.n, nchunks, arrays, kRowWaves).total * sizeof(float);
-        const bool fits = h.N >= (PK == RDK_PROB_F32 ? 4 : kOnePassMinN) && h.n >= 4 && lds_bytes <= row_lds_limit();
-        const bool pays = PK == RDK_PROB_F32 ? B >= kRowMinBatch || h.N <= kRowShortN : B >= kRowMinBatchLogit || h.N <= kRowShortLogitN;
+        // short that splitting them saves less than the extra launches cost (from the vocabulary size on at which the series of
+        // the chunk sums are exact to fp32 rounding)
+        size_t lds_bytes = (size_t)row_lds_layout(h.n, nchunks, kRowWaves).total * sizeof(float);
+        const bool fits = h.N >= kRowMaskMinN && h.n >= 4 && lds_bytes <= row_lds_limit();
+        const bool pays = PK == RDK_PROB_F32 ? B >= kRowMinBatch : B >= kRowMinBatchLogit || h.N <= kRowShortLogitN;
         if (c && !out && fits && pays) {
             // More rows than compute units: workgroups of half the size, two on a unit where their LDS allows it, so that
             // one streams while the other is at its barriers and its finish.
             bool halves = false;
             if (B > kComputeUnits) {
-                const size_t half_bytes = (size_t)row_lds_layout(h.n, nchunks, arrays, kRowWaves / 2).total * sizeof(float);
+                const size_t half_bytes = (size_t)row_lds_layout(h.n, nchunks, kRowWaves / 2).total * sizeof(float);
                 halves = 2 * align_up(half_bytes, 2048) <= row_lds_limit();
                 if (halves) lds_bytes = half_bytes;
             }
-            if (q.kind != RDK_LOGIT_BF16 && ((uintptr_t)q.ptr % 4 != 0)) return RDK_ERR_ALIGN;
             FinalizeArgs fa{};                // the block sums stay in the workgroup's LDS
             fa.d = c->d;
             fa.p = p.ptr; fa.ldp = p.ld;
@@ -1618,23 +1542,17 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             // with more positions than compute units the workgroups take turns, and each would add its round trips to the
             // chain of its unit: the scan is a launch of its own then
             if (B <= kComputeUnits) set_scan(fa, seq_rec);
-#define RDK_ROW_LAUNCH(POW, THREADS)                                                                                         \
+#define RDK_ROW_LAUNCH(THREADS)                                                                                              \
     {                                                                                                                       \
         static LdsGrant grant;                                                                                              \
-        rc = grant((const void *)taylor_row_kernel<PK, QK, POW, THREADS>, row_lds_limit());                                 \
+        rc = grant((const void *)taylor_row_kernel<PK, QK, THREADS>, row_lds_limit());                                      \
         if (rc != RDK_OK) return rc;                                                                                        \
-        RDK_TIMED_LAUNCH("taylor_row_kernel", (taylor_row_kernel<PK, QK, POW, THREADS>), dim3((unsigned)B), dim3(THREADS),  \
+        RDK_TIMED_LAUNCH("taylor_row_kernel", (taylor_row_kernel<PK, QK, THREADS>), dim3((unsigned)B), dim3(THREADS),       \
                          lds_bytes, st, p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.row_masks, h.chunk_lo, h.item_lo, h.row_items, \
-                         h.N, h.n, h.slot_of, fa);                                                                             \
+                         h.N, h.n, h.slot_of, fa);                                                                          \
     }
-            constexpr Powers kSmall = PK == RDK_PROB_F32 ? Powers::Exact : Powers::Cubic;
-            if (pow == Powers::Series) {
-                if (halves) RDK_ROW_LAUNCH(Powers::Series, kRowThreads / 2)
-                else RDK_ROW_LAUNCH(Powers::Series, kRowThreads)
-            } else {
-                if (halves) RDK_ROW_LAUNCH(kSmall, kRowThreads / 2)
-                else RDK_ROW_LAUNCH(kSmall, kRowThreads)
-            }
+            if (halves) RDK_ROW_LAUNCH(kRowThreads / 2)
+            else RDK_ROW_LAUNCH(kRowThreads)
 #undef RDK_ROW_LAUNCH
             RDK_LAUNCH_CHECK("taylor_row_kernel");
             return scan_if_left(fa, st);
