@@ -831,8 +831,10 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             sq = wave_sum(sq);
             sr = wave_sum(sr);
             sa = wave_sum(sa);
-            sr += ths * 0.f;   // a row with a NaN or an infinity has a NaN in sum q^ p, which the minima and maxima above would hide
-            sa += ths * 0.f;
+            if (t == 0) {   // a row with a NaN or an infinity has a NaN in sum q^ p, which the minima and maxima above would hide
+                sr += ths * 0.f;
+                sa += ths * 0.f;
+            }
             if (lane == 0) {
                 sums[0][c] = sq;
                 sums[1][c] = sr;
