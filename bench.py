@@ -86,6 +86,7 @@ def algorithmic_bytes(kernel, w, B, kk, fused, esz):
         "taylor_stats_kernel": B * esz * (N + n) + ids,                     # read p, q
         "taylor_write_kernel": B * (esz * (N + n) + (0 if fused else 4 * N)) + ids,
         "taylor_row_kernel": B * esz * (N + n) + ids,                       # one pass: p and q read once
+        "taylor_whole_kernel": B * (esz * (N + n) + (0 if fused else 4 * N)) + ids,
         "q_transpose_kernel": B * (esz + 4) * n,
         "row_stats_kernel": B * esz * n,
         "verify_finalize_kernel": B * 3 * 4 * ((N + 1023) // 1024),
@@ -94,7 +95,7 @@ def algorithmic_bytes(kernel, w, B, kk, fused, esz):
 
 
 KERNEL_NAMES = ["row_stats_kernel", "q_transpose_kernel", "sparse_product_kernel", "taylor_stats_kernel", "taylor_write_kernel",
-                "taylor_row_kernel", "verify_stream_kernel", "verify_finalize_kernel", "sequence_scan_kernel"]
+                "taylor_row_kernel", "taylor_whole_kernel", "verify_stream_kernel", "verify_finalize_kernel", "sequence_scan_kernel"]
 
 
 def timed_regions(torch, fn, steps, first):

@@ -1500,11 +1500,9 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             if (B <= kWholeManyRows) set_scan(fa, seq_rec);
             if (waves < kFinishWaves) waves = kFinishWaves;
         }
-        // timed as the kernel whose calls it takes
-        const char *name = out || (PK != RDK_PROB_F32 && h.N < kOnePassMinN) ? "taylor_write_kernel" : "taylor_row_kernel";
 #define RDK_WHOLE_LAUNCH(FUSE, LDS)                                                                                           \
-    RDK_TIMED_LAUNCH(name, (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), LDS, st, p.ptr, p.ld, q.ptr, \
-                     q.ld, h.lane_map, h.chunk_lo, h.slot_of, h.N, h.n, out, ldo, fa)
+    RDK_TIMED_LAUNCH("taylor_whole_kernel", (taylor_whole_kernel<PK, QK, FUSE>), dim3((unsigned)B), dim3(waves * kWave), LDS, st, \
+                     p.ptr, p.ld, q.ptr, q.ld, h.lane_map, h.chunk_lo, h.slot_of, h.N, h.n, out, ldo, fa)
         if (c) {
             static LdsGrant grant;
             rc = grant((const void *)taylor_whole_kernel<PK, QK, true>, kHeldQuads * sizeof(float4));
@@ -1514,7 +1512,7 @@ rdk_status_t run_taylor(const KernelHandle &h, RowInput p, RowInput q, int32_t B
             RDK_WHOLE_LAUNCH(false, 0);
         }
 #undef RDK_WHOLE_LAUNCH
-        RDK_LAUNCH_CHECK("taylor_write_kernel");
+        RDK_LAUNCH_CHECK("taylor_whole_kernel");
         return c ? scan_if_left(fa, st) : RDK_OK;
     }
     {

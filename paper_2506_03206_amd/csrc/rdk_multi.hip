@@ -424,9 +424,9 @@ rdk_status_t run_multi(MultiArgs a, RowInput p, void *ws, size_t ws_bytes, hipSt
         const bool early = a.d.B <= kRoundEarlyRows;
         const int per = waves * (early ? 1 : 2);
         for (int round = 0; round <= a.d.C; ++round) {
-            RDK_TIMED_LAUNCH("verify_multi_kernel", (verify_multi_round_kernel<KIND>), dim3((nblk + per - 1) / per, (unsigned)a.d.B),
+            RDK_TIMED_LAUNCH("verify_multi_round_kernel", (verify_multi_round_kernel<KIND>), dim3((nblk + per - 1) / per, (unsigned)a.d.B),
                              dim3(kRoundThreads), 0, st, a, s, round, early);
-            RDK_LAUNCH_CHECK("verify_multi_kernel");
+            RDK_LAUNCH_CHECK("verify_multi_round_kernel");
         }
         return RDK_OK;
     }

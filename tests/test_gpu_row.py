@@ -1,5 +1,5 @@
-"""Eq. 3 in one pass where it can go wrong: the smallest vocabularies, both sides of the sizes at which the series of its sums
-change, ends inside a quad, runs of one slot at the end of the row, chunks without kept ids or without any target mass, two
+"""Eq. 3 without q' where it can go wrong, in one pass, out of registers and in two passes: the smallest vocabularies of each, ends
+inside a quad, runs of one slot at the end of the row, chunks without kept ids or without any target mass, two
 workgroups on a compute unit, rows at odd strides -- against the oracle."""
 import numpy as np
 import pytest
@@ -11,15 +11,24 @@ from parity_util import check_verify_outputs
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [  # N, n, B, gamma, which ids are kept
-    (5, 4, 6, 3, "any"),
-    (1023, 130, 3, 1, "any"),
-    (1025, 131, 3, 3, "any"),
-    (4095, 900, 258, 2, "any"),     # more rows than compute units
-    (4099, 1030, 4, 2, "tail"),     # the last three runs hold one slot each
-    (9001, 700, 260, 4, "first"),   # the kept ids in one chunk
-    (24576, 6001, 2, 2, "any"),
-    (49152, 9999, 2, 1, "tail"),
+ROW, WHOLE, TWO = "taylor_row_kernel", "taylor_whole_kernel", "taylor_write_kernel"   # one pass, out of registers, two passes
+
+SHAPES = [  # N, n, B, gamma, which ids are kept, what takes probabilities, logits
+    (5, 4, 6, 3, "any", WHOLE, WHOLE),
+    (1023, 130, 3, 1, "any", WHOLE, WHOLE),
+    (1025, 131, 3, 3, "any", WHOLE, WHOLE),
+    (4095, 900, 258, 2, "any", WHOLE, WHOLE),     # more rows than compute units
+    (4099, 1030, 4, 2, "tail", WHOLE, WHOLE),     # the last three runs hold one slot each
+    (4097, 900, 514, 2, "any", WHOLE, ROW),       # the shortest logit rows in one pass
+    (8193, 2000, 257, 1, "any", ROW, ROW),        # the shortest rows of probabilities
+    (8195, 1030, 300, 2, "tail", ROW, ROW),
+    (9001, 700, 260, 4, "first", ROW, ROW),       # the kept ids in one chunk
+    (12289, 1001, 3, 3, "tail", WHOLE, ROW),
+    (12291, 12291, 300, 1, "any", ROW, ROW),      # every id is kept
+    (24576, 6001, 2, 2, "any", WHOLE, ROW),
+    (32769, 4, 88, 4, "any", ROW, ROW),           # one quad of slots, in at most four chunks
+    (33003, 8190, 90, 3, "any", ROW, ROW),
+    (49152, 9999, 2, 1, "tail", TWO, ROW),
 ]
 
 
@@ -27,7 +36,8 @@ SHAPES = [  # N, n, B, gamma, which ids are kept
 @pytest.mark.parametrize("shape", SHAPES)
 def test_one_pass_rows_against_oracle(shape, kind):
     from paper_2506_03206_amd import rdk
-    N, n, B, gamma, where = shape
+    N, n, B, gamma, where, *takes = shape
+    kernel = takes[kind != "prob"]
     rng = np.random.default_rng(N + n)
     if where == "first":
         kept = np.sort(rng.choice(1000, size=n, replace=False))
@@ -51,21 +61,20 @@ def test_one_pass_rows_against_oracle(shape, kind):
     kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
     p64, q64 = oracle.probs_from(zp, pk), oracle.probs_from(zq, pk)
     ref_qp = oracle.redistribute_batch("taylor", q64, kept, N, p=p64)
-    rdk.rdk_timing_select("taylor_row_kernel")
+    rdk.rdk_timing_select(kernel)
     out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, wide(zp), wide(zq), 9, 4, gamma, pk, pk)
     torch.cuda.synchronize()
     rdk.rdk_timing_select(None)
-    one_pass = N >= 1024 if pk == "logit" else N <= 24576
-    assert rdk.rdk_timing_read("taylor_row_kernel")[0] == one_pass
+    assert rdk.rdk_timing_read(kernel)[0] == 1
     ref = oracle.verify_batch(p64, ref_qp, 9, 4, gamma=gamma)
     check_verify_outputs(out, ref, p64, ref_qp, 9, 4, gamma, pk, min_exact=0.6)
 
 
 @pytest.mark.parametrize("kind", ["logit", "bf16"])
-@pytest.mark.parametrize("N,B", [(4099, 6), (4099, 260), (60001, 66), (60001, 6)])
-def test_rows_masked_with_the_lowest_finite_value(N, B, kind):
-    """Masks of finfo.min instead of -inf, over part of a row and over all of it (a uniform row then), in one pass and, for the
-    last shape, split over workgroups; a logit near the largest finite value beside them."""
+@pytest.mark.parametrize("N,B,kernel", [(4099, 6, WHOLE), (4099, 260, WHOLE), (4099, 514, ROW), (12301, 6, ROW), (60001, 66, ROW), (60001, 6, TWO)])
+def test_rows_masked_with_the_lowest_finite_value(N, B, kernel, kind):
+    """Masks of finfo.min instead of -inf, over part of a row and over all of it (a uniform row then), out of registers, in one pass and
+    split over workgroups; a logit near the largest finite value beside them."""
     from paper_2506_03206_amd import rdk
     rng = np.random.default_rng(N + B)
     kept = np.sort(rng.choice(N, size=N // 5, replace=False)).astype(np.int32)
@@ -86,11 +95,11 @@ def test_rows_masked_with_the_lowest_finite_value(N, B, kind):
     ref_qp = oracle.redistribute_batch("taylor", q64, kept, N, p=p64)
     ref = oracle.verify_batch(p64, ref_qp, 9, 4, gamma=2)
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda().to(dt)
-    rdk.rdk_timing_select("taylor_row_kernel")
+    rdk.rdk_timing_select(kernel)
     out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, t(zp), t(zq), 9, 4, 2, "logit", "logit")
     torch.cuda.synchronize()
     rdk.rdk_timing_select(None)
-    assert rdk.rdk_timing_read("taylor_row_kernel")[0] == ((N, B) != (60001, 6))
+    assert rdk.rdk_timing_read(kernel)[0] == 1
     check_verify_outputs(out, ref, p64, ref_qp, 9, 4, 2, "logit", min_exact=0.6)
 
 

@@ -11,10 +11,13 @@ from parity_util import check_verify_outputs
 
 pytestmark = pytest.mark.gpu
 
+ROW, WHOLE = "taylor_row_kernel", "taylor_whole_kernel"   # one pass, and out of registers where the rows are short
+
 
 @pytest.mark.parametrize("kind", ["logit", "bf16"])
-@pytest.mark.parametrize("N,n,B", [(40001, 5000, 6), (40001, 5000, 260), (4096, 1500, 4), (2050, 700, 4)])
-def test_moving_references_against_oracle(N, n, B, kind):
+@pytest.mark.parametrize("N,n,B,kernel", [(40001, 5000, 6, ROW), (40001, 5000, 260, ROW), (12300, 1500, 4, ROW), (4100, 1500, 514, ROW),
+                                          (4096, 1500, 4, WHOLE), (2050, 700, 4, WHOLE)])
+def test_moving_references_against_oracle(N, n, B, kernel, kind):
     from paper_2506_03206_amd import rdk
     rng = np.random.default_rng(N + B)
     last = (N - 1) // 1024 * 1024
@@ -39,11 +42,11 @@ def test_moving_references_against_oracle(N, n, B, kind):
     ref = oracle.verify_batch(p64, ref_qp, 9, 4, gamma=2)
     dt = torch.bfloat16 if kind == "bf16" else torch.float32
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda().to(dt)
-    rdk.rdk_timing_select("taylor_row_kernel")
+    rdk.rdk_timing_select(kernel)
     out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, t(zp), t(zq), 9, 4, 2, "logit", "logit")
     torch.cuda.synchronize()
     rdk.rdk_timing_select(None)
-    assert rdk.rdk_timing_read("taylor_row_kernel")[0] == 1
+    assert rdk.rdk_timing_read(kernel)[0] == 1
     check_verify_outputs(out, ref, p64, ref_qp, 9, 4, 2, "logit", min_exact=0.6)
 
 

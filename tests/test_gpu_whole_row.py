@@ -61,11 +61,13 @@ def test_rows_written_in_one_launch(shape, kinds):
         dev.append(torch.nn.functional.pad(t, (0, 1), value=float("nan"))[:, :-1])
     kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
     held = torch.full((B, N + 3), 7.0, device="cuda")
-    rdk.rdk_timing_select("taylor_stats_kernel")
+    rdk.rdk_timing_select("*")
     rdk.rdk_redistribute_linear(kern, rdk.LINEAR_TAYLOR, dev[1], rows[1], p=dev[0], p_kind=rows[0], out=held[:, :N])
     torch.cuda.synchronize()
     rdk.rdk_timing_select(None)
-    assert rdk.rdk_timing_read("taylor_stats_kernel")[0] == (0 if one else 1)
+    launches = {name: rdk.rdk_timing_read(name)[0] for name in ("taylor_whole_kernel", "taylor_stats_kernel", "row_stats_kernel")}
+    assert launches["taylor_whole_kernel"] == (1 if one else 0) and launches["taylor_stats_kernel"] == (0 if one else 1)
+    assert not one or launches["row_stats_kernel"] == 0
     assert bool((held[:, N:] == 7.0).all())  # nothing behind a row is written
     got = held[:, :N].cpu().numpy().astype(np.float64)
     ref = oracle.redistribute_batch("taylor", p64[1], kept, N, p=p64[0])
@@ -78,14 +80,19 @@ def test_rows_written_in_one_launch(shape, kinds):
     check_verify_outputs(out, want, p64[0], ref, 9, 4, gamma, rows[0], min_exact=0.6)
 
 
-# The fused call without q': both sides of the lines to the kernel that keeps the kept values in LDS, whose forms for small
-# vocabularies are left to more positions than this one takes.
+# The fused call without q': both sides of the lines to the kernel that keeps the kept values in LDS (the shapes that a kernel of one
+# launch for probabilities and for logits takes are named).
+WHOLE, ROW = "taylor_whole_kernel", "taylor_row_kernel"
+
+
 @pytest.mark.parametrize("kind", ["prob", "logit", "bf16"])
-@pytest.mark.parametrize("N,n,B,gamma", [(1001, 1000, 5, 1), (1023, 131, 1026, 3), (1025, 131, 1026, 3), (4096, 900, 257, 1),
-                                         (4097, 900, 257, 1), (8192, 2000, 256, 4), (8193, 2000, 6, 3), (8192, 2000, 513, 3),
-                                         (8193, 2000, 257, 1), (12288, 3000, 5, 1), (12289, 3000, 256, 2), (32768, 8000, 3, 3), (600, 200, 1024, 4),
-                                         (3001, 700, 1026, 2)])
-def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
+@pytest.mark.parametrize("N,n,B,gamma,takes", [
+    (1001, 1000, 5, 1, (WHOLE, WHOLE)), (1023, 131, 1026, 3, (WHOLE, WHOLE)), (1025, 131, 1026, 3, (WHOLE, WHOLE)),
+    (4096, 900, 257, 1, (WHOLE, WHOLE)), (4097, 900, 257, 1, (WHOLE, WHOLE)), (8192, 2000, 256, 4, (WHOLE, WHOLE)),
+    (8193, 2000, 6, 3, (WHOLE, WHOLE)), (8192, 2000, 513, 3, (WHOLE, ROW)), (8193, 2000, 257, 1, (ROW, ROW)),
+    (12288, 3000, 5, 1, (WHOLE, WHOLE)), (12289, 3000, 256, 2, (WHOLE, ROW)), (32768, 8000, 3, 3, (WHOLE, ROW)),
+    (600, 200, 1024, 4, (WHOLE, WHOLE)), (3001, 700, 1026, 2, (WHOLE, WHOLE))])
+def test_rows_finished_in_one_launch(N, n, B, gamma, takes, kind):
     from paper_2506_03206_amd import rdk
     rng = np.random.default_rng(N + B)
     kept = np.sort(rng.choice(N, size=n, replace=False)).astype(np.int32)
@@ -103,9 +110,12 @@ def test_rows_finished_in_one_launch(N, n, B, gamma, kind):
     p64, q64 = oracle.probs_from(zp, pk), oracle.probs_from(zq, pk)
     ref = oracle.redistribute_batch("taylor", q64, kept, N, p=p64)
     want = oracle.verify_batch(p64, ref, 9, 4, gamma=gamma)
+    rdk.rdk_timing_select(takes[kind != "prob"])
     for _ in range(2):                       # the records of the scan are as they were after a call
         out = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, wide(zp), wide(zq), 9, 4, gamma, pk, pk)
         check_verify_outputs(out, want, p64, ref, 9, 4, gamma, pk, min_exact=0.6)
+    rdk.rdk_timing_select(None)
+    assert rdk.rdk_timing_read(takes[kind != "prob"])[0] == 2
 
 
 # Rows by one workgroup, and (probabilities, or q' written; the last also for logits) in two passes.
