@@ -93,3 +93,44 @@ def test_rounds_in_a_graph():
         ref = rdk.rdk_verify_multi(p, qp, C, 5, 9, cand_ids=cand)
         for name in ("accepted", "token", "resid_mass"):
             assert torch.equal(getattr(o, name), getattr(ref, name)), name
+
+
+@pytest.mark.parametrize("kind", ["prob", "logit"])
+def test_least_workspace_gives_the_same_results(kind):
+    """A shape that goes a launch a round, with the workspace for that and with the least that the call accepts."""
+    import ctypes
+    from paper_2506_03206_amd import rdk
+    B, N, C, seed, offset = 6, 70001, 2, 11, 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    z = torch.randn((B, N), generator=gen, device="cuda").mul_(2)
+    qp = torch.softmax(z + torch.randn((B, N), generator=gen, device="cuda"), 1)
+    p = torch.softmax(z, 1) if kind == "prob" else z
+    cand = torch.topk(qp, C, dim=1).indices.int()
+    cand[1], cand[2, 1:], cand[3] = N, -1, -1
+    full = rdk.rdk_verify_multi(p, qp, C, seed, offset, kind, cand_ids=cand)
+    o = rdk.MultiOutputs(B, C, "cuda")
+    o.cand_ids.copy_(cand)
+    code = rdk.PROB_F32 if kind == "prob" else rdk.LOGIT_F32
+    d = rdk.MultiDesc(B=B, N=N, C=C, seed=seed, offset=offset, sample_candidates=1)
+    asked, least = ctypes.c_size_t(), ctypes.c_size_t()
+    assert rdk.lib().rdk_verify_multi_workspace_bytes(ctypes.byref(d), code, ctypes.byref(least)) == rdk.OK   # no rounds where they are drawn
+    d.sample_candidates = 0
+    assert rdk.lib().rdk_verify_multi_workspace_bytes(ctypes.byref(d), code, ctypes.byref(asked)) == rdk.OK
+    assert least.value < asked.value
+    ws = torch.empty(asked.value, dtype=torch.uint8, device="cuda")
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    call = lambda size: rdk.lib().rdk_verify_multi(ctypes.byref(d), ptr(p), code, N, ptr(qp), N, ptr(o.cand_ids), ptr(o.accepted), ptr(o.token),
+                                                   ptr(o.resid_mass), ptr(ws), size, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    slack = 256                                        # which the query adds and the call does not need
+    assert call(least.value - slack - 1) == 6          # RDK_ERR_WORKSPACE
+    for size, kernel in ((least.value - slack, "verify_multi_kernel"), (asked.value - slack - 1, "verify_multi_kernel"),
+                         (asked.value - slack, "verify_multi_round_kernel")):
+        for t in (o.accepted, o.token, o.resid_mass):
+            t.fill_(-7)
+        rdk.rdk_timing_select(kernel)
+        assert call(size) == rdk.OK
+        torch.cuda.synchronize()
+        rdk.rdk_timing_select(None)
+        assert rdk.rdk_timing_read(kernel)[0] == (1 if kernel == "verify_multi_kernel" else C + 1)
+        assert torch.equal(o.accepted, full.accepted) and torch.equal(o.token, full.token) and torch.equal(o.resid_mass, full.resid_mass)

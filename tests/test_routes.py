@@ -95,3 +95,18 @@ def test_rows_of_eq3_finished_in_one_launch(ask, N, B, kinds):
         one = kinds & (1 if i < 1 else 2)
         names = [x.kernel.split("<")[0] for x in r.launches]
         assert names == ["taylor_whole_kernel" if one else "taylor_row_kernel"], (i, names)
+
+
+def test_workspace_of_rounds(ask, tmp_path):
+    """Token trees of long rows: a launch a round with the workspace that the library asks for, one workgroup a position with less, and
+    nothing with less than the partial statistics of the target rows take."""
+    for kind in (PROB, LOGIT, BF16):
+        for N, C, B, rounds in ((40000, 1, 128, 1), (39999, 1, 128, 0), (50000, 1, 129, 1), (49999, 1, 129, 0), (100000, 4, 32, 1), (200000, 1, 256, 1), (200000, 1, 257, 0)):
+            r = ask(["multi %d %d %d %d -1" % (kind, B, N, C)])[0]
+            names = [x.kernel.split("<")[0] for x in r.launches if x.kernel.startswith("verify")]
+            assert names == ["verify_multi_round_kernel"] * (C + 1) if rounds else names == ["verify_multi_kernel"], (N, C, B, names)
+            if rounds:
+                less = ask(["multi %d %d %d %d %d" % (kind, B, N, C, r.workspace - 257)])[0]   # 256 of them are slack
+                assert [x.kernel.split("<")[0] for x in less.launches if x.kernel.startswith("verify")] == ["verify_multi_kernel"]
+    exe = build_driver(tmp_path)
+    assert [r.status for r in routes(exe, ["multi %d 4 100000 1 256" % PROB, "multi %d 4 100000 1 255" % PROB])] == [0, 6]
