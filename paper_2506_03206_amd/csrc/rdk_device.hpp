@@ -46,7 +46,8 @@ __device__ __forceinline__ double lane_value(double v, int src)
 }
 
 // sum over each row of 16 lanes, the same bits in all 16
-__device__ __forceinline__ float row16_sum(float v)
+template <typename T>
+__device__ __forceinline__ T row16_sum(T v)
 {
     v += dpp_move<0xB1>(v);
     v += dpp_move<0x4E>(v);
@@ -59,10 +60,7 @@ __device__ __forceinline__ float row16_sum(float v)
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v)
 {
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x140>(v);   // every lane holds the sum of its row of 16
+    v = row16_sum(v);
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 

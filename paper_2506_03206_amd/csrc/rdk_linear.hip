@@ -643,13 +643,23 @@ __device__ __forceinline__ void row_finish(float *lds, int l_fin, int l_sum_q, i
 // wavefront holds its chunks (one, or two sixteen chunks apart) of the target row and of the drafter row in id order in registers
 // from the first sum to the store.  The kept ids of a quad own consecutive slots, so their drafter values are one 16-byte load at
 // the slot that lane_map gives, and three selects a value put them in their places.  The terms are those of taylor_stats_kernel, with
-// the row's own maximum and normaliser (no series), and the drafter row's mass is not needed at all.  Against 64-bit sums, 120 sets
-// of rows of 1000 to 32768 ids, mean relative error of q' with two passes -> this: probabilities 8.8e-8 -> 7.7e-8, fp32 logits 9.7e-8 ->
-// 8.2e-8, bf16 logits 9.9e-8 -> 8.2e-8; of alpha and the residual mass 0 to 15 % less as well.
-// What bounds it: the chain of a launch, two dependent reads, one barrier (three for logits) and the stores.
+// the row's own normaliser (no series), and the drafter row's mass is not needed at all.  Against 64-bit sums, 12 sets of 64 rows of
+// each of 600 to 32000 ids, mean relative error with two passes -> this: q' of probabilities 8.9e-8 -> 8.1e-8, of fp32 logits 3.7e-7 ->
+// 3.0e-7, of bf16 logits 2.9e-7 -> 2.4e-7; alpha and residual mass of probabilities 3.6e-8 and 3.3e-8 as before, of logits 6.8e-8 ->
+// 5.0e-8 and 6.5e-8 -> 4.8e-8.  Rows of 2500 to 12000 logits without q' in one pass (taylor_row_kernel) -> this: alpha 6.5e-8 -> 5.1e-8,
+// residual mass 5.1e-8 -> 4.8e-8.
+// What bounds it: the chain of a launch, two dependent reads, one barrier (two for logits) and the stores.
 constexpr int kWholeThreads = 1024, kFinishWaves = 8;   // of a workgroup at most; at least where it finishes its row
 constexpr int kWholeHeld = 2;                                                       // chunks of a wavefront
 constexpr int kWholeMaxN = kWholeHeld * (kWholeThreads / kWave) * kChunk;
+
+// Sum of one value for every wavefront, sixteen at most, in the first lanes.
+template <typename T>
+__device__ __forceinline__ T waves_sum(T v)
+{
+    static_assert(kWholeThreads / kWave == 16, "one row of lanes");
+    return lane_value(row16_sum(v), 0);
+}
 
 // Totals over the workgroup of M values of every wavefront, the same bits in each; at: M * waves floats of LDS, used once.
 template <int M>
@@ -663,7 +673,7 @@ __device__ __forceinline__ void whole_totals(float (&v)[M], float *at, int wid, 
     }
     __syncthreads();
 #pragma unroll
-    for (int m = 0; m < M; ++m) v[m] = wave_sum(lane < waves ? at[m * waves + lane] : 0.f);
+    for (int m = 0; m < M; ++m) v[m] = waves_sum(lane < waves ? at[m * waves + lane] : 0.f);
 }
 
 struct WholeRcp {
@@ -715,7 +725,7 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
     }
     // the values in id order; ids that are not kept, and those beyond N, have no weight
     float pv[kWholeHeld][4][4], qv[kWholeHeld][4][4];
-    float pm = kNoLogit, qm = kNoLogit;
+    float wp = kNoLogit, wq = kNoLogit;   // largest logits of the wavefront's own chunks
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
         const int c = wid + t * waves;
@@ -737,45 +747,58 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             qv[t][i][3] = b3 ? (b2 ? r3 : r2) : none;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (PK != RDK_PROB_F32) pm = fmaxf(pm, pv[t][i][e]);
-                if (QK != RDK_PROB_F32) qm = fmaxf(qm, qv[t][i][e]);
+                if (PK != RDK_PROB_F32) wp = fmaxf(wp, pv[t][i][e]);
+                if (QK != RDK_PROB_F32) wq = fmaxf(wq, qv[t][i][e]);
             }
         }
     }
-    float *red = lds;
-    if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) {
-        if (PK != RDK_PROB_F32) pm = wave_max(pm);
-        if (QK != RDK_PROB_F32) qm = wave_max(qm);
-        if (lane == 0) {
-            red[wid] = pm;
-            red[waves + wid] = qm;
-        }
-        __syncthreads();
-        if (PK != RDK_PROB_F32) pm = wave_max(lane < waves ? red[lane] : kNoLogit);
-        if (QK != RDK_PROB_F32) qm = wave_max(lane < waves ? red[waves + lane] : kNoLogit);
-        red += 2 * waves;
-    }
-    qm = weight_reference(qm);
-    float z[1] = {0.f};
+    // Weights of logits are formed against the wavefront's own maximum, and how far that lies below the row's comes in as one factor,
+    // finely rounded: a weight is off by its distance from its reference times 6e-8, and there is no maximum of the row to wait for.
+    if (PK != RDK_PROB_F32) wp = wave_max(wp);
+    if (QK != RDK_PROB_F32) wq = wave_max(wq);
+    const float pref = weight_reference(wp), qref = weight_reference(wq);
+    float z = 0.f;
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
         if (wid + t * waves >= nchunks) break;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; ++i) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (PK != RDK_PROB_F32) {
-                    pv[t][i][e] = soft_exp(pv[t][i][e] - pm);
-                    z[0] += pv[t][i][e];
-                }
-                if (QK != RDK_PROB_F32) qv[t][i][e] = (map[t] >> (4 * i + e)) & 1 ? soft_exp(qv[t][i][e] - qm) : 0.f;
+                if (PK != RDK_PROB_F32) pv[t][i][e] = soft_exp(pv[t][i][e] - pref);
+                if (QK != RDK_PROB_F32) qv[t][i][e] = (map[t] >> (4 * i + e)) & 1 ? soft_exp(qv[t][i][e] - qref) : 0.f;
             }
+            if (PK != RDK_PROB_F32) z += (pv[t][i][0] + pv[t][i][1]) + (pv[t][i][2] + pv[t][i][3]);
+        }
     }
-    float pinv = 1.f;
-    if (PK != RDK_PROB_F32) {
-        whole_totals(z, red, wid, lane, waves);
-        pinv = 1.0f / z[0];
-        red += waves;
+    float *red = lds;
+    float pm = 0.f, pinv = 1.f, pscale = 1.f, prest = 0.f, qm = 0.f, qscale = 1.f;   // of the row; weight of the wavefront -> of the row
+    if (PK != RDK_PROB_F32 || QK != RDK_PROB_F32) {
+        if (PK != RDK_PROB_F32) z = wave_sum(z);
+        if (lane == 0) {
+            red[wid] = wp;
+            red[waves + wid] = wq;
+            red[2 * waves + wid] = z;
+        }
+        __syncthreads();
+        if (PK != RDK_PROB_F32) {
+            const float m = lane < waves ? red[lane] : kNoLogit;
+            pm = wave_max(m);
+            // The errors that all ids share are kept out of the weights: the normaliser is added up in 64 bits, and what its reciprocal and
+            // the product with the factor round off comes in as a second, small factor.  Without, the residual mass of 2500 to 12000 logits
+            // was 1.1 to 1.3 times as far from 64-bit sums as the one-pass form's, with it 0.84 to 1.01 times; it costs nothing up to 512
+            // rows, and 1024 rows of 1001 ids 0.3 us of 16.
+            const double zt = waves_sum(lane < waves ? (double)red[2 * waves + lane] * (double)soft_exp_fine(m - pm) : 0.0);
+            const float f = soft_exp_fine(wp - pm);
+            pinv = 1.0f / (float)zt;
+            pscale = f * pinv;
+            prest = fmaf(f, pinv, -pscale) - pscale * (float)fma((double)pinv, zt, -1.0);
+        }
+        if (QK != RDK_PROB_F32) {
+            qm = weight_reference(wave_max(lane < waves ? red[waves + lane] : kNoLogit));
+            qscale = soft_exp_fine(wq - qm);
+        }
+        red += 3 * waves;
     }
     const float fN = (float)N;
     float s[3] = {0.f, 0.f, 0.f};   // sum q^ p, sum q^ / (N + p), sum p / (N + p)
@@ -786,17 +809,22 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                if (PK != RDK_PROB_F32) pv[t][i][e] *= pinv;
+                if (PK != RDK_PROB_F32) pv[t][i][e] = fmaf(pv[t][i][e], pscale, pv[t][i][e] * prest);
                 const float pe = pv[t][i][e], qh = qv[t][i][e], r = __builtin_amdgcn_rcpf(fN + pe);
                 s[0] += qh * pe;
                 s[1] += qh * r;
                 s[2] += pe * r;
             }
     }
+    if (QK != RDK_PROB_F32) {
+        s[0] *= qscale;
+        s[1] *= qscale;
+    }
     whole_totals(s, red, wid, lane, waves);
     // with the drafter row's mass Z, theta = s0 / Z and S = (N s1 + s0 s2) / Z: Z cancels in N / (Z S) and in theta / S
     const float T = fmaf(s[1], fN, s[0] * s[2]);
     const float nzs = T > 0.f ? fN / T : 0.f, ths = T > 0.f ? s[0] / T : s[0] * 0.f;   // a row without mass gives the zero row
+    const float nzw = nzs * qscale;
     float *orow = out ? out + row * ldo : nullptr;
 #pragma unroll
     for (int t = 0; t < kWholeHeld; ++t) {
@@ -808,7 +836,7 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
             const int id = c * kChunk + 256 * i + 4 * lane;
             float o[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (nzs * qv[t][i][e] + ths * pv[t][i][e]) * __builtin_amdgcn_rcpf(fN + pv[t][i][e]);
+            for (int e = 0; e < 4; ++e) o[e] = (nzw * qv[t][i][e] + ths * pv[t][i][e]) * __builtin_amdgcn_rcpf(fN + pv[t][i][e]);
             if (FUSE && !orow) {
             } else if ((c + 1) * kChunk <= N) {
                 store4(orow + id, o[0], o[1], o[2], o[3]);
@@ -818,13 +846,16 @@ __global__ __launch_bounds__(kWholeThreads) void taylor_whole_kernel(const void 
                     if (id + e < N) orow[id + e] = o[e];
             }
             if (FUSE) {
+                float r[4], m[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {   // beyond N both weights are zero, and so is q'
                     qv[t][i][e] = o[e];
-                    sq += o[e];
-                    sr += fmaxf(pv[t][i][e] - o[e], 0.f);
-                    sa += fminf(pv[t][i][e], o[e]);
+                    r[e] = fmaxf(pv[t][i][e] - o[e], 0.f);
+                    m[e] = fminf(pv[t][i][e], o[e]);
                 }
+                sq += (o[0] + o[1]) + (o[2] + o[3]);
+                sr += (r[0] + r[1]) + (r[2] + r[3]);
+                sa += (m[0] + m[1]) + (m[2] + m[3]);
             }
         }
         if (FUSE) {

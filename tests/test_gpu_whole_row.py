@@ -65,7 +65,7 @@ def test_rows_written_in_one_launch(shape, kinds):
     rdk.rdk_redistribute_linear(kern, rdk.LINEAR_TAYLOR, dev[1], rows[1], p=dev[0], p_kind=rows[0], out=held[:, :N])
     torch.cuda.synchronize()
     rdk.rdk_timing_select(None)
-    launches = {name: rdk.rdk_timing_read(name)[0] for name in ("taylor_whole_kernel", "taylor_stats_kernel", "row_stats_kernel")}
+    launches = {name: rdk.rdk_timing_read(name)[0] for name in ("taylor_whole_kernel", "taylor_stats_kernel", "taylor_write_kernel", "row_stats_kernel")}
     assert launches["taylor_whole_kernel"] == (1 if one else 0) and launches["taylor_stats_kernel"] == (0 if one else 1)
     assert not one or launches["row_stats_kernel"] == 0
     assert bool((held[:, N:] == 7.0).all())  # nothing behind a row is written
@@ -179,3 +179,25 @@ def test_graph_replays_of_rows_in_one_launch(N, B, keep):
         for name in ("draft_ids", "accept", "alpha", "resid_mass", "resid_ids", "n_accepted", "out_tokens"):
             assert torch.equal(getattr(o, name), getattr(ref, name)), name
         assert (o.n_accepted >= 0).all() and (not keep or torch.equal(qp, held))
+
+
+@pytest.mark.parametrize("N", [4000, 8003])
+def test_rounding_that_the_ids_of_a_row_share(N):
+    """Errors of the normaliser, of its reciprocal and of the factor between a wavefront's weights and the row's move every id of a row
+    alike, and alpha and the residual mass with them.  Their mean relative error over 512 rows of logits is 3.9e-8 to 4.4e-8 where these
+    are carried along and 5.4e-8 to 5.8e-8 where they are rounded; a mean over 1024 values of that spread is good to 2e-9."""
+    from paper_2506_03206_amd import rdk
+    rng = np.random.default_rng(N)
+    B, n = 512, N // 4
+    kept = np.sort(rng.choice(N, size=n, replace=False)).astype(np.int32)
+    zp = (rng.normal(size=(B, N)) * 2.0 - np.log1p(rng.permutation(N))).astype(np.float32)
+    zq = np.ascontiguousarray((zp + rng.normal(size=(B, N)).astype(np.float32))[:, kept])
+    kern = rdk.rdk_build_kernel(N, torch.from_numpy(kept).cuda(), rdk.IDENTITY)
+    p, q = oracle.probs_from(zp, "logit"), np.zeros((B, N))
+    q[:, kept] = oracle.probs_from(zq, "logit")
+    pt = (N * q + (p * q).sum(1, keepdims=True) * p) / (N + p)
+    qp = pt / pt.sum(1, keepdims=True)
+    o = rdk.rdk_redistribute_verify(kern, rdk.LINEAR_TAYLOR, torch.from_numpy(zp).cuda(), torch.from_numpy(zq).cuda(), 3, 0, 0, "logit", "logit")
+    alpha, resid = np.minimum(p, qp).sum(1), np.maximum(p - qp, 0).sum(1)
+    off = lambda got, ref: np.abs(got.cpu().numpy().astype(np.float64) / ref - 1).mean()
+    assert (off(o.alpha, alpha) + off(o.resid_mass, resid)) / 2 < 4.9e-8
