@@ -151,7 +151,8 @@ rdk_status_t rdk_workspace_bytes(const rdk_kernel_t *kernel, int32_t B, size_t *
  *            image under Eq. 1: every redistribution call (exact, both linear forms, the fused call and the
  *            draft draw) returns the zero row for it, so that verification sees alpha = 0, resid_mass = sum(p),
  *            draft_ids = -1, accept = 0, and draws resid_ids from the target row alone.
- *            LOGIT: the softmax over the n slots, which equals Eq. 1 applied to a full softmax.
+ *            LOGIT: the softmax over the n slots, which equals Eq. 1 applied to a full softmax; a row of which every
+ *            logit is -inf is one whose sum is zero.
  *   q_prime  [B, ldo]  fp32, the redistributed drafter over all N target ids.
  * Kernel format must be DENSE_F32, DENSE_BF16 or IDENTITY.  With DENSE_BF16 the kernel entries are rounded to
  * bf16 and the normalised drafter rows to eleven significant bits (both are fed to the matrix cores as fp16 numbers
@@ -288,7 +289,8 @@ rdk_status_t rdk_sample_draft(const rdk_kernel_t *kernel, const void *q, rdk_inp
  * that were not reached.  p [B, ldp] of kind p_kind, q_prime [B, ldq] fp32; 1 <= C <= 16, N <= 2 097 152.
  * A call with less workspace than it asks for, but enough for the softmax partials of logit rows, takes a form that is slower for few
  * long rows, with the same results.
- * Errors: RDK_ERR_NULL, RDK_ERR_SHAPE (B, N, C, strides), RDK_ERR_DTYPE, RDK_ERR_ALIGN (rows not 16-byte aligned),
+ * Errors: RDK_ERR_NULL, RDK_ERR_SHAPE (B, N, C, strides), RDK_ERR_DTYPE, RDK_ERR_ALIGN (p, q_prime or the workspace not 16-byte
+ * aligned; the rows may lie at any stride),
  * RDK_ERR_UNSUPPORTED (N or C above the limits), RDK_ERR_WORKSPACE, RDK_ERR_HIP.
  */
 typedef struct {

@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kStatThreads) void prep_a_records_kernel(const void
 // zero beyond n, rows of M are clamped to the last one).  Tiles of 64 ids at two wavefronts per SIMD were slower
 // (0.26 ms against 0.22 ms): every wavefront reads all drafter records of its split.
 //
-// What bounds it: reading M (N = 32000, n = 8000, 64 positions: 1 GB in about 175 us, 5.9 TB/s, where a bare read stream reaches
+// What bounds it: reading M (N = 32000, n = 8000, 64 positions: 1 GB in 180 us, 5.7 TB/s, where a bare read stream reaches
 // 6.9), and the matrix unit for several row groups.  A lone wavefront has to keep both busy from one instruction stream, so the
 // parts of a pair of columns are taken one unit ahead of their products and every MFMA is followed by five vector instructions
 // and now and then one load: eight loads at once fill the queue of the vector memory pipe, and the wavefront waits there
@@ -525,8 +525,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_a_bf16_kernel(const void *q
 //   * requests run two (A) and three (B) stages ahead of the MFMAs; large batches use one wavefront per SIMD with
 //     the whole register file (accumulators in the AGPR half), which halves the LDS reads per MFMA.
 // With requests in one go at the head of a stage, and the stage's LDS writes, barrier and first reads at its end, the matrix pipe was
-// busy 70 % of the clocks; spread between the MFMAs, with the barrier in mid-stage, 81 % (N = 256000, n = 32000, 512 positions: 11.55 ->
-// 9.89 M clocks, at 1.60 -> 1.51 GHz: 7114 -> 6755 us a call of two).  The clock follows the power from here on.
+// busy 70 % of the clocks; spread between the MFMAs, with the barrier in mid-stage, 80 % (N = 256000, n = 32000, 512 positions: 11.55 ->
+// 10.0 M clocks under the counters, at 1.60 -> 1.45 GHz: 7114 -> 6755 us a call of two).  The clock follows the power from here on.
 // M is streamed from HBM exactly once when all positions fit one row of workgroups (B <= 512).
 // Where there are fewer column groups than the chip has compute units, be it in the whole call or in its last round, the slots are
 // split over blockIdx.z, in whole turns of six stages, and the partial products of the groups from group0 on go to `out` without
