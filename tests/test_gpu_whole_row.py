@@ -146,7 +146,7 @@ def test_rows_without_mass_and_with_nan(N, keep):
         assert o.alpha[2:5].isnan().all() and o.resid_mass[2:5].isnan().all() and (o.resid_ids[2:5] == -1).all()
 
 
-@pytest.mark.parametrize("N,B,keep", [(3000, 20, False), (3000, 20, True), (20001, 640, True), (8000, 512, False)])
+@pytest.mark.parametrize("N,B,keep", [(3000, 20, False), (3000, 20, True), (20001, 640, True), (8000, 512, False), (3000, 1100, False), (3000, 1100, True)])
 def test_graph_replays_of_rows_in_one_launch(N, B, keep):
     """Replays on other rows, with eager calls between them, against the eager call; every sequence is scanned."""
     from paper_2506_03206_amd import rdk
